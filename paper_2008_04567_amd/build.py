@@ -2,8 +2,8 @@
 
 ``python -m paper_2008_04567_amd.build`` (add ``--changed`` to compile only what is stale) or
 ``build_library()``.  Translation units are compiled
-in parallel: the host part, the API/dispatch part and eight instantiation parts of the tiled
-kernel family.  Works without a GPU (hipcc cross-compiles).
+in parallel: the host part, the API/dispatch part, eight instantiation parts of the tiled
+kernel family and three of its split members.  Works without a GPU (hipcc cross-compiles).
 """
 import concurrent.futures
 import os
@@ -75,11 +75,15 @@ def build_library(force=True, verbose=False):
     add([hipcc] + COMMON + ["-c", src("wpk_host.cpp"), "-o", os.path.join(OBJ, "wpk_host.o")],
         headers + [src("wpk_host.cpp"), src("wpk_variants.def")])
     add([hipcc] + COMMON + DEVICE + ["-c", src("wpk_api.hip"), "-o", os.path.join(OBJ, "wpk_api.o")],
-        kernel_headers + [src("wpk_api.hip")])
+        kernel_headers + [src("wpk_split.h"), src("wpk_api.hip")])
     for part in range(N_PARTS):
         add([hipcc] + COMMON + DEVICE + ["-DWPK_PART=%d" % part, "-c", src("wpk_igemm_inst.hip"),
                                          "-o", os.path.join(OBJ, "wpk_igemm_%d.o" % part)],
             kernel_headers + [src("wpk_igemm_inst.hip")])
+    for wn in (1, 2, 4):
+        add([hipcc] + COMMON + DEVICE + ["-DWPK_PART=%d" % wn, "-c", src("wpk_split_inst.hip"),
+                                         "-o", os.path.join(OBJ, "wpk_split_%d.o" % wn)],
+            headers + [src("wpk_igemm.h"), src("wpk_split.h"), src("wpk_split_inst.hip")])
     if jobs:
         workers = min(len(jobs), max(1, (os.cpu_count() or 4)), 16)
         with concurrent.futures.ThreadPoolExecutor(workers) as ex:

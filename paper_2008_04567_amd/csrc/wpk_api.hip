@@ -14,7 +14,7 @@
 #include <thread>
 #include <vector>
 
-#include "wpk_igemm.h"
+#include "wpk_split.h"
 
 namespace wpk {
 
@@ -62,6 +62,67 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restri
     const int kq = threadIdx.x >> 5, kc = threadIdx.x & 31;
     float4 v = make_float4(tile[kc][4 * kq], tile[kc][4 * kq + 1], tile[kc][4 * kq + 2], tile[kc][4 * kq + 3]);
     *reinterpret_cast<float4 *>(wp + ((size_t)(kk0 / 4 + kq) * Kpad + k0 + kc) * 4) = v;
+}
+
+// Where row kk of the split members' reduction comes from: its place among the C*R*S rows of the source, or
+// -1 for a padding row.  With RS > 0 the rows run (c / 32, r, s, c % 32), else in the source's order.
+__device__ inline int split_source_row(int kk, int CRS, int RS)
+{
+    if (RS <= 0) return kk < CRS ? kk : -1;
+    const int c32 = kk / (32 * RS), t = kk - c32 * 32 * RS;
+    // (sixteen rows at a time: the two halves of the 32 channels follow each other for every tap)
+    return (c32 * 32 + (t & 31)) * RS + (t >> 5);
+}
+
+// w[K][CRS] -> [CRSpad/16][Kpad/32][3 parts][64 lanes][8 bf16], zero padded: what lane l of a wave feeds the
+// bf16 MFMA of one depth and 32-channel block is channel l % 32, rows (l / 32)*8 .. +7.  Parts: w rounded to
+// bf16, the remainder rounded to bf16, the rest; their sum is w exactly (down to 2^-133).  A w that would round
+// to infinity is cut off instead, and an infinity or NaN has its remainders zero.
+__global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict__ w, v4u *__restrict__ wp, int K,
+                                                         int CRS, int depths, int blocks, int RS)
+{
+    const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6), kb = blockIdx.y;
+    if (t >= depths) return;
+    const int k = kb * 32 + (lane & 31);
+    unsigned part[3][4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int row = split_source_row(t * 16 + (lane >> 5) * 8 + j, CRS, RS);
+        const float v = k < K && row >= 0 ? w[(size_t)k * CRS + row] : 0.0f;
+        const unsigned bits = __float_as_uint(v);
+        unsigned h = pack_bf16(v, 0.0f) & 0xffffu;
+        if ((h & 0x7fffu) == 0x7f80u && (bits & 0x7f800000u) != 0x7f800000u) h = bits >> 16;
+        const float r1 = (bits & 0x7f800000u) == 0x7f800000u ? 0.0f : v - bf16_low(h);
+        const unsigned m = pack_bf16(r1, 0.0f) & 0xffffu;
+        const unsigned l = pack_bf16(r1 - bf16_low(m), 0.0f) & 0xffffu;
+        const unsigned v3[3] = {h, m, l};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) part[q][j / 2] = j % 2 ? part[q][j / 2] | v3[q] << 16 : v3[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        wp[(((size_t)t * blocks + kb) * 3 + q) * 64 + lane] = (v4u){part[q][0], part[q][1], part[q][2], part[q][3]};
+}
+
+// The way back, from either packed form: w[K][CRS] (a plan whose configuration moves to the other form).
+__global__ void __launch_bounds__(256) unpack_weights_kernel(const void *__restrict__ packed, float *__restrict__ w,
+                                                             int K, int C, int CRS, int Kpad, int RS, int split)
+{
+    const long long total = (long long)K * CRS;
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+        const int k = (int)(i / CRS), row = (int)(i - (long long)k * CRS);
+        const int c = RS > 0 ? row / RS : 0, rs = RS > 0 ? row - c * RS : 0;
+        if (split) {
+            const int kk = RS > 0 ? (c / 32 * RS + rs) * 32 + c % 32 : row;
+            const int lane = (kk >> 3 & 1) * 32 + (k & 31);
+            const unsigned short *p = (const unsigned short *)packed +
+                                      (((size_t)(kk >> 4) * (Kpad / 32) + k / 32) * 3 * 64 + lane) * 8 + (kk & 7);
+            w[i] = (bf16_low(p[2 * 512]) + bf16_low(p[512])) + bf16_low(p[0]);
+        } else {
+            const int kk = RS > 0 ? rs * C + c : row;
+            w[i] = ((const float *)packed)[((size_t)(kk / 4) * Kpad + k) * 4 + kk % 4];
+        }
+    }
 }
 
 // One output element per lane, the three reduction loops written out; 64-bit indexing.
@@ -373,11 +434,24 @@ static int upload_tap_table(const Problem &pr, int32_t **out, hipStream_t st)
     return WPK_OK;
 }
 
-static int pack_weights(const Problem &pr, const float *w, float *wp, hipStream_t st)
+// Bytes of a problem's weights in the form the tiled and wave-split members (split = false) or the split members
+// read them.
+static size_t packed_bytes(const Problem &pr, bool split)
 {
-    dim3 grid(pr.CRSpad / 32, pr.Kpad / 32);
-    hipLaunchKernelGGL(pack_weights_kernel, grid, dim3(256), 0, st, w, wp, pr.d.k, pr.CRS, pr.Kpad, pr.d.c,
-                       pr.xquad || pr.tapmajor ? pr.d.r * pr.d.s : 0);
+    return (size_t)pr.CRSpad * pr.Kpad * (split ? kSplitWeightBytes : sizeof(float));
+}
+
+static int pack_weights(const Problem &pr, bool split, const float *w, float *wp, hipStream_t st)
+{
+    const int RS = pr.xquad || pr.tapmajor ? pr.d.r * pr.d.s : 0;
+    if (split) {
+        const int depths = pr.CRSpad / 16, blocks = pr.Kpad / 32;
+        hipLaunchKernelGGL(pack_split_kernel, dim3((depths + 3) / 4, blocks), dim3(256), 0, st, w, (v4u *)wp, pr.d.k,
+                           pr.CRS, depths, blocks, RS);
+    } else {
+        dim3 grid(pr.CRSpad / 32, pr.Kpad / 32);
+        hipLaunchKernelGGL(pack_weights_kernel, grid, dim3(256), 0, st, w, wp, pr.d.k, pr.CRS, pr.Kpad, pr.d.c, RS);
+    }
     WPK_HIP(hipGetLastError());
     return WPK_OK;
 }
@@ -456,12 +530,12 @@ static bool zeroes_all_of_y(const Problem &pr, const wpk_conv_config &cfg, const
 {
     FixupNeed need = fixup_need(pr, cfg, g_cus);
     if (need.bytes > 0 && fix && fix->ptr && fix->bytes >= (size_t)need.bytes) return false;
-    int nsteps = (pr.CRS + cfg.bk - 1) / cfg.bk;
+    int nsteps = reduction_of(pr, cfg).steps;
     int per = (nsteps + cfg.split_k - 1) / cfg.split_k;
     if ((nsteps + per - 1) / per > 1) return true;
-    if (cfg.persist > 0) {
+    if (const int persist = persistent_of(pr, cfg, g_cus)) {
         int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
-        int64_t G = (int64_t)cfg.persist * (g_cus > 0 ? g_cus : 256);
+        int64_t G = (int64_t)persist * (g_cus > 0 ? g_cus : 256);
         return tiles < G;
     }
     return false;
@@ -479,14 +553,17 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.x = x; a.wp = wp; a.y = y; a.ktab = ktab;
     a.RS = d.r * d.s;
     a.HW4 = pr.xl ? 4 : d.h * d.w * 4;  // byte stride between channels of x
-    a.bk_div_rs = cfg.bk / a.RS;
-    a.bk_mod_rs = cfg.bk % a.RS;
-    a.ttab = ktab + ((size_t)a.RS + (cfg.bk == 8 ? 0 : cfg.bk == 16 ? 1 : 2)) * 32 * 2;
+    const Reduction red = reduction_of(pr, cfg);
+    const int persist = persistent_of(pr, cfg, g_cus);
+    a.bk_div_rs = red.rows / a.RS;
+    a.bk_mod_rs = red.rows % a.RS;
+    a.ttab = ktab + ((size_t)a.RS + (red.rows == 8 ? 0 : red.rows == 16 ? 1 : 2)) * 32 * 2;
     a.N = d.n; a.C = d.c; a.H = d.h; a.W = d.w; a.K = d.k; a.P = pr.P; a.Q = pr.Q; a.R = d.r; a.S = d.s;
     a.stride_h = d.stride_h; a.stride_w = d.stride_w; a.pad_h = d.pad_h; a.pad_w = d.pad_w;
     a.dil_h = d.dil_h; a.dil_w = d.dil_w;
     a.M = (int32_t)pr.M; a.PQ = pr.P * pr.Q; a.HW = d.h * d.w; a.CRS = pr.CRS; a.Kpad = pr.Kpad;
-    a.nsteps = (pr.CRS + cfg.bk - 1) / cfg.bk;
+    a.nsteps = red.steps;
+    a.halo = split_member(cfg) && split_point(pr) ? -1 : halo_positions(pr, cfg);
     // slices of ceil(nsteps/split_k) steps; launch only as many as are not empty
     a.steps_per_split = (a.nsteps + cfg.split_k - 1) / cfg.split_k;
     a.split_k = (a.nsteps + a.steps_per_split - 1) / a.steps_per_split;
@@ -501,15 +578,15 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     if (pr.yl && d.k % 4 == 0 && ((uintptr_t)y & 15) == 0 && ((uintptr_t)epi.res & 15) == 0 &&
         ((uintptr_t)epi.bias & 15) == 0)
         a.yl = 2;
-    a.w_bytes = (uint32_t)((int64_t)pr.CRSpad * pr.Kpad * 4);
+    a.w_bytes = (uint32_t)packed_bytes(pr, split_member(cfg));
     a.y_bytes = (uint32_t)(pr.y_elems * 4);
-    a.persist = cfg.persist;
-    a.grid_persist = cfg.persist * (g_cus > 0 ? g_cus : 256);
+    a.persist = persist;
+    a.grid_persist = persist * (g_cus > 0 ? g_cus : 256);
     a.tiles = a.tiles_m * a.tiles_n;
-    a.tiles_dp = cfg.persist > 0 ? a.tiles / a.grid_persist * a.grid_persist : 0;
+    a.tiles_dp = persist > 0 ? a.tiles / a.grid_persist * a.grid_persist : 0;
     {
         int64_t units = (int64_t)(a.tiles - a.tiles_dp) * a.nsteps;  // < 2^31: checked by legal_for
-        int64_t groups = cfg.persist > 0 ? streamk_groups(units, a.grid_persist, cfg.bk) : 0;
+        int64_t groups = persist > 0 ? streamk_groups(units, a.grid_persist, red.rows) : 0;
         a.sk_groups = (int32_t)groups;
         a.sk_q = groups > 0 ? (int32_t)(units / groups) : 0;
         a.sk_rem = groups > 0 ? (int32_t)(units % groups) : 0;
@@ -526,7 +603,8 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.div_nsteps = make_fastdiv((uint32_t)a.nsteps);
     a.div_q1 = make_fastdiv((uint32_t)a.sk_q + 1);
     a.div_q0 = make_fastdiv((uint32_t)std::max(a.sk_q, 1));
-    a.div_tap = make_fastdiv((uint32_t)(pr.xquad || pr.tapmajor ? d.c : a.RS));
+    a.div_tap = make_fastdiv((uint32_t)(a.halo > 0 ? d.h * d.w
+                                               : (pr.xquad || pr.tapmajor) && !split_member(cfg) ? d.c : a.RS));
     a.ws = nullptr;
     a.ws_cnt = nullptr;
     a.ws_maxc = 0;
@@ -538,14 +616,14 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     }
     // with atomics into y nobody holds a finished output: the epilogue follows as its own pass
     const bool shared_by_atomics =
-        !a.ws && (a.split_k > 1 || (cfg.persist > 0 && (a.tiles_m * a.tiles_n) % a.grid_persist != 0));
+        !a.ws && (a.split_k > 1 || (persist > 0 && (a.tiles_m * a.tiles_n) % a.grid_persist != 0));
     a.bias = shared_by_atomics ? nullptr : epi.bias;
     a.res = shared_by_atomics ? nullptr : epi.res;
     a.relu = shared_by_atomics ? 0 : epi.relu;
     if (a.split_k > 1 && !a.ws) {
         int rc = y_zeroed ? WPK_OK : zero_fill(y, pr.y_elems, st);
         if (rc != WPK_OK) return rc;
-    } else if (a.split_k == 1 && cfg.persist > 0 && !a.ws) {
+    } else if (a.split_k == 1 && persist > 0 && !a.ws) {
         // tiles beyond the last whole round are accumulated with atomics: zero their pixels
         int tiles = a.tiles_m * a.tiles_n;
         int tiles_dp = tiles / a.grid_persist * a.grid_persist;
@@ -577,7 +655,7 @@ struct Prepared {
 static std::map<std::string, Prepared> g_prepared;
 static FixupBuf g_fixup;
 static float *g_wscratch = nullptr;
-static size_t g_wscratch_elems = 0;
+static size_t g_wscratch_bytes = 0;
 
 static int get_prepared(const Problem &pr, Prepared **out, hipStream_t st)
 {
@@ -593,14 +671,14 @@ static int get_prepared(const Problem &pr, Prepared **out, hipStream_t st)
     return WPK_OK;
 }
 
-static int get_wscratch(size_t elems, float **out)
+static int get_wscratch(size_t bytes, float **out)
 {
-    if (elems > g_wscratch_elems) {
+    if (bytes > g_wscratch_bytes) {
         if (g_wscratch) WPK_HIP(hipFree(g_wscratch));  // synchronises: earlier users are done
         g_wscratch = nullptr;
-        g_wscratch_elems = 0;
-        WPK_HIP(hipMalloc((void **)&g_wscratch, elems * sizeof(float)));
-        g_wscratch_elems = elems;
+        g_wscratch_bytes = 0;
+        WPK_HIP(hipMalloc((void **)&g_wscratch, bytes));
+        g_wscratch_bytes = bytes;
     }
     *out = g_wscratch;
     return WPK_OK;
@@ -625,9 +703,9 @@ static int fwd_with(const Problem &pr, const wpk_conv_config &cfg, const float *
     rc = get_prepared(pr, &prep, st);
     if (rc != WPK_OK) return rc;
     float *wp;
-    rc = get_wscratch((size_t)pr.CRSpad * pr.Kpad, &wp);
+    rc = get_wscratch(packed_bytes(pr, split_member(cfg)), &wp);
     if (rc != WPK_OK) return rc;
-    rc = pack_weights(pr, w, wp, st);
+    rc = pack_weights(pr, split_member(cfg), w, wp, st);
     if (rc != WPK_OK) return rc;
     FixupNeed need = fixup_need(pr, cfg, g_cus);
     if (need.bytes > 0) {
@@ -643,7 +721,7 @@ struct TuneCtx {
     wpk_tune_options opt;
     hipStream_t st;
     hipEvent_t e0, e1;
-    float *x, *w, *wp, *y, *yref, *dref;
+    float *x, *w, *wp[2], *y, *yref, *dref;  // wp: packed for the split members ([1]) and for the others
     unsigned *err_bits;
     int32_t *ktab;
     FixupBuf fix;
@@ -669,7 +747,7 @@ static int measure_us(TuneCtx &t, const wpk_conv_config &cfg, double *us_out, do
         int rf = fixup_reserve(t.fix, (size_t)need.bytes);
         if (rf != WPK_OK) return rf;
     }
-    int rc = run_config(t.pr, cfg, t.ktab, t.x, t.wp, t.y, &t.fix, t.st);
+    int rc = run_config(t.pr, cfg, t.ktab, t.x, t.wp[split_member(cfg)], t.y, &t.fix, t.st);
     if (rc != WPK_OK) return rc;
     hipLaunchKernelGGL(compare_kernel, dim3(512), dim3(256), 0, t.st, t.y, t.yref, t.dref,
                        (long long)t.pr.y_elems, t.err_bits);
@@ -691,7 +769,8 @@ static int measure_us(TuneCtx &t, const wpk_conv_config &cfg, double *us_out, do
             // (zero_ahead: y keeps accumulating from launch to launch, which costs the same time)
             Epilogue epi;
             epi.relu = t.opt.epilogue != 0;
-            int r = run_config(t.pr, cfg, t.ktab, t.x, t.wp, t.y, &t.fix, t.st, epi, t.opt.zero_ahead != 0);
+            int r = run_config(t.pr, cfg, t.ktab, t.x, t.wp[split_member(cfg)], t.y, &t.fix, t.st, epi,
+                               t.opt.zero_ahead != 0);
             if (r != WPK_OK) return r;
         }
         WPK_HIP(hipEventRecord(t.e1, t.st));
@@ -759,7 +838,8 @@ static void tune_free(TuneCtx &t)
 {
     if (t.x) (void)hipFree(t.x);
     if (t.w) (void)hipFree(t.w);
-    if (t.wp) (void)hipFree(t.wp);
+    for (float *p : t.wp)
+        if (p) (void)hipFree(p);
     if (t.y) (void)hipFree(t.y);
     if (t.yref) (void)hipFree(t.yref);
     if (t.dref) (void)hipFree(t.dref);
@@ -779,7 +859,7 @@ static int tune_setup(TuneCtx &t)
     WPK_HIP(hipEventCreate(&t.e1));
     WPK_HIP(hipMalloc((void **)&t.x, pr.x_elems * 4));
     WPK_HIP(hipMalloc((void **)&t.w, pr.w_elems * 4));
-    WPK_HIP(hipMalloc((void **)&t.wp, (size_t)pr.CRSpad * pr.Kpad * 4));
+    for (int split = 0; split < 2; ++split) WPK_HIP(hipMalloc((void **)&t.wp[split], packed_bytes(pr, split != 0)));
     WPK_HIP(hipMalloc((void **)&t.y, pr.y_elems * 4));
     WPK_HIP(hipMalloc((void **)&t.yref, pr.y_elems * 4));
     WPK_HIP(hipMalloc((void **)&t.dref, pr.y_elems * 4));
@@ -792,8 +872,10 @@ static int tune_setup(TuneCtx &t)
     hipLaunchKernelGGL(fill_hash_kernel, dim3(1024), dim3(256), 0, t.st, t.w, (long long)pr.w_elems,
                        0x9876u, -wscale, wscale);
     WPK_HIP(hipGetLastError());
-    rc = pack_weights(pr, t.w, t.wp, t.st);
-    if (rc != WPK_OK) return rc;
+    for (int split = 0; split < 2; ++split) {
+        rc = pack_weights(pr, split != 0, t.w, t.wp[split], t.st);
+        if (rc != WPK_OK) return rc;
+    }
     rc = run_ref(pr, t.x, t.w, t.yref, t.dref, t.st);
     if (rc != WPK_OK) return rc;
     WPK_HIP(hipStreamSynchronize(t.st));
@@ -810,11 +892,13 @@ struct wpk_plan {
         Problem pr;
         wpk_conv_config cfg;
         int unique;
-        float *wp;
+        // packed weights, in the form of the split members ([1]) and of the others ([0]): whichever the layer's
+        // configurations need; the direct kernel's plain [K][C][R][S] weights are in [0]
+        float *wp[2];
         bool has_w;
         float *bias;  // library-owned copy of the layer's bias, or NULL
         int relu;
-        bool direct;  // outside the tiled family: wp holds plain [K][C][R][S] weights for the direct kernel
+        bool direct;  // outside the tiled family
         // two-way pipelining: the batch split into images [0, half[0].d.n) and the rest
         Problem half[2];
         wpk_conv_config half_cfg[2];
@@ -834,6 +918,40 @@ struct wpk_plan {
     bool chk_independent = false;
     std::vector<int32_t> tensor_layout;  // wpk_conv_plan_graph: the layout chosen for every tensor
 };
+
+// Makes sure that the layer holds its weights in the form cfg reads.  A plan allocates when it is built; only a
+// configuration of the other form set afterwards comes here with weights already in place: they are
+// taken from the form at hand (exactly), with the device drained before and after.
+static int plan_need_weights(wpk_plan::Layer &L, const wpk_conv_config &cfg)
+{
+    const int s = split_member(cfg);
+    if (L.wp[s]) return WPK_OK;
+    float *packed = nullptr, *plain = nullptr;
+    WPK_HIP(hipMalloc((void **)&packed, packed_bytes(L.pr, s != 0)));
+    if (!L.has_w) {
+        L.wp[s] = packed;
+        return WPK_OK;
+    }
+    const int RS = L.pr.xquad || L.pr.tapmajor ? L.pr.d.r * L.pr.d.s : 0;
+    int rc = WPK_OK;
+    hipError_t e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = hipMalloc((void **)&plain, (size_t)L.pr.w_elems * sizeof(float));
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(unpack_weights_kernel, dim3((unsigned)std::min<int64_t>(4096, (L.pr.w_elems + 255) / 256)),
+                           dim3(256), 0, nullptr, (const void *)L.wp[1 - s], plain, L.pr.d.k, L.pr.d.c, L.pr.CRS,
+                           L.pr.Kpad, RS, 1 - s);
+        rc = pack_weights(L.pr, s != 0, plain, packed, nullptr);
+        e = hipDeviceSynchronize();
+    }
+    if (plain) (void)hipFree(plain);
+    if (e != hipSuccess) {
+        set_last_hip_error((int)e);
+        rc = WPK_E_HIP;
+    }
+    if (rc == WPK_OK) L.wp[s] = packed;
+    else (void)hipFree(packed);
+    return rc;
+}
 
 extern "C" {
 
@@ -967,11 +1085,13 @@ int wpk_conv2d_fwd(const wpk_conv_desc *d, const float *x, const float *w, float
 // the counters stay where they are from call to call, so they are zero whenever a launch starts.
 // In host code the array's name is only a handle: its device address is asked for once per
 // device and kept.
-static __device__ __align__(256) unsigned char scratch[WPK_NOALLOC_SCRATCH_BYTES];
-static const int kScratchMaxDevices = 64;
-static char *g_scratch_ptr[kScratchMaxDevices];   // per device, filled on first use (under g_mu)
 static const size_t kScratchTapBytes = 64 << 10;
 static const size_t kScratchRoom = (size_t)WPK_NOALLOC_SCRATCH_BYTES - kScratchTapBytes - (size_t)kFixupCounterBytes;
+// (the limits are stated for weights of four bytes; the split members' take six, and so does the array's room)
+static const size_t kScratchRoomSplit = kScratchRoom / sizeof(float) * kSplitWeightBytes;
+static __device__ __align__(256) unsigned char scratch[kScratchTapBytes + kFixupCounterBytes + kScratchRoomSplit];
+static const int kScratchMaxDevices = 64;
+static char *g_scratch_ptr[kScratchMaxDevices];   // per device, filled on first use (under g_mu)
 
 extern "C" int wpk_conv2d_fwd_noalloc(const wpk_conv_desc *d, const wpk_conv_config *cfg_in, const float *x,
                                       const float *w, float *y, void *stream)
@@ -1002,15 +1122,16 @@ extern "C" int wpk_conv2d_fwd_noalloc(const wpk_conv_desc *d, const wpk_conv_con
     if (cfg_in) cfg = *cfg_in;
     else if (wpk_cache_lookup(d, &cfg) != 1 || !legal_for(pr, cfg)) default_config(pr, g_cus, &cfg);
     auto round256 = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t wbytes = round256((size_t)pr.CRSpad * pr.Kpad * sizeof(float));
-    if (tap_table_bytes(pr) > kScratchTapBytes || wbytes > kScratchRoom) return WPK_E_TOO_LARGE;
+    const bool split = split_member(cfg);
+    const size_t wbytes = round256(packed_bytes(pr, split)), room = split ? kScratchRoomSplit : kScratchRoom;
+    if (tap_table_bytes(pr) > kScratchTapBytes || round256(packed_bytes(pr, false)) > kScratchRoom) return WPK_E_TOO_LARGE;
     // shared tiles meet in the slots if they fit beside the weights, else through atomics into y
     const FixupNeed need = fixup_need(pr, cfg, g_cus);
     const size_t slot_bytes = need.bytes > 0 ? round256((size_t)(need.bytes - need.slots_offset)) : 0;
     FixupBuf fix;
     fix.ptr = base + kScratchTapBytes;
     fix.bytes = 0;
-    if (need.bytes > 0 && wbytes + slot_bytes <= kScratchRoom) fix.bytes = (size_t)need.bytes;
+    if (need.bytes > 0 && wbytes + slot_bytes <= room) fix.bytes = (size_t)need.bytes;
     float *const wp = (float *)(base + kScratchTapBytes + kFixupCounterBytes + (fix.bytes ? slot_bytes : 0));
     int32_t *const ktab = (int32_t *)base;
     if (fix.bytes) {
@@ -1023,7 +1144,7 @@ extern "C" int wpk_conv2d_fwd_noalloc(const wpk_conv_desc *d, const wpk_conv_con
     }
     rc = write_tap_table(pr, ktab, st);
     if (rc != WPK_OK) return rc;
-    rc = pack_weights(pr, w, wp, st);
+    rc = pack_weights(pr, split, w, wp, st);
     if (rc != WPK_OK) return rc;
     return run_config(pr, cfg, ktab, x, wp, y, fix.bytes ? &fix : nullptr, st);
 }
@@ -1093,7 +1214,7 @@ int wpk_conv_tune_ex(const wpk_conv_desc *d, const wpk_tune_options *opt_in, int
     t.pr = pr;
     if (opt_in) t.opt = *opt_in; else wpk_tune_default_options(&t.opt);
     t.st = nullptr; t.e0 = t.e1 = nullptr;
-    t.x = t.w = t.wp = t.y = t.yref = t.dref = nullptr;
+    t.x = t.w = t.wp[0] = t.wp[1] = t.y = t.yref = t.dref = nullptr;
     t.err_bits = nullptr; t.ktab = nullptr;
     t.rejected = 0; t.hip_failed = 0;
     t.phase = WPK_STAGE_SEARCH;
@@ -1371,7 +1492,7 @@ static int layer_runtime_us(const wpk_conv_desc *d, int32_t tune, double *us)
     wpk_tune_default_options(&t.opt);
     t.opt.reps = 3;
     t.st = nullptr; t.e0 = t.e1 = nullptr;
-    t.x = t.w = t.wp = t.y = t.yref = t.dref = nullptr;
+    t.x = t.w = t.wp[0] = t.wp[1] = t.y = t.yref = t.dref = nullptr;
     t.err_bits = nullptr; t.ktab = nullptr;
     t.rejected = 0; t.hip_failed = 0;
     t.phase = WPK_STAGE_DEFAULT;
@@ -1463,7 +1584,7 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
         wpk_plan::Layer L;
         rc = make_problem(&layers[i], &L.pr);
         if (rc != WPK_OK) break;
-        L.wp = nullptr;
+        L.wp[0] = L.wp[1] = nullptr;
         L.has_w = false;
         L.bias = nullptr;
         L.relu = 0;
@@ -1471,7 +1592,7 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
         if (L.direct) {  // oversized filter, or a channels-last shape the tiled gather does not take
             memset(&L.cfg, 0, sizeof L.cfg);
             L.unique = -1;
-            hipError_t e = hipMalloc((void **)&L.wp, (size_t)L.pr.w_elems * sizeof(float));
+            hipError_t e = hipMalloc((void **)&L.wp[0], (size_t)L.pr.w_elems * sizeof(float));
             if (e != hipSuccess) { set_last_hip_error((int)e); rc = WPK_E_HIP; break; }
             plan->layers.push_back(L);
             continue;
@@ -1492,9 +1613,9 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
         L.unique = it->second;
         if (wpk_cache_lookup(&layers[i], &L.cfg) != 1 || !legal_for(L.pr, L.cfg))
             default_config(L.pr, g_cus, &L.cfg);
-        hipError_t e = hipMalloc((void **)&L.wp, (size_t)L.pr.CRSpad * L.pr.Kpad * sizeof(float));
-        if (e != hipSuccess) { set_last_hip_error((int)e); rc = WPK_E_HIP; break; }
+        rc = plan_need_weights(L, L.cfg);
         plan->layers.push_back(L);
+        if (rc != WPK_OK) break;
         FixupNeed need = fixup_need(L.pr, L.cfg, g_cus);
         if (need.bytes > 0) rc = fixup_reserve(plan->fix, (size_t)need.bytes);
     }
@@ -1516,12 +1637,14 @@ int wpk_plan_set_weights(wpk_plan *plan, int32_t layer, const float *w, void *st
     if (layer < 0 || layer >= (int)plan->layers.size()) return WPK_E_BAD_ARG;
     wpk_plan::Layer &L = plan->layers[layer];
     if (L.direct) {
-        WPK_HIP(hipMemcpyAsync(L.wp, w, (size_t)L.pr.w_elems * sizeof(float), hipMemcpyDeviceToDevice,
+        WPK_HIP(hipMemcpyAsync(L.wp[0], w, (size_t)L.pr.w_elems * sizeof(float), hipMemcpyDeviceToDevice,
                                (hipStream_t)stream));
         L.has_w = true;
         return WPK_OK;
     }
-    int rc = pack_weights(L.pr, w, L.wp, (hipStream_t)stream);
+    int rc = WPK_OK;
+    for (int s = 0; s < 2 && rc == WPK_OK; ++s)
+        if (L.wp[s]) rc = pack_weights(L.pr, s != 0, w, L.wp[s], (hipStream_t)stream);
     if (rc == WPK_OK) L.has_w = true;
     return rc;
 }
@@ -1557,11 +1680,11 @@ static int plan_launch(wpk_plan *plan, wpk_plan::Layer &L, int which, const floa
     Epilogue epi;
     epi.bias = L.bias; epi.res = residual; epi.relu = L.relu;
     if (L.direct) {
-        int rc = run_ref(pr, x, L.wp, y, nullptr, st);
+        int rc = run_ref(pr, x, L.wp[0], y, nullptr, st);
         return rc != WPK_OK ? rc : run_epilogue(pr, epi, y, st);
     }
-    return run_config(pr, cfg, plan->ktabs[L.unique], x, L.wp, y, which == 1 ? &plan->fix_side : &plan->fix,
-                      st, epi, y_zeroed);
+    return run_config(pr, cfg, plan->ktabs[L.unique], x, L.wp[split_member(cfg)], y,
+                      which == 1 ? &plan->fix_side : &plan->fix, st, epi, y_zeroed);
 }
 
 static int plan_fork(wpk_plan *plan, hipStream_t user)
@@ -1618,6 +1741,8 @@ int wpk_plan_set_pipeline(wpk_plan *plan, int32_t ways)
             if (L.direct) continue;
             if (wpk_cache_lookup(&d, &L.half_cfg[h]) != 1 || !legal_for(L.half[h], L.half_cfg[h]))
                 default_config(L.half[h], g_cus, &L.half_cfg[h]);
+            rc = plan_need_weights(L, L.half_cfg[h]);
+            if (rc != WPK_OK) return rc;
             FixupNeed need = fixup_need(L.half[h], L.half_cfg[h], g_cus);
             if (need.bytes > 0) {
                 rc = fixup_reserve(h == 0 ? plan->fix : plan->fix_side, (size_t)need.bytes);
@@ -1776,6 +1901,8 @@ int wpk_plan_set_layer_config(wpk_plan *plan, int32_t layer, const wpk_conv_conf
     if (!plan || !cfg) return WPK_E_NULL_PTR;
     if (layer < 0 || layer >= (int)plan->layers.size()) return WPK_E_BAD_ARG;
     if (plan->layers[layer].direct || !legal_for(plan->layers[layer].pr, *cfg)) return WPK_E_NO_CONFIG;
+    int rw = plan_need_weights(plan->layers[layer], *cfg);
+    if (rw != WPK_OK) return rw;
     FixupNeed need = fixup_need(plan->layers[layer].pr, *cfg, g_cus);
     if (need.bytes > (int64_t)plan->fix.bytes) {
         WPK_HIP(hipDeviceSynchronize());  // the old workspace may still be in use
@@ -1805,7 +1932,8 @@ void wpk_plan_destroy(wpk_plan *plan)
 {
     if (!plan) return;
     for (auto &L : plan->layers) {
-        if (L.wp) (void)hipFree(L.wp);
+        for (float *p : L.wp)
+            if (p) (void)hipFree(p);
         if (L.bias) (void)hipFree(L.bias);
     }
     for (int32_t *t : plan->ktabs)

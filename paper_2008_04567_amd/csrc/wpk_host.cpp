@@ -173,6 +173,7 @@ bool legal_for(const Problem &pr, const wpk_conv_config &cfg)
     } else {
         if (2 * (cfg.bk + 4) * (cfg.bm + cfg.bn) * 4 > kMaxLdsBytes) return false;    // two LDS stages
         if (threads > cfg.bm && (cfg.bk * cfg.bm / threads) % 4 != 0) return false;   // whole k quads per thread
+        if (split_member(cfg) && (int64_t)pr.CRSpad * pr.Kpad * kSplitWeightBytes > kMaxTiledBytes) return false;
     }
     int32_t nsteps = (pr.CRS + cfg.bk - 1) / cfg.bk;
     if (cfg.split_k > nsteps) return false;
@@ -190,6 +191,39 @@ bool legal_for(const Problem &pr, const wpk_conv_config &cfg)
     return true;
 }
 
+int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
+{
+    const wpk_conv_desc &d = pr.d;
+    if (!split_member(cfg) || cfg.bk != 16 || cfg.bm != 64 || cfg.bn != 32 * cfg.wn || !(pr.tapmajor || pr.xquad) || d.r != 3 || d.s != 3) return 0;
+    if (d.pad_h > 2 * (int64_t)d.dil_h || d.pad_w > 2 * (int64_t)d.dil_w) return 0;
+    // From the first pixel's window to the last one's: bm - 1 steps along the row, for every change of row
+    // what the next row's start is further away than a step, for every change of image alike; then the window itself.
+    const int64_t W = d.w, HW = (int64_t)d.h * W, PQ = (int64_t)pr.P * pr.Q, n = cfg.bm - 1;
+    const int64_t rows = (n + pr.Q - 1) / pr.Q, images = (n + PQ - 1) / PQ;
+    const int64_t span = n * d.stride_w + rows * std::max<int64_t>(0, d.stride_h * W - (int64_t)pr.Q * d.stride_w) +
+                         images * std::max<int64_t>(0, HW - pr.P * d.stride_h * W) +
+                         2 * ((int64_t)d.dil_h * W + d.dil_w) + 1;
+    return span <= kHaloMax ? (int)span : 0;
+}
+
+Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg)
+{
+    if (halo_positions(pr, cfg) > 0) return Reduction{pr.d.c / 16, 9 * 16};
+    const int rows = split_member(cfg) ? 32 : cfg.bk;
+    return Reduction{(pr.CRS + rows - 1) / rows, rows};
+}
+
+// A split member whose tiles make up one round that fills more than half of the persistent workgroups
+// runs them whole, a workgroup each: dealing the steps of every tile out would have all of them meet in memory
+// (3x3, 128 channels, 28x28, 16 images, 196 tiles on 256 compute units: 22.4 us whole, 28.7 dealt out).
+int persistent_of(const Problem &pr, const wpk_conv_config &cfg, int compute_units)
+{
+    if (cfg.persist == 0 || !split_member(cfg)) return cfg.persist;
+    const int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
+    const int64_t G = (int64_t)cfg.persist * (compute_units > 0 ? compute_units : 256);
+    return tiles <= G && 2 * tiles > G ? 0 : cfg.persist;
+}
+
 // Workspace of the persistent schedule's fix-up: the tiles beyond the last whole round are shared;
 // a tile of nsteps consecutive units cut into runs of at least q units meets at most
 // ceil((nsteps-1)/q) + 1 runs (every run holds one unit when there are fewer units than runs).
@@ -201,15 +235,16 @@ FixupNeed fixup_need(const Problem &pr, const wpk_conv_config &cfg, int compute_
     if (cfg.reduce != 0) return n;  // atomics asked for
     if (compute_units <= 0) compute_units = 256;
     int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
-    int64_t nsteps = (pr.CRS + cfg.bk - 1) / cfg.bk;
-    if (cfg.persist > 0) {
+    const Reduction red = reduction_of(pr, cfg);
+    const int64_t nsteps = red.steps;
+    if (const int persist = persistent_of(pr, cfg, compute_units)) {
         // tiles of the last partial round, their steps dealt in runs of q or q+1 to at most G
         // workgroups: a tile's nsteps steps meet at most ceil((nsteps-1)/q)+1 runs, and never
         // more than nsteps
-        int64_t G = (int64_t)cfg.persist * compute_units;
+        int64_t G = (int64_t)persist * compute_units;
         int64_t shared = tiles - tiles / G * G;
         if (shared == 0 || nsteps <= 1) return n;
-        int64_t q = shared * nsteps / streamk_groups(shared * nsteps, G, cfg.bk);
+        int64_t q = shared * nsteps / streamk_groups(shared * nsteps, G, red.rows);
         n.shared_tiles = shared;
         n.maxc = q > 0 ? std::min<int64_t>(nsteps, (nsteps - 1 + q - 1) / q + 1) : nsteps;
     } else {
@@ -260,6 +295,55 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
     *out = c;
     return true;
 }
+// The split members' default, where filter taps are fetched whole (C a multiple of 32; row by row they gain nothing over
+// the tiled members: 24 against 22 us on 72 channels).  Waves of 64 pixels by 32 channels; patches where a 3x3
+// layer allows them.
+//  - As many waves per workgroup as the channels call for, four at most: a wider workgroup fetches and splits its pixels
+//    for more channels at once; what that is worth against padded channels is the weight of 20 / bn, from the measured
+//    times of 64- and 128-channel tiles.  1x1 layers fetched four pixels at a time take two: fetching is cheap there, the
+//    launch is bound by memory, and four small workgroups on a compute unit are out of step with each other where two
+//    large ones fetch, multiply and store at the same time (256 to 128 channels, 56x56, 16 images: 29.5 us against 42;
+//    256 to 1024 at 14x14: 15.3 against 21.4).
+//  - The reduction is cut until there is about one wave per SIMD, no further: a second wave hides what a second
+//    slice's prologue and meeting cost, no more (3x3, 256 channels, 14x14, 16 images, 98 tiles: 25.5 us in 2 slices,
+//    27-30 in 1 or 3-5; 512 channels at 7x7, 52 tiles: 28.0 in 4, 28.7 in 3, 32.6 in 8).
+static bool split_default(const Problem &pr, int compute_units, wpk_conv_config *out)
+{
+    if (!(pr.tapmajor || pr.xquad)) return false;
+    const bool point = split_point(pr);
+    int wn = 4;
+    double best = 1e300;
+    for (int w = point ? 2 : 4; w >= 1; w /= 2) {
+        const int bn = 32 * w;
+        const double cost = (double)((pr.d.k + bn - 1) / bn * bn) * (1.0 + 20.0 / bn);
+        if (cost < best) {
+            best = cost;
+            wn = w;
+        }
+    }
+    wpk_conv_config c = {64, 32 * wn, 16, 1, wn, 1, 1, 0, 1, 0};
+    if (halo_positions(pr, c) == 0) c.bk = 32;
+    const Reduction red = reduction_of(pr, c);
+    const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);
+    const int64_t want = point ? 5 * (int64_t)compute_units / 2 : 4 / wn * (int64_t)compute_units;
+    const int64_t G = 3 * (int64_t)compute_units;
+    if (2 * tiles <= want) {
+        // (slices of 64 rows at least, see kMinRunRows)
+        const int64_t most = std::min<int64_t>(want / tiles, red.steps / std::max(1, kMinRunRows / red.rows));
+        for (int i = 0; i < kGeneCounts[5]; ++i)
+            if (kSplitVals[i] <= most) c.split_k = kSplitVals[i];
+    } else if (tiles <= want) {
+        c.persist = std::min(4 / wn, 2);  // one round: whole tiles (persistent_of)
+    } else if (wn <= 2 && tiles > G && tiles % G * 8 <= G) {
+        // just over whole rounds of three workgroups per compute unit: the tiles left over are dealt out
+        // (3x3, 64 channels, 56x56, 16 images, 784 tiles: 25.0 us against 25.4 with a workgroup per tile; 1x1, 256 to 128
+        // channels, 1568 tiles: 29.5 against 31.4)
+        c.persist = 3;
+    }
+    if (!legal_for(pr, c)) return false;
+    *out = c;
+    return true;
+}
 void default_config(const Problem &pr, int compute_units, wpk_conv_config *out)
 {
     if (compute_units <= 0) compute_units = 256;
@@ -269,6 +353,7 @@ void default_config(const Problem &pr, int compute_units, wpk_conv_config *out)
     // four slices or more add up with atomics.  (Measured on the single-image ResNet-50 layers: 4.3-9.8 us where
     // the tiled members' best is 4.9-10.6.)
     if (wave_split_default(pr, compute_units, out)) return;
+    if (split_default(pr, compute_units, out)) return;
     wpk_conv_config c = {64, pr.d.k <= 32 ? 32 : 64, pr.CRS >= 64 ? 32 : pr.CRS >= 32 ? 16 : 8, 2,
                          pr.d.k <= 32 ? 1 : 2, 1, 1, 0, 2, 0};
     int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);

@@ -30,6 +30,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -176,10 +177,12 @@ __device__ __forceinline__ void pixel_window(const ARGS c, const int m, int &vof
 }
 
 // ---- what leaves a wave: its NNT x NMT accumulator blocks, whose first pixel is mbase and first
-//      channel nbase, go to y -- plain stores with the fused epilogue applied, or fp32 atomics ----
+//      channel nbase, go to y -- plain stores with the fused epilogue applied, or fp32 atomics.  lds_bias, where
+//      given: the bias of channels nbase .. in LDS, zeros where there is none ----
 template <int NNT, int NMT, class ARGS>
 __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)[NNT * NMT], const int mbase,
-                                                const int nbase, const int lrow, const int lcol, const bool atomic)
+                                                const int nbase, const int lrow, const int lcol, const bool atomic,
+                                                const float *const lds_bias = nullptr)
 {
     // the host applies the epilogue itself after a launch that accumulates with atomics
     const bool fused = !atomic && (ce->bias || ce->res || ce->relu);
@@ -223,8 +226,9 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
                         if (fused)
                             static_for<4>([&](auto G) WPK_LAMBDA {
                                 constexpr int g = decltype(G)::value;
-                                v4f t = __builtin_bit_cast(
-                                    v4f, __builtin_amdgcn_raw_buffer_load_b128(brsrc, kbase * 4, 32 * g, 0));
+                                v4f t = lds_bias ? *reinterpret_cast<const v4f *>(lds_bias + i * 32 + 4 * lrow + 8 * g)
+                                                 : __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                                                                               brsrc, kbase * 4, 32 * g, 0));
                                 if (full || kbase + 8 * g < ce->K)
                                     t += __builtin_bit_cast(
                                         v4f, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, voff, 32 * g, 0));
@@ -255,8 +259,9 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
                         float add[16];
                         static_for<16>([&](auto E) WPK_LAMBDA {
                             constexpr int e = decltype(E)::value, de = 8 * (e / 4) + (e & 3);
-                            float t = __builtin_bit_cast(
-                                float, __builtin_amdgcn_raw_buffer_load_b32(brsrc, kbase * 4, de * 4, 0));
+                            float t = lds_bias ? lds_bias[i * 32 + 4 * lrow + de]
+                                               : __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                                               brsrc, kbase * 4, de * 4, 0));
                             if (full || kbase + de < ce->K)
                                 t += __builtin_bit_cast(
                                     float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, voff, de * PQ4, 0));
@@ -308,6 +313,183 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
             });
         }
     });
+}
+
+// How the result of one segment of work leaves a workgroup:
+//   kStore  plain stores (the segment is the tile's whole reduction);
+//   kAtomic fp32 atomics into y, which the host zeroed (no workspace given);
+//   kFixup  the tile is shared by fix_n workgroups (reduction slices, or neighbouring runs of a
+//           persistent launch), this one being number fix_slot: each stores its partial tile to its
+//           slot of the workspace and bumps the tile's arrival counter; whoever arrives last adds up the
+//           other slots and stores y.  Nobody waits for anybody, y needs no zeroing, and the counter is
+//           back at zero when the kernel ends.
+enum SegmentMode { kStore = 0, kAtomic = 1, kFixup = 2 };
+
+// The meeting of a shared tile (kFixup) for a workgroup of T lanes whose lanes hold NBLK accumulator blocks
+// each.  True for the last to arrive, whose accumulators then hold the whole sum.
+template <int NBLK, int T>
+__device__ __forceinline__ bool meet_shared_tile(const cold_ptr ce, v16f (&acc)[NBLK], const int slot_floats,
+                                                 const int tid, const int fix_j, const int fix_slot,
+                                                 const int fix_n, int *const arrival)
+{
+    // Slot layout: accumulator quad (ij, e4) of thread t at float (ij*4 + e4)*4*T + 4*t.
+    // Partials travel between workgroups that may sit on different XCDs, whose L2 caches do
+    // not snoop each other.  Instead of fences that write back and invalidate whole caches,
+    // the partials alone are stored and loaded with the system-scope cache policy (write
+    // through / read past the non-coherent levels); everything else stays cached.
+    constexpr int kCoherent = 17;  // sc0 | sc1
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(ce->ws + (size_t)fix_j * ce->ws_maxc * slot_floats), 0, ce->ws_maxc * slot_floats * 4,
+        0x00020000);
+    const int mine = (fix_slot * slot_floats + 4 * tid) * 4;
+    static_for<NBLK * 4>([&](auto Q) WPK_LAMBDA {
+        constexpr int qd = decltype(Q)::value, ij = qd / 4, e4 = qd % 4;
+        v4f v = {acc[ij][4 * e4], acc[ij][4 * e4 + 1], acc[ij][4 * e4 + 2], acc[ij][4 * e4 + 3]};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), srsrc, mine, qd * 16 * T, kCoherent);
+    });
+    // every store of this wave acknowledged, then every wave of the workgroup, before the
+    // arrival is counted
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) *arrival = atomicAdd(ce->ws_cnt + fix_j, 1);
+    __syncthreads();
+    const int arrived_before = *arrival;
+    __syncthreads();  // everyone has read `arrival` before a later segment overwrites it
+    if (arrived_before != fix_n - 1) return false;
+    if (tid == 0) ce->ws_cnt[fix_j] = 0;        // leave the counter clean for the next launch
+    // Add the other workgroups' slots to this one's accumulators.
+    if constexpr (NBLK == 1) {
+        // a single 32x32 block per wave has little to load per slot: four slots at a time, all
+        // requested before the first is added, so the sharers of a tile cost one memory round
+        // trip per four of them (a slot number past the last becomes an out-of-range offset,
+        // which loads 0)
+        constexpr int kGang = 4;
+        for (int t0 = 0; t0 < fix_n - 1; t0 += kGang) {
+            v4f part[kGang][4];
+            static_for<kGang>([&](auto U) WPK_LAMBDA {
+                constexpr int u = decltype(U)::value;
+                const int t = t0 + u, sl = t + (t >= fix_slot ? 1 : 0);  // t-th slot not mine
+                const unsigned off = t < fix_n - 1 ? (unsigned)((sl * slot_floats + 4 * tid) * 4) : 0xffffffffu;
+                static_for<4>([&](auto Q) WPK_LAMBDA {
+                    constexpr int qd = decltype(Q)::value;
+                    part[u][qd] = __builtin_bit_cast(
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(srsrc, off, qd * 16 * T, kCoherent));
+                });
+            });
+            static_for<4 * kGang>([&](auto UQ) WPK_LAMBDA {
+                constexpr int u = decltype(UQ)::value / 4, qd = decltype(UQ)::value % 4;
+                acc[0][4 * qd] += part[u][qd][0];
+                acc[0][4 * qd + 1] += part[u][qd][1];
+                acc[0][4 * qd + 2] += part[u][qd][2];
+                acc[0][4 * qd + 3] += part[u][qd][3];
+            });
+        }
+    } else {
+        for (int sl = 0; sl < fix_n; ++sl) {
+            if (sl == fix_slot) continue;
+            const int other = (sl * slot_floats + 4 * tid) * 4;
+            static_for<NBLK * 4>([&](auto Q) WPK_LAMBDA {
+                constexpr int qd = decltype(Q)::value, ij = qd / 4, e4 = qd % 4;
+                v4f v = __builtin_bit_cast(
+                    v4f, __builtin_amdgcn_raw_buffer_load_b128(srsrc, other, qd * 16 * T, kCoherent));
+                acc[ij][4 * e4] += v[0];
+                acc[ij][4 * e4 + 1] += v[1];
+                acc[ij][4 * e4 + 2] += v[2];
+                acc[ij][4 * e4 + 3] += v[3];
+            });
+        }
+    }
+    return true;
+}
+
+// Which segments of work a workgroup runs: run(tile, kbeg, kend, mode, fix_j, fix_slot, fix_n) for each.
+// persist == 0: one workgroup per (tile, reduction slice): blockIdx -> tile, slice; the slices
+//   of a tile meet through the workspace if the host gave one, else through atomics.
+// persist  > 0: gridDim.x = G persistent workgroups.  Each takes whole tiles g, g+G, ...
+//   of the first tiles_dp = floor(tiles/G)*G tiles.  The reduction steps of the remaining
+//   tiles, laid end to end (`units` of them), are cut into runs of q or q+1 steps (the first
+//   `rem` get q+1), sk_groups of them: G, unless that would make the runs too short to be
+//   worth a prologue.  Either sk_groups further workgroups are appended to the grid and take
+//   one run each (a.runners: whenever all of them fit the device beside the G), or each of
+//   the first sk_groups workgroups does a run first, then its whole tiles.  A run that does
+//   not cover a tile's whole reduction shares the tile with its neighbours in g: fix-up
+//   through the workspace if the host gave one, else atomics into zeroed y.
+// (tiles_dp, sk_groups, q = sk_q, rem = sk_rem and the divisors come from the host: they
+// depend on the launch alone, and all of it fits 32 bits)
+template <class F>
+__device__ __forceinline__ void for_each_segment(const IgemmArgs &a, F &&run)
+{
+    const bool persistent = a.persist > 0;
+    const int g = blockIdx.x;
+    // With a.runners > 0 the grid is grid_persist + runners workgroups: the first grid_persist take
+    // whole tiles only, the others one dealt-out run each and nothing else, so that a run and a
+    // whole tile of the same compute unit proceed side by side instead of one after the other.
+    const int G = a.runners ? a.grid_persist : (int)gridDim.x;
+    const bool runner = a.runners && g >= G;
+    int next_dp = g;
+    // (remap: run number gr instead of g, so that consecutive runs -- neighbouring tiles, the
+    // slices of one tile -- sit on one XCD and share its L2; G is a multiple of the number of XCDs,
+    // so a runner's XCD is (g - G) % 8 as well)
+    const int gl = runner ? g - G : g;
+    const int gr = a.remap ? xcd_remap(gl, runner ? a.runners : G) : gl;
+    int u0, u1;
+    {
+        const cold_ptr c = cold_args();
+        const int q = c->sk_q, rem = c->sk_rem;
+        const bool dealt = persistent && gr < c->sk_groups && (!a.runners || runner);
+        u0 = dealt ? gr * q + min(gr, rem) : 0;
+        u1 = dealt ? (gr + 1) * q + min(gr + 1, rem) : 0;
+        if (runner) next_dp = c->tiles_dp;  // no whole tiles
+    }
+    bool once = !persistent;
+    for (;;) {
+        int tile, kbeg, kend, mode = kStore, fix_j = 0, fix_slot = 0, fix_n = 1;
+        const cold_ptr c = cold_args();   // the iterator's constants, once per segment
+        if (once) {
+            once = false;
+            const int slice = fdiv(gr, WPK_COLD_DIV(c, div_tiles));
+            tile = gr - slice * c->tiles;
+            kbeg = slice * c->steps_per_split;
+            kend = min(a.nsteps, kbeg + c->steps_per_split);
+            if (c->split_k > 1) {
+                mode = c->ws ? kFixup : kAtomic;
+                fix_j = tile;
+                fix_slot = slice;
+                fix_n = c->split_k;
+            }
+        } else if (persistent && u0 < u1) {
+            // (the dealt-out run comes BEFORE the workgroup's whole tiles: the sharers of a tile then
+            // meet while everybody else still has whole tiles to multiply, instead of after it, when
+            // the chain of memory round trips of the meeting would be all the device has left to do)
+            const int q = c->sk_q, rem = c->sk_rem;
+            auto owner_of = [&](int u) {  // which workgroup's run holds unit u
+                if (u < rem * (q + 1)) return fdiv(u, WPK_COLD_DIV(c, div_q1));
+                return rem + fdiv(u - rem * (q + 1), WPK_COLD_DIV(c, div_q0));
+            };
+            fix_j = fdiv(u0, WPK_COLD_DIV(c, div_nsteps));
+            tile = c->tiles_dp + fix_j;
+            kbeg = u0 - fix_j * a.nsteps;
+            kend = min(a.nsteps, kbeg + (u1 - u0));
+            u0 += kend - kbeg;
+            if (!(kbeg == 0 && kend == a.nsteps)) {
+                const int first = owner_of(fix_j * a.nsteps);
+                fix_n = owner_of((fix_j + 1) * a.nsteps - 1) - first + 1;
+                fix_slot = gr - first;
+                mode = c->ws ? kFixup : kAtomic;
+            }
+        } else if (persistent && next_dp < c->tiles_dp) {
+            // (remap: within a round, each XCD takes a contiguous range of the round's G tiles, so
+            // that tiles which share rows of x share an L2)
+            tile = next_dp - g + gr;
+            kbeg = 0;
+            kend = a.nsteps;
+            next_dp += G;
+        } else {
+            break;
+        }
+        run(tile, kbeg, kend, mode, fix_j, fix_slot, fix_n);
+    }
 }
 
 // XL = 0: reduction rows ordered (c, r, s) and gathered one row at a time as described above, for
@@ -370,16 +552,7 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
     const int wstep_bytes = (BK / 4) * a.Kpad * 16;  // one reduction step further
     const int wquad_bytes = (T / BN) * a.Kpad * 16;  // this thread's next quad in the same step
 
-    // One segment of work: reduction steps [kbeg, kend) of output tile `tile`.  How the result
-    // leaves the workgroup (mode):
-    //   kStore  plain stores (the segment is the tile's whole reduction);
-    //   kAtomic fp32 atomics into y, which the host zeroed (no workspace given);
-    //   kFixup  the tile is shared by fix_n workgroups (reduction slices, or neighbouring runs
-    //           of a persistent launch), this one being number fix_slot: each stores its partial
-    //           tile to its slot of the workspace and bumps the tile's arrival counter; whoever
-    //           arrives last adds up the other slots and stores y.  Nobody waits for anybody, y
-    //           needs no zeroing, and the counter is back at zero when the kernel ends.
-    enum { kStore = 0, kAtomic = 1, kFixup = 2 };
+    // One segment of work: reduction steps [kbeg, kend) of output tile `tile`.
     __shared__ int arrival;
     auto run_segment = [&](const int tile, const int kbeg, const int kend, const int mode,
                            const int fix_j, const int fix_slot, const int fix_n) WPK_LAMBDA {
@@ -669,172 +842,23 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
     }
 
     const cold_ptr ce = cold_args();  // (after the steps: what the meeting and the stores need)
-    // ---- fix-up of a shared tile -----------------------------------------------------------------
-    if (mode == kFixup) {
-        // Slot layout: accumulator quad (ij, e4) of thread t at float (ij*4 + e4)*4*T + 4*t.
-        // Partials travel between workgroups that may sit on different XCDs, whose L2 caches do
-        // not snoop each other.  Instead of fences that write back and invalidate whole caches,
-        // the partials alone are stored and loaded with the system-scope cache policy (write
-        // through / read past the non-coherent levels); everything else stays cached.
-        constexpr int kCoherent = 17;  // sc0 | sc1
-        const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(ce->ws + (size_t)fix_j * ce->ws_maxc * (BM * BN)), 0, ce->ws_maxc * (BM * BN) * 4,
-            0x00020000);
-        const int mine = (fix_slot * (BM * BN) + 4 * tid) * 4;
-        static_for<NNT * NMT * 4>([&](auto Q) WPK_LAMBDA {
-            constexpr int qd = decltype(Q)::value, ij = qd / 4, e4 = qd % 4;
-            v4f v = {acc[ij][4 * e4], acc[ij][4 * e4 + 1], acc[ij][4 * e4 + 2], acc[ij][4 * e4 + 3]};
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), srsrc, mine,
-                                                   qd * 16 * T, kCoherent);
-        });
-        // every store of this wave acknowledged, then every wave of the workgroup, before the
-        // arrival is counted
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (tid == 0) arrival = atomicAdd(ce->ws_cnt + fix_j, 1);
-        __syncthreads();
-        const int arrived_before = arrival;
-        __syncthreads();  // everyone has read `arrival` before a later segment overwrites it
-        if (arrived_before != fix_n - 1) return;  // not the last: done with this tile
-        if (tid == 0) ce->ws_cnt[fix_j] = 0;        // leave the counter clean for the next launch
-        // Add the other workgroups' slots to this one's accumulators.
-        if constexpr (NNT * NMT == 1) {
-            // a single 32x32 block per wave has little to load per slot: four slots at a time, all
-            // requested before the first is added, so the sharers of a tile cost one memory round
-            // trip per four of them (a slot number past the last becomes an out-of-range offset,
-            // which loads 0)
-            constexpr int kGang = 4;
-            for (int t0 = 0; t0 < fix_n - 1; t0 += kGang) {
-                v4f part[kGang][4];
-                static_for<kGang>([&](auto U) WPK_LAMBDA {
-                    constexpr int u = decltype(U)::value;
-                    const int t = t0 + u, sl = t + (t >= fix_slot ? 1 : 0);  // t-th slot not mine
-                    const unsigned off =
-                        t < fix_n - 1 ? (unsigned)((sl * (BM * BN) + 4 * tid) * 4) : 0xffffffffu;
-                    static_for<4>([&](auto Q) WPK_LAMBDA {
-                        constexpr int qd = decltype(Q)::value;
-                        part[u][qd] = __builtin_bit_cast(
-                            v4f, __builtin_amdgcn_raw_buffer_load_b128(srsrc, off, qd * 16 * T, kCoherent));
-                    });
-                });
-                static_for<4 * kGang>([&](auto UQ) WPK_LAMBDA {
-                    constexpr int u = decltype(UQ)::value / 4, qd = decltype(UQ)::value % 4;
-                    acc[0][4 * qd] += part[u][qd][0];
-                    acc[0][4 * qd + 1] += part[u][qd][1];
-                    acc[0][4 * qd + 2] += part[u][qd][2];
-                    acc[0][4 * qd + 3] += part[u][qd][3];
-                });
-            }
-        } else {
-            for (int sl = 0; sl < fix_n; ++sl) {
-                if (sl == fix_slot) continue;
-                const int other = (sl * (BM * BN) + 4 * tid) * 4;
-                static_for<NNT * NMT * 4>([&](auto Q) WPK_LAMBDA {
-                    constexpr int qd = decltype(Q)::value, ij = qd / 4, e4 = qd % 4;
-                    v4f v = __builtin_bit_cast(
-                        v4f, __builtin_amdgcn_raw_buffer_load_b128(srsrc, other, qd * 16 * T, kCoherent));
-                    acc[ij][4 * e4] += v[0];
-                    acc[ij][4 * e4 + 1] += v[1];
-                    acc[ij][4 * e4 + 2] += v[2];
-                    acc[ij][4 * e4 + 3] += v[3];
-                });
-            }
-        }
-    }
+    if (mode == kFixup &&
+        !meet_shared_tile<NNT * NMT, T>(ce, acc, BM * BN, tid, fix_j, fix_slot, fix_n, &arrival))
+        return;  // not the last: done with this tile
     store_wave_tile<NNT, NMT>(ce, acc, m0 + wave_m * TM, n0 + wave_n * TN, lrow, lcol, mode == kAtomic);
     };  // run_segment
 
-    // ---- which segments this workgroup runs ----------------------------------------------------
-    // persist == 0: one workgroup per (tile, reduction slice): blockIdx -> tile, slice; the slices
-    //   of a tile meet through the workspace if the host gave one, else through atomics.
-    // persist  > 0: gridDim.x = G persistent workgroups.  Each takes whole tiles g, g+G, ...
-    //   of the first tiles_dp = floor(tiles/G)*G tiles.  The reduction steps of the remaining
-    //   tiles, laid end to end (`units` of them), are cut into runs of q or q+1 steps (the first
-    //   `rem` get q+1), sk_groups of them: G, unless that would make the runs too short to be
-    //   worth a prologue.  Either sk_groups further workgroups are appended to the grid and take
-    //   one run each (a.runners: whenever all of them fit the device beside the G), or each of
-    //   the first sk_groups workgroups does a run first, then its whole tiles.  A run that does
-    //   not cover a tile's whole reduction shares the tile with its neighbours in g: fix-up
-    //   through the workspace if the host gave one, else atomics into zeroed y.
-    // (tiles_dp, sk_groups, q = sk_q, rem = sk_rem and the divisors come from the host: they
-    // depend on the launch alone, and all of it fits 32 bits)
-    const bool persistent = a.persist > 0;
-    const int g = blockIdx.x;
-    // With a.runners > 0 the grid is grid_persist + runners workgroups: the first grid_persist take
-    // whole tiles only, the others one dealt-out run each and nothing else, so that a run and a
-    // whole tile of the same compute unit proceed side by side instead of one after the other.
-    const int G = a.runners ? a.grid_persist : (int)gridDim.x;
-    const bool runner = a.runners && g >= G;
-    int next_dp = g;
-    // (remap: run number gr instead of g, so that consecutive runs -- neighbouring tiles, the
-    // slices of one tile -- sit on one XCD and share its L2; G is a multiple of the number of XCDs,
-    // so a runner's XCD is (g - G) % 8 as well)
-    const int gl = runner ? g - G : g;
-    const int gr = a.remap ? xcd_remap(gl, runner ? a.runners : G) : gl;
-    int u0, u1;
-    {
-        const cold_ptr c = cold_args();
-        const int q = c->sk_q, rem = c->sk_rem;
-        const bool dealt = persistent && gr < c->sk_groups && (!a.runners || runner);
-        u0 = dealt ? gr * q + min(gr, rem) : 0;
-        u1 = dealt ? (gr + 1) * q + min(gr + 1, rem) : 0;
-        if (runner) next_dp = c->tiles_dp;  // no whole tiles
-    }
-    bool once = !persistent;
-    for (;;) {
-        int tile, kbeg, kend, mode = kStore, fix_j = 0, fix_slot = 0, fix_n = 1;
-        const cold_ptr c = cold_args();   // the iterator's constants, once per segment
-        if (once) {
-            once = false;
-            const int slice = fdiv(gr, WPK_COLD_DIV(c, div_tiles));
-            tile = gr - slice * c->tiles;
-            kbeg = slice * c->steps_per_split;
-            kend = min(a.nsteps, kbeg + c->steps_per_split);
-            if (c->split_k > 1) {
-                mode = c->ws ? kFixup : kAtomic;
-                fix_j = tile;
-                fix_slot = slice;
-                fix_n = c->split_k;
-            }
-        } else if (persistent && u0 < u1) {
-            // (the dealt-out run comes BEFORE the workgroup's whole tiles: the sharers of a tile then
-            // meet while everybody else still has whole tiles to multiply, instead of after it, when
-            // the chain of memory round trips of the meeting would be all the device has left to do)
-            const int q = c->sk_q, rem = c->sk_rem;
-            auto owner_of = [&](int u) {  // which workgroup's run holds unit u
-                if (u < rem * (q + 1)) return fdiv(u, WPK_COLD_DIV(c, div_q1));
-                return rem + fdiv(u - rem * (q + 1), WPK_COLD_DIV(c, div_q0));
-            };
-            fix_j = fdiv(u0, WPK_COLD_DIV(c, div_nsteps));
-            tile = c->tiles_dp + fix_j;
-            kbeg = u0 - fix_j * a.nsteps;
-            kend = min(a.nsteps, kbeg + (u1 - u0));
-            u0 += kend - kbeg;
-            if (!(kbeg == 0 && kend == a.nsteps)) {
-                const int first = owner_of(fix_j * a.nsteps);
-                fix_n = owner_of((fix_j + 1) * a.nsteps - 1) - first + 1;
-                fix_slot = gr - first;
-                mode = c->ws ? kFixup : kAtomic;
-            }
-        } else if (persistent && next_dp < c->tiles_dp) {
-            // (remap: within a round, each XCD takes a contiguous range of the round's G tiles, so
-            // that tiles which share rows of x share an L2)
-            tile = next_dp - g + gr;
-            kbeg = 0;
-            kend = a.nsteps;
-            next_dp += G;
-        } else {
-            break;
-        }
-        run_segment(tile, kbeg, kend, mode, fix_j, fix_slot, fix_n);
-    }
+    for_each_segment(a, run_segment);
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int PD, int XL>
-hipError_t launch_gather_form(IgemmArgs a, hipStream_t stream)
+// Launch of a kernel whose workgroups of T lanes run for_each_segment.
+template <void (*KERNEL)(const IgemmArgs), int T>
+hipError_t launch_kernel(IgemmArgs a, hipStream_t stream, const size_t dynamic_lds = 0)
 {
-    const auto kernel = igemm_kernel<BM, BN, BK, WM, WN, PD, XL>;
+    if (dynamic_lds > 64 * 1024) {  // (the runtime's default limit per launch)
+        hipError_t e = hipFuncSetAttribute((const void *)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dynamic_lds);
+        if (e != hipSuccess) return e;
+    }
     if (a.persist > 0 && a.tiles_dp > 0 && a.sk_groups > 0) {
         // The tiles beyond the whole rounds go to workgroups of their own when every workgroup of
         // the larger grid is resident at once (how many a compute unit holds is asked once per
@@ -844,23 +868,30 @@ hipError_t launch_gather_form(IgemmArgs a, hipStream_t stream)
         int n = resident.load(std::memory_order_relaxed);
         if (n < 0) {
             n = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 64 * WM * WN, 0) != hipSuccess) {
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, KERNEL, T, 0) != hipSuccess) {
                 (void)hipGetLastError();
                 n = 0;
             }
             resident.store(n, std::memory_order_relaxed);
         }
+        if (dynamic_lds) n = std::min(n, (int)(160 * 1024 / (dynamic_lds + 256)));
         const long long cus = a.grid_persist / a.persist;
         if ((long long)n * cus >= (long long)a.grid_persist + a.sk_groups) a.runners = a.sk_groups;
     }
     dim3 grid((unsigned)(a.persist > 0 ? a.grid_persist + a.runners : a.tiles_m * a.tiles_n * a.split_k));
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * WM * WN), 0, stream, a);
+    hipLaunchKernelGGL(KERNEL, grid, dim3(T), dynamic_lds, stream, a);
     return hipGetLastError();
 }
 
 // (wpk_wsplit.h)
 template <int BN, int WK, int PD>
 hipError_t launch_wsplit(const IgemmArgs &a, hipStream_t stream);
+// (wpk_split.h, compiled by wpk_split_inst.hip)
+template <int WN>
+hipError_t launch_split(const IgemmArgs &a, hipStream_t stream);
+extern template hipError_t launch_split<1>(const IgemmArgs &, hipStream_t);
+extern template hipError_t launch_split<2>(const IgemmArgs &, hipStream_t);
+extern template hipError_t launch_split<4>(const IgemmArgs &, hipStream_t);
 
 template <int BM, int BN, int BK, int WM, int WN, int PD>
 hipError_t launch_igemm(const IgemmArgs &a, hipStream_t stream)
@@ -868,10 +899,14 @@ hipError_t launch_igemm(const IgemmArgs &a, hipStream_t stream)
     if constexpr (BM == kWaveSplitBm) {
         static_assert(BK == 8, "the wave-split members work in octets");
         return launch_wsplit<BN, WM * WN, 4 * PD>(a, stream);
+    } else if constexpr (WM == 1) {
+        static_assert(BM == 64 && BN == 32 * WN, "two MFMA blocks per wave");
+        return launch_split<WN>(a, stream);
     } else {
-        if (a.xl == 2) return launch_gather_form<BM, BN, BK, WM, WN, PD, 1>(a, stream);
-        if (a.xl == 3) return launch_gather_form<BM, BN, BK, WM, WN, PD, 2>(a, stream);
-        return launch_gather_form<BM, BN, BK, WM, WN, PD, 0>(a, stream);
+        constexpr int T = 64 * WM * WN;
+        if (a.xl == 2) return launch_kernel<igemm_kernel<BM, BN, BK, WM, WN, PD, 1>, T>(a, stream);
+        if (a.xl == 3) return launch_kernel<igemm_kernel<BM, BN, BK, WM, WN, PD, 2>, T>(a, stream);
+        return launch_kernel<igemm_kernel<BM, BN, BK, WM, WN, PD, 0>, T>(a, stream);
     }
 }
 

@@ -47,6 +47,12 @@ static const int kNumXcd = 8;
 // Members with this pixel tile are the wave-split form (wpk_wsplit.h): their wm x wn waves cut the
 // reduction between them, bk is the octet they work in, and `stages` counts four octets in flight each.
 static const int kWaveSplitBm = 32;
+// Tiled members whose waves all lie along the channels (wm = 1) are the split form (wpk_split.h): fp32
+// products formed on the bf16 matrix pipes, weights packed as three bf16 parts (kSplitWeightBytes each).
+inline bool split_member(const wpk_conv_config &c) { return c.bm != kWaveSplitBm && c.wm == 1; }
+static const int kSplitWeightBytes = 6;
+// Positions of x that the split members' patch form holds at most (two patches of 112 bytes each in LDS: 84 KB).
+static const int kHaloMax = 384;
 // LDS per workgroup: two stages of (BM + BN) columns of BK + 4 floats; two workgroups of the
 // largest tile still fit the 160 KB of a compute unit.
 static const int kMaxLdsBytes = 80 * 1024;
@@ -102,10 +108,10 @@ inline FastDiv make_fastdiv(uint32_t d)
 // rows against 49-59 us with runs of one or two K-steps of 16), so fewer workgroups take part
 // when there is little to deal out.
 static const int kMinRunRows = 64;
-inline int64_t streamk_groups(int64_t units, int64_t G, int bk)
+inline int64_t streamk_groups(int64_t units, int64_t G, int rows)
 {
     if (units <= 0) return 0;
-    int64_t min_steps = kMinRunRows / bk > 1 ? kMinRunRows / bk : 1;
+    int64_t min_steps = kMinRunRows / rows > 1 ? kMinRunRows / rows : 1;
     int64_t want = units / min_steps;
     return want < 1 ? 1 : want < G ? want : G;
 }
@@ -113,7 +119,7 @@ inline int64_t streamk_groups(int64_t units, int64_t G, int bk)
 // Kernel argument block of the tiled implicit-GEMM family (passed by value).
 struct IgemmArgs {
     const float *x;
-    const float *wp;      // packed weights [CRSpad/4][Kpad][4]
+    const float *wp;      // packed weights [CRSpad/4][Kpad][4]; split members: [CRSpad/16][Kpad/32][3 parts][64 lanes][8 bf16]
     float *y;
     const int32_t *ktab;  // periodic tap table [R*S phases][32 rows][2]: byte offset relative to the
                           // step's channel base (biased); mask bit of r | mask bit of s << 8
@@ -150,12 +156,14 @@ struct IgemmArgs {
     FastDiv div_pq, div_q, div_tiles_n, div_tiles, div_nsteps, div_q1, div_q0;  // by PQ, Q, tiles_n,
                         // tiles, nsteps, sk_q + 1, max(sk_q, 1)
     FastDiv div_tap;    // by what a reduction row index is divided to find its first table entry: C where a
-                        // K-step lies inside one filter tap, else R*S
+                        // K-step lies inside one filter tap, else R*S (split members: R*S, or H*W if halo)
     int32_t mfast;      // order of the tiles: 0: tile = tile_m * tiles_n + tile_n (neighbours in the order share rows
                         // of x); 1: tile = tile_n * tiles_m + tile_m (neighbours share weights) -- whichever operand is
                         // the larger, since with XCD-contiguous ranges the other one is what every XCD fetches whole
     FastDiv div_tiles_m;  // by tiles_m
     FastDiv div_s;        // by S (the wave-split members find their first filter tap with it)
+    int32_t halo;       // split members: positions of x the patch of a 3x3 tile holds, 0: each tap fetched by itself, -1: a
+                        // 1x1 layer fetched four pixels at a time (split_point)
     int32_t xl;         // 0: x is [N][C][H][W]; 1: channels-last, gathered row by row; 2: channels-last,
                         // gathered as 16-byte channel quads (reduction rows ordered (r, s, c)); 3: [N][C][H][W]
                         // with the reduction ordered (r, s, c), one filter tap per step
@@ -187,6 +195,44 @@ void set_last_hip_error(int e);
 void set_device_name(const std::string &name);
 std::string device_name();
 bool legal_for(const Problem &pr, const wpk_conv_config &cfg);
+// Bound on the positions of x that the windows of bm consecutive output pixels cover, where a split member with a
+// K-step of 16 works from such a patch (3x3 filters, ordinary padding, at most kHaloMax positions); else 0.
+int halo_positions(const Problem &pr, const wpk_conv_config &cfg);
+#ifdef __HIP__
+#define WPK_HOST_DEVICE __host__ __device__
+#else
+#define WPK_HOST_DEVICE
+#endif
+// First position of x (numbered through the images) that a tap of a 3x3 tile's pixels can touch: that of the first pixel's
+// window, (n, p, q), clipped to the image -- unless the row below is clipped to the same row, where a later pixel's
+// window begins further left.
+WPK_HOST_DEVICE inline int patch_first(int n, int p, int q, int stride_h, int stride_w, int pad_h, int pad_w, int H, int W)
+{
+    const int r = p * stride_h - pad_h, c = q * stride_w - pad_w;
+    return (n * H + (r > 0 ? r : 0)) * W + (r + stride_h > 0 && c > 0 ? c : 0);
+}
+// The last one alike, from the last pixel.
+WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int stride_w, int pad_h, int pad_w, int dil_h,
+                                      int dil_w, int H, int W)
+{
+    const int r = p * stride_h - pad_h + 2 * dil_h, c = q * stride_w - pad_w + 2 * dil_w;
+    return (n * H + (r < H - 1 ? r : H - 1)) * W + (r - stride_h < H - 1 && c < W - 1 ? c : W - 1);
+}
+// Whether a split member fetches pr's x four neighbouring pixels at a time: 1x1 filters on [N][C][H][W], stride 1, no
+// padding, images of a multiple of four pixels.
+inline bool split_point(const Problem &pr)
+{
+    const wpk_conv_desc &d = pr.d;
+    return pr.tapmajor && d.r == 1 && d.s == 1 && d.stride_h == 1 && d.stride_w == 1 && d.pad_h == 0 && d.pad_w == 0 &&
+           (int64_t)d.h * d.w % 4 == 0;
+}
+// What a configuration counts the reduction in: K-steps, or chunks of 16 channels where it works from patches.
+struct Reduction {
+    int32_t steps, rows;  // how many, and how many rows of the reduction each holds
+};
+Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg);
+// Persistent workgroups per compute unit a launch of cfg has, 0 where it runs one workgroup per tile and slice.
+int persistent_of(const Problem &pr, const wpk_conv_config &cfg, int compute_units);
 void default_config(const Problem &pr, int compute_units, wpk_conv_config *out);
 // Whether the wave-split members can run pr at all and its 32 x 32 output blocks times its octets of
 // reduction rows stay within the bound (the work is then small enough for them to be worth timing).

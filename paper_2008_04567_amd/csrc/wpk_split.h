@@ -1,0 +1,706 @@
+// The split members of the convolution kernel family for gfx950: fp32 products formed on the bf16 matrix
+// pipes, which multiply sixteen times as fast as the fp32 ones.
+//
+// Arithmetic.  An fp32 number is the exact sum of three bf16 numbers, v = h + m + l: h is v rounded to
+// bf16 (8 significant bits), m what is left of v rounded to bf16, l the rest (24 = 8 + 8 + 8 bits).  A
+// product of two such sums has nine terms; the six of them down to 2^-17 of the product,
+//     hh,  hm + mh + mm + hl + lh,
+// are formed by v_mfma_f32_32x32x16_bf16 (bf16 products are exact in fp32) and the other three, below
+// 2^-25 each, are dropped.  hh accumulates in one set of registers and the five small terms in another,
+// added once at the end: the running sum of hh is rounded once per sixteen terms of the reduction
+// instead of once per term, and the small terms are rounded at a 256th of its size, so the result is
+// closer to the exact sum than fp32 FMAs bring it (2-norm of the error over 2-norm of the result, normal operands:
+// 3.5e-7 against 8.6e-7 at 4608 terms, 1.1e-7 against 3.1e-7 at 576, 4.2e-8 against 1.1e-7 at 64; with
+// all six in one accumulator 1.0e-6, 3.5e-7, 1.1e-7).  Six MFMAs of 32 cycles per 32 x 32 block and
+// sixteen rows of the reduction stand against eight fp32 ones of 64.
+//
+// What three bf16 cannot hold -- infinities (inf - inf is NaN in m), finite numbers that round to a bf16
+// infinity, and numbers below 2^-110, whose l would fall under the smallest bf16 -- shows in the accumulators: not
+// finite, or all of a lane's outputs under 2^-90 without being zero.  A wave that finds that computes its
+// tile again with fp32 MFMAs (fp32_tile below), slowly, from the same operands.
+//
+// Workgroup.  64 pixels x 32 WN channels.  WN waves multiply, each all 64 pixels by 32 channels of its own: every
+// weight is wanted by one wave only and goes from memory straight into the registers the MFMAs read; it is
+// packed for that (pack_split_kernel), already split, 16 bytes per lane.  Activations are shared by the waves: NP further
+// waves fetch them as fp32, split them once and put them into LDS, from where a lane of a multiplying wave
+// reads eight consecutive rows of its pixel per part with one 16-byte access.  Two buffers, one barrier per step.
+// Why waves of their own for it: (a) loads return in order, so in a wave that fetches both, a weight waits for
+// every activation asked for before it, however far ahead that was -- with both in one wave a 1x1 layer of 256
+// channels at 56x56 (N = 16, K = 128) ran at 2.2 TB/s whatever the depth of its prefetch; (b) the splitting (5.5 vector
+// instructions per element) and the address arithmetic leave the waves that multiply with 2.5 instructions per MFMA,
+// and one such wave per SIMD keeps the matrix pipes busy.  What bounds the loop then is power: with random operands
+// back-to-back bf16 MFMAs hold the clock at 1.75-1.85 GHz (2.3 with zeros), 17.7 ns each instead of 13.3.
+// Registers are held to 168, three waves per SIMD: the accumulators are 64 of them.
+#ifndef WPK_SPLIT_H
+#define WPK_SPLIT_H
+
+#include "wpk_igemm.h"
+
+namespace wpk {
+
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+
+// two floats rounded to nearest even, packed: a in the low half
+__device__ __forceinline__ unsigned pack_bf16(float a, float b)
+{
+    const v2f v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, v2bf));
+}
+__device__ __forceinline__ float bf16_low(unsigned p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+
+// eight floats as their three bf16 parts, sixteen bytes each
+__device__ __forceinline__ void split_octet(const float (&v)[8], v4u &h, v4u &m, v4u &l)
+{
+    static_for<4>([&](auto P) WPK_LAMBDA {
+        constexpr int p = decltype(P)::value;
+        const unsigned ph = pack_bf16(v[2 * p], v[2 * p + 1]);
+        const float r0 = v[2 * p] - bf16_low(ph), r1 = v[2 * p + 1] - bf16_high(ph);
+        const unsigned pm = pack_bf16(r0, r1);
+        h[p] = ph;
+        m[p] = pm;
+        l[p] = pack_bf16(r0 - bf16_low(pm), r1 - bf16_high(pm));
+    });
+}
+
+// The two sums of every output become one; true if the split was not able to hold this wave's tile.
+template <int NB>
+__device__ __forceinline__ bool join_sums(v16f (&acc)[NB], const v16f (&sml)[NB])
+{
+    unsigned top = 0;
+    static_for<NB>([&](auto I) WPK_LAMBDA {
+        static_for<16>([&](auto E) WPK_LAMBDA {
+            constexpr int i = decltype(I)::value, e = decltype(E)::value;
+            const float v = acc[i][e] + sml[i][e];
+            acc[i][e] = v;
+            top = max(top, __builtin_bit_cast(unsigned, v) & 0x7fffffffu);
+        });
+    });
+    const bool odd = top >= 0x7f800000u || (top != 0u && top < 0x12800000u);  // inf or NaN; below 2^-90
+    return __builtin_amdgcn_ballot_w64(odd) != 0;
+}
+
+// The wave's blocks again, in fp32, one pixel block after the other, over the MFMA depths depth(0 .. count - 1), with
+// the operands where a lane's eight rows of a depth are: MFMA number q of eight contracts rows q and 8 + q.
+// GENERIC: rows in the source's order (c, r, s), else (c / 32, r, s, c % 32).
+template <int NNT, int NMT, bool GENERIC, class D>
+__device__ __forceinline__ void fp32_tile(v16f (&acc)[NNT * NMT], const __amdgpu_buffer_rsrc_t xrsrc,
+                                          const __amdgpu_buffer_rsrc_t wrsrc, const int m0, const unsigned wbase,
+                                          const int count, D &&depth, const int lane)
+{
+    const cold_ptr c = cold_args();
+    const int lrow = lane >> 5, lcol = lane & 31;
+    const unsigned wblk_bytes = (unsigned)(c->Kpad / 32) * 3072u;
+    const int px4 = c->xl == 1 || c->xl == 2 ? c->C * 4 : 4;
+    static_for<NMT>([&](auto J) WPK_LAMBDA {
+        constexpr int j = decltype(J)::value;
+        int voff;
+        unsigned inv;
+        pixel_window(c, m0 + j * 32 + lcol, voff, inv);
+        v16f f[NNT];
+        static_for<NNT>([&](auto I) WPK_LAMBDA {
+            static_for<16>([&](auto E) WPK_LAMBDA { f[decltype(I)::value][decltype(E)::value] = 0.0f; });
+        });
+        for (int it = 0; it < count; ++it) {
+            const int t = depth(it);
+            float xv[8];
+            static_for<8>([&](auto Q) WPK_LAMBDA {
+                constexpr int q = decltype(Q)::value;
+                int ch, rs;
+                bool past = false;
+                if constexpr (GENERIC) {
+                    const int kk = t * 16 + lrow * 8 + q;
+                    ch = kk / c->RS;
+                    rs = kk - ch * c->RS;
+                    past = kk >= c->CRS;
+                } else {
+                    const int c32 = t / (2 * c->RS);
+                    ch = c32 * 32 + (t & 1) * 16 + lrow * 8 + q;
+                    rs = (t - c32 * 2 * c->RS) >> 1;
+                }
+                const int fr = rs / c->S, fs = rs - fr * c->S;
+                const bool out = past || ((inv >> fr) & 1) || ((inv >> (16 + fs)) & 1);
+                const int off = out ? -1 : voff + (fr * c->dil_h * c->W + fs * c->dil_w) * px4 + ch * c->HW4;
+                xv[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, off, 0, 0));
+            });
+            static_for<NNT>([&](auto I) WPK_LAMBDA {
+                constexpr int i = decltype(I)::value;
+                v8bf w[3];
+                static_for<3>([&](auto Q) WPK_LAMBDA {
+                    w[decltype(Q)::value] = __builtin_bit_cast(
+                        v8bf, __builtin_amdgcn_raw_buffer_load_b128(
+                                  wrsrc, lane * 16, wbase + (unsigned)t * wblk_bytes +
+                                                        (i * 3 + decltype(Q)::value) * 1024, 0));
+                });
+                static_for<8>([&](auto Q) WPK_LAMBDA {
+                    constexpr int q = decltype(Q)::value;
+                    const float wv = ((float)w[2][q] + (float)w[1][q]) + (float)w[0][q];
+                    f[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, xv[q], f[i], 0, 0, 0);
+                });
+            });
+        }
+        static_for<NNT>([&](auto I) WPK_LAMBDA { acc[decltype(I)::value * NMT + j] = f[decltype(I)::value]; });
+    });
+}
+
+// How activations are found (the XL of the tiled members, and the patch):
+//   kRows   row by row through the tap table, any C; rows in the source's order (c, r, s)
+//   kQuads  channels-last, C a multiple of 32: a lane fetches an octet of one pixel with two 16-byte loads
+//   kTaps   [N][C][H][W], C a multiple of 32: one filter tap per step, eight one-dword loads per octet
+//   kPoint  [N][C][H][W], 1x1 filters, stride 1, no padding, H * W a multiple of 4: four neighbouring pixels of a
+//           channel are sixteen contiguous bytes, so a wave fetches a whole step with eight loads instead of 32
+//   kPatch, kPatchQuads: 3x3 filters (C as above): the nine taps of sixteen channels read one patch of x.  The pixels of a
+//           tile are consecutive, and so are the positions of x that their windows cover (numbered through the
+//           images): `halo` of them at most, any stride and dilation for which that fits.  A position is fetched and
+//           split once per sixteen channels instead of nine times.  A multiplying wave knows the LDS address of every
+//           tap of its pixels from the start; a tap outside the image has the address of a row of zeros.
+// Rows of the reduction are ordered (c / 32, r, s, c % 32) but for kRows, so that the taps of 32 channels follow each
+// other and find their pixels in the L1; a step is 32 rows, for patches the nine taps of sixteen channels.
+enum SplitForm { kRows, kQuads, kTaps, kPoint, kPatch, kPatchQuads };
+constexpr int kHaloPitch = 112;    // LDS bytes per position of a patch: one depth of 3 parts x 32 bytes, 16 of padding, and
+constexpr int kStepPitch = 240;    // per pixel of a step: two depths, 48 of padding, of which a pixel's rows
+                                   // are moved on by 16 for every 16 pixels.  Both put the 16 lanes served at a time
+                                   // on 16 different groups of four banks, whether they hold neighbouring pixels or
+                                   // every fourth.
+__host__ __device__ constexpr int step_place(int px) { return px * kStepPitch + (px >> 4) * 16; }
+__host__ __device__ constexpr int split_producers(int wn, SplitForm form)
+{
+    return form == kPatch || form == kPatchQuads ? 1 : wn == 4 || form == kRows || form == kTaps ? 2 : 1;
+}
+
+template <int WN, SplitForm FORM>
+__global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) split_kernel(const IgemmArgs a)
+{
+    constexpr bool PATCH = FORM == kPatch || FORM == kPatchQuads, QUAD = FORM == kQuads || FORM == kPatchQuads;
+    constexpr int NP = split_producers(WN, FORM);
+    constexpr int BM = 64, BN = 32 * WN, NMT = 2, T = 64 * WN;
+    constexpr int NT = PATCH ? 9 : 2;          // MFMA depths (of 16 rows) per step
+    extern __shared__ __attribute__((aligned(16))) char lds[];  // two steps of activations
+    __shared__ float bias[2][BN];              // of this segment's channels and of the one before
+    __shared__ int arrival;
+
+    touch_kernarg_lines();
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lrow = lane >> 5, lcol = lane & 31;
+    const int buf_bytes = PATCH ? (a.halo + 1) * kHaloPitch : BM * kStepPitch;
+    int parity = 0;                            // of the segment
+
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const char *)a.x - a.x_bias), 0, (int)(a.x_bytes + a.x_bias), 0x00020000);
+    const __amdgpu_buffer_rsrc_t wrsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void *)a.wp, 0, (int)a.w_bytes, 0x00020000);
+
+    if (PATCH && tid < 14)  // the rows of zeros
+        *reinterpret_cast<v4u *>(lds + (tid < 7 ? 0 : buf_bytes) + a.halo * kHaloPitch + tid % 7 * 16) = (v4u){0, 0, 0, 0};
+
+    // ---- a wave that fetches: its part of a segment ---------------------------------------------------------
+    // Step 0 goes to LDS, then while the others multiply step r, step r + 1 does, from registers into which it was
+    // fetched DEPTH steps (patches: one) before.  Past the end of the segment the same instructions are issued with lane
+    // offsets of all ones: nothing is fetched, zeros are stored and nobody reads them.
+    auto fetch_segment = [&](const int m0, const int n0, const int kbeg, const int kend) WPK_LAMBDA {
+        const int nr = kend - kbeg;
+        const int prod = wave - WN;
+        // the channels' bias: asked for now, stored once the first fetches are on their way
+        constexpr int BI = (BN + NP * 64 - 1) / (NP * 64);
+        float bval[BI];
+        {
+            const cold_ptr c = cold_args();
+            const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(c->bias ? c->bias : c->y), 0, c->bias ? c->K * 4 : 0, 0x00020000);
+            static_for<BI>([&](auto I) WPK_LAMBDA {
+                bval[decltype(I)::value] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(
+                               brsrc, (n0 + prod * 64 + lane + decltype(I)::value * NP * 64) * 4, 0, 0));
+            });
+        }
+        auto store_bias = [&]() WPK_LAMBDA {
+            static_for<BI>([&](auto I) WPK_LAMBDA {
+                const int i = prod * 64 + lane + decltype(I)::value * NP * 64;
+                if (BN % (NP * 64) == 0 || i < BN) bias[parity][i] = bval[decltype(I)::value];
+            });
+        };
+        if constexpr (PATCH) {
+            constexpr int NPB = kHaloMax / 64;  // blocks of 64 positions
+            int j0, npos;
+            {
+                const cold_ptr c = cold_args();
+                const int mb = min(c->M, m0 + BM) - 1;
+                const int na = fdiv(m0, WPK_COLD_DIV(c, div_pq)), pqa = m0 - na * c->PQ;
+                const int pa = fdiv(pqa, WPK_COLD_DIV(c, div_q)), qa = pqa - pa * c->Q;
+                const int nb = fdiv(mb, WPK_COLD_DIV(c, div_pq)), pqb = mb - nb * c->PQ;
+                const int pb = fdiv(pqb, WPK_COLD_DIV(c, div_q)), qb = pqb - pb * c->Q;
+                j0 = patch_first(na, pa, qa, c->stride_h, c->stride_w, c->pad_h, c->pad_w, c->H, c->W);
+                npos = min(patch_last(nb, pb, qb, c->stride_h, c->stride_w, c->pad_h, c->pad_w, c->dil_h, c->dil_w, c->H,
+                                      c->W) - j0 + 1, c->halo);
+            }
+            // a lane holds sixteen channels of position `lane` of a block; QUAD: an octet each of positions
+            // lane / 2 and 32 + lane / 2
+            float v[NPB][16];
+            int off[NPB][2];
+            auto fetch = [&](auto PB, const int chunk) WPK_LAMBDA {
+                constexpr int pb = decltype(PB)::value;
+                static_for<2>([&](auto O) WPK_LAMBDA {
+                    constexpr int o = decltype(O)::value;
+                    if constexpr (QUAD) {
+                        static_for<2>([&](auto H) WPK_LAMBDA {
+                            constexpr int b = o * 8 + decltype(H)::value * 4;
+                            const v4f q = __builtin_bit_cast(
+                                v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, off[pb][o],
+                                                                           chunk * 64 + decltype(H)::value * 16, 0));
+                            static_for<4>([&](auto E) WPK_LAMBDA { v[pb][b + decltype(E)::value] = q[decltype(E)::value]; });
+                        });
+                    } else {
+                        static_for<8>([&](auto J) WPK_LAMBDA {
+                            constexpr int b = o * 8 + decltype(J)::value;
+                            v[pb][b] = __builtin_bit_cast(
+                                float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, off[pb][0], (chunk * 16 + b) * a.HW4, 0));
+                        });
+                    }
+                });
+            };
+            auto put = [&](auto PB, const int buf) WPK_LAMBDA {
+                constexpr int pb = decltype(PB)::value;
+                static_for<2>([&](auto O) WPK_LAMBDA {
+                    constexpr int o = decltype(O)::value;
+                    const int pos = QUAD ? pb * 64 + o * 32 + (lane >> 1) : pb * 64 + lane;
+                    float e[8];
+                    static_for<8>([&](auto J) WPK_LAMBDA { e[decltype(J)::value] = v[pb][o * 8 + decltype(J)::value]; });
+                    v4u h, m, l;
+                    split_octet(e, h, m, l);
+                    if (pos < npos) {
+                        char *const p = lds + buf * buf_bytes + pos * kHaloPitch + (QUAD ? lane & 1 : o) * 16;
+                        *reinterpret_cast<v4u *>(p) = h;
+                        *reinterpret_cast<v4u *>(p + 32) = m;
+                        *reinterpret_cast<v4u *>(p + 64) = l;
+                    }
+                });
+            };
+            auto each_block = [&](auto &&f) WPK_LAMBDA {
+                static_for<NPB>([&](auto PB) WPK_LAMBDA {
+                    if (decltype(PB)::value * 64 < npos) f(PB);
+                });
+            };
+            each_block([&](auto PB) WPK_LAMBDA {
+                constexpr int pb = decltype(PB)::value;
+                static_for<2>([&](auto O) WPK_LAMBDA {  // byte offset of a position in x, or all ones
+                    constexpr int o = decltype(O)::value;
+                    if constexpr (o == 0 || QUAD) {
+                        const int pos = QUAD ? pb * 64 + o * 32 + (lane >> 1) : pb * 64 + lane, j = j0 + pos;
+                        const int n = fdiv(j, a.div_tap);
+                        const int at = (QUAD ? j * a.C * 4 + (lane & 1) * 32 : (n * a.C * a.HW + j - n * a.HW) * 4) +
+                                       (int)a.x_bias;
+                        off[pb][o] = pos < npos && n < a.N ? at : -1;
+                    }
+                });
+                fetch(PB, kbeg);
+            });
+            store_bias();
+            each_block([&](auto PB) WPK_LAMBDA {
+                put(PB, 0);
+                if (nr > 1) fetch(PB, kbeg + 1);
+            });
+            __syncthreads();
+            for (int r = 0; r < nr; ++r) {
+                if (r + 1 < nr)
+                    each_block([&](auto PB) WPK_LAMBDA {
+                        put(PB, (r + 1) & 1);
+                        if (r + 2 < nr) fetch(PB, kbeg + r + 2);
+                    });
+                __syncthreads();
+            }
+        } else if constexpr (FORM == kPoint) {
+            // A lane holds four pixels of an octet: pixels 4 (lane % 16) .., octet lane / 16.  The NP waves take turns, a
+            // whole step each: one that stores step r + 1 while step r is multiplied has NP steps' time for it.
+            constexpr int DEPTH = 3;  // of this wave's steps: 24 KB in flight
+            const int m = m0 + 4 * (lane & 15);
+            int voff;
+            {
+                const cold_ptr c = cold_args();
+                const int n = fdiv(m, WPK_COLD_DIV(c, div_pq));
+                voff = m < c->M ? (n * c->C * c->HW + m - n * c->HW + (lane >> 4) * 8 * c->HW) * 4 : -1;
+            }
+            const int place = step_place((lane & 15) * 4) + (lane >> 5) * 96 + (lane >> 4 & 1) * 16;
+            float v[DEPTH][32];  // channel of the octet, pixel
+            int step = kbeg + prod;
+            auto fetch = [&](auto SLOT) WPK_LAMBDA {
+                constexpr int sl = decltype(SLOT)::value;
+                const int at = voff | (step < kend ? 0 : -1), first = step * 32 * a.HW4;
+                static_for<8>([&](auto J) WPK_LAMBDA {
+                    constexpr int j = decltype(J)::value;
+                    const v4f q = __builtin_bit_cast(
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, at, first + j * a.HW4, 0));
+                    static_for<4>([&](auto E) WPK_LAMBDA { v[sl][j * 4 + decltype(E)::value] = q[decltype(E)::value]; });
+                });
+                step += NP;
+            };
+            auto put = [&](auto SLOT, const int buf) WPK_LAMBDA {
+                constexpr int sl = decltype(SLOT)::value;
+                static_for<4>([&](auto PX) WPK_LAMBDA {
+                    constexpr int px = decltype(PX)::value;
+                    float e[8];
+                    static_for<8>([&](auto J) WPK_LAMBDA { e[decltype(J)::value] = v[sl][decltype(J)::value * 4 + px]; });
+                    v4u h, m, l;
+                    split_octet(e, h, m, l);
+                    char *const p = lds + place + buf * buf_bytes + px * kStepPitch;
+                    *reinterpret_cast<v4u *>(p) = h;
+                    *reinterpret_cast<v4u *>(p + 32) = m;
+                    *reinterpret_cast<v4u *>(p + 64) = l;
+                });
+            };
+            static_for<DEPTH>([&](auto D) WPK_LAMBDA {
+                fetch(D);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            store_bias();
+            // nr + 1 meetings in all: number r has step r in place and the buffer of step r - 1 free.  Step r is stored
+            // between meetings r - 1 and r.
+            int left = nr + 1, turn = 0;  // (of the two buffers, where one wave fills both)
+            static_for<NP>([&](auto P) WPK_LAMBDA {
+                if (decltype(P)::value < prod) {
+                    __syncthreads();
+                    --left;
+                }
+            });
+            auto one = [&](auto P) WPK_LAMBDA {
+                constexpr int p = decltype(P)::value;
+                using SLOT = std::integral_constant<int, p % DEPTH>;
+                if (left <= 0) return false;
+                put(SLOT{}, NP == 2 ? prod : turn);
+                turn ^= 1;
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(SLOT{});
+                __builtin_amdgcn_sched_barrier(0);
+                __syncthreads();
+                --left;
+                if constexpr (NP == 2) {
+                    if (left <= 0) return false;
+                    __syncthreads();
+                    --left;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                return true;
+            };
+            while (static_all<DEPTH>(one)) {}
+        } else {
+            constexpr int UN = 4 / NP;                  // octets of 64 pixels per wave and step
+            // steps in flight: 24 KB of x per wave, or as much as the counter of loads in flight (63) allows
+            constexpr int DEPTH = QUAD ? 3 * NP : 3;
+            static_assert(QUAD || NP == 2, "three steps of 16 loads");
+            constexpr int XP = QUAD ? UN : 1;           // pixels per lane
+            // QUAD: four lanes hold the four octets of a pixel (128 contiguous bytes of x), else a lane its pixel's
+            int xvoff[XP], xvb[XP];
+            unsigned xinv[XP];
+            {
+                const cold_ptr c = cold_args();
+                static_for<XP>([&](auto I) WPK_LAMBDA {
+                    constexpr int i = decltype(I)::value;
+                    pixel_window(c, m0 + (QUAD ? (prod * UN + i) * 16 + (lane >> 2) : lane), xvoff[i], xinv[i]);
+                    if constexpr (QUAD) xvoff[i] += (lane & 3) * 32;
+                });
+            }
+            // the place in the reduction of the step fetched next: kRows: channel and phase of its first row (see the
+            // tap table of the tiled members); else filter tap (r, s), its byte offset and the first channel
+            const tap_ptr taps = (tap_ptr)(unsigned long long)a.ktab;
+            const int px4 = QUAD ? a.C * 4 : 4;  // bytes between neighbouring pixels of x
+            const int tap_step_s = a.dil_w * px4;
+            const int tap_step_r = (a.dil_h * a.W - (a.S - 1) * a.dil_w) * px4;
+            int step = kbeg, tap_r = 0, tap_s = 0, tap_off = 0, ch = 0;
+            {
+                const cold_ptr c = cold_args();
+                if constexpr (FORM == kRows) {
+                    ch = fdiv(kbeg * 32, WPK_COLD_DIV(c, div_tap));
+                    tap_s = kbeg * 32 - ch * a.RS;
+                } else {
+                    const int c32 = fdiv(kbeg, WPK_COLD_DIV(c, div_tap)), tap = kbeg - c32 * a.RS;
+                    ch = c32 * 32;
+                    tap_r = fdiv(tap, WPK_COLD_DIV(c, div_s));
+                    tap_s = tap - tap_r * a.S;
+                    tap_off = (tap_r * a.dil_h * a.W + tap_s * a.dil_w) * px4;
+                }
+            }
+            float v[DEPTH][UN * 8];
+            auto fetch = [&](auto SLOT) WPK_LAMBDA {
+                constexpr int sl = decltype(SLOT)::value;
+                const int dead = step < kend ? 0 : -1;
+                if constexpr (FORM == kRows) {
+                    const bool last = step == a.nsteps - 1;
+                    const tap_ptr tp = (last ? (tap_ptr)(unsigned long long)a.ttab : taps + 2 * tap_s * 32) + prod * UN * 16;
+                    const int base = last ? 0 : ch * a.HW4;
+                    static_for<UN * 8>([&](auto E) WPK_LAMBDA {
+                        constexpr int e = decltype(E)::value;
+                        const int off = tp[2 * e], rs = tp[2 * e + 1];
+                        const int bad = __builtin_amdgcn_sbfe((int)xinv[0], rs & 0xff, 1) |
+                                        __builtin_amdgcn_sbfe((int)xinv[0], rs >> 8, 1) | dead;
+                        v[sl][e] = __builtin_bit_cast(
+                            float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xvoff[0] | bad, off + base, 0));
+                    });
+                    const int over = ~((tap_s + a.bk_mod_rs - a.RS) >> 31);  // all ones: past the last tap
+                    ch += a.bk_div_rs + (over & 1);
+                    tap_s += a.bk_mod_rs - (over & a.RS);
+                } else {
+                    static_for<XP>([&](auto I) WPK_LAMBDA {
+                        constexpr int i = decltype(I)::value;
+                        xvb[i] = xvoff[i] | __builtin_amdgcn_sbfe((int)xinv[i], tap_r, 1) |
+                                 __builtin_amdgcn_sbfe((int)xinv[i], 16 + tap_s, 1) | dead;
+                    });
+                    static_for<UN>([&](auto U) WPK_LAMBDA {
+                        constexpr int u = decltype(U)::value;
+                        if constexpr (QUAD) {
+                            static_for<2>([&](auto H) WPK_LAMBDA {
+                                constexpr int hf = decltype(H)::value;
+                                const v4f q = __builtin_bit_cast(
+                                    v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xvb[u], tap_off + ch * 4 + hf * 16, 0));
+                                static_for<4>([&](auto E) WPK_LAMBDA {
+                                    v[sl][u * 8 + hf * 4 + decltype(E)::value] = q[decltype(E)::value];
+                                });
+                            });
+                        } else {
+                            const int first = tap_off + (ch + (prod * UN + u) * 8) * a.HW4;
+                            static_for<8>([&](auto J) WPK_LAMBDA {
+                                constexpr int j = decltype(J)::value;
+                                v[sl][u * 8 + j] = __builtin_bit_cast(
+                                    float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xvb[0], first + j * a.HW4, 0));
+                            });
+                        }
+                    });
+                    // one step on, by masks (selects become branches here, and at every join of two paths the compiler
+                    // has all loads in flight waited for): along the filter row, to the next one, to the next 32 channels
+                    const int row = (tap_s + 1 - a.S) >> 31, chn = (((tap_r + 1 - a.R) >> 31) | row);  // 0: moves on
+                    ch += ~chn & 32;
+                    tap_off = chn & (tap_off + (row & tap_step_s) + (~row & tap_step_r));
+                    tap_r = chn & (tap_r + (~row & 1));
+                    tap_s = row & (tap_s + 1);
+                }
+                step += 1;
+            };
+            auto put = [&](auto SLOT, const int buf) WPK_LAMBDA {
+                constexpr int sl = decltype(SLOT)::value;
+                static_for<UN>([&](auto U) WPK_LAMBDA {
+                    constexpr int u = decltype(U)::value;
+                    float e[8];
+                    static_for<8>([&](auto J) WPK_LAMBDA { e[decltype(J)::value] = v[sl][u * 8 + decltype(J)::value]; });
+                    v4u h, m, l;
+                    split_octet(e, h, m, l);
+                    const int px = QUAD ? (prod * UN + u) * 16 + (lane >> 2) : lane;
+                    const int oct = QUAD ? lane & 3 : prod * UN + u;
+                    char *const p = lds + buf * buf_bytes + step_place(px) + (oct >> 1) * 96 + (oct & 1) * 16;
+                    *reinterpret_cast<v4u *>(p) = h;
+                    *reinterpret_cast<v4u *>(p + 32) = m;
+                    *reinterpret_cast<v4u *>(p + 64) = l;
+                });
+            };
+            static_for<DEPTH>([&](auto D) WPK_LAMBDA {
+                fetch(D);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            store_bias();
+            put(std::integral_constant<int, 0>{}, 0);
+            fetch(std::integral_constant<int, 0>{});
+            __syncthreads();
+            int r = 0;
+            auto one = [&](auto P) WPK_LAMBDA {
+                constexpr int p = decltype(P)::value;
+                if (r + p >= nr) return false;
+                using SLOT = std::integral_constant<int, (p + 1) % DEPTH>;
+                put(SLOT{}, (r + p + 1) & 1);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(SLOT{});
+                __builtin_amdgcn_sched_barrier(0);
+                __syncthreads();
+                __builtin_amdgcn_sched_barrier(0);
+                return true;
+            };
+            // (the compiler has every load in flight waited for at the top of the body: twelve steps long)
+            constexpr int LAPS = 12;
+            while (static_all<LAPS>(one)) r += LAPS;
+        }
+    };
+
+    auto run_segment = [&](const int tile, const int kbeg, const int kend, const int mode,
+                           const int fix_j, const int fix_slot, const int fix_n) WPK_LAMBDA {
+    if (kbeg >= kend) return;
+    int tile_m, tile_n;
+    {
+        const cold_ptr c = cold_args();
+        if (c->mfast) {
+            tile_n = fdiv(tile, WPK_COLD_DIV(c, div_tiles_m));
+            tile_m = tile - tile_n * c->tiles_m;
+        } else {
+            tile_m = fdiv(tile, WPK_COLD_DIV(c, div_tiles_n));
+            tile_n = tile - tile_m * c->tiles_n;
+        }
+    }
+    const int m0 = tile_m * BM;
+    parity ^= 1;
+    if (wave >= WN) {
+        fetch_segment(m0, tile_n * BN, kbeg, kend);
+        if (mode == kFixup) {  // (the three barriers of the meeting)
+            __syncthreads();
+            __syncthreads();
+            __syncthreads();
+        }
+        return;
+    }
+
+    // ---- a wave that multiplies ---------------------------------------------------------------------------
+    const int nr = kend - kbeg, n0 = tile_n * BN + wave * 32;
+    const unsigned depth_bytes = (unsigned)(a.Kpad / 32) * 3072u;  // weights: one depth further
+    const unsigned wbase = (unsigned)(n0 / 32) * 3072u;
+    // (patches: the two halves of 32 channels alternate in the packed order, see split_source_row)
+    constexpr unsigned kTapStride = PATCH ? 2 : 1;
+    auto step_base = [&](const int r) WPK_LAMBDA {
+        return wbase + (unsigned)(PATCH ? (r >> 1) * 18 + (r & 1) : r * 2) * depth_bytes;
+    };
+    v8bf aw[3 * 3];  // weights: three depths, two of them ahead
+    auto load_a = [&](auto SET, const unsigned base, auto E) WPK_LAMBDA {
+        constexpr int set = decltype(SET)::value, e = decltype(E)::value;
+        aw[set * 3 + e] = __builtin_bit_cast(
+            v8bf, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16, base + e * 1024, 0));
+    };
+    unsigned wcur = step_base(kbeg);
+    static_for<2>([&](auto S) WPK_LAMBDA {
+        static_for<3>([&](auto E) WPK_LAMBDA { load_a(S, wcur + decltype(S)::value * kTapStride * depth_bytes, E); });
+    });
+    unsigned addr[PATCH ? NMT * 5 : 1];  // of every tap, in units of 16 bytes, two per register
+    if constexpr (PATCH) {
+        // (the tile's first position, as the wave that fetches has it)
+        const cold_ptr c = cold_args();
+        const int na = fdiv(m0, WPK_COLD_DIV(c, div_pq)), pqa = m0 - na * c->PQ;
+        const int pa = fdiv(pqa, WPK_COLD_DIV(c, div_q)), qa = pqa - pa * c->Q;
+        const int j0 = patch_first(na, pa, qa, c->stride_h, c->stride_w, c->pad_h, c->pad_w, c->H, c->W);
+        static_for<NMT>([&](auto J) WPK_LAMBDA {
+            constexpr int j = decltype(J)::value;
+            const int m = m0 + j * 32 + lcol;
+            const int n = fdiv(m, WPK_COLD_DIV(c, div_pq)), pq = m - n * c->PQ;
+            const int p = fdiv(pq, WPK_COLD_DIV(c, div_q)), q = pq - p * c->Q;
+            const int ih = p * c->stride_h - c->pad_h, iw = q * c->stride_w - c->pad_w;
+            const int first = n * c->HW + ih * c->W + iw - j0;
+            static_for<9>([&](auto TAP) WPK_LAMBDA {
+                constexpr int t = decltype(TAP)::value, r = t / 3, s = t % 3;
+                const bool in = m < c->M && (unsigned)(ih + r * c->dil_h) < (unsigned)c->H &&
+                                (unsigned)(iw + s * c->dil_w) < (unsigned)c->W;
+                const int pos = first + r * c->dil_h * c->W + s * c->dil_w;
+                // (never out of range by construction; the unsigned minimum keeps it so whatever happens)
+                const unsigned at = min(in ? (unsigned)pos : (unsigned)c->halo, (unsigned)c->halo) * (kHaloPitch / 16) + lrow;
+                addr[j * 5 + t / 2] = t % 2 ? addr[j * 5 + t / 2] | at << 16 : at;
+            });
+        });
+    }
+    v16f acc[NMT], sml[NMT];
+    static_for<NMT>([&](auto I) WPK_LAMBDA {
+        static_for<16>([&](auto E) WPK_LAMBDA {
+            acc[decltype(I)::value][decltype(E)::value] = 0.0f;
+            sml[decltype(I)::value][decltype(E)::value] = 0.0f;
+        });
+    });
+    // The operands of a depth: three parts for each of the wave's two pixel blocks.  The products are issued in an
+    // order that is done with l after two MFMAs, with m after six and with h after twelve, and each part of the
+    // NEXT depth is read into the registers the moment they are free: six MFMAs or more ahead of its use.
+    v8bf bx[NMT * 3];
+    int bofs = 0;  // the step's buffer
+    auto read_part = [&](auto PART, auto TAP) WPK_LAMBDA {
+        constexpr int part = decltype(PART)::value, t = decltype(TAP)::value;
+        static_for<NMT>([&](auto J) WPK_LAMBDA {
+            constexpr int j = decltype(J)::value;
+            if constexpr (PATCH) {
+                const unsigned at = t % 2 ? addr[j * 5 + t / 2] >> 16 : addr[j * 5 + t / 2] & 0xffffu;
+                bx[j * 3 + part] = *reinterpret_cast<const v8bf *>(lds + (at * 16 + bofs) + part * 32);
+            } else {
+                bx[j * 3 + part] = *reinterpret_cast<const v8bf *>(lds + (bofs + step_place(lcol) + lrow * 16) +
+                                                                   step_place(j * 32) + t * 96 + part * 32);
+            }
+        });
+    };
+    // step number r of the segment; P: its number within the loop's body
+    auto step_body = [&](const int r, auto P) WPK_LAMBDA {
+        const unsigned wnext = PATCH ? step_base(kbeg + r + 1) : wcur + 2 * depth_bytes;
+        static_for<NT>([&](auto TAP) WPK_LAMBDA {
+            constexpr int t = decltype(TAP)::value, g = decltype(P)::value * NT + t;
+            using NEXT = std::integral_constant<int, (t + 1) % NT>;
+            using SET = std::integral_constant<int, (g + 2) % 3>;  // the set that the depth before this one has left
+            const unsigned ahead = t + 2 < NT ? wcur + (t + 2) * kTapStride * depth_bytes
+                                              : wnext + (t + 2 - NT) * kTapStride * depth_bytes;
+            static_for<6>([&](auto PQ) WPK_LAMBDA {
+                constexpr int q = decltype(PQ)::value;
+                // (A part, B part), 0 h, 1 m, 2 l: hl | mm, hm | hh, mh, lh
+                constexpr int pa = q == 1 || q == 4 ? 1 : q == 5 ? 2 : 0, pb = q == 0 ? 2 : q == 1 || q == 2 ? 1 : 0;
+                static_for<NMT>([&](auto J) WPK_LAMBDA {
+                    constexpr int j = decltype(J)::value;
+                    const v8bf av = aw[g % 3 * 3 + pa];
+                    if constexpr (q == 3)
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bx[j * 3 + pb], acc[j], 0, 0, 0);
+                    else
+                        sml[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bx[j * 3 + pb], sml[j], 0, 0, 0);
+                    // weights two depths ahead
+                    if constexpr (q * NMT + j < 3) load_a(SET{}, ahead, std::integral_constant<int, q * NMT + j>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if constexpr (t + 1 == NT) {
+                    if constexpr (q == 1) {
+                        // every wave holds its last operands of this step, and the next one is in place (the MFMAs
+                        // just issued run on while the waves meet)
+                        __syncthreads();
+                        bofs = buf_bytes - bofs;
+                        read_part(std::integral_constant<int, 2>{}, NEXT{});
+                    }
+                } else {
+                    if constexpr (q == 0) read_part(std::integral_constant<int, 2>{}, NEXT{});
+                }
+                if constexpr (q == 2) read_part(std::integral_constant<int, 1>{}, NEXT{});
+                if constexpr (q == 5) read_part(std::integral_constant<int, 0>{}, NEXT{});
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        wcur = wnext;
+    };
+    __syncthreads();
+    static_for<3>([&](auto PART) WPK_LAMBDA { read_part(PART, std::integral_constant<int, 0>{}); });
+    constexpr int BODY = PATCH ? 1 : 3;  // steps after which the weights' sets come round
+    int r = 0;
+    auto step = [&](auto P) WPK_LAMBDA {
+        if (r + decltype(P)::value >= nr) return false;
+        step_body(r + decltype(P)::value, P);
+        return true;
+    };
+    while (static_all<BODY>(step)) r += BODY;
+
+    if (join_sums(acc, sml))
+        fp32_tile<1, NMT, FORM == kRows>(acc, xrsrc, wrsrc, m0, wbase, nr * NT, [&](int i) WPK_LAMBDA {
+            const int c = kbeg + i / NT;
+            return PATCH ? (c >> 1) * 18 + (c & 1) + i % NT * 2 : kbeg * NT + i;
+        }, lane);
+    const cold_ptr ce = cold_args();
+    if (mode == kFixup &&
+        !meet_shared_tile<NMT, T>(ce, acc, BM * BN, tid, fix_j, fix_slot, fix_n, &arrival))
+        return;  // not the last: done with this tile
+    store_wave_tile<1, NMT>(ce, acc, m0, n0, lrow, lcol, mode == kAtomic, &bias[parity][wave * 32]);
+    };  // run_segment
+
+    for_each_segment(a, run_segment);
+}
+
+template <int WN, SplitForm FORM>
+hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
+{
+    const size_t lds = 2 * (size_t)(FORM >= kPatch ? (a.halo + 1) * kHaloPitch : 64 * kStepPitch);
+    return launch_kernel<split_kernel<WN, FORM>, 64 * (WN + split_producers(WN, FORM))>(a, stream, lds);
+}
+
+// (the K-step gene says whether patches may be used, which the host has looked at; `stages` has no meaning here)
+template <int WN>
+hipError_t launch_split(const IgemmArgs &a, hipStream_t stream)
+{
+    if (a.halo > 0)
+        return a.xl == 2 ? launch_split_form<WN, kPatchQuads>(a, stream) : launch_split_form<WN, kPatch>(a, stream);
+    if (a.xl == 2) return launch_split_form<WN, kQuads>(a, stream);
+    if (a.halo < 0) return launch_split_form<WN, kPoint>(a, stream);
+    if (a.xl == 3) return launch_split_form<WN, kTaps>(a, stream);
+    return launch_split_form<WN, kRows>(a, stream);
+}
+
+}  // namespace wpk
+#endif

@@ -1,0 +1,152 @@
+"""The split members (wm = 1: fp32 products on the bf16 matrix pipes) against the CPU oracle: every way they find their
+activations, at the sizes where it can go wrong, and operands that three bf16 numbers cannot hold."""
+import numpy as np
+import pytest
+
+from oracle import conv as oc
+from paper_2008_04567_amd import binding as B
+from paper_2008_04567_amd import workloads as W
+from tests.parity import check_layer, check_layout, to_dev, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def cfg(wn, bk, **kw):
+    return B.make_config(64, 32 * wn, bk, 1, wn, stages=1, **kw)
+
+
+# 3x3 with C % 32 == 0 and bk = 16: patches.  Pixel counts just off whole tiles, tiles over several images, one image
+# row longer than a tile, padding 0 / 1 / the most that is taken, strides and dilations that still fit, one that does
+# not (112 wide with dilation 2: falls back to taps), one and several chunks of channels.
+PATCH = [
+    W.layer("7x7_n5", 5, 64, 7, 40, 3, 1, 1, x_dist="u11", seed=1),
+    W.layer("one_row", 2, 32, (1, 130), 33, 3, 1, 1, x_dist="u11", seed=2),
+    W.layer("nopad", 3, 32, (9, 11), 64, 3, 1, 0, x_dist="u11", seed=3),
+    W.layer("pad2", 2, 96, (6, 13), 96, 3, 1, 2, x_dist="u11", seed=4),
+    W.layer("stride2", 2, 64, (17, 19), 128, 3, 2, 1, x_dist="u11", seed=5),
+    W.layer("stride31", 2, 32, (20, 9), 20, 3, (3, 1), 1, x_dist="u11", seed=6),
+    W.layer("dil2", 2, 32, 12, 64, 3, 1, 2, dil=2, x_dist="u11", seed=7),
+    W.layer("dil31", 1, 32, (15, 10), 64, 3, 1, (3, 1), dil=(3, 1), x_dist="u11", seed=8),
+    W.layer("wide", 1, 32, (5, 112), 64, 3, 1, 1, x_dist="u11", seed=9),
+    W.layer("too_wide", 1, 32, (7, 112), 64, 3, 1, 2, dil=2, x_dist="u11", seed=10),
+]
+
+
+@pytest.mark.parametrize("layer", PATCH, ids=lambda l: l["name"])
+@pytest.mark.parametrize("wn", [1, 2, 4])
+def test_patches(layer, wn):
+    check_layer(layer, cfg(wn, 16), what=layer["name"])
+    check_layout(layer, B.NHWC, cfg(wn, 16), what=layer["name"] + " nhwc")
+
+
+# the other ways: 1x1 four pixels at a time (H * W % 4 == 0, stride 1), 1x1 and larger filters tap by tap, rows (any C).
+# Reductions of one step up to more than the steps in flight, odd and even.
+OTHER = [
+    W.layer("point_1step", 3, 32, (6, 6), 64, 1, x_dist="u11", seed=20),
+    W.layer("point_11steps", 1, 352, (2, 34), 70, 1, x_dist="u11", seed=21),
+    W.layer("point_odd_pixels", 5, 64, 7, 40, 1, x_dist="u11", seed=22),
+    W.layer("point_stride2", 2, 96, 14, 64, 1, 2, x_dist="u11", seed=23),
+    W.layer("point_pad1", 2, 32, 10, 64, 1, 1, 1, x_dist="u11", seed=24),
+    W.layer("taps_5x5", 2, 32, (9, 12), 96, 5, 1, 2, x_dist="u11", seed=25),
+    W.layer("taps_3x3_s2", 2, 64, (11, 14), 64, 3, 2, 1, x_dist="u11", seed=26),
+    W.layer("taps_1x7", 1, 64, (8, 17), 48, (1, 7), 1, (0, 3), x_dist="u11", seed=27),
+    W.layer("rows_c3_7x7", 2, 3, (30, 26), 64, 7, 2, 3, x_dist="u11", seed=28),
+    W.layer("rows_c20", 2, 20, (9, 10), 36, 3, 1, 1, x_dist="u11", seed=29),
+    W.layer("rows_c1", 3, 1, 8, 8, 1, x_dist="u11", seed=30),
+]
+
+
+@pytest.mark.parametrize("layer", OTHER, ids=lambda l: l["name"])
+@pytest.mark.parametrize("wn", [1, 2, 4])
+def test_other_forms(layer, wn):
+    check_layer(layer, cfg(wn, 32), what=layer["name"])
+    for layout in (B.NHWC, B.X_NHWC, B.Y_NHWC):
+        check_layout(layer, layout, cfg(wn, 32), what="%s layout %d" % (layer["name"], layout))
+
+
+@pytest.mark.parametrize("kw", [dict(split_k=2), dict(split_k=3, reduce=1), dict(split_k=16), dict(persist=1),
+                                dict(persist=4), dict(persist=2, reduce=1)], ids=str)
+def test_schedules_and_epilogue(kw):
+    """Shared tiles both ways, persistent workgroups with whole rounds and dealt-out steps, each with the fused epilogue.
+    (144 and 1200 tiles of 64 x 32 on 256 compute units: less than one round, one and a remainder.)"""
+    rng = np.random.default_rng(3)
+    for layer in (W.layer("sched_patch", 3, 64, 28, 96, 3, 1, 1, x_dist="u11", seed=40),
+                  W.layer("sched_point", 4, 96, 40, 380, 1, x_dist="u11", seed=41),
+                  W.layer("sched_taps", 3, 64, 28, 96, 3, 2, 1, x_dist="u11", seed=42)):
+        P, Q = B.conv_out_shape(B.make_desc(layer))
+        bias = rng.uniform(-1, 1, layer["k"]).astype(np.float32)
+        res = rng.uniform(-1, 1, (layer["n"], layer["k"], P, Q)).astype(np.float32)
+        for wn, bk in ((1, 16), (2, 16), (4, 32)):
+            c = cfg(wn, bk, **kw)
+            if not B.config_legal(B.make_desc(layer), c):   # more slices than steps
+                assert kw["split_k"] * bk > layer["c"] * layer["r"] * layer["s"]
+                continue
+            for layout in (B.NCHW, B.NHWC):
+                check_layout(layer, layout, c, bias=bias, residual=res, relu=True,
+                             what="%s %r layout %d" % (layer["name"], kw, layout))
+
+
+SPECIAL = [W.layer("sp_patch", 2, 32, 9, 40, 3, 1, 1, seed=50), W.layer("sp_point", 2, 64, 8, 40, 1, seed=51),
+           W.layer("sp_rows", 2, 5, 9, 40, 3, 1, 1, seed=52)]
+
+
+@pytest.mark.parametrize("layer", SPECIAL, ids=lambda l: l["name"])
+@pytest.mark.parametrize("split_k", [1, 2])
+def test_values_three_bf16_cannot_hold(layer, split_k):
+    """Infinities, NaN, numbers that round to a bf16 infinity, and tensors under 2^-110: what an fp32 sum gives."""
+    rng = np.random.default_rng(9)
+    x, w = W.make_inputs(layer)
+    w[:, :, 0, 0] = np.where(rng.uniform(size=w.shape[:2]) < 0.5, 0.5, -2.0)   # exact in bf16: zero remainders
+    c = cfg(2, 16, split_k=split_k)
+    sh = oc.shape_from_layer(layer)
+
+    def run(xv, wv):
+        torch, dev = torch_dev()
+        desc = B.make_desc(layer)
+        y = torch.empty((layer["n"], layer["k"]) + B.conv_out_shape(desc), device=dev)
+        B.conv2d_fwd_config(desc, c, to_dev(xv), to_dev(wv), y)
+        torch.cuda.synchronize()
+        return y.cpu().numpy()
+
+    hot = x.copy()
+    hot[0, 1, 3, 4], hot[0, 2, 5, 5], hot[1, 0, 0, 0], hot[1, 3, 7, 7] = np.inf, -np.inf, np.nan, np.inf
+    # (which outputs are infinite, and of which sign, by the rules of the numbers: the oracle sums the same products)
+    with np.errstate(invalid="ignore"):
+        want, _, _ = oc.conv2d(sh, hot, w)
+    got = run(hot, w)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert inf.any() and np.array_equal(got[inf], want[inf].astype(np.float32))
+    fine = np.isfinite(want)
+    assert np.max(np.abs(got[fine] - want[fine])) <= 1e-4 * np.max(np.abs(want[fine]))
+
+    # (3.4e38 rounds to infinity in bf16; the weights keep the sums finite)
+    big = np.where(x > 0.5, np.float32(3.4e38), np.float32(1e30)).astype(np.float32)
+    small_w = (w * np.float32(1e-6)).astype(np.float32)
+    for xv, wv in ((big, small_w), ((x * np.float32(1e-36)).astype(np.float32), w)):
+        want, d, _ = oc.conv2d(sh, xv, wv)
+        err = np.abs(run(xv, wv).astype(np.float64) - want) / np.where(d == 0, 1.0, d)
+        # (subnormal products of the second are rounded at 2^-149 each: 1e-45 / 1e-37 per term, far below)
+        assert err.max() <= 1e-4 and np.isfinite(err).all()
+
+
+def test_plan_moves_its_weights_between_the_two_packed_forms():
+    """A configuration of the other form set after the weights: the plan takes them from the form at hand, exactly."""
+    torch, dev = torch_dev()
+    for layer in (W.layer("mv_tap", 2, 64, 10, 72, 3, 1, 1, x_dist="u11", seed=60),
+                  W.layer("mv_rows", 2, 20, 10, 72, 3, 1, 1, x_dist="u11", seed=61)):
+        desc = B.make_desc(layer)
+        x, w = W.make_inputs(layer)
+        xd, wd = to_dev(x), to_dev(w)
+        shape = (layer["n"], layer["k"]) + B.conv_out_shape(desc)
+        a, b = torch.empty(shape, device=dev), torch.empty(shape, device=dev)
+        tiled, split = B.make_config(64, 64, 32, 2, 2), cfg(2, 32)
+        for first, second in ((tiled, split), (split, tiled)):
+            plan = B.Plan([desc])
+            plan.set_layer_config(0, first)
+            plan.set_weights(0, wd)
+            plan.set_layer_config(0, second)
+            plan.run_layer(0, xd, a)
+            B.conv2d_fwd_config(desc, second, xd, wd, b)
+            torch.cuda.synchronize()
+            assert torch.equal(a, b)
