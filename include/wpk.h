@@ -97,20 +97,28 @@ int wpk_last_hip_error(void);
  * split_k may not exceed the number of reduction steps, and the persistent schedule excludes
  * split_k > 1 and always has xcd_remap = 1.
  *
- * Two forms of kernel share the genes.  With bm >= 64 a workgroup stages a bm x bn tile's operands
+ * Three forms of kernel share the genes.  With bm >= 64 and wm > 1 a workgroup stages a bm x bn tile's operands
  * through LDS and its wm x wn waves each own a part of the tile (the tiled members).  With bm = 32
  * (the wave-split members, for launches of a few microseconds: single images, layers of few
  * pixels) a workgroup owns a 32 x bn tile and its wm * wn waves cut the reduction between them,
  * each fetching its operands straight into registers, and add their partial tiles up in LDS;
  * these take bk = 8 (they work in octets of reduction rows), need the reduction ordered
  * (r, s, c) (C a multiple of 32) and have no persistent schedule.
+ * With bm = 64 and wm = 1 (the split members) a workgroup's wn waves each own the 64 pixels by 32 channels and
+ * multiply on the bf16 matrix pipes: every fp32 operand is taken as the exact sum of three bf16 numbers and six of the
+ * nine products are summed, with an error against 64 bits below that of the fp32 MFMAs.  Operands that
+ * three bf16 numbers cannot hold (infinities, NaN, magnitudes above bf16's largest or activations below 2^-110) are
+ * found in the sums and the tile is computed again in fp32; weights below 2^-110 keep an absolute precision of 2^-134.
+ * One or two further waves per workgroup fetch activations.  bk = 16 lets 3x3 layers work from patches of x, in chunks of 16
+ * channels; otherwise, and with bk = 32, a step is 32 rows; `stages` has no meaning; a persistent schedule
+ * whose one round is more than half full runs plain.
  */
 #define WPK_N_GENES 10
 typedef struct wpk_conv_config {
     int32_t bm;        /* output pixels per workgroup tile:      32 (wave-split), 64, 128, 256      */
     int32_t bn;        /* output channels per workgroup tile:    32, 64, 128                        */
     int32_t bk;        /* reduction (c,r,s) entries per step:    8, 16, 32                          */
-    int32_t wm;        /* waves along the pixel dimension:       1, 2, 4                            */
+    int32_t wm;        /* waves along the pixel dimension:       1 (split), 2, 4                    */
     int32_t wn;        /* waves along the channel dimension:     1, 2, 4                            */
                        /* (bm = 32: wm * wn = 1, 2, 4 or 8 waves along the reduction)               */
     int32_t split_k;   /* slices of the reduction done by separate workgroups: 1 .. 16, 20, 24     */
@@ -183,8 +191,8 @@ int wpk_conv2d_fwd_fused_config(const wpk_conv_desc *d, const wpk_conv_config *c
  * (`cfg` may also be NULL: the cached tuned configuration of `d`, else the default); it calls no
  * hipMalloc, hipFree or other allocating routine and does not synchronise.  Its lookup table,
  * packed weights and the workspace of shared tiles live in one static device array of
- * WPK_NOALLOC_SCRATCH_BYTES (32 MiB) that every GPU the library runs on holds until the process
- * ends.  Limit: the packed weights, (C*R*S rounded up to 32) x (K rounded up to 128) floats, must
+ * WPK_NOALLOC_SCRATCH_BYTES (32 MiB; half as much again for the split members' weights, which take six bytes) that
+ * every GPU the library runs on holds until the process ends.  Limit: the packed weights, (C*R*S rounded up to 32) x (K rounded up to 128) floats, must
  * fit 32 MiB less 1088 KiB (e.g. 3x3 with C = K = 896, or 1x1 2048 -> 3840), else WPK_E_TOO_LARGE
  * and nothing is enqueued; where the workspace of shared tiles does not fit beside them the launch
  * sums with atomics into y instead (zeroed by a launch of its own).  Every call on a GPU uses
@@ -377,6 +385,8 @@ int wpk_plan_run_fused(wpk_plan *plan, const float *const *x, const float *const
 int wpk_plan_num_layers(const wpk_plan *plan);
 int wpk_plan_num_unique(const wpk_plan *plan);                       /* distinct descriptors     */
 int wpk_plan_layer_config(const wpk_plan *plan, int32_t layer, wpk_conv_config *out);
+/* (May grow the plan's workspace, and where `cfg` reads the weights in the other packed form, split or not, than the
+ * plan holds, allocates that form and fills it from the one at hand: both synchronise the device.) */
 int wpk_plan_set_layer_config(wpk_plan *plan, int32_t layer, const wpk_conv_config *cfg);
 void wpk_plan_destroy(wpk_plan *plan);
 

@@ -66,20 +66,20 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restri
 
 // Where row kk of the split members' reduction comes from: its place among the C*R*S rows of the source, or
 // -1 for a padding row.  With RS > 0 the rows run (c / 32, r, s, c % 32), else in the source's order.
-__device__ inline int split_source_row(int kk, int CRS, int RS)
+__device__ inline int split_source_row(int kk, int C, int CRS, int RS)
 {
     if (RS <= 0) return kk < CRS ? kk : -1;
-    const int c32 = kk / (32 * RS), t = kk - c32 * 32 * RS;
+    const int c32 = kk / (32 * RS), t = kk - c32 * 32 * RS, c = c32 * 32 + (t & 31);
     // (sixteen rows at a time: the two halves of the 32 channels follow each other for every tap)
-    return (c32 * 32 + (t & 31)) * RS + (t >> 5);
+    return c < C ? c * RS + (t >> 5) : -1;
 }
 
-// w[K][CRS] -> [CRSpad/16][Kpad/32][3 parts][64 lanes][8 bf16], zero padded: what lane l of a wave feeds the
+// w[K][CRS] -> [depths of 16 rows][Kpad/32][3 parts][64 lanes][8 bf16], zero padded: what lane l of a wave feeds the
 // bf16 MFMA of one depth and 32-channel block is channel l % 32, rows (l / 32)*8 .. +7.  Parts: w rounded to
 // bf16, the remainder rounded to bf16, the rest; their sum is w exactly (down to 2^-133).  A w that would round
 // to infinity is cut off instead, and an infinity or NaN has its remainders zero.
 __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict__ w, v4u *__restrict__ wp, int K,
-                                                         int CRS, int depths, int blocks, int RS)
+                                                         int C, int CRS, int depths, int blocks, int RS)
 {
     const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6), kb = blockIdx.y;
     if (t >= depths) return;
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict
     unsigned part[3][4];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int row = split_source_row(t * 16 + (lane >> 5) * 8 + j, CRS, RS);
+        const int row = split_source_row(t * 16 + (lane >> 5) * 8 + j, C, CRS, RS);
         const float v = k < K && row >= 0 ? w[(size_t)k * CRS + row] : 0.0f;
         const unsigned bits = __float_as_uint(v);
         unsigned h = pack_bf16(v, 0.0f) & 0xffffu;
@@ -438,16 +438,16 @@ static int upload_tap_table(const Problem &pr, int32_t **out, hipStream_t st)
 // read them.
 static size_t packed_bytes(const Problem &pr, bool split)
 {
-    return (size_t)pr.CRSpad * pr.Kpad * (split ? kSplitWeightBytes : sizeof(float));
+    return split ? (size_t)split_rows(pr) * pr.Kpad * kSplitWeightBytes : (size_t)pr.CRSpad * pr.Kpad * sizeof(float);
 }
 
 static int pack_weights(const Problem &pr, bool split, const float *w, float *wp, hipStream_t st)
 {
-    const int RS = pr.xquad || pr.tapmajor ? pr.d.r * pr.d.s : 0;
+    const int RS = (split ? split_taps(pr) : pr.xquad || pr.tapmajor) ? pr.d.r * pr.d.s : 0;
     if (split) {
-        const int depths = pr.CRSpad / 16, blocks = pr.Kpad / 32;
+        const int depths = (int)(split_rows(pr) / 16), blocks = pr.Kpad / 32;
         hipLaunchKernelGGL(pack_split_kernel, dim3((depths + 3) / 4, blocks), dim3(256), 0, st, w, (v4u *)wp, pr.d.k,
-                           pr.CRS, depths, blocks, RS);
+                           pr.d.c, pr.CRS, depths, blocks, RS);
     } else {
         dim3 grid(pr.CRSpad / 32, pr.Kpad / 32);
         hipLaunchKernelGGL(pack_weights_kernel, grid, dim3(256), 0, st, w, wp, pr.d.k, pr.CRS, pr.Kpad, pr.d.c, RS);
@@ -572,7 +572,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.remap = cfg.xcd_remap;
     a.x_bytes = (uint32_t)(pr.x_elems * 4);
     a.x_bias = (uint32_t)((d.pad_h * d.w + d.pad_w) * 4 * (pr.xl ? d.c : 1));
-    a.xl = pr.xquad ? 2 : pr.tapmajor ? 3 : pr.xl ? 1 : 0;
+    a.xl = pr.xquad ? 2 : pr.tapmajor || (split_member(cfg) && split_taps(pr)) ? 3 : pr.xl ? 1 : 0;
     a.yl = pr.yl ? 1 : 0;
     // whole channel quads with 16-byte stores when the tensors allow it
     if (pr.yl && d.k % 4 == 0 && ((uintptr_t)y & 15) == 0 && ((uintptr_t)epi.res & 15) == 0 &&
@@ -932,7 +932,7 @@ static int plan_need_weights(wpk_plan::Layer &L, const wpk_conv_config &cfg)
         L.wp[s] = packed;
         return WPK_OK;
     }
-    const int RS = L.pr.xquad || L.pr.tapmajor ? L.pr.d.r * L.pr.d.s : 0;
+    const int RS = (s ? L.pr.xquad || L.pr.tapmajor : split_taps(L.pr)) ? L.pr.d.r * L.pr.d.s : 0;  // (of the form at hand)
     int rc = WPK_OK;
     hipError_t e = hipDeviceSynchronize();
     if (e == hipSuccess) e = hipMalloc((void **)&plain, (size_t)L.pr.w_elems * sizeof(float));
@@ -1122,6 +1122,9 @@ extern "C" int wpk_conv2d_fwd_noalloc(const wpk_conv_desc *d, const wpk_conv_con
     if (cfg_in) cfg = *cfg_in;
     else if (wpk_cache_lookup(d, &cfg) != 1 || !legal_for(pr, cfg)) default_config(pr, g_cus, &cfg);
     auto round256 = [](size_t v) { return (v + 255) / 256 * 256; };
+    // (split weights of padded channels may not fit where four bytes each of the plain ones do)
+    if (split_member(cfg) && round256(packed_bytes(pr, true)) > kScratchRoomSplit)
+        cfg = wpk_conv_config{64, 64, 32, 2, 2, 1, 1, 0, 2, 0};
     const bool split = split_member(cfg);
     const size_t wbytes = round256(packed_bytes(pr, split)), room = split ? kScratchRoomSplit : kScratchRoom;
     if (tap_table_bytes(pr) > kScratchTapBytes || round256(packed_bytes(pr, false)) > kScratchRoom) return WPK_E_TOO_LARGE;

@@ -173,7 +173,7 @@ bool legal_for(const Problem &pr, const wpk_conv_config &cfg)
     } else {
         if (2 * (cfg.bk + 4) * (cfg.bm + cfg.bn) * 4 > kMaxLdsBytes) return false;    // two LDS stages
         if (threads > cfg.bm && (cfg.bk * cfg.bm / threads) % 4 != 0) return false;   // whole k quads per thread
-        if (split_member(cfg) && (int64_t)pr.CRSpad * pr.Kpad * kSplitWeightBytes > kMaxTiledBytes) return false;
+        if (split_member(cfg) && split_rows(pr) * pr.Kpad * kSplitWeightBytes > kMaxSplitBytes) return false;
     }
     int32_t nsteps = (pr.CRS + cfg.bk - 1) / cfg.bk;
     if (cfg.split_k > nsteps) return false;
@@ -191,14 +191,13 @@ bool legal_for(const Problem &pr, const wpk_conv_config &cfg)
     return true;
 }
 
-int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
+static int patch_bound(const Problem &pr)
 {
     const wpk_conv_desc &d = pr.d;
-    if (!split_member(cfg) || cfg.bk != 16 || cfg.bm != 64 || cfg.bn != 32 * cfg.wn || !(pr.tapmajor || pr.xquad) || d.r != 3 || d.s != 3) return 0;
-    if (d.pad_h > 2 * (int64_t)d.dil_h || d.pad_w > 2 * (int64_t)d.dil_w) return 0;
-    // From the first pixel's window to the last one's: bm - 1 steps along the row, for every change of row
+    if (d.r != 3 || d.s != 3 || d.pad_h > 2 * (int64_t)d.dil_h || d.pad_w > 2 * (int64_t)d.dil_w) return 0;
+    // From the first pixel's window to the last one's: 63 steps along the row, for every change of row
     // what the next row's start is further away than a step, for every change of image alike; then the window itself.
-    const int64_t W = d.w, HW = (int64_t)d.h * W, PQ = (int64_t)pr.P * pr.Q, n = cfg.bm - 1;
+    const int64_t W = d.w, HW = (int64_t)d.h * W, PQ = (int64_t)pr.P * pr.Q, n = 64 - 1;
     const int64_t rows = (n + pr.Q - 1) / pr.Q, images = (n + PQ - 1) / PQ;
     const int64_t span = n * d.stride_w + rows * std::max<int64_t>(0, d.stride_h * W - (int64_t)pr.Q * d.stride_w) +
                          images * std::max<int64_t>(0, HW - pr.P * d.stride_h * W) +
@@ -206,10 +205,25 @@ int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
     return span <= kHaloMax ? (int)span : 0;
 }
 
+bool split_taps(const Problem &pr)
+{
+    if (pr.tapmajor || pr.xquad) return true;
+    const int64_t c16 = (pr.d.c + 15) / 16 * 16, c32 = (pr.d.c + 31) / 32 * 32;
+    return !pr.xl && 2 * c16 <= 3 * (int64_t)pr.d.c && patch_bound(pr) > 0 &&
+           c32 * 9 * pr.Kpad * kSplitWeightBytes <= kMaxSplitBytes;
+}
+
+int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
+{
+    if (!split_member(cfg) || !split_taps(pr) || ((pr.tapmajor || pr.xquad) && cfg.bk != 16)) return 0;
+    return patch_bound(pr);
+}
+
 Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg)
 {
-    if (halo_positions(pr, cfg) > 0) return Reduction{pr.d.c / 16, 9 * 16};
+    if (halo_positions(pr, cfg) > 0) return Reduction{(pr.d.c + 15) / 16, 9 * 16};
     const int rows = split_member(cfg) ? 32 : cfg.bk;
+    if (split_member(cfg) && split_taps(pr)) return Reduction{(int32_t)(split_rows(pr) / 32), 32};
     return Reduction{(pr.CRS + rows - 1) / rows, rows};
 }
 
@@ -295,8 +309,8 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
     *out = c;
     return true;
 }
-// The split members' default, where filter taps are fetched whole (C a multiple of 32; row by row they gain nothing over
-// the tiled members: 24 against 22 us on 72 channels).  Waves of 64 pixels by 32 channels; patches where a 3x3
+// The split members' default, where they order the reduction by taps (row by row they gain nothing over the tiled
+// members: 53 against 47 us on the 7x7 stride-2 stem of three channels).  Waves of 64 pixels by 32 channels; patches where a 3x3
 // layer allows them.
 //  - As many waves per workgroup as the channels call for, four at most: a wider workgroup fetches and splits its pixels
 //    for more channels at once; what that is worth against padded channels is the weight of 20 / bn, from the measured
@@ -309,7 +323,7 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
 //    27-30 in 1 or 3-5; 512 channels at 7x7, 52 tiles: 28.0 in 4, 28.7 in 3, 32.6 in 8).
 static bool split_default(const Problem &pr, int compute_units, wpk_conv_config *out)
 {
-    if (!(pr.tapmajor || pr.xquad)) return false;
+    if (!split_taps(pr)) return false;
     const bool point = split_point(pr);
     int wn = 4;
     double best = 1e300;
@@ -327,6 +341,11 @@ static bool split_default(const Problem &pr, int compute_units, wpk_conv_config 
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);
     const int64_t want = point ? 5 * (int64_t)compute_units / 2 : 4 / wn * (int64_t)compute_units;
     const int64_t G = 3 * (int64_t)compute_units;
+    // A few four-wave tiles beyond one per compute unit, fetched tap by tap: the tiled members deal them out better (5x5,
+    // stride 2, 64 to 960 channels, 38x53, 4 images, 264 tiles on 256 compute units: 57.6 us there, 69.1 here).
+    if (wn == 4 && c.bk == 32 && tiles > compute_units && tiles < 2 * (int64_t)compute_units &&
+        tiles % compute_units * 8 <= compute_units)
+        return false;
     if (2 * tiles <= want) {
         // (slices of 64 rows at least, see kMinRunRows)
         const int64_t most = std::min<int64_t>(want / tiles, red.steps / std::max(1, kMinRunRows / red.rows));
@@ -413,7 +432,7 @@ static void model_config(const Problem &pr, int compute_units, wpk_conv_config *
     wpk_conv_config bc = {128, 64, 16, 2, 2, 1, 1, 0, 2, 0};
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &v = kVariants[i];
-        if (v.bm == kWaveSplitBm) continue;  // (the model prices LDS-staged tiles)
+        if (v.bm == kWaveSplitBm || v.wm == 1) continue;  // (the model prices fp32 LDS-staged tiles)
         for (int si = 0; si < kGeneCounts[5]; ++si) {
             wpk_conv_config c = {v.bm, v.bn, v.bk, v.wm, v.wn, kSplitVals[si], 1, 0, v.stages, 0};
             if (!legal_for(pr, c)) continue;

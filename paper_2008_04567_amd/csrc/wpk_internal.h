@@ -51,6 +51,7 @@ static const int kWaveSplitBm = 32;
 // products formed on the bf16 matrix pipes, weights packed as three bf16 parts (kSplitWeightBytes each).
 inline bool split_member(const wpk_conv_config &c) { return c.bm != kWaveSplitBm && c.wm == 1; }
 static const int kSplitWeightBytes = 6;
+static const int64_t kMaxSplitBytes = 0xffff0000;  // (their offsets are unsigned: every layer whose plain weights fit does)
 // Positions of x that the split members' patch form holds at most (two patches of 112 bytes each in LDS: 84 KB).
 static const int kHaloMax = 384;
 // LDS per workgroup: two stages of (BM + BN) columns of BK + 4 floats; two workgroups of the
@@ -162,13 +163,13 @@ struct IgemmArgs {
                         // the larger, since with XCD-contiguous ranges the other one is what every XCD fetches whole
     FastDiv div_tiles_m;  // by tiles_m
     FastDiv div_s;        // by S (the wave-split members find their first filter tap with it)
-    int32_t halo;       // split members: positions of x the patch of a 3x3 tile holds, 0: each tap fetched by itself, -1: a
-                        // 1x1 layer fetched four pixels at a time (split_point)
     int32_t xl;         // 0: x is [N][C][H][W]; 1: channels-last, gathered row by row; 2: channels-last,
                         // gathered as 16-byte channel quads (reduction rows ordered (r, s, c)); 3: [N][C][H][W]
                         // with the reduction ordered (r, s, c), one filter tap per step
     int32_t yl;         // 1: y (and the residual) are channels-last; 2: also K % 4 == 0 and y, residual and
                         // bias 16-byte aligned, so a pixel's channel quads move as 16-byte accesses
+    int32_t halo;       // split members: positions of x the patch of a 3x3 tile holds, 0: each tap fetched by itself, -1: a
+                        // 1x1 layer fetched four pixels at a time (split_point)
 };
 
 // What follows the convolution inside the same launch (Section 2.1, operator fusion).
@@ -196,7 +197,8 @@ void set_device_name(const std::string &name);
 std::string device_name();
 bool legal_for(const Problem &pr, const wpk_conv_config &cfg);
 // Bound on the positions of x that the windows of bm consecutive output pixels cover, where a split member with a
-// K-step of 16 works from such a patch (3x3 filters, ordinary padding, at most kHaloMax positions); else 0.
+// K-step of 16 (any K-step where C is no multiple of 32) works from such a patch (3x3 filters, ordinary padding, at most
+// kHaloMax positions); else 0.
 int halo_positions(const Problem &pr, const wpk_conv_config &cfg);
 #ifdef __HIP__
 #define WPK_HOST_DEVICE __host__ __device__
@@ -218,8 +220,20 @@ WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int str
     const int r = p * stride_h - pad_h + 2 * dil_h, c = q * stride_w - pad_w + 2 * dil_w;
     return (n * H + (r < H - 1 ? r : H - 1)) * W + (r - stride_h < H - 1 && c < W - 1 ? c : W - 1);
 }
-// Whether a split member fetches pr's x four neighbouring pixels at a time: 1x1 filters on [N][C][H][W], stride 1, no
-// padding, images of a multiple of four pixels.
+// Whether the split members order pr's reduction by filter taps, (c / 32, r, s, c % 32): where the tiled members do, and for
+// 3x3 filters on [N][C][H][W] that can work from patches if padding C to whole groups of 16 lengthens the reduction by
+// half at most (72 to 144 channels, 28x28, 16 images: 27.4 us against 36 on the tiled members; for other filters the
+// padding, to 32, takes what it gives: 1x1, 48 to 96 channels, 56x56: 19.9 against 16.3).  The weights of the padding are
+// zero, and the activations fetched for it are those of the last channel: what is finite adds nothing, and what is not
+// has the tile computed again (wpk_split.h).
+bool split_taps(const Problem &pr);
+// Rows of the reduction as the split members pack it.
+inline int64_t split_rows(const Problem &pr)
+{
+    return split_taps(pr) ? (int64_t)((pr.d.c + 31) / 32 * 32) * pr.d.r * pr.d.s : pr.CRSpad;
+}
+// Whether a split member fetches pr's x four neighbouring pixels at a time: 1x1 filters on [N][C][H][W], C a multiple of
+// 32, stride 1, no padding, images of a multiple of four pixels.
 inline bool split_point(const Problem &pr)
 {
     const wpk_conv_desc &d = pr.d;

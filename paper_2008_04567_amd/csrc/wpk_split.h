@@ -119,6 +119,7 @@ __device__ __forceinline__ void fp32_tile(v16f (&acc)[NNT * NMT], const __amdgpu
                     const int c32 = t / (2 * c->RS);
                     ch = c32 * 32 + (t & 1) * 16 + lrow * 8 + q;
                     rs = (t - c32 * 2 * c->RS) >> 1;
+                    past = ch >= c->C;
                 }
                 const int fr = rs / c->S, fs = rs - fr * c->S;
                 const bool out = past || ((inv >> fr) & 1) || ((inv >> (16 + fs)) & 1);
@@ -149,9 +150,9 @@ __device__ __forceinline__ void fp32_tile(v16f (&acc)[NNT * NMT], const __amdgpu
 //   kRows   row by row through the tap table, any C; rows in the source's order (c, r, s)
 //   kQuads  channels-last, C a multiple of 32: a lane fetches an octet of one pixel with two 16-byte loads
 //   kTaps   [N][C][H][W], C a multiple of 32: one filter tap per step, eight one-dword loads per octet
-//   kPoint  [N][C][H][W], 1x1 filters, stride 1, no padding, H * W a multiple of 4: four neighbouring pixels of a
+//   kPoint  [N][C][H][W], C a multiple of 32, 1x1 filters, stride 1, no padding, H * W a multiple of 4: four neighbouring pixels of a
 //           channel are sixteen contiguous bytes, so a wave fetches a whole step with eight loads instead of 32
-//   kPatch, kPatchQuads: 3x3 filters (C as above): the nine taps of sixteen channels read one patch of x.  The pixels of a
+//   kPatch, kPatchQuads: 3x3 filters ([N][C][H][W], any C; channels-last, C a multiple of 32): the nine taps of sixteen channels read one patch of x.  The pixels of a
 //           tile are consecutive, and so are the positions of x that their windows cover (numbered through the
 //           images): `halo` of them at most, any stride and dilation for which that fits.  A position is fetched and
 //           split once per sixteen channels instead of nine times.  A multiplying wave knows the LDS address of every
@@ -204,6 +205,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     auto fetch_segment = [&](const int m0, const int n0, const int kbeg, const int kend) WPK_LAMBDA {
         const int nr = kend - kbeg;
         const int prod = wave - WN;
+        const int last_ch = (a.C - 1) * a.HW4;  // kPatch: where the last channel is; padding channels are fetched there
         // the channels' bias: asked for now, stored once the first fetches are on their way
         constexpr int BI = (BN + NP * 64 - 1) / (NP * 64);
         float bval[BI];
@@ -257,7 +259,8 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
                         static_for<8>([&](auto J) WPK_LAMBDA {
                             constexpr int b = o * 8 + decltype(J)::value;
                             v[pb][b] = __builtin_bit_cast(
-                                float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, off[pb][0], (chunk * 16 + b) * a.HW4, 0));
+                                float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, off[pb][0],
+                                                                            min((chunk * 16 + b) * a.HW4, last_ch), 0));
                         });
                     }
                 });
@@ -687,7 +690,8 @@ template <int WN, SplitForm FORM>
 hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 {
     const size_t lds = 2 * (size_t)(FORM >= kPatch ? (a.halo + 1) * kHaloPitch : 64 * kStepPitch);
-    return launch_kernel<split_kernel<WN, FORM>, 64 * (WN + split_producers(WN, FORM))>(a, stream, lds);
+    return launch_kernel<split_kernel<WN, FORM>, 64 * (WN + split_producers(WN, FORM))>(
+        a, stream, lds, 2 * 32 * WN * sizeof(float) + sizeof(int));  // (bias, arrival)
 }
 
 // (the K-step gene says whether patches may be used, which the host has looked at; `stages` has no meaning here)

@@ -28,6 +28,10 @@ PATCH = [
     W.layer("dil2", 2, 32, 12, 64, 3, 1, 2, dil=2, x_dist="u11", seed=7),
     W.layer("dil31", 1, 32, (15, 10), 64, 3, 1, (3, 1), dil=(3, 1), x_dist="u11", seed=8),
     W.layer("wide", 1, 32, (5, 112), 64, 3, 1, 1, x_dist="u11", seed=9),
+    # (channels padded to 16, to 32; the last chunk half empty, full)
+    W.layer("c72", 2, 72, (9, 21), 100, 3, 1, 2, dil=2, x_dist="u11", seed=11),
+    W.layer("c11", 3, 11, 13, 30, 3, 1, 1, x_dist="u11", seed=12),
+    W.layer("c48", 2, 48, 10, 64, 3, 2, 1, x_dist="u11", seed=13),
     W.layer("too_wide", 1, 32, (7, 112), 64, 3, 1, 2, dil=2, x_dist="u11", seed=10),
 ]
 
@@ -50,6 +54,9 @@ OTHER = [
     W.layer("taps_5x5", 2, 32, (9, 12), 96, 5, 1, 2, x_dist="u11", seed=25),
     W.layer("taps_3x3_s2", 2, 64, (11, 14), 64, 3, 2, 1, x_dist="u11", seed=26),
     W.layer("taps_1x7", 1, 64, (8, 17), 48, (1, 7), 1, (0, 3), x_dist="u11", seed=27),
+    W.layer("taps_c24_1x1", 2, 24, 9, 64, 1, x_dist="u11", seed=31),
+    W.layer("taps_c43_5x5", 1, 43, (8, 15), 40, 5, 1, 2, x_dist="u11", seed=32),
+    W.layer("taps_c72_wide", 1, 72, (6, 130), 40, 3, 1, 2, dil=2, x_dist="u11", seed=33),
     W.layer("rows_c3_7x7", 2, 3, (30, 26), 64, 7, 2, 3, x_dist="u11", seed=28),
     W.layer("rows_c20", 2, 20, (9, 10), 36, 3, 1, 1, x_dist="u11", seed=29),
     W.layer("rows_c1", 3, 1, 8, 8, 1, x_dist="u11", seed=30),
@@ -87,7 +94,8 @@ def test_schedules_and_epilogue(kw):
 
 
 SPECIAL = [W.layer("sp_patch", 2, 32, 9, 40, 3, 1, 1, seed=50), W.layer("sp_point", 2, 64, 8, 40, 1, seed=51),
-           W.layer("sp_rows", 2, 5, 9, 40, 3, 1, 1, seed=52)]
+           W.layer("sp_rows", 2, 5, 9, 40, 3, 1, 1, seed=52), W.layer("sp_patch_c27", 2, 27, 9, 40, 3, 1, 1, seed=53),
+           W.layer("sp_taps_c27", 2, 27, 9, 40, 1, 2, 1, seed=54)]
 
 
 @pytest.mark.parametrize("layer", SPECIAL, ids=lambda l: l["name"])
@@ -109,7 +117,7 @@ def test_values_three_bf16_cannot_hold(layer, split_k):
         return y.cpu().numpy()
 
     hot = x.copy()
-    hot[0, 1, 3, 4], hot[0, 2, 5, 5], hot[1, 0, 0, 0], hot[1, 3, 7, 7] = np.inf, -np.inf, np.nan, np.inf
+    hot[0, 1, 3, 4], hot[0, 2, 5, 5], hot[1, 0, 0, 0], hot[1, -1, 7, 7] = np.inf, -np.inf, np.nan, np.inf
     # (which outputs are infinite, and of which sign, by the rules of the numbers: the oracle sums the same products)
     with np.errstate(invalid="ignore"):
         want, _, _ = oc.conv2d(sh, hot, w)
@@ -134,6 +142,7 @@ def test_plan_moves_its_weights_between_the_two_packed_forms():
     """A configuration of the other form set after the weights: the plan takes them from the form at hand, exactly."""
     torch, dev = torch_dev()
     for layer in (W.layer("mv_tap", 2, 64, 10, 72, 3, 1, 1, x_dist="u11", seed=60),
+                  W.layer("mv_patch", 2, 24, 10, 72, 3, 1, 1, x_dist="u11", seed=62),
                   W.layer("mv_rows", 2, 20, 10, 72, 3, 1, 1, x_dist="u11", seed=61)):
         desc = B.make_desc(layer)
         x, w = W.make_inputs(layer)
