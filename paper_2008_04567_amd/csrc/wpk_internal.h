@@ -240,6 +240,21 @@ inline bool split_point(const Problem &pr)
     return pr.tapmajor && d.r == 1 && d.s == 1 && d.stride_h == 1 && d.stride_w == 1 && d.pad_h == 0 && d.pad_w == 0 &&
            (int64_t)d.h * d.w % 4 == 0;
 }
+// The split members' weights lie depth by depth (16 rows of the reduction); step `step` of the reduction multiplies depths
+// split_depth(patch, step, 0), (.., 1), ...  A step is two depths that follow each other, or with a patch the nine taps of
+// sixteen channels: the two halves of 32 channels alternate (split_source_row).
+WPK_HOST_DEVICE inline int split_depth(bool patch, int step, int t)
+{
+    return patch ? (step >> 1) * 18 + (step & 1) + 2 * t : step * 2 + t;
+}
+// Byte offset of one depth of the 32 channels that start at `block` in the first depth.  A wave asks for weights two
+// depths ahead of those it multiplies, past the last one as well (nobody reads these): there the last depth's are
+// fetched again, since the whole offset is a scalar one and a buffer's range check does not cover that.
+WPK_HOST_DEVICE inline uint32_t split_weights_at(uint32_t block, int depth, uint32_t depth_bytes, uint32_t w_bytes)
+{
+    const uint32_t at = block + (uint32_t)depth * depth_bytes, last = block + w_bytes - depth_bytes;
+    return at < last ? at : last;
+}
 // What a configuration counts the reduction in: K-steps, or chunks of 16 channels where it works from patches.
 struct Reduction {
     int32_t steps, rows;  // how many, and how many rows of the reduction each holds

@@ -553,20 +553,18 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     const int nr = kend - kbeg, n0 = tile_n * BN + wave * 32;
     const unsigned depth_bytes = (unsigned)(a.Kpad / 32) * 3072u;  // weights: one depth further
     const unsigned wbase = (unsigned)(n0 / 32) * 3072u;
-    // (patches: the two halves of 32 channels alternate in the packed order, see split_source_row)
-    constexpr unsigned kTapStride = PATCH ? 2 : 1;
-    auto step_base = [&](const int r) WPK_LAMBDA {
-        return wbase + (unsigned)(PATCH ? (r >> 1) * 18 + (r & 1) : r * 2) * depth_bytes;
-    };
     v8bf aw[3 * 3];  // weights: three depths, two of them ahead
+    // (depth t of step r of the segment; t may be that of a later step's)
+    auto weights_at = [&](const int r, const int t) WPK_LAMBDA {
+        return split_weights_at(wbase, split_depth(PATCH, kbeg + r + t / NT, t % NT), depth_bytes, a.w_bytes);
+    };
     auto load_a = [&](auto SET, const unsigned base, auto E) WPK_LAMBDA {
         constexpr int set = decltype(SET)::value, e = decltype(E)::value;
         aw[set * 3 + e] = __builtin_bit_cast(
             v8bf, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16, base + e * 1024, 0));
     };
-    unsigned wcur = step_base(kbeg);
     static_for<2>([&](auto S) WPK_LAMBDA {
-        static_for<3>([&](auto E) WPK_LAMBDA { load_a(S, wcur + decltype(S)::value * kTapStride * depth_bytes, E); });
+        static_for<3>([&](auto E) WPK_LAMBDA { load_a(S, weights_at(0, decltype(S)::value), E); });
     });
     unsigned addr[PATCH ? NMT * 5 : 1];  // of every tap, in units of 16 bytes, two per register
     if constexpr (PATCH) {
@@ -620,13 +618,11 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     };
     // step number r of the segment; P: its number within the loop's body
     auto step_body = [&](const int r, auto P) WPK_LAMBDA {
-        const unsigned wnext = PATCH ? step_base(kbeg + r + 1) : wcur + 2 * depth_bytes;
         static_for<NT>([&](auto TAP) WPK_LAMBDA {
             constexpr int t = decltype(TAP)::value, g = decltype(P)::value * NT + t;
             using NEXT = std::integral_constant<int, (t + 1) % NT>;
             using SET = std::integral_constant<int, (g + 2) % 3>;  // the set that the depth before this one has left
-            const unsigned ahead = t + 2 < NT ? wcur + (t + 2) * kTapStride * depth_bytes
-                                              : wnext + (t + 2 - NT) * kTapStride * depth_bytes;
+            const unsigned ahead = weights_at(r, t + 2);
             static_for<6>([&](auto PQ) WPK_LAMBDA {
                 constexpr int q = decltype(PQ)::value;
                 // (A part, B part), 0 h, 1 m, 2 l: hl | mm, hm | hh, mh, lh
@@ -658,7 +654,6 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
-        wcur = wnext;
     };
     __syncthreads();
     static_for<3>([&](auto PART) WPK_LAMBDA { read_part(PART, std::integral_constant<int, 0>{}); });
@@ -673,8 +668,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
 
     if (join_sums(acc, sml))
         fp32_tile<1, NMT, FORM == kRows>(acc, xrsrc, wrsrc, m0, wbase, nr * NT, [&](int i) WPK_LAMBDA {
-            const int c = kbeg + i / NT;
-            return PATCH ? (c >> 1) * 18 + (c & 1) + i % NT * 2 : kbeg * NT + i;
+            return split_depth(PATCH, kbeg + i / NT, i % NT);
         }, lane);
     const cold_ptr ce = cold_args();
     if (mode == kFixup &&
