@@ -240,6 +240,14 @@ inline bool split_point(const Problem &pr)
     return pr.tapmajor && d.r == 1 && d.s == 1 && d.stride_h == 1 && d.stride_w == 1 && d.pad_h == 0 && d.pad_w == 0 &&
            (int64_t)d.h * d.w % 4 == 0;
 }
+// Byte offset of channel ch in an image of [N][C][H][W], HW4 bytes per channel.  Chunks of 16 channels may run past the
+// last one: what is fetched there is the last channel (its weights are zero).  (Unsigned: split_taps keeps ch below 3/2 C, so
+// with C * HW4 below 2^31 the product is below 2^32, but not always below 2^31.)
+WPK_HOST_DEVICE inline uint32_t patch_channel_at(int ch, int C, int HW4)
+{
+    const uint32_t at = (uint32_t)ch * (uint32_t)HW4, last = (uint32_t)(C - 1) * (uint32_t)HW4;
+    return at < last ? at : last;
+}
 // The split members' weights lie depth by depth (16 rows of the reduction); step `step` of the reduction multiplies depths
 // split_depth(patch, step, 0), (.., 1), ...  A step is two depths that follow each other, or with a patch the nine taps of
 // sixteen channels: the two halves of 32 channels alternate (split_source_row).

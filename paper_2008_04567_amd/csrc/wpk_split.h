@@ -205,7 +205,6 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     auto fetch_segment = [&](const int m0, const int n0, const int kbeg, const int kend) WPK_LAMBDA {
         const int nr = kend - kbeg;
         const int prod = wave - WN;
-        const int last_ch = (a.C - 1) * a.HW4;  // kPatch: where the last channel is; padding channels are fetched there
         // the channels' bias: asked for now, stored once the first fetches are on their way
         constexpr int BI = (BN + NP * 64 - 1) / (NP * 64);
         float bval[BI];
@@ -259,8 +258,8 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
                         static_for<8>([&](auto J) WPK_LAMBDA {
                             constexpr int b = o * 8 + decltype(J)::value;
                             v[pb][b] = __builtin_bit_cast(
-                                float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, off[pb][0],
-                                                                            min((chunk * 16 + b) * a.HW4, last_ch), 0));
+                                float, __builtin_amdgcn_raw_buffer_load_b32(
+                                           xrsrc, off[pb][0], patch_channel_at(chunk * 16 + b, a.C, a.HW4), 0));
                         });
                     }
                 });

@@ -57,11 +57,53 @@ int main()
 """
 
 
-def test_every_tap_lies_in_the_patch_and_the_patch_within_its_bound(tmp_path):
+# Channels of the last chunk, in layers that the split members take and whose x comes close to 2 GiB (N = 1): every channel's
+# plane lies in x, also where 16 planes would not fit 32 bits.
+CHANNELS = r"""
+#include <stdio.h>
+#include "wpk_internal.h"
+using namespace wpk;
+int main()
+{
+    const int shapes[][3] = {{11, 300000, 146}, {11, 330000, 146}, {12, 300000, 147}, {23, 150000, 150}, {45, 80000, 140},
+                             {41, 90000, 142}, {200, 18000, 144}, {13, 40, 40}};
+    int wide = 0, checked = 0;
+    for (const auto &s : shapes) {
+        wpk_conv_desc d = {1, s[0], s[1], s[2], 8, 3, 3, 1, 1, 1, 1, 1, 1, WPK_F32, WPK_NCHW};
+        Problem pr;
+        const wpk_conv_config cfg = {64, 32, 16, 1, 1, 1, 1, 0, 1, 0};
+        if (make_problem(&d, &pr) != WPK_OK || !legal_for(pr, cfg) || halo_positions(pr, cfg) == 0) continue;
+        ++checked;
+        const long long plane = (long long)d.h * d.w * 4;
+        for (int ch = 0; ch < reduction_of(pr, cfg).steps * 16; ++ch) {
+            const long long at = patch_channel_at(ch, d.c, (int)plane);
+            wide += ch * plane > 0x7fffffff;
+            if (at != (ch < d.c ? ch : d.c - 1) * plane || at + plane > pr.x_elems * 4) {
+                printf("c %d h %d w %d channel %d: %lld\n", d.c, d.h, d.w, ch, at);
+                return 1;
+            }
+        }
+    }
+    printf("%d %d\n", checked, wide);
+    return checked >= 6 && wide > 3 ? 0 : 2;
+}
+"""
+
+
+def run_program(tmp_path, text):
     src, exe = tmp_path / "patch.cpp", tmp_path / "patch"
-    src.write_text(PROGRAM)
+    src.write_text(text)
     csrc = os.path.join(ROOT, "paper_2008_04567_amd", "csrc")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", csrc, str(src),
                     os.path.join(csrc, "wpk_host.cpp"), "-o", str(exe)], check=True)
-    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True)
+
+
+def test_channels_of_the_last_chunk_lie_in_x(tmp_path):
+    res = run_program(tmp_path, CHANNELS)
+    assert res.returncode == 0, (res.returncode, res.stdout)
+
+
+def test_every_tap_lies_in_the_patch_and_the_patch_within_its_bound(tmp_path):
+    res = run_program(tmp_path, PROGRAM)
     assert res.returncode == 0, res.stdout
