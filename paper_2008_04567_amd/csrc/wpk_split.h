@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     constexpr int BM = 64, BN = 32 * WN, NMT = 2, T = 64 * WN;
     constexpr int NT = PATCH ? 9 : 2;          // MFMA depths (of 16 rows) per step
     extern __shared__ __attribute__((aligned(16))) char lds[];  // two steps of activations
-    __shared__ float bias[2][BN];              // of this segment's channels and of the one before
+    __shared__ __attribute__((aligned(16))) float bias[2][BN];  // of this segment's channels and of the one before
     __shared__ int arrival;
 
     touch_kernarg_lines();
