@@ -75,9 +75,7 @@ __device__ inline int split_source_row(int kk, int C, int CRS, int RS)
 }
 
 // w[K][CRS] -> [depths of 16 rows][Kpad/32][3 parts][64 lanes][8 bf16], zero padded: what lane l of a wave feeds the
-// bf16 MFMA of one depth and 32-channel block is channel l % 32, rows (l / 32)*8 .. +7.  Parts: w rounded to
-// bf16, the remainder rounded to bf16, the rest; their sum is w exactly (down to 2^-133).  A w that would round
-// to infinity is cut off instead, and an infinity or NaN has its remainders zero.
+// bf16 MFMA of one depth and 32-channel block is channel l % 32, rows (l / 32)*8 .. +7.  Parts: see split_weight.
 __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict__ w, v4u *__restrict__ wp, int K,
                                                          int C, int CRS, int depths, int blocks, int RS)
 {
@@ -89,13 +87,8 @@ __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict
     for (int j = 0; j < 8; ++j) {
         const int row = split_source_row(t * 16 + (lane >> 5) * 8 + j, C, CRS, RS);
         const float v = k < K && row >= 0 ? w[(size_t)k * CRS + row] : 0.0f;
-        const unsigned bits = __float_as_uint(v);
-        unsigned h = pack_bf16(v, 0.0f) & 0xffffu;
-        if ((h & 0x7fffu) == 0x7f80u && (bits & 0x7f800000u) != 0x7f800000u) h = bits >> 16;
-        const float r1 = (bits & 0x7f800000u) == 0x7f800000u ? 0.0f : v - bf16_low(h);
-        const unsigned m = pack_bf16(r1, 0.0f) & 0xffffu;
-        const unsigned l = pack_bf16(r1 - bf16_low(m), 0.0f) & 0xffffu;
-        const unsigned v3[3] = {h, m, l};
+        unsigned v3[3];
+        split_weight(v, v3);
 #pragma unroll
         for (int q = 0; q < 3; ++q) part[q][j / 2] = j % 2 ? part[q][j / 2] | v3[q] << 16 : v3[q];
     }
@@ -104,7 +97,7 @@ __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict
         wp[(((size_t)t * blocks + kb) * 3 + q) * 64 + lane] = (v4u){part[q][0], part[q][1], part[q][2], part[q][3]};
 }
 
-// The way back, from either packed form: w[K][CRS] (a plan whose configuration moves to the other form).
+// The way back, from either packed form, exactly: w[K][CRS] (a plan whose configuration moves to the other form).
 __global__ void __launch_bounds__(256) unpack_weights_kernel(const void *__restrict__ packed, float *__restrict__ w,
                                                              int K, int C, int CRS, int Kpad, int RS, int split)
 {
@@ -117,7 +110,7 @@ __global__ void __launch_bounds__(256) unpack_weights_kernel(const void *__restr
             const int lane = (kk >> 3 & 1) * 32 + (k & 31);
             const unsigned short *p = (const unsigned short *)packed +
                                       (((size_t)(kk >> 4) * (Kpad / 32) + k / 32) * 3 * 64 + lane) * 8 + (kk & 7);
-            w[i] = (bf16_low(p[2 * 512]) + bf16_low(p[512])) + bf16_low(p[0]);
+            w[i] = join_weight(p[0], p[512], p[2 * 512]);
         } else {
             const int kk = RS > 0 ? rs * C + c : row;
             w[i] = ((const float *)packed)[((size_t)(kk / 4) * Kpad + k) * 4 + kk % 4];

@@ -14,9 +14,10 @@
 // all six in one accumulator 1.0e-6, 3.5e-7, 1.1e-7).  Six MFMAs of 32 cycles per 32 x 32 block and
 // sixteen rows of the reduction stand against eight fp32 ones of 64.
 //
-// What three bf16 cannot hold -- infinities (inf - inf is NaN in m), finite numbers that round to a bf16
-// infinity, and numbers below 2^-110, whose l would fall under the smallest bf16 -- shows in the accumulators: not
-// finite, or all of a lane's outputs under 2^-90 without being zero.  A wave that finds that computes its
+// Weights are packed scaled by 2^16, which makes every one below 2^111 three bf16 numbers exactly, however small; the others are packed
+// whole beside a NaN (split_weight).  What else three bf16 cannot hold -- infinite activations (inf - inf is NaN in m), finite ones
+// that round to a bf16 infinity, and activations below 2^-110, whose l would fall under the smallest bf16 -- shows in the
+// accumulators: not finite, or all of a lane's outputs under 2^-90 without being zero.  A wave that finds that computes its
 // tile again with fp32 MFMAs (fp32_tile below), slowly, from the same operands.
 //
 // Workgroup.  64 pixels x 32 WN channels.  WN waves multiply, each all 64 pixels by 32 channels of its own: every
@@ -51,6 +52,31 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 __device__ __forceinline__ float bf16_low(unsigned p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
+// Weights are packed 2^16 times as large as they are, so that the smallest fp32 number, 2^-149, is the smallest bf16
+// one, 2^-133, and every weight below 2^111 is exactly three bf16 numbers; the sums are scaled back by join_sums.
+constexpr float kWeightScale = 0x1p16f;
+// The parts of a weight as bf16 bits: the scaled weight rounded to bf16, the remainder rounded to bf16, the rest.  A weight that
+// would round to infinity so, an infinity or NaN has NaN as its first part, which shows in every sum it enters, and its own
+// bits in the other two.
+__device__ __forceinline__ void split_weight(const float w, unsigned (&part)[3])
+{
+    const float v = w * kWeightScale;
+    const unsigned h = pack_bf16(v, 0.0f) & 0xffffu;
+    const float r = v - bf16_low(h);
+    const unsigned m = pack_bf16(r, 0.0f) & 0xffffu, l = pack_bf16(r - bf16_low(m), 0.0f) & 0xffffu;
+    const unsigned bits = __builtin_bit_cast(unsigned, w);
+    const bool whole = (h & 0x7f80u) == 0x7f80u;
+    part[0] = whole ? 0x7fffu : h;
+    part[1] = whole ? bits >> 16 : m;
+    part[2] = whole ? bits & 0xffffu : l;
+}
+// The weight again, exactly.
+__device__ __forceinline__ float join_weight(const unsigned h, const unsigned m, const unsigned l)
+{
+    if ((h & 0x7f80u) == 0x7f80u) return __builtin_bit_cast(float, m << 16 | l);
+    return ((bf16_low(l) + bf16_low(m)) + bf16_low(h)) * (1.0f / kWeightScale);
+}
+
 // eight floats as their three bf16 parts, sixteen bytes each
 __device__ __forceinline__ void split_octet(const float (&v)[8], v4u &h, v4u &m, v4u &l)
 {
@@ -73,7 +99,7 @@ __device__ __forceinline__ bool join_sums(v16f (&acc)[NB], const v16f (&sml)[NB]
     static_for<NB>([&](auto I) WPK_LAMBDA {
         static_for<16>([&](auto E) WPK_LAMBDA {
             constexpr int i = decltype(I)::value, e = decltype(E)::value;
-            const float v = acc[i][e] + sml[i][e];
+            const float v = (acc[i][e] + sml[i][e]) * (1.0f / kWeightScale);
             acc[i][e] = v;
             top = max(top, __builtin_bit_cast(unsigned, v) & 0x7fffffffu);
         });
@@ -128,16 +154,15 @@ __device__ __forceinline__ void fp32_tile(v16f (&acc)[NNT * NMT], const __amdgpu
             });
             static_for<NNT>([&](auto I) WPK_LAMBDA {
                 constexpr int i = decltype(I)::value;
-                v8bf w[3];
+                v4u w[3];
                 static_for<3>([&](auto Q) WPK_LAMBDA {
-                    w[decltype(Q)::value] = __builtin_bit_cast(
-                        v8bf, __builtin_amdgcn_raw_buffer_load_b128(
-                                  wrsrc, lane * 16, wbase + (unsigned)t * wblk_bytes +
-                                                        (i * 3 + decltype(Q)::value) * 1024, 0));
+                    w[decltype(Q)::value] = __builtin_amdgcn_raw_buffer_load_b128(
+                        wrsrc, lane * 16, wbase + (unsigned)t * wblk_bytes + (i * 3 + decltype(Q)::value) * 1024, 0);
                 });
                 static_for<8>([&](auto Q) WPK_LAMBDA {
-                    constexpr int q = decltype(Q)::value;
-                    const float wv = ((float)w[2][q] + (float)w[1][q]) + (float)w[0][q];
+                    constexpr int q = decltype(Q)::value, sh = q % 2 * 16;
+                    const float wv = join_weight(w[0][q / 2] >> sh & 0xffffu, w[1][q / 2] >> sh & 0xffffu,
+                                                 w[2][q / 2] >> sh & 0xffffu);
                     f[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, xv[q], f[i], 0, 0, 0);
                 });
             });

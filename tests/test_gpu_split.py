@@ -138,6 +138,100 @@ def test_values_three_bf16_cannot_hold(layer, split_k):
         assert err.max() <= 1e-4 and np.isfinite(err).all()
 
 
+# Every way of finding activations (the kernel's six forms, the patch with and without padded channels): layer, layout, bk.
+FORMS = {
+    "patch": (W.layer("f_patch", 2, 32, 9, 40, 3, 1, 1, x_dist="u11", seed=70), B.NCHW, 16),
+    "patch_c27": (W.layer("f_patch27", 2, 27, 9, 40, 3, 1, 1, x_dist="u11", seed=71), B.NCHW, 16),
+    "patch_quads": (W.layer("f_pquads", 2, 64, 9, 40, 3, 1, 1, x_dist="u11", seed=72), B.NHWC, 16),
+    "point": (W.layer("f_point", 2, 64, 8, 40, 1, x_dist="u11", seed=73), B.NCHW, 32),
+    "taps": (W.layer("f_taps", 2, 32, 9, 40, 5, 1, 2, x_dist="u11", seed=74), B.NCHW, 32),
+    "quads": (W.layer("f_quads", 2, 32, 9, 40, 3, 1, 1, x_dist="u11", seed=75), B.NHWC, 32),
+    "rows": (W.layer("f_rows", 2, 5, 9, 40, 3, 1, 1, x_dist="u11", seed=76), B.NCHW, 32),
+    "rows_nhwc": (W.layer("f_rows_cl", 2, 20, 9, 40, 3, 1, 1, x_dist="u11", seed=77), B.NHWC, 32),
+}
+
+
+def run_form(form, x, w, split_k=1):
+    """The layer of a form on these operands ([N][C][H][W]); the output as [N][K][P][Q]."""
+    torch, dev = torch_dev()
+    layer, layout, bk = FORMS[form]
+    desc = B.make_desc(layer, layout=layout)
+    P, Q = B.conv_out_shape(desc)
+    n, k = layer["n"], layer["k"]
+    y = torch.empty((n, P, Q, k) if layout else (n, k, P, Q), device=dev)
+    B.conv2d_fwd_config(desc, cfg(2, bk, split_k=split_k), to_dev(x.transpose(0, 2, 3, 1) if layout else x), to_dev(w), y)
+    torch.cuda.synchronize()
+    y = y.cpu().numpy()
+    return y.transpose(0, 3, 1, 2) if layout else y
+
+
+def scaled(a, power):
+    """a * 2^power, rounded to fp32 once."""
+    return np.ldexp(a.astype(np.float64), power).astype(np.float32)
+
+
+# What fp32 sums are off by at most on these layers, over sum |x w|: 45 to 800 terms, each step of the sum rounded by
+# 2^-24 of a partial sum that is a small part of sum |x w|; and half the smallest number.
+SUM_ERROR = 1e-6
+
+
+def assert_fp32_sums(got, want, d, what):
+    err = np.abs(got.astype(np.float64) - want) - 2.0 ** -149
+    worst = float(np.max(err / np.where(d == 0, 1.0, d)))
+    assert bool(np.isfinite(got).all()) and worst <= SUM_ERROR, (what, worst)
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("powers", [(-118, 0), (-124, 40), (-126, 0), (-140, 50), (-148, 100)], ids=str)
+def test_small_weights(form, powers):
+    """Weights as small as fp32 has them, against ordinary and large activations, alone and in every other channel: the
+    oracle's sums to fp32's precision."""
+    layer = FORMS[form][0]
+    x, w = W.make_inputs(layer)
+    w = w / np.abs(w).max()   # the powers are those of the largest weight
+    x = scaled(x, powers[1])
+    small = scaled(w, powers[0])
+    mixed = np.where((np.arange(layer["k"]) % 2 == 0)[:, None, None, None], small, w)
+    for wv in (small, mixed):
+        want, d, _ = oc.conv2d(oc.shape_from_layer(layer), x, wv)
+        assert_fp32_sums(run_form(form, x, wv), want, d, (form, powers))
+
+
+def test_weights_of_any_value_move_between_the_packed_forms():
+    """The smallest numbers, the largest, infinities and NaN through the split form into the tiled one: bit for bit."""
+    torch, dev = torch_dev()
+    layer = W.layer("mv_any", 1, 32, 6, 48, 1, x_dist="u11", seed=63)
+    desc = B.make_desc(layer)
+    x = np.zeros((1, 32, 6, 6), np.float32)
+    x[0, np.arange(32), np.arange(32) // 6, np.arange(32) % 6] = 1   # pixel c sees channel c alone
+    rng = np.random.default_rng(4)
+    w = rng.integers(0, 2 ** 32, (48, 32), dtype=np.uint32)
+    w[0, :8] = (1, 0x80000001, 0x007fffff, 0x7f7fffff, 0xff7fffff, 0x77ffffff, 0x7f000000, 0x00800000)
+    # infinities and NaN in filters of their own: elsewhere 0 * inf would hide its neighbours
+    special = (w >> 23 & 0xff) == 0xff
+    special[0] = False
+    w[special] &= 0xbfffffff
+    w[40], w[41], w[42] = 0x7f800000, 0xff800000, 0x7fc00000
+    wd = to_dev(w.view(np.float32).reshape(48, 32, 1, 1))
+    xd = to_dev(x)
+    a, b = (torch.empty((1, 48, 6, 6), device=dev) for _ in range(2))
+    plan = B.Plan([desc])
+    plan.set_layer_config(0, cfg(2, 32))
+    plan.set_weights(0, wd)
+    plan.set_layer_config(0, B.make_config(64, 64, 32, 2, 2))
+    plan.run_layer(0, xd, a)
+    B.conv2d_fwd_config(desc, B.make_config(64, 64, 32, 2, 2), xd, wd, b)
+    torch.cuda.synchronize()
+    ai, bi = a.cpu().numpy(), b.cpu().numpy()
+    assert np.array_equal(ai, bi, equal_nan=True)
+    keep = np.arange(48) < 40
+    assert np.array_equal(ai.reshape(48, 36)[keep][:, :32], w.view(np.float32)[keep])
+    # and the split kernel on them
+    B.conv2d_fwd_config(desc, cfg(2, 32), xd, wd, b)
+    torch.cuda.synchronize()
+    assert np.array_equal(b.cpu().numpy(), ai, equal_nan=True)
+
+
 def test_plan_moves_its_weights_between_the_two_packed_forms():
     """A configuration of the other form set after the weights: the plan takes them from the form at hand, exactly."""
     torch, dev = torch_dev()
