@@ -251,17 +251,16 @@ WPK_HOST_DEVICE inline uint32_t patch_channel_at(int ch, int C, int HW4)
 // The split members' weights lie depth by depth (16 rows of the reduction); step `step` of the reduction multiplies depths
 // split_depth(patch, step, 0), (.., 1), ...  A step is two depths that follow each other, or with a patch the nine taps of
 // sixteen channels: the two halves of 32 channels alternate (split_source_row).
-WPK_HOST_DEVICE inline int split_depth(bool patch, int step, int t)
+WPK_HOST_DEVICE constexpr int split_depth(bool patch, int step, int t)
 {
     return patch ? (step >> 1) * 18 + (step & 1) + 2 * t : step * 2 + t;
 }
-// Byte offset of one depth of the 32 channels that start at `block` in the first depth.  A wave asks for weights two
-// depths ahead of those it multiplies, past the last one as well (nobody reads these): there the last depth's are
+// Byte offset of a step's first depth for the 32 channels that start at `block` in the first depth of all.  A wave asks for
+// weights two depths ahead of those it multiplies, past the last step as well (nobody reads these): there the last step's are
 // fetched again, since the whole offset is a scalar one and a buffer's range check does not cover that.
-WPK_HOST_DEVICE inline uint32_t split_weights_at(uint32_t block, int depth, uint32_t depth_bytes, uint32_t w_bytes)
+WPK_HOST_DEVICE inline uint32_t split_weights_at(bool patch, uint32_t block, int step, int nsteps, uint32_t depth_bytes)
 {
-    const uint32_t at = block + (uint32_t)depth * depth_bytes, last = block + w_bytes - depth_bytes;
-    return at < last ? at : last;
+    return block + (uint32_t)split_depth(patch, step < nsteps ? step : nsteps - 1, 0) * depth_bytes;
 }
 // What a configuration counts the reduction in: K-steps, or chunks of 16 channels where it works from patches.
 struct Reduction {

@@ -578,17 +578,18 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     const unsigned depth_bytes = (unsigned)(a.Kpad / 32) * 3072u;  // weights: one depth further
     const unsigned wbase = (unsigned)(n0 / 32) * 3072u;
     v8bf aw[3 * 3];  // weights: three depths, two of them ahead
-    // (depth t of step r of the segment; t may be that of a later step's)
-    auto weights_at = [&](const int r, const int t) WPK_LAMBDA {
-        return split_weights_at(wbase, split_depth(PATCH, kbeg + r + t / NT, t % NT), depth_bytes, a.w_bytes);
+    constexpr unsigned kTapStride = split_depth(PATCH, 0, 1);
+    auto step_base = [&](const int r) WPK_LAMBDA {
+        return split_weights_at(PATCH, wbase, kbeg + r, a.nsteps, depth_bytes);
     };
     auto load_a = [&](auto SET, const unsigned base, auto E) WPK_LAMBDA {
         constexpr int set = decltype(SET)::value, e = decltype(E)::value;
         aw[set * 3 + e] = __builtin_bit_cast(
             v8bf, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16, base + e * 1024, 0));
     };
+    unsigned wcur = step_base(0);
     static_for<2>([&](auto S) WPK_LAMBDA {
-        static_for<3>([&](auto E) WPK_LAMBDA { load_a(S, weights_at(0, decltype(S)::value), E); });
+        static_for<3>([&](auto E) WPK_LAMBDA { load_a(S, wcur + decltype(S)::value * kTapStride * depth_bytes, E); });
     });
     unsigned addr[PATCH ? NMT * 5 : 1];  // of every tap, in units of 16 bytes, two per register
     if constexpr (PATCH) {
@@ -642,11 +643,13 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     };
     // step number r of the segment; P: its number within the loop's body
     auto step_body = [&](const int r, auto P) WPK_LAMBDA {
+        const unsigned wnext = step_base(r + 1);
         static_for<NT>([&](auto TAP) WPK_LAMBDA {
             constexpr int t = decltype(TAP)::value, g = decltype(P)::value * NT + t;
             using NEXT = std::integral_constant<int, (t + 1) % NT>;
             using SET = std::integral_constant<int, (g + 2) % 3>;  // the set that the depth before this one has left
-            const unsigned ahead = weights_at(r, t + 2);
+            const unsigned ahead = t + 2 < NT ? wcur + (t + 2) * kTapStride * depth_bytes
+                                              : wnext + (t + 2 - NT) * kTapStride * depth_bytes;
             static_for<6>([&](auto PQ) WPK_LAMBDA {
                 constexpr int q = decltype(PQ)::value;
                 // (A part, B part), 0 h, 1 m, 2 l: hl | mm, hm | hh, mh, lh
@@ -678,6 +681,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
+        wcur = wnext;
     };
     __syncthreads();
     static_for<3>([&](auto PART) WPK_LAMBDA { read_part(PART, std::integral_constant<int, 0>{}); });
