@@ -106,9 +106,9 @@ int wpk_last_hip_error(void);
  * (r, s, c) (C a multiple of 32) and have no persistent schedule.
  * With bm = 64 and wm = 1 (the split members) a workgroup's wn waves each own the 64 pixels by 32 channels and
  * multiply on the bf16 matrix pipes: every fp32 operand is taken as the exact sum of three bf16 numbers and six of the
- * nine products are summed, with an error against 64 bits below that of the fp32 MFMAs.  Operands that
- * three bf16 numbers cannot hold (infinities, NaN, magnitudes above bf16's largest or activations below 2^-110) are
- * found in the sums and the tile is computed again in fp32; weights are held exactly, whatever their value.
+ * nine products are summed, with an error against 64 bits below that of the fp32 MFMAs.  That holds down to the smallest
+ * fp32 numbers.  Operands of 2^111 and more, infinities and NaN, and sums of 2^95 and more are found in the sums and the
+ * tile is computed again in fp32, at a fraction of the speed.
  * One or two further waves per workgroup fetch activations.  bk = 16 lets 3x3 layers work from patches of x, in chunks of 16
  * channels; otherwise, and with bk = 32, a step is 32 rows; `stages` has no meaning; a persistent schedule
  * whose one round is more than half full runs plain.

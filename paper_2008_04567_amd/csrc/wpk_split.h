@@ -14,11 +14,11 @@
 // all six in one accumulator 1.0e-6, 3.5e-7, 1.1e-7).  Six MFMAs of 32 cycles per 32 x 32 block and
 // sixteen rows of the reduction stand against eight fp32 ones of 64.
 //
-// Weights are packed scaled by 2^16, which makes every one below 2^111 three bf16 numbers exactly, however small; the others are packed
-// whole beside a NaN (split_weight).  What else three bf16 cannot hold -- infinite activations (inf - inf is NaN in m), finite ones
-// that round to a bf16 infinity, and activations below 2^-110, whose l would fall under the smallest bf16 -- shows in the
-// accumulators: not finite, or all of a lane's outputs under 2^-90 without being zero.  A wave that finds that computes its
-// tile again with fp32 MFMAs (fp32_tile below), slowly, from the same operands.
+// Both operands are split 2^16 times as large as they are, which makes every one below 2^111 three bf16 numbers exactly, however
+// small (one more vector instruction per activation).  Weights above that are packed whole beside a NaN (split_weight); an activation
+// above that, or infinite, leaves NaN in m or l (inf - inf): both show in the accumulators, as do sums above 2^95, scaled, and
+// infinities or NaN that fp32 sums would give too.  A wave that finds a sum not finite computes its tile again with fp32 MFMAs
+// (fp32_tile below), slowly, from the same operands.
 //
 // Workgroup.  64 pixels x 32 WN channels.  WN waves multiply, each all 64 pixels by 32 channels of its own: every
 // weight is wanted by one wave only and goes from memory straight into the registers the MFMAs read; it is
@@ -27,7 +27,7 @@
 // reads eight consecutive rows of its pixel per part with one 16-byte access.  Two buffers, one barrier per step.
 // Why waves of their own for it: (a) loads return in order, so in a wave that fetches both, a weight waits for
 // every activation asked for before it, however far ahead that was -- with both in one wave a 1x1 layer of 256
-// channels at 56x56 (N = 16, K = 128) ran at 2.2 TB/s whatever the depth of its prefetch; (b) the splitting (5.5 vector
+// channels at 56x56 (N = 16, K = 128) ran at 2.2 TB/s whatever the depth of its prefetch; (b) the splitting (6.5 vector
 // instructions per element) and the address arithmetic leave the waves that multiply with 2.5 instructions per MFMA,
 // and one such wave per SIMD keeps the matrix pipes busy.  What bounds the loop then is power: with random operands
 // back-to-back bf16 MFMAs hold the clock at 1.75-1.85 GHz (2.3 with zeros), 17.7 ns each instead of 13.3.
@@ -52,15 +52,15 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 __device__ __forceinline__ float bf16_low(unsigned p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
-// Weights are packed 2^16 times as large as they are, so that the smallest fp32 number, 2^-149, is the smallest bf16
-// one, 2^-133, and every weight below 2^111 is exactly three bf16 numbers; the sums are scaled back by join_sums.
-constexpr float kWeightScale = 0x1p16f;
+// Operands are split 2^16 times as large as they are, so that the smallest fp32 number, 2^-149, is the smallest bf16
+// one, 2^-133, and every operand below 2^111 is exactly three bf16 numbers; the sums are scaled back by join_sums.
+constexpr float kOperandScale = 0x1p16f, kSumScale = 0x1p-32f;
 // The parts of a weight as bf16 bits: the scaled weight rounded to bf16, the remainder rounded to bf16, the rest.  A weight that
 // would round to infinity so, an infinity or NaN has NaN as its first part, which shows in every sum it enters, and its own
 // bits in the other two.
 __device__ __forceinline__ void split_weight(const float w, unsigned (&part)[3])
 {
-    const float v = w * kWeightScale;
+    const float v = w * kOperandScale;
     const unsigned h = pack_bf16(v, 0.0f) & 0xffffu;
     const float r = v - bf16_low(h);
     const unsigned m = pack_bf16(r, 0.0f) & 0xffffu, l = pack_bf16(r - bf16_low(m), 0.0f) & 0xffffu;
@@ -74,16 +74,17 @@ __device__ __forceinline__ void split_weight(const float w, unsigned (&part)[3])
 __device__ __forceinline__ float join_weight(const unsigned h, const unsigned m, const unsigned l)
 {
     if ((h & 0x7f80u) == 0x7f80u) return __builtin_bit_cast(float, m << 16 | l);
-    return ((bf16_low(l) + bf16_low(m)) + bf16_low(h)) * (1.0f / kWeightScale);
+    return ((bf16_low(l) + bf16_low(m)) + bf16_low(h)) * (1.0f / kOperandScale);
 }
 
-// eight floats as their three bf16 parts, sixteen bytes each
+// eight activations as their three bf16 parts, sixteen bytes each
 __device__ __forceinline__ void split_octet(const float (&v)[8], v4u &h, v4u &m, v4u &l)
 {
     static_for<4>([&](auto P) WPK_LAMBDA {
         constexpr int p = decltype(P)::value;
-        const unsigned ph = pack_bf16(v[2 * p], v[2 * p + 1]);
-        const float r0 = v[2 * p] - bf16_low(ph), r1 = v[2 * p + 1] - bf16_high(ph);
+        const float v0 = v[2 * p] * kOperandScale, v1 = v[2 * p + 1] * kOperandScale;
+        const unsigned ph = pack_bf16(v0, v1);
+        const float r0 = v0 - bf16_low(ph), r1 = v1 - bf16_high(ph);
         const unsigned pm = pack_bf16(r0, r1);
         h[p] = ph;
         m[p] = pm;
@@ -99,13 +100,12 @@ __device__ __forceinline__ bool join_sums(v16f (&acc)[NB], const v16f (&sml)[NB]
     static_for<NB>([&](auto I) WPK_LAMBDA {
         static_for<16>([&](auto E) WPK_LAMBDA {
             constexpr int i = decltype(I)::value, e = decltype(E)::value;
-            const float v = (acc[i][e] + sml[i][e]) * (1.0f / kWeightScale);
-            acc[i][e] = v;
+            const float v = acc[i][e] + sml[i][e];
             top = max(top, __builtin_bit_cast(unsigned, v) & 0x7fffffffu);
+            acc[i][e] = v * kSumScale;
         });
     });
-    const bool odd = top >= 0x7f800000u || (top != 0u && top < 0x12800000u);  // inf or NaN; below 2^-90
-    return __builtin_amdgcn_ballot_w64(odd) != 0;
+    return __builtin_amdgcn_ballot_w64(top >= 0x7f800000u) != 0;  // inf or NaN
 }
 
 // The wave's blocks again, in fp32, one pixel block after the other, over the MFMA depths depth(0 .. count - 1), with

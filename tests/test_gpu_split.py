@@ -197,6 +197,27 @@ def test_small_weights(form, powers):
         assert_fp32_sums(run_form(form, x, wv), want, d, (form, powers))
 
 
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("split_k", [1, 2])
+@pytest.mark.parametrize("powers", [(-118, 0), (-124, 40), (-126, 0), (-140, 50), (-148, 100)], ids=str)
+def test_small_activations(form, split_k, powers):
+    """Activations as small as fp32 has them, against ordinary and large weights: everywhere, in one image of two, in
+    single pixels and in single channels beside ordinary ones."""
+    layer = FORMS[form][0]
+    x, w = W.make_inputs(layer)
+    x = x / np.abs(x).max()
+    w = scaled(w, powers[1])
+    small = scaled(x, powers[0])
+    n, c, h, v = x.shape
+    image = np.arange(n)[:, None, None, None] == 1
+    pixel = (np.arange(h * v).reshape(h, v) // 5 % 2 == 0)[None, None]
+    channel = (np.arange(c) % 2 == 0)[None, :, None, None]
+    for where in (np.ones(1, bool), image, pixel, channel):
+        xv = np.where(where, small, x)
+        want, d, _ = oc.conv2d(oc.shape_from_layer(layer), xv, w)
+        assert_fp32_sums(run_form(form, xv, w, split_k), want, d, (form, powers))
+
+
 def test_weights_of_any_value_move_between_the_packed_forms():
     """The smallest numbers, the largest, infinities and NaN through the split form into the tiled one: bit for bit."""
     torch, dev = torch_dev()
