@@ -18,7 +18,7 @@
 // small (one more vector instruction per activation).  Weights above that are packed whole beside a NaN (split_weight); an activation
 // above that, or infinite, leaves NaN in m or l (inf - inf): both show in the accumulators, as do sums above 2^95, scaled, and
 // infinities or NaN that fp32 sums would give too.  A wave that finds a sum not finite computes its tile again with fp32 MFMAs
-// (fp32_tile below), slowly, from the same operands.
+// (fp32_tile below) from the same operands.
 //
 // Workgroup.  64 pixels x 32 WN channels.  WN waves multiply, each all 64 pixels by 32 channels of its own: every
 // weight is wanted by one wave only and goes from memory straight into the registers the MFMAs read; it is
@@ -73,8 +73,10 @@ __device__ __forceinline__ void split_weight(const float w, unsigned (&part)[3])
 // The weight again, exactly.
 __device__ __forceinline__ float join_weight(const unsigned h, const unsigned m, const unsigned l)
 {
-    if ((h & 0x7f80u) == 0x7f80u) return __builtin_bit_cast(float, m << 16 | l);
-    return ((bf16_low(l) + bf16_low(m)) + bf16_low(h)) * (1.0f / kOperandScale);
+    // (all ones where the exponent is; masks, since a select becomes a branch in the kernel)
+    const unsigned whole = (unsigned)__builtin_amdgcn_sbfe((int)((h & 0x7f80u) + 0x80u), 15, 1);
+    const float sum = ((bf16_low(l) + bf16_low(m)) + bf16_low(h)) * (1.0f / kOperandScale);
+    return __builtin_bit_cast(float, (whole & (m << 16 | l)) | (~whole & __builtin_bit_cast(unsigned, sum)));
 }
 
 // eight activations as their three bf16 parts, sixteen bytes each
@@ -108,69 +110,6 @@ __device__ __forceinline__ bool join_sums(v16f (&acc)[NB], const v16f (&sml)[NB]
     return __builtin_amdgcn_ballot_w64(top >= 0x7f800000u) != 0;  // inf or NaN
 }
 
-// The wave's blocks again, in fp32, one pixel block after the other, over the MFMA depths depth(0 .. count - 1), with
-// the operands where a lane's eight rows of a depth are: MFMA number q of eight contracts rows q and 8 + q.
-// GENERIC: rows in the source's order (c, r, s), else (c / 32, r, s, c % 32).
-template <int NNT, int NMT, bool GENERIC, class D>
-__device__ __forceinline__ void fp32_tile(v16f (&acc)[NNT * NMT], const __amdgpu_buffer_rsrc_t xrsrc,
-                                          const __amdgpu_buffer_rsrc_t wrsrc, const int m0, const unsigned wbase,
-                                          const int count, D &&depth, const int lane)
-{
-    const cold_ptr c = cold_args();
-    const int lrow = lane >> 5, lcol = lane & 31;
-    const unsigned wblk_bytes = (unsigned)(c->Kpad / 32) * 3072u;
-    const int px4 = c->xl == 1 || c->xl == 2 ? c->C * 4 : 4;
-    static_for<NMT>([&](auto J) WPK_LAMBDA {
-        constexpr int j = decltype(J)::value;
-        int voff;
-        unsigned inv;
-        pixel_window(c, m0 + j * 32 + lcol, voff, inv);
-        v16f f[NNT];
-        static_for<NNT>([&](auto I) WPK_LAMBDA {
-            static_for<16>([&](auto E) WPK_LAMBDA { f[decltype(I)::value][decltype(E)::value] = 0.0f; });
-        });
-        for (int it = 0; it < count; ++it) {
-            const int t = depth(it);
-            float xv[8];
-            static_for<8>([&](auto Q) WPK_LAMBDA {
-                constexpr int q = decltype(Q)::value;
-                int ch, rs;
-                bool past = false;
-                if constexpr (GENERIC) {
-                    const int kk = t * 16 + lrow * 8 + q;
-                    ch = kk / c->RS;
-                    rs = kk - ch * c->RS;
-                    past = kk >= c->CRS;
-                } else {
-                    const int c32 = t / (2 * c->RS);
-                    ch = c32 * 32 + (t & 1) * 16 + lrow * 8 + q;
-                    rs = (t - c32 * 2 * c->RS) >> 1;
-                    past = ch >= c->C;
-                }
-                const int fr = rs / c->S, fs = rs - fr * c->S;
-                const bool out = past || ((inv >> fr) & 1) || ((inv >> (16 + fs)) & 1);
-                const int off = out ? -1 : voff + (fr * c->dil_h * c->W + fs * c->dil_w) * px4 + ch * c->HW4;
-                xv[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, off, 0, 0));
-            });
-            static_for<NNT>([&](auto I) WPK_LAMBDA {
-                constexpr int i = decltype(I)::value;
-                v4u w[3];
-                static_for<3>([&](auto Q) WPK_LAMBDA {
-                    w[decltype(Q)::value] = __builtin_amdgcn_raw_buffer_load_b128(
-                        wrsrc, lane * 16, wbase + (unsigned)t * wblk_bytes + (i * 3 + decltype(Q)::value) * 1024, 0);
-                });
-                static_for<8>([&](auto Q) WPK_LAMBDA {
-                    constexpr int q = decltype(Q)::value, sh = q % 2 * 16;
-                    const float wv = join_weight(w[0][q / 2] >> sh & 0xffffu, w[1][q / 2] >> sh & 0xffffu,
-                                                 w[2][q / 2] >> sh & 0xffffu);
-                    f[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, xv[q], f[i], 0, 0, 0);
-                });
-            });
-        }
-        static_for<NNT>([&](auto I) WPK_LAMBDA { acc[decltype(I)::value * NMT + j] = f[decltype(I)::value]; });
-    });
-}
-
 // How activations are found (the XL of the tiled members, and the patch):
 //   kRows   row by row through the tap table, any C; rows in the source's order (c, r, s)
 //   kQuads  channels-last, C a multiple of 32: a lane fetches an octet of one pixel with two 16-byte loads
@@ -185,6 +124,90 @@ __device__ __forceinline__ void fp32_tile(v16f (&acc)[NNT * NMT], const __amdgpu
 // Rows of the reduction are ordered (c / 32, r, s, c % 32) but for kRows, so that the taps of 32 channels follow each
 // other and find their pixels in the L1; a step is 32 rows, for patches the nine taps of sixteen channels.
 enum SplitForm { kRows, kQuads, kTaps, kPoint, kPatch, kPatchQuads };
+// The wave's blocks again, in fp32, over the MFMA depths depth(0 .. count - 1), with the operands where a lane's eight rows of a
+// depth are: MFMA number q of eight contracts rows q and 8 + q.  Bound by the 16 MFMAs of 64 cycles and some 240 other instructions
+// of a depth, without branches (masks instead of selects) and with the next two depths' operands on their way.  A launch with
+// one infinity in x takes 86 us on the 256-channel 3x3 layer at 14x14 (N = 16; 24 without one) and 51 on the 64-channel
+// one at 56x56 (24); with branches and one depth after the other 232 and 125.  The tiled members take 40 and 42 on any data.
+template <SplitForm FORM, int NMT, class D>
+__device__ __forceinline__ void fp32_tile(v16f (&acc)[NMT], const __amdgpu_buffer_rsrc_t xrsrc,
+                                          const __amdgpu_buffer_rsrc_t wrsrc, const int m0, const unsigned wbase,
+                                          const int count, D &&depth, const int lane)
+{
+    constexpr bool PATCH = FORM == kPatch || FORM == kPatchQuads;
+    const cold_ptr c = cold_args();
+    const int lrow = lane >> 5, lcol = lane & 31;
+    const unsigned wblk_bytes = (unsigned)(c->Kpad / 32) * 3072u;
+    const int px4 = c->xl == 1 || c->xl == 2 ? c->C * 4 : 4;
+    int voff[NMT];
+    unsigned inv[NMT];
+    static_for<NMT>([&](auto J) WPK_LAMBDA {
+        constexpr int j = decltype(J)::value;
+        pixel_window(c, m0 + j * 32 + lcol, voff[j], inv[j]);
+        static_for<16>([&](auto E) WPK_LAMBDA { acc[j][decltype(E)::value] = 0.0f; });
+    });
+    constexpr int DEPTH = 2;
+    float xv[DEPTH][NMT][8];
+    v4u wv[DEPTH][3];
+    auto fetch = [&](auto SET, const int it) WPK_LAMBDA {
+        constexpr int set = decltype(SET)::value;
+        const int t = depth(min(it, count - 1));
+        static_for<3>([&](auto Q) WPK_LAMBDA {
+            wv[set][decltype(Q)::value] = __builtin_amdgcn_raw_buffer_load_b128(
+                wrsrc, lane * 16, wbase + (unsigned)t * wblk_bytes + decltype(Q)::value * 1024, 0);
+        });
+        static_for<8>([&](auto Q) WPK_LAMBDA {
+            constexpr int q = decltype(Q)::value;
+            int ch, rs, past;  // past: all ones beyond the last row
+            if constexpr (FORM == kRows) {  // rows in the source's order (c, r, s)
+                const int kk = t * 16 + lrow * 8 + q;
+                ch = fdiv(kk, WPK_COLD_DIV(c, div_tap));
+                rs = kk - ch * c->RS;
+                past = (c->CRS - 1 - kk) >> 31;
+            } else {                        // (c / 32, r, s, c % 32)
+                const int c32 = PATCH ? t / 18 : fdiv(t >> 1, WPK_COLD_DIV(c, div_tap));
+                rs = (t >> 1) - c32 * c->RS;
+                ch = c32 * 32 + (t & 1) * 16 + lrow * 8 + q;
+                past = (c->C - 1 - ch) >> 31;
+            }
+            const int fr = fdiv(rs, WPK_COLD_DIV(c, div_s)), fs = rs - fr * c->S;
+            const int at = (fr * c->dil_h * c->W + fs * c->dil_w) * px4 + ch * c->HW4;
+            static_for<NMT>([&](auto J) WPK_LAMBDA {
+                constexpr int j = decltype(J)::value;
+                const int out = past | __builtin_amdgcn_sbfe((int)inv[j], fr, 1) |
+                                __builtin_amdgcn_sbfe((int)inv[j], 16 + fs, 1);
+                xv[set][j][q] =
+                    __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (voff[j] + at) | out, 0, 0));
+            });
+        });
+    };
+    auto multiply = [&](auto SET) WPK_LAMBDA {
+        constexpr int set = decltype(SET)::value;
+        static_for<8>([&](auto Q) WPK_LAMBDA {
+            constexpr int q = decltype(Q)::value, sh = q % 2 * 16;
+            const float w = join_weight(wv[set][0][q / 2] >> sh & 0xffffu, wv[set][1][q / 2] >> sh & 0xffffu,
+                                        wv[set][2][q / 2] >> sh & 0xffffu);
+            static_for<NMT>([&](auto J) WPK_LAMBDA {
+                constexpr int j = decltype(J)::value;
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, xv[set][j][q], acc[j], 0, 0, 0);
+            });
+        });
+    };
+    static_for<DEPTH>([&](auto S) WPK_LAMBDA { fetch(S, decltype(S)::value); });
+    constexpr int LAPS = 4;
+    int it = 0;
+    auto one = [&](auto P) WPK_LAMBDA {
+        constexpr int p = decltype(P)::value;
+        using SET = std::integral_constant<int, p % DEPTH>;
+        if (it + p >= count) return false;
+        multiply(SET{});
+        fetch(SET{}, it + p + DEPTH);
+        __builtin_amdgcn_sched_barrier(0);
+        return true;
+    };
+    while (static_all<LAPS>(one)) it += LAPS;
+}
+
 constexpr int kHaloPitch = 112;    // LDS bytes per position of a patch: one depth of 3 parts x 32 bytes, 16 of padding, and
 constexpr int kStepPitch = 240;    // per pixel of a step: two depths, 48 of padding, of which a pixel's rows
                                    // are moved on by 16 for every 16 pixels.  Both put the 16 lanes served at a time
@@ -695,7 +718,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     while (static_all<BODY>(step)) r += BODY;
 
     if (join_sums(acc, sml))
-        fp32_tile<1, NMT, FORM == kRows>(acc, xrsrc, wrsrc, m0, wbase, nr * NT, [&](int i) WPK_LAMBDA {
+        fp32_tile<FORM, NMT>(acc, xrsrc, wrsrc, m0, wbase, nr * NT, [&](int i) WPK_LAMBDA {
             return split_depth(PATCH, kbeg + i / NT, i % NT);
         }, lane);
     const cold_ptr ce = cold_args();
