@@ -93,51 +93,6 @@ def test_schedules_and_epilogue(kw):
                              what="%s %r layout %d" % (layer["name"], kw, layout))
 
 
-SPECIAL = [W.layer("sp_patch", 2, 32, 9, 40, 3, 1, 1, seed=50), W.layer("sp_point", 2, 64, 8, 40, 1, seed=51),
-           W.layer("sp_rows", 2, 5, 9, 40, 3, 1, 1, seed=52), W.layer("sp_patch_c27", 2, 27, 9, 40, 3, 1, 1, seed=53),
-           W.layer("sp_taps_c27", 2, 27, 9, 40, 1, 2, 1, seed=54)]
-
-
-@pytest.mark.parametrize("layer", SPECIAL, ids=lambda l: l["name"])
-@pytest.mark.parametrize("split_k", [1, 2])
-def test_values_three_bf16_cannot_hold(layer, split_k):
-    """Infinities, NaN, numbers that round to a bf16 infinity, and tensors under 2^-110: what an fp32 sum gives."""
-    rng = np.random.default_rng(9)
-    x, w = W.make_inputs(layer)
-    w[:, :, 0, 0] = np.where(rng.uniform(size=w.shape[:2]) < 0.5, 0.5, -2.0)   # exact in bf16: zero remainders
-    c = cfg(2, 16, split_k=split_k)
-    sh = oc.shape_from_layer(layer)
-
-    def run(xv, wv):
-        torch, dev = torch_dev()
-        desc = B.make_desc(layer)
-        y = torch.empty((layer["n"], layer["k"]) + B.conv_out_shape(desc), device=dev)
-        B.conv2d_fwd_config(desc, c, to_dev(xv), to_dev(wv), y)
-        torch.cuda.synchronize()
-        return y.cpu().numpy()
-
-    hot = x.copy()
-    hot[0, 1, 3, 4], hot[0, 2, 5, 5], hot[1, 0, 0, 0], hot[1, -1, 7, 7] = np.inf, -np.inf, np.nan, np.inf
-    # (which outputs are infinite, and of which sign, by the rules of the numbers: the oracle sums the same products)
-    with np.errstate(invalid="ignore"):
-        want, _, _ = oc.conv2d(sh, hot, w)
-    got = run(hot, w)
-    assert np.array_equal(np.isnan(got), np.isnan(want))
-    inf = np.isinf(want)
-    assert inf.any() and np.array_equal(got[inf], want[inf].astype(np.float32))
-    fine = np.isfinite(want)
-    assert np.max(np.abs(got[fine] - want[fine])) <= 1e-4 * np.max(np.abs(want[fine]))
-
-    # (3.4e38 rounds to infinity in bf16; the weights keep the sums finite)
-    big = np.where(x > 0.5, np.float32(3.4e38), np.float32(1e30)).astype(np.float32)
-    small_w = (w * np.float32(1e-6)).astype(np.float32)
-    for xv, wv in ((big, small_w), ((x * np.float32(1e-36)).astype(np.float32), w)):
-        want, d, _ = oc.conv2d(sh, xv, wv)
-        err = np.abs(run(xv, wv).astype(np.float64) - want) / np.where(d == 0, 1.0, d)
-        # (subnormal products of the second are rounded at 2^-149 each: 1e-45 / 1e-37 per term, far below)
-        assert err.max() <= 1e-4 and np.isfinite(err).all()
-
-
 # Every way of finding activations (the kernel's six forms, the patch with and without padded channels): layer, layout, bk.
 FORMS = {
     "patch": (W.layer("f_patch", 2, 32, 9, 40, 3, 1, 1, x_dist="u11", seed=70), B.NCHW, 16),
@@ -179,6 +134,39 @@ def assert_fp32_sums(got, want, d, what):
     err = np.abs(got.astype(np.float64) - want) - 2.0 ** -149
     worst = float(np.max(err / np.where(d == 0, 1.0, d)))
     assert bool(np.isfinite(got).all()) and worst <= SUM_ERROR, (what, worst)
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("split_k", [1, 2])
+def test_values_three_bf16_cannot_hold(form, split_k):
+    """Infinities, NaN, operands of 2^111 and more and sums of 2^95 and more: what an fp32 sum gives."""
+    layer = FORMS[form][0]
+    rng = np.random.default_rng(9)
+    x, w = W.make_inputs(layer)
+    w[:, :, 0, 0] = np.where(rng.uniform(size=w.shape[:2]) < 0.5, 0.5, -2.0)   # exact in bf16: zero remainders
+    sh = oc.shape_from_layer(layer)
+
+    hot = x.copy()
+    hot[0, 1, 3, 4], hot[0, 2, 5, 5], hot[1, 0, 0, 0], hot[1, -1, 7, 7] = np.inf, -np.inf, np.nan, np.inf
+    # (which outputs are infinite, and of which sign, by the rules of the numbers: the oracle sums the same products)
+    with np.errstate(invalid="ignore"):
+        want, d, _ = oc.conv2d(sh, hot, w)
+    got = run_form(form, hot, w, split_k)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert inf.any() and np.array_equal(got[inf], want[inf].astype(np.float32))
+    fine = np.isfinite(want)
+    assert_fp32_sums(got[fine], want[fine], d[fine], form)
+
+    # (3.4e38 rounds to infinity in bf16; the weights keep the sums finite.  Then a single large operand of either kind, and
+    # ordinary operands whose sums are large.)
+    one_x, one_w = x.copy(), w.copy()
+    one_x[1, 2, 6, 5] = 2.0 ** 120
+    one_w[7, 1, 0, 0] = -2.0 ** 120
+    for xv, wv in ((np.where(x > 0.5, np.float32(3.4e38), np.float32(1e30)).astype(np.float32), w * np.float32(1e-6)),
+                   (one_x, w), (x, one_w), (scaled(x, 60), scaled(w, 40)), (scaled(x, 100), scaled(w, 20))):
+        want, d, _ = oc.conv2d(sh, xv, wv)
+        assert_fp32_sums(run_form(form, xv, wv, split_k), want, d, form)
 
 
 @pytest.mark.parametrize("form", FORMS)
