@@ -54,9 +54,9 @@ OTHER = [
     W.layer("taps_5x5", 2, 32, (9, 12), 96, 5, 1, 2, x_dist="u11", seed=25),
     W.layer("taps_3x3_s2", 2, 64, (11, 14), 64, 3, 2, 1, x_dist="u11", seed=26),
     W.layer("taps_1x7", 1, 64, (8, 17), 48, (1, 7), 1, (0, 3), x_dist="u11", seed=27),
-    W.layer("taps_c24_1x1", 2, 24, 9, 64, 1, x_dist="u11", seed=31),
-    W.layer("taps_c43_5x5", 1, 43, (8, 15), 40, 5, 1, 2, x_dist="u11", seed=32),
-    W.layer("taps_c72_wide", 1, 72, (6, 130), 40, 3, 1, 2, dil=2, x_dist="u11", seed=33),
+    W.layer("rows_c24_1x1", 2, 24, 9, 64, 1, x_dist="u11", seed=31),
+    W.layer("rows_c43_5x5", 1, 43, (8, 15), 40, 5, 1, 2, x_dist="u11", seed=32),
+    W.layer("rows_c72_wide", 1, 72, (6, 130), 40, 3, 1, 2, dil=2, x_dist="u11", seed=33),
     W.layer("rows_c3_7x7", 2, 3, (30, 26), 64, 7, 2, 3, x_dist="u11", seed=28),
     W.layer("rows_c20", 2, 20, (9, 10), 36, 3, 1, 1, x_dist="u11", seed=29),
     W.layer("rows_c1", 3, 1, 8, 8, 1, x_dist="u11", seed=30),
@@ -118,6 +118,36 @@ def run_form(form, x, w, split_k=1):
     torch.cuda.synchronize()
     y = y.cpu().numpy()
     return y.transpose(0, 3, 1, 2) if layout else y
+
+
+@pytest.mark.parametrize("c,hw,r", [(64, 14, 1), (64, 14, 3), (512, 9, 3)], ids=str)
+@pytest.mark.parametrize("layout,bk", [(B.NCHW, 16), (B.NHWC, 16), (B.NCHW, 32), (B.NHWC, 32)], ids=str)
+def test_error_against_64_bits(c, hw, r, layout, bk):
+    """The six products and two sums leave less than fp32 multiply-adds do.  2-norm of the error over that of the result, normal
+    operands, n = C R S terms: the large sum is rounded once per 16 of them, each time by 0.4 * 2^-24 (rms) of a sum that grows
+    like a random walk: 0.4 * 2^-24 sqrt(n / 32) in all, and the last rounding; stated twice as large.  Leaving out one
+    of the three smallest products costs 1e-6, more than is allowed at any n here."""
+    layer = W.layer("precision", 2, c, hw, 64, r, 1, r // 2, seed=90)
+    n = c * r * r
+    rng = np.random.default_rng(17)
+    x = rng.standard_normal((2, c, hw, hw)).astype(np.float32)
+    w = rng.standard_normal((64, c, r, r)).astype(np.float32)
+    want, _, _ = oc.conv2d(oc.shape_from_layer(layer), x, w)
+    torch, dev = torch_dev()
+    desc = B.make_desc(layer, layout=layout)
+    xd, wd = to_dev(x.transpose(0, 2, 3, 1) if layout else x), to_dev(w)
+
+    def error(config):
+        y = torch.empty((2, hw, hw, 64) if layout else (2, 64, hw, hw), device=dev)
+        B.conv2d_fwd_config(desc, config, xd, wd, y)
+        torch.cuda.synchronize()
+        got = y.cpu().numpy().astype(np.float64)
+        return np.linalg.norm((got.transpose(0, 3, 1, 2) if layout else got) - want) / np.linalg.norm(want)
+
+    split = error(cfg(2, bk))
+    assert split <= 0.8 * 2.0 ** -24 * (1 + np.sqrt(n / 32)), split
+    fp32 = error(B.make_config(64, 64, 32, 2, 2))
+    assert split <= 0.75 * fp32, (split, fp32)
 
 
 def scaled(a, power):
