@@ -851,12 +851,14 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
     for_each_segment(a, run_segment);
 }
 
-// Launch of a kernel whose workgroups of T lanes run for_each_segment.
-template <void (*KERNEL)(const IgemmArgs), int T>
+// Launch of a kernel whose workgroups of T lanes run for_each_segment, with at most MAX_LDS bytes of dynamic LDS.  (The limit that
+// is set where that is more than the runtime's default is the kernel's own, not this launch's: another thread may be launching
+// the kernel with another size.)
+template <void (*KERNEL)(const IgemmArgs), int T, int MAX_LDS = 0>
 hipError_t launch_kernel(IgemmArgs a, hipStream_t stream, const size_t dynamic_lds = 0, const size_t static_lds = 0)
 {
     if (dynamic_lds > 64 * 1024) {  // (the runtime's default limit per launch)
-        hipError_t e = hipFuncSetAttribute((const void *)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dynamic_lds);
+        hipError_t e = hipFuncSetAttribute((const void *)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
         if (e != hipSuccess) return e;
     }
     if (a.persist > 0 && a.tiles_dp > 0 && a.sk_groups > 0) {

@@ -735,7 +735,7 @@ template <int WN, SplitForm FORM>
 hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 {
     const size_t lds = 2 * (size_t)(FORM >= kPatch ? (a.halo + 1) * kHaloPitch : 64 * kStepPitch);
-    return launch_kernel<split_kernel<WN, FORM>, 64 * (WN + split_producers(WN, FORM))>(
+    return launch_kernel<split_kernel<WN, FORM>, 64 * (WN + split_producers(WN, FORM)), 2 * (kHaloMax + 1) * kHaloPitch>(
         a, stream, lds, 2 * 32 * WN * sizeof(float) + sizeof(int));  // (bias, arrival)
 }
 

@@ -292,3 +292,40 @@ def test_plan_moves_its_weights_between_the_two_packed_forms():
             B.conv2d_fwd_config(desc, second, xd, wd, b)
             torch.cuda.synchronize()
             assert torch.equal(a, b)
+
+
+def test_two_threads_launch_patches_of_different_sizes():
+    """Patches of more than 64 KB of LDS need a limit raised that belongs to the kernel and not to a launch: two threads on
+    streams of their own, with patches of 308 and 372 positions, many launches each."""
+    import threading
+    torch, dev = torch_dev()
+    jobs = []
+    for width, seed in ((60, 80), (76, 81)):
+        layer = W.layer("lds", 2, 32, (9, width), 64, 3, 1, 2, dil=2, x_dist="u11", seed=seed)
+        x, w = W.make_inputs(layer)
+        want, d = oc.conv2d(oc.shape_from_layer(layer), x, w)[:2]
+        desc = B.make_desc(layer)
+        plan = B.Plan([desc])
+        plan.set_layer_config(0, cfg(2, 16))
+        plan.set_weights(0, to_dev(w))
+        y = torch.full(want.shape, float("nan"), device=dev)
+        jobs.append((plan, to_dev(x), y, want, d, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(plan, x, y, stream):
+        try:
+            for _ in range(300):
+                plan.run_layer(0, x, y, stream)
+        except Exception as e:      # pytest sees exceptions of its own thread only
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(p, x, y, s)) for p, x, y, _, _, s in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for _, _, y, want, d, _ in jobs:
+        assert_fp32_sums(y.cpu().numpy(), want, d, "threads")
