@@ -309,6 +309,55 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
     *out = c;
     return true;
 }
+// What a launch of a split or a tiled member is estimated to take, in microseconds: the workgroups' chain of latencies, the
+// matrix pipes, the memory and the way into a compute unit, their squares added up.  The constants are fitted to the
+// measured times of 747 layers (ResNet-50 at N = 1 to 32 and layers drawn over the same ranges as those that the library's speed is
+// measured on, bias and rectifier fused): 8600 launches of split members within 1.5 times the layer's best, off by 14 %
+// (standard deviation), and one tiled default each, off by 11 %.  They are good for choosing between the two, no more.
+static double split_time(const Problem &pr, const wpk_conv_config &c, int compute_units)
+{
+    const wpk_conv_desc &d = pr.d;
+    const int halo = halo_positions(pr, c), wn = c.wn;
+    const bool patch = halo > 0, point = !patch && split_point(pr), taps = !patch && !point && !pr.xquad;
+    const int producers = !patch && (wn == 4 || taps) ? 2 : 1;
+    const Reduction red = reduction_of(pr, c);
+    const int per = (red.steps + c.split_k - 1) / c.split_k, slices = (red.steps + per - 1) / per;
+    const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((d.k + c.bn - 1) / c.bn);
+    const int64_t lds = ((patch ? (halo + 1) * 224 : 30720) + 256 * wn + 256 + 1279) / 1280;  // (of 128 units)
+    const double resident = (double)std::min<int64_t>(128 / lds, 12 / (wn + producers));
+    const double depths = per * (patch ? 9 : 2);
+    const double fetched = patch ? (halo + 63) / 64 * 64 * 16 / 9.0 : 1024.0;  // elements split per depth
+    const double start = patch ? 0.07 + 0.0063 * halo : point ? 0.15 : taps ? 1.2 : 0.99;
+    const double depth = std::max(0.12, fetched / producers * 17e-5 + (taps ? 0.092 : 0.0));
+    const double end = 4.5 + (slices > 1 ? 0.57 + 0.42 * slices : 0.0);
+    const double n = (double)((tiles * slices + compute_units - 1) / compute_units);  // workgroups of the busiest compute unit
+    const double chain = (start + depths * depth + end) * std::max(1.0, n / resident);
+    const double pipes = n * depths * (wn * 0.25 + fetched * 20e-5) / 4 + start + end;
+    const double memory = 4.0 * (pr.x_elems + pr.y_elems * (slices > 1 ? 1.0 + 2 * slices : 1.0)) / 4.0e6;
+    const double way_in = n * depths * (wn * 3072 + (patch ? halo * 64 / 9.0 : 4096.0)) / 230e3 + start;
+    return 0.08 + sqrt(chain * chain + pipes * pipes + memory * memory + way_in * way_in);
+}
+static double tiled_time(const Problem &pr, const wpk_conv_config &c, int compute_units)
+{
+    const wpk_conv_desc &d = pr.d;
+    const int steps = (pr.CRS + c.bk - 1) / c.bk, per = (steps + c.split_k - 1) / c.split_k;
+    const int slices = (steps + per - 1) / per;
+    const int64_t tiles_m = (pr.M + c.bm - 1) / c.bm, tiles_n = (d.k + c.bn - 1) / c.bn;
+    const bool atomics = c.reduce != 0 && slices > 1, dealt = c.persist == 1;
+    const double all = (double)(tiles_m * tiles_n * slices) / compute_units;
+    const double n = c.persist > 0 ? std::max(1.0, all) : ceil(all);
+    // (steps of 32 rows; one persistent workgroup per compute unit shares them out evenly)
+    const double depth = dealt ? (double)(tiles_m * tiles_n) * steps * c.bk / 32.0 / compute_units : per * c.bk / 32.0;
+    const double ends = 1.8 + (slices > 1 && !atomics ? 1.2 + 0.029 * slices : 0.0) + (dealt ? 1.2 : 0.0);
+    const double chain = (depth * (d.c % kRedAlign ? 0.457 : 0.38) + ends) * (dealt ? 1.0 : std::max(1.0, n / 1.4));
+    const double pipes = depth * (dealt ? 1.0 : n) * 0.38 * c.wm * c.wn / 4 + ends;
+    const double memory =
+        4.0 * (pr.x_elems * (1 + 0.2 * (tiles_n - 1)) + pr.y_elems * (slices > 1 ? 1.0 + 2 * slices : 1.0)) / 7.7e6;
+    // atomics: y zeroed ahead and the epilogue behind; into channels-last outputs they are slow
+    const double y_mb = 4e-6 * pr.y_elems;
+    return 2.9 + sqrt(chain * chain + pipes * pipes + memory * memory) +
+           (atomics ? 5.7 + 3 * y_mb / 7.7 + (pr.yl ? 5.5 * y_mb * slices : 0.0) : 0.0);
+}
 // The split members' default, where they order the reduction by taps (row by row they gain nothing over the tiled
 // members: 53 against 47 us on the 7x7 stride-2 stem of three channels).  Waves of 64 pixels by 32 channels; patches where a 3x3
 // layer allows them.
@@ -321,9 +370,19 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
 //  - The reduction is cut until there is about one wave per SIMD, no further: a second wave hides what a second
 //    slice's prologue and meeting cost, no more (3x3, 256 channels, 14x14, 16 images, 98 tiles: 25.5 us in 2 slices,
 //    27-30 in 1 or 3-5; 512 channels at 7x7, 52 tiles: 28.0 in 4, 28.7 in 3, 32.6 in 8).
-static bool split_default(const Problem &pr, int compute_units, wpk_conv_config *out)
+//  - Any other number of waves or slices that is estimated to be faster by more than a tenth goes before that (1x1 and 3x3 layers of 260 to
+//    340 tiles of two waves, one per compute unit and a few over: 175 -> 87 us in 3 slices, 832 to 448 channels at 10x10, N = 24).
+//  - The tiled default stays where it is estimated to be faster by more than a twentieth (the split members are the more exact), and
+//    below 0.45 GFLOP, where it was faster for 78 of 84 measured layers -- but where it would sum with atomics into
+//    channels-last outputs (up to four times as slow).
+// The tiled default was the faster one by more than 10 % for 139 of the 747 layers before the last two rules and is for 23 with
+// them; of 719 others, drawn afterwards, for 120 and 18.  On average the split members, where chosen, and the tiled default elsewhere
+// are 1.23 (1.28) times as fast as the tiled default alone, 1.14 (1.21) before.
+static bool split_default(const Problem &pr, int compute_units, const wpk_conv_config &tiled, wpk_conv_config *out)
 {
     if (!split_taps(pr)) return false;
+    const double flops = 2.0 * pr.M * pr.d.k * pr.CRS;
+    if (flops < 0.45e9 && !(pr.yl && tiled.reduce)) return false;
     const bool point = split_point(pr);
     int wn = 4;
     double best = 1e300;
@@ -336,33 +395,52 @@ static bool split_default(const Problem &pr, int compute_units, wpk_conv_config 
         }
     }
     wpk_conv_config c = {64, 32 * wn, 16, 1, wn, 1, 1, 0, 1, 0};
-    if (halo_positions(pr, c) == 0) c.bk = 32;
+    const int halo = halo_positions(pr, c);
+    if (halo == 0) c.bk = 32;
     const Reduction red = reduction_of(pr, c);
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);
     const int64_t want = point ? 5 * (int64_t)compute_units / 2 : 4 / wn * (int64_t)compute_units;
     const int64_t G = 3 * (int64_t)compute_units;
-    // A few four-wave tiles beyond one per compute unit, fetched tap by tap: the tiled members deal them out better (5x5,
-    // stride 2, 64 to 960 channels, 38x53, 4 images, 264 tiles on 256 compute units: 57.6 us there, 69.1 here).
-    if (wn == 4 && c.bk == 32 && tiles > compute_units && tiles < 2 * (int64_t)compute_units &&
-        tiles % compute_units * 8 <= compute_units)
-        return false;
     if (2 * tiles <= want) {
         // (slices of 64 rows at least, see kMinRunRows)
         const int64_t most = std::min<int64_t>(want / tiles, red.steps / std::max(1, kMinRunRows / red.rows));
         for (int i = 0; i < kGeneCounts[5]; ++i)
             if (kSplitVals[i] <= most) c.split_k = kSplitVals[i];
-    } else if (tiles <= want) {
+    } else if (tiles <= std::min(4 / wn, 2) * (int64_t)compute_units) {
         c.persist = std::min(4 / wn, 2);  // one round: whole tiles (persistent_of)
-    } else if (wn <= 2 && tiles > G && tiles % G * 8 <= G) {
-        // just over whole rounds of three workgroups per compute unit: the tiles left over are dealt out
-        // (3x3, 64 channels, 56x56, 16 images, 784 tiles: 25.0 us against 25.4 with a workgroup per tile; 1x1, 256 to 128
-        // channels, 1568 tiles: 29.5 against 31.4)
-        c.persist = 3;
     }
-    if (!legal_for(pr, c)) return false;
+    double time = split_time(pr, c, compute_units);
+    if (wn <= 2 && tiles > G && tiles < (point && wn == 2 ? 5 : 3) * G && tiles % G * 12 <= G &&
+        (point ? red.steps >= 2 : halo > 0 && halo <= 240 && tiles % G * 20 <= G)) {
+        // Just over one or two whole rounds of three workgroups per compute unit (1x1 layers of two waves: four): the tiles
+        // left over are dealt out (3x3, 64 channels, 56x56, 16 images, 784 tiles: 25.0 us against 25.4 with a workgroup
+        // per tile; 1x1, 256 to 128 channels, 1568 tiles: 29.5 against 31.4; -5 to +24 % over 35 such layers).  Beyond that,
+        // with more tiles left over, patches of which three do not fit, taps or single steps it loses up to half.
+        c.persist = 3;
+        time *= 0.95;
+    } else {
+        wpk_conv_config other = c;
+        double least = 1e300;
+        for (int w = point ? 2 : 4; w >= 1; w /= 2)
+            for (const int slices : {1, 2, 3, 4, 5, 6, 8, 12}) {
+                if (slices > red.steps) break;
+                wpk_conv_config o = {64, 32 * w, c.bk, 1, w, slices, 1, 0, 1, 0};
+                const double t = split_time(pr, o, compute_units);
+                if (t < least) {
+                    least = t;
+                    other = o;
+                }
+            }
+        if (1.1 * least < time) {
+            c = other;
+            time = least;
+        }
+    }
+    if (time > 1.05 * tiled_time(pr, tiled, compute_units) || !legal_for(pr, c)) return false;
     *out = c;
     return true;
 }
+static void tiled_default(const Problem &pr, int compute_units, wpk_conv_config *out);
 void default_config(const Problem &pr, int compute_units, wpk_conv_config *out)
 {
     if (compute_units <= 0) compute_units = 256;
@@ -372,7 +450,13 @@ void default_config(const Problem &pr, int compute_units, wpk_conv_config *out)
     // four slices or more add up with atomics.  (Measured on the single-image ResNet-50 layers: 4.3-9.8 us where
     // the tiled members' best is 4.9-10.6.)
     if (wave_split_default(pr, compute_units, out)) return;
-    if (split_default(pr, compute_units, out)) return;
+    wpk_conv_config tiled;
+    tiled_default(pr, compute_units, &tiled);
+    if (!split_default(pr, compute_units, tiled, out)) *out = tiled;
+}
+
+static void tiled_default(const Problem &pr, int compute_units, wpk_conv_config *out)
+{
     wpk_conv_config c = {64, pr.d.k <= 32 ? 32 : 64, pr.CRS >= 64 ? 32 : pr.CRS >= 32 ? 16 : 8, 2,
                          pr.d.k <= 32 ? 1 : 2, 1, 1, 0, 2, 0};
     int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);

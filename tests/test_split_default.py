@@ -1,0 +1,84 @@
+"""Where a layer without a tuned configuration goes (CPU): layers whose measured times decide between the split and the tiled
+members, or between numbers of slices; and every default is a legal one."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "wpk_internal.h"
+using namespace wpk;
+struct Case { wpk_conv_desc d; int split, wn, slices_min, slices_max, persist; };  // (wn 0: any)
+#define L(n, c, h, w, k, r, s, st, pad, dil, lay) {n, c, h, w, k, r, s, st, st, pad, pad, dil, dil, WPK_F32, lay}
+// (times: tiled, split as it was by waves per SIMD alone; us)
+static const Case cases[] = {
+    // split members gain here
+    {L(16, 64, 56, 56, 64, 3, 3, 1, 1, 1, 0), 1, 2, 1, 1, 3},
+    {L(16, 128, 28, 28, 128, 3, 3, 1, 1, 1, 0), 1, 4, 1, 1, 0},
+    {L(16, 256, 14, 14, 256, 3, 3, 1, 1, 1, 0), 1, 4, 2, 2, 0},
+    {L(16, 64, 56, 56, 256, 1, 1, 1, 0, 1, 0), 1, 2, 1, 1, 3},
+    {L(16, 256, 56, 56, 128, 1, 1, 1, 0, 1, 0), 1, 2, 1, 1, 3},
+    {L(16, 128, 56, 56, 128, 3, 3, 2, 1, 1, 3), 1, 4, 1, 1, 0},
+    {L(4, 72, 45, 61, 100, 3, 3, 1, 2, 2, 0), 1, 4, 1, 1, 0},
+    {L(4, 576, 13, 13, 224, 3, 3, 1, 0, 1, 2), 1, 4, 2, 24, 0},        // 81 (atomics into channels-last), 22
+    // small layers: start and meeting are most of it
+    {L(10, 192, 23, 23, 171, 1, 1, 1, 0, 1, 0), 0, 0, 1, 1, 0},        // 8.8, 16.7
+    {L(2, 43, 40, 40, 96, 3, 3, 2, 1, 1, 0), 0, 0, 1, 24, 0},          // 9.8, 12.7
+    {L(3, 320, 34, 34, 24, 3, 3, 1, 0, 1, 0), 0, 0, 1, 24, 0},         // 16.3, 32.7
+    // one workgroup of two waves per compute unit and a few over: slices
+    {L(24, 832, 10, 10, 448, 3, 3, 1, 1, 1, 3), 1, 0, 2, 6, 0},        // 136, 183; 87 in 3 of 2 waves
+    {L(47, 704, 12, 12, 137, 3, 3, 1, 1, 1, 0), 1, 0, 2, 6, 0},        // 124, 145; 78 in 3 of 2 waves
+    {L(4, 96, 69, 69, 64, 5, 5, 1, 0, 1, 1), 1, 0, 2, 6, 0},           // 45, 60
+    // single steps: nothing to deal out
+    {L(21, 32, 26, 26, 864, 1, 1, 1, 0, 1, 0), 1, 2, 1, 1, 0},         // 21.5, 45.7 dealt out, 23.3 whole
+};
+int main()
+{
+    for (const Case &t : cases) {
+        Problem pr;
+        wpk_conv_config c;
+        if (make_problem(&t.d, &pr) != WPK_OK) return 3;
+        default_config(pr, 256, &c);
+        const bool split = split_member(c);
+        if (split != (t.split != 0) || c.split_k < t.slices_min || c.split_k > t.slices_max ||
+            (split && ((t.wn && c.wn != t.wn) || persistent_of(pr, c, 256) != t.persist))) {
+            printf("n %d c %d %dx%d k %d r %d: %d x %d x %d, %d x %d, split_k %d, persist %d\n", t.d.n, t.d.c, t.d.h, t.d.w, t.d.k,
+                   t.d.r, c.bm, c.bn, c.bk, c.wm, c.wn, c.split_k, c.persist);
+            return 1;
+        }
+    }
+    srand(5);
+    long split = 0, all = 0;
+    for (int it = 0; it < 60000; ++it) {
+        auto pick = [](int lo, int hi) { return lo + rand() % (hi - lo + 1); };
+        wpk_conv_desc d = {1 << rand() % 7, rand() % 2 ? 32 * pick(1, 32) : pick(1, 300), pick(1, 112), pick(1, 112), pick(1, 1024),
+                           pick(1, 7), pick(1, 7), pick(1, 3), pick(1, 3), pick(0, 4), pick(0, 4), pick(1, 2), pick(1, 2),
+                           WPK_F32, rand() % 4};
+        if (rand() % 2) d.r = d.s = rand() % 2 ? 3 : 1;
+        Problem pr;
+        wpk_conv_config c;
+        if (make_problem(&d, &pr) != WPK_OK || !pr.tiled_ok) continue;
+        default_config(pr, rand() % 8 ? 256 : pick(1, 304), &c);
+        ++all;
+        split += split_member(c);
+        if (!legal_for(pr, c)) {
+            printf("n %d c %d %dx%d k %d r %d s %d: illegal default\n", d.n, d.c, d.h, d.w, d.k, d.r, d.s);
+            return 2;
+        }
+    }
+    printf("%ld of %ld\n", split, all);
+    return split > 1000 && all > 20000 ? 0 : 4;
+}
+"""
+
+
+def test_defaults_follow_the_measured_times_and_are_legal(tmp_path):
+    src, exe = tmp_path / "default.cpp", tmp_path / "default"
+    src.write_text(PROGRAM)
+    csrc = os.path.join(ROOT, "paper_2008_04567_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "include"), "-I", csrc, str(src),
+                    os.path.join(csrc, "wpk_host.cpp"), "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, (res.returncode, res.stdout)
