@@ -97,6 +97,47 @@ __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict
         wp[(((size_t)t * blocks + kb) * 3 + q) * 64 + lane] = (v4u){part[q][0], part[q][1], part[q][2], part[q][3]};
 }
 
+// The same for large weights: a block takes eight c of 32 k (`octets` times), whose values lie together in w, and fetches them
+// into LDS as they lie.  Above, a line of w is fetched again for every tap (512 x 512 x 3x3: 14.0 us, here 6.5; 1024 x 1024 x 3x3: 48.0 and
+// 20.6; 1536 x 1024: 6.4 and 4.7; 256 x 256: 3.4 and 3.0).  With few blocks of many taps each the order turns (96 x 96 x 7x7, 48 blocks:
+// 4.0 and 8.1).  Rows in the source's order are CRS c of one tap.
+__global__ void __launch_bounds__(256) pack_split_staged_kernel(const float *__restrict__ w, v4u *__restrict__ wp, int K,
+                                                                int C, int RS, int blocks, int octets, int all_octets)
+{
+    extern __shared__ float rows[];  // [32 k][8 * RS * octets + 1]
+    const int o0 = blockIdx.x * octets, kb = blockIdx.y, CRS = C * RS;
+    const int span = min(octets, all_octets - o0) * 8 * RS, pitch = octets * 8 * RS + 1;
+    for (int i = threadIdx.x & 31; i < span; i += 32) {
+        const int at = o0 * 8 * RS + i;
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = kb * 32 + j * 8 + (threadIdx.x >> 5);
+            v[j] = k < K && at < CRS ? w[(size_t)k * CRS + at] : 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rows[(j * 8 + (threadIdx.x >> 5)) * pitch + i] = v[j];
+    }
+    __syncthreads();
+    const int k = threadIdx.x & 31;
+    for (int u = threadIdx.x >> 5; u < span / 8; u += 8) {  // a tap of an octet
+        const int o = u / RS, rs = u - o * RS;
+        unsigned part[3][4];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            unsigned v3[3];
+            split_weight(rows[k * pitch + (o * 8 + j) * RS + rs], v3);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) part[q][j / 2] = j % 2 ? part[q][j / 2] | v3[q] << 16 : v3[q];
+        }
+        const int oc = o0 + o, t = (oc >> 2) * 2 * RS + rs * 2 + (oc >> 1 & 1);
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            wp[(((size_t)t * blocks + kb) * 3 + q) * 64 + (oc & 1) * 32 + k] =
+                (v4u){part[q][0], part[q][1], part[q][2], part[q][3]};
+    }
+}
+
 // The way back, from either packed form, exactly: w[K][CRS] (a plan whose configuration moves to the other form).
 __global__ void __launch_bounds__(256) unpack_weights_kernel(const void *__restrict__ packed, float *__restrict__ w,
                                                              int K, int C, int CRS, int Kpad, int RS, int split)
@@ -438,9 +479,19 @@ static int pack_weights(const Problem &pr, bool split, const float *w, float *wp
 {
     const int RS = (split ? split_taps(pr) : pr.xquad || pr.tapmajor) ? pr.d.r * pr.d.s : 0;
     if (split) {
-        const int depths = (int)(split_rows(pr) / 16), blocks = pr.Kpad / 32;
-        hipLaunchKernelGGL(pack_split_kernel, dim3((depths + 3) / 4, blocks), dim3(256), 0, st, w, (v4u *)wp, pr.d.k,
-                           pr.d.c, pr.CRS, depths, blocks, RS);
+        const int blocks = pr.Kpad / 32, taps = RS > 0 ? RS : 1;
+        const int all_octets = (int)(split_rows(pr) / taps / 8), octets = std::max(1, 8 / taps);
+        const int chunks = (all_octets + octets - 1) / octets;
+        // a block per compute unit, or a single tap (see there); at most 64 KB of LDS
+        if ((taps == 1 || (int64_t)chunks * blocks >= 256) && taps < 64) {
+            hipLaunchKernelGGL(pack_split_staged_kernel, dim3(chunks, blocks), dim3(256),
+                               32 * (octets * 8 * taps + 1) * sizeof(float), st, w, (v4u *)wp, pr.d.k,
+                               RS > 0 ? pr.d.c : pr.CRS, taps, blocks, octets, all_octets);
+        } else {
+            const int depths = (int)(split_rows(pr) / 16);
+            hipLaunchKernelGGL(pack_split_kernel, dim3((depths + 3) / 4, blocks), dim3(256), 0, st, w, (v4u *)wp, pr.d.k,
+                               pr.d.c, pr.CRS, depths, blocks, RS);
+        }
     } else {
         dim3 grid(pr.CRSpad / 32, pr.Kpad / 32);
         hipLaunchKernelGGL(pack_weights_kernel, grid, dim3(256), 0, st, w, wp, pr.d.k, pr.CRS, pr.Kpad, pr.d.c, RS);

@@ -250,7 +250,7 @@ WPK_HOST_DEVICE inline uint32_t patch_channel_at(int ch, int C, int HW4)
 }
 // The split members' weights lie depth by depth (16 rows of the reduction); step `step` of the reduction multiplies depths
 // split_depth(patch, step, 0), (.., 1), ...  A step is two depths that follow each other, or with a patch the nine taps of
-// sixteen channels: the two halves of 32 channels alternate (split_source_row).
+// sixteen channels: the two halves of 32 channels alternate (pack_split_kernel).
 WPK_HOST_DEVICE constexpr int split_depth(bool patch, int step, int t)
 {
     return patch ? (step >> 1) * 18 + (step & 1) + 2 * t : step * 2 + t;

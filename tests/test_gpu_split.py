@@ -32,6 +32,8 @@ PATCH = [
     W.layer("c72", 2, 72, (9, 21), 100, 3, 1, 2, dil=2, x_dist="u11", seed=11),
     W.layer("c11", 3, 11, 13, 30, 3, 1, 1, x_dist="u11", seed=12),
     W.layer("c48", 2, 48, 10, 64, 3, 2, 1, x_dist="u11", seed=13),
+    # (weights packed through LDS: a block per compute unit and more)
+    W.layer("c200_k1100", 1, 200, 6, 1100, 3, 1, 1, x_dist="u11", seed=14),
     W.layer("too_wide", 1, 32, (7, 112), 64, 3, 1, 2, dil=2, x_dist="u11", seed=10),
 ]
 
@@ -57,6 +59,11 @@ OTHER = [
     W.layer("rows_c24_1x1", 2, 24, 9, 64, 1, x_dist="u11", seed=31),
     W.layer("rows_c43_5x5", 1, 43, (8, 15), 40, 5, 1, 2, x_dist="u11", seed=32),
     W.layer("rows_c72_wide", 1, 72, (6, 130), 40, 3, 1, 2, dil=2, x_dist="u11", seed=33),
+    # (weights packed through LDS, by eight c of all taps, and of 63 and of 64 taps in place)
+    W.layer("taps_5x5_k1100", 1, 96, (5, 6), 1100, 5, 1, 2, x_dist="u11", seed=37),
+    W.layer("taps_9x7", 1, 64, (13, 12), 70, (9, 7), 1, (4, 3), x_dist="u11", seed=34),
+    W.layer("taps_8x8", 1, 32, (12, 13), 40, 8, 1, 3, x_dist="u11", seed=35),
+    W.layer("rows_16x15", 1, 5, (17, 18), 36, (16, 15), 1, (2, 3), x_dist="u11", seed=36),
     W.layer("rows_c3_7x7", 2, 3, (30, 26), 64, 7, 2, 3, x_dist="u11", seed=28),
     W.layer("rows_c20", 2, 20, (9, 10), 36, 3, 1, 1, x_dist="u11", seed=29),
     W.layer("rows_c1", 3, 1, 8, 8, 1, x_dist="u11", seed=30),
