@@ -56,14 +56,39 @@ const Variant kVariants[] = {
 #undef WPK_VARIANT
 const int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
+static int value_index(int g, int32_t v)
+{
+    const int32_t *vals = gene_values(g);
+    for (int i = 0; i < kGeneCounts[g]; ++i)
+        if (vals[i] == v) return i;
+    return -1;
+}
+
+// (A table over the genes' values: every default of a layer that the model has to price asks 2400 times, and each time a
+// search through all variants made that 40 to 120 us of host time per one-shot call.)
 int find_variant(int bm, int bn, int bk, int wm, int wn, int stages)
 {
-    for (int i = 0; i < kNumVariants; ++i) {
-        const Variant &v = kVariants[i];
-        if (v.bm == bm && v.bn == bn && v.bk == bk && v.wm == wm && v.wn == wn && v.stages == stages)
-            return i;
-    }
-    return -1;
+    auto place = [](const int32_t (&v)[6]) {
+        static const int genes[6] = {0, 1, 2, 3, 4, 8};
+        int at = 0;
+        for (int j = 0; j < 6; ++j) {
+            const int i = value_index(genes[j], v[j]);
+            if (i < 0) return -1;
+            at = at * kGeneCounts[genes[j]] + i;
+        }
+        return at;
+    };
+    static const std::vector<int16_t> table = [&] {
+        std::vector<int16_t> t(kGeneCounts[0] * kGeneCounts[1] * kGeneCounts[2] * kGeneCounts[3] * kGeneCounts[4] * kGeneCounts[8], -1);
+        for (int i = 0; i < kNumVariants; ++i) {
+            const Variant &v = kVariants[i];
+            const int at = place({v.bm, v.bn, v.bk, v.wm, v.wn, v.stages});
+            if (at >= 0 && t[at] < 0) t[at] = (int16_t)i;
+        }
+        return t;
+    }();
+    const int at = place({bm, bn, bk, wm, wn, stages});
+    return at < 0 ? -1 : table[at];
 }
 
 static thread_local int g_last_hip_error = 0;
@@ -135,14 +160,6 @@ std::string desc_key(const wpk_conv_desc *d)
              d->w, d->k, d->r, d->s, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dil_h,
              d->dil_w, d->dtype, d->layout);
     return buf;
-}
-
-static int value_index(int g, int32_t v)
-{
-    const int32_t *vals = gene_values(g);
-    for (int i = 0; i < kGeneCounts[g]; ++i)
-        if (vals[i] == v) return i;
-    return -1;
 }
 
 static const int32_t *cfg_fields(const wpk_conv_config *c, int32_t f[WPK_N_GENES])
