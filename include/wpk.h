@@ -110,8 +110,9 @@ int wpk_last_hip_error(void);
  * fp32 numbers.  Operands of 2^111 and more, infinities and NaN, and sums of 2^95 and more are found in the sums and the
  * tile is computed again in fp32, at a fraction of the speed.
  * One or two further waves per workgroup fetch activations.  bk = 16 lets 3x3 layers work from patches of x, in chunks of 16
- * channels; otherwise, and with bk = 32, a step is 32 rows; `stages` has no meaning; a persistent schedule
- * whose one round is more than half full runs plain.
+ * channels (those whose C is no multiple of 32 do so with 32 as well); otherwise a step is 32 rows with either; `stages` has no
+ * meaning; a persistent schedule whose one round is more than half full runs plain.  The search times
+ * configurations that come out as the same launch once.
  */
 #define WPK_N_GENES 10
 typedef struct wpk_conv_config {

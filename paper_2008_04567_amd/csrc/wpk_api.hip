@@ -772,7 +772,7 @@ struct TuneCtx {
     int rejected;
     int hip_failed;
     int phase;                       // which stage of the search is evaluating (WPK_STAGE_*)
-    std::map<int, double> times_us;  // config id -> median microseconds
+    std::map<int, double> times_us;  // config id (of same_launch) -> median microseconds
     std::map<int, int> stage_of;     // config id -> stage that first timed it
 };
 
@@ -852,11 +852,21 @@ static int tune_constraint(const int32_t *genes, int32_t n, void *user)
 }
 
 // Step2: fitness = 1 / measured runtime; a candidate that fails verification gets 0.
+// Whether the launch that cfg makes has been timed (and passed).
+static bool tune_known(const TuneCtx &t, const wpk_conv_config &cfg)
+{
+    const wpk_conv_config c = same_launch(t.pr, cfg, g_cus);
+    return t.times_us.count(wpk_config_id(&c)) != 0;
+}
+
 static double tune_fitness(const int32_t *genes, int32_t n, void *user)
 {
     TuneCtx *t = (TuneCtx *)user;
     wpk_conv_config cfg;
     if (n != WPK_N_GENES || wpk_config_from_genes(genes, &cfg) != WPK_OK) return 0.0;
+    cfg = same_launch(t->pr, cfg, g_cus);
+    const auto known = t->times_us.find(wpk_config_id(&cfg));
+    if (known != t->times_us.end()) return 1.0 / known->second;
     double us = 0, err = 0;
     int rc = measure_us(*t, cfg, &us, &err);
     if (rc != WPK_OK) {
@@ -1315,8 +1325,7 @@ int wpk_conv_tune_ex(const wpk_conv_desc *d, const wpk_tune_options *opt_in, int
                                                  {128, 64, 16, 2, 2, 2}, {64, 64, 32, 2, 2, 1}, {128, 64, 32, 4, 2, 2}};
             auto consider = [&](const wpk_conv_config &c) {
                 int32_t g[WPK_N_GENES];
-                if (wpk_config_to_genes(&c, g) != WPK_OK || !tune_constraint(g, WPK_N_GENES, &t) ||
-                    t.times_us.count(wpk_config_id(&c)))
+                if (wpk_config_to_genes(&c, g) != WPK_OK || !tune_constraint(g, WPK_N_GENES, &t) || tune_known(t, c))
                     return;
                 double f = tune_fitness(g, WPK_N_GENES, &t);
                 ++evals;
@@ -1407,7 +1416,7 @@ int wpk_conv_tune_ex(const wpk_conv_desc *d, const wpk_tune_options *opt_in, int
                     cand[gi] = v;
                     wpk_conv_config c;
                     if (v == best_genes[gi] || !tune_constraint(cand, WPK_N_GENES, &t) ||
-                        wpk_config_from_genes(cand, &c) != WPK_OK || t.times_us.count(wpk_config_id(&c)))
+                        wpk_config_from_genes(cand, &c) != WPK_OK || tune_known(t, c))
                         continue;
                     double f = tune_fitness(cand, WPK_N_GENES, &t);
                     ++evals;
@@ -1487,6 +1496,7 @@ int wpk_conv_tune_ex(const wpk_conv_desc *d, const wpk_tune_options *opt_in, int
     } else {
         wpk_conv_config best;
         wpk_config_from_genes(best_genes, &best);
+        best = same_launch(pr, best, g_cus);
         double best_us = 1.0 / best_f;
         if (def_us > 0.0 && def_us < best_us) {  // never hand back something slower than the default
             best = defcfg;

@@ -255,6 +255,27 @@ int persistent_of(const Problem &pr, const wpk_conv_config &cfg, int compute_uni
     return tiles <= G && 2 * tiles > G ? 0 : cfg.persist;
 }
 
+wpk_conv_config same_launch(const Problem &pr, const wpk_conv_config &cfg, int compute_units)
+{
+    wpk_conv_config c = cfg;
+    if (!split_member(cfg)) return c;
+    c.stages = 1;
+    wpk_conv_config other = c;
+    other.bk = 16;
+    if (halo_positions(pr, other) == halo_positions(pr, c)) c.bk = 16;
+    if (c.persist > 0 && persistent_of(pr, c, compute_units) == 0) {
+        c.persist = 0;
+        c.reduce = 0;
+    }
+    if (c.split_k > 1) {
+        const int steps = reduction_of(pr, c).steps, per = (steps + c.split_k - 1) / c.split_k;
+        c.split_k = (steps + per - 1) / per;
+        if (value_index(5, c.split_k) < 0) c.split_k = cfg.split_k;  // (no such gene)
+        if (c.split_k == 1) c.reduce = 0;
+    }
+    return c;
+}
+
 // Workspace of the persistent schedule's fix-up: the tiles beyond the last whole round are shared;
 // a tile of nsteps consecutive units cut into runs of at least q units meets at most
 // ceil((nsteps-1)/q) + 1 runs (every run holds one unit when there are fewer units than runs).

@@ -269,6 +269,9 @@ struct Reduction {
 Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg);
 // Persistent workgroups per compute unit a launch of cfg has, 0 where it runs one workgroup per tile and slice.
 int persistent_of(const Problem &pr, const wpk_conv_config &cfg, int compute_units);
+// The configuration that stands for all those that make the same launch as cfg: split members have no prefetch depths, K-steps
+// only where they decide about patches, and slices and persistent schedules that come out as another's.
+wpk_conv_config same_launch(const Problem &pr, const wpk_conv_config &cfg, int compute_units);
 void default_config(const Problem &pr, int compute_units, wpk_conv_config *out);
 // Whether the wave-split members can run pr at all and its 32 x 32 output blocks times its octets of
 // reduction rows stay within the bound (the work is then small enough for them to be worth timing).

@@ -73,12 +73,70 @@ int main()
 }
 """
 
+# The configurations that same_launch puts together do make one launch: what the kernel and its grid depend on is equal, the
+# one that stands for the others is legal, and the search space is so much smaller.
+SAME = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <set>
+#include "wpk_internal.h"
+using namespace wpk;
+int main()
+{
+    srand(3);
+    long points = 0, launches = 0;
+    for (int it = 0; it < 60; ++it) {
+        auto pick = [](int lo, int hi) { return lo + rand() % (hi - lo + 1); };
+        const int r = rand() % 2 ? 3 : pick(1, 5);
+        wpk_conv_desc d = {pick(1, 16), rand() % 2 ? 32 * pick(1, 20) : pick(1, 300), pick(r, 60), pick(r, 60), pick(1, 600), r, r,
+                           1, 1, r / 2, r / 2, 1, 1, WPK_F32, rand() % 4};
+        Problem pr;
+        if (make_problem(&d, &pr) != WPK_OK || !pr.tiled_ok) continue;
+        std::set<int> ids;
+        for (int id = 0;; ++id) {
+            wpk_conv_config c;
+            if (wpk_config_from_id(id, &c) != WPK_OK) break;
+            if (!legal_for(pr, c)) continue;
+            const wpk_conv_config s = same_launch(pr, c, 256), s2 = same_launch(pr, s, 256);
+            if (wpk_config_id(&s) != wpk_config_id(&s2) || !legal_for(pr, s)) return 1;
+            if (!split_member(c)) {
+                if (wpk_config_id(&s) != id) return 2;
+                continue;
+            }
+            ++points;
+            ids.insert(wpk_config_id(&s));
+            const Reduction a = reduction_of(pr, c), b = reduction_of(pr, s);
+            const int pa = (a.steps + c.split_k - 1) / c.split_k, pb = (b.steps + s.split_k - 1) / s.split_k;
+            const FixupNeed fa = fixup_need(pr, c, 256), fb = fixup_need(pr, s, 256);
+            if (s.wn != c.wn || s.bn != c.bn || halo_positions(pr, c) != halo_positions(pr, s) || a.steps != b.steps ||
+                a.rows != b.rows || pa != pb || persistent_of(pr, c, 256) != persistent_of(pr, s, 256) ||
+                s.xcd_remap != c.xcd_remap || fa.bytes != fb.bytes || fa.maxc != fb.maxc) {
+                printf("c %d r %d: bk %d split %d persist %d reduce %d stages %d\n", d.c, r, c.bk, c.split_k, c.persist, c.reduce, c.stages);
+                return 3;
+            }
+        }
+        launches += ids.size();
+    }
+    printf("%ld points, %ld launches\n", points, launches);
+    return points > 2 * launches && launches > 500 ? 0 : 4;
+}
+"""
 
-def test_defaults_follow_the_measured_times_and_are_legal(tmp_path):
+
+def run_program(tmp_path, text):
     src, exe = tmp_path / "default.cpp", tmp_path / "default"
-    src.write_text(PROGRAM)
+    src.write_text(text)
     csrc = os.path.join(ROOT, "paper_2008_04567_amd", "csrc")
     subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "include"), "-I", csrc, str(src),
                     os.path.join(csrc, "wpk_host.cpp"), "-o", str(exe)], check=True)
-    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True)
+
+
+def test_configurations_put_together_make_one_launch(tmp_path):
+    res = run_program(tmp_path, SAME)
+    assert res.returncode == 0, (res.returncode, res.stdout)
+
+
+def test_defaults_follow_the_measured_times_and_are_legal(tmp_path):
+    res = run_program(tmp_path, PROGRAM)
     assert res.returncode == 0, (res.returncode, res.stdout)
