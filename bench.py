@@ -29,6 +29,7 @@ MATRIX_PEAK_TFLOPS = 419.4
 HBM_PEAK_GBS = 8000.0           # HBM3E, published
 TOL = 1e-4                      # |y_gpu - y_oracle| <= TOL * sum|x*w| per output
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic_per_launch.txt")
+TRAFFIC_TABLE_SPLIT = os.path.join(ROOT, "profiles", "hbm_traffic_per_launch_split.txt")
 
 
 def log(*a):
@@ -434,7 +435,7 @@ def main():
     # ---- the oracle: timed on the host cores, and every layer's device output held to it ---------
     cpu_rec, full = (None, {}) if args.no_cpu else cpu_baseline(W, layers)
     errs, err_kinds = run.check(full, 4096)
-    traffic = load_traffic_table(TRAFFIC_TABLE)
+    traffic, traffic_split = load_traffic_table(TRAFFIC_TABLE), load_traffic_table(TRAFFIC_TABLE_SPLIT)
 
     n = len(layers)
     rows = []
@@ -461,7 +462,9 @@ def main():
         row.update(tune_info.get(W.shape_key(l) + ((run.codes[i],) if run.auto else ()),
                                  {"found_by": "default (no search)"}))
         row["layout_code"] = run.codes[i]
-        hit = traffic.get((l["name"], cfg.bm, cfg.bn, cfg.split_k, cfg.xcd_remap, cfg.persist, cfg.reduce)) \
+        # (split members read other bytes than tiled ones of the same tile: weights of six bytes, patches)
+        hit = (traffic_split if B.is_split_member(cfg) else traffic).get(
+            (l["name"], cfg.bm, cfg.bn, cfg.split_k, cfg.xcd_remap, cfg.persist, cfg.reduce)) \
             if run.codes[i] == 0 and not epi else None
         if hit:
             row["traffic_bytes"] = {"fetched": hit[0], "written": hit[1],
@@ -494,14 +497,16 @@ def main():
                     "bytes_per_launch": total_bytes / n}
     dom = int(np.argmin([r["tflops"] / MATRIX_PEAK_TFLOPS if r["bound"] == "mfma"
                          else r["gbs_algorithmic"] / HBM_PEAK_GBS for r in rows]))
-    roofline.update({"kernel": "wpk::igemm_kernel<...> / wpk::wsplit_kernel<...> (implicit-GEMM family, tiled members "
-                               "and wave-split ones, named wpk_igemm_32x...; all %d launches of a pass: %s)"
+    roofline.update({"kernel": "wpk::split_kernel<...> / wpk::igemm_kernel<...> / wpk::wsplit_kernel<...> (implicit-GEMM "
+                               "family: split members, named ..._1x<waves>_p..., tiled ones, and wave-split ones, "
+                               "named wpk_igemm_32x...; all %d launches of a pass: %s)"
                                % (n, ", ".join(sorted(set(r["kernel"] for r in rows)))),
                      "launches_per_pass": n, "avg_us": round(region_us / n, 2),
                      "how": "algorithmic work of a pass / duration of the %d timed passes between two events on the "
                             "launch stream; avg_us = that duration / launches" % args.steps,
-                     "traffic_unit": "bytes per launch (mean over the pass), fetched + written, from profiles/%s"
-                                     % os.path.basename(TRAFFIC_TABLE) if traffic_avg else
+                     "traffic_unit": "bytes per launch (mean over the pass), fetched + written, from profiles/%s and %s"
+                                     % (os.path.basename(TRAFFIC_TABLE), os.path.basename(TRAFFIC_TABLE_SPLIT))
+                                     if traffic_avg else
                                      "null: no counter run on record for some layer under its configuration",
                      "slowest_layer": {"layer": rows[dom]["layer"], "kernel": rows[dom]["kernel"],
                                        "us_event_separated": rows[dom]["us"],

@@ -258,6 +258,11 @@ def config_from_id(cid):
     return c
 
 
+def is_split_member(cfg):
+    """Whether a configuration names a split member (bm >= 64 and all waves along the channels)."""
+    return cfg.bm != 32 and cfg.wm == 1
+
+
 def config_default(desc):
     c = ConvConfig()
     _check(lib().wpk_config_default(ctypes.byref(desc), ctypes.byref(c)), "wpk_config_default")
