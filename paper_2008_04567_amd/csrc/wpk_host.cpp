@@ -333,16 +333,23 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
 {
     if (!wave_split_candidate(pr, 20000)) return false;
     const int64_t blocks = ((pr.M + 31) / 32) * ((pr.d.k + 31) / 32), octets = pr.CRS / 8;
-    // as many waves per tile (four at most) as keep the launch within one wave per SIMD and every wave
-    // at four octets or more
+    // As many waves per tile (four at most) as leave every wave two octets and keep the launch within two waves per SIMD
+    // (1x1, 256 -> 128 channels, 56x56, N = 1, 392 tiles: 5.4 us with four, 7.1 with two), or within one where they would get
+    // fewer than four (3x3, 32 channels); many tiles of one short run take a wave each (64 -> 256, 56x56: 4.3, with two 4.8).
     int wk = 4;
-    while (wk > 1 && (blocks * wk > 4 * (int64_t)compute_units || octets / wk < 4)) wk /= 2;
-    int64_t want = std::max<int64_t>(1, 4 * (int64_t)compute_units / (blocks * wk));
-    while (want > 1 && octets / (wk * want) < 8) --want;
+    while (wk > 1 && (octets / wk < 2 || blocks * wk > (octets / wk >= 4 ? 8 : 4) * (int64_t)compute_units)) wk /= 2;
+    if (octets <= 8 && blocks > 2 * (int64_t)compute_units) wk = 1;
+    // The reduction is cut until there is one wave per SIMD, but not into runs of fewer than ten octets (five for eight tiles
+    // or fewer, whose slices meet sooner): the meeting through the workspace takes as long as eight or so (1x1, 512 -> 2048
+    // channels, 7x7, N = 1: 5.1 us in one, 6.1 in two; 512 -> 128 at 28x28: 5.1, 5.9; 3x3, 512 channels, 7x7: 8.4 in eight).
+    // Atomics take two more launches, y zeroed and the epilogue: 13.9 us for that layer with the rule before, 9.5 without them.
+    // (233 layers, ResNet-50 at N = 1 and 2 and drawn ones, bias and rectifier fused: 1.4 % above the best of all
+    // waves, slices and channels on average, 8 by more than a tenth; the rule before: 3.2 %, 28.)
+    int64_t want = std::min<int64_t>(16, std::max<int64_t>(1, 4 * (int64_t)compute_units / (blocks * wk)));
+    while (want > 1 && octets / (wk * want) < (blocks <= 8 ? 5 : 10)) --want;
     wpk_conv_config c = {kWaveSplitBm, 32, 8, wk, 1, 1, 1, 0, 1, 0};
     for (int i = 0; i < kGeneCounts[5]; ++i)
         if (kSplitVals[i] <= want) c.split_k = kSplitVals[i];
-    c.reduce = c.split_k >= 4 ? 1 : 0;
     if (!legal_for(pr, c)) return false;
     *out = c;
     return true;
@@ -485,10 +492,8 @@ void default_config(const Problem &pr, int compute_units, wpk_conv_config *out)
 {
     if (compute_units <= 0) compute_units = 256;
     // A launch with a few microseconds of arithmetic at most (single images, late layers): the
-    // wave-split members, up to four waves per 32 x 32 tile, the reduction cut further between
-    // workgroups until about one wave per SIMD is busy, but not into runs of fewer than eight octets;
-    // four slices or more add up with atomics.  (Measured on the single-image ResNet-50 layers: 4.3-9.8 us where
-    // the tiled members' best is 4.9-10.6.)
+    // wave-split members.  (Measured on the single-image ResNet-50 layers: 3.4-9.1 us where the tiled members' best
+    // is 4.9-10.6.)
     if (wave_split_default(pr, compute_units, out)) return;
     wpk_conv_config tiled;
     tiled_default(pr, compute_units, &tiled);

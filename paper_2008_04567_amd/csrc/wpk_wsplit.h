@@ -32,6 +32,107 @@
 
 namespace wpk {
 
+// What a wave carries out of a tile: accumulator quads first .. first + QW - 1, quad q being channels
+// 8 (q % 4) + 4 (lane / 32) .. + 3 of block q / 4 for pixel lane % 32.  fetch_bias() and fetch_residual() ask for what its
+// outputs add (live: the loads are issued either way, out of range where not), store() adds that and stores, or adds to y
+// by atomics.
+template <int QW>
+struct OutQuads {
+    float b[QW * 4], r[QW * 4];
+    int k;           // the lane's first channel
+    unsigned place;  // byte offset in y of that channel of the lane's pixel; all ones past the last pixel
+
+    // channel of register e behind the first
+    static constexpr int channel(const int e) { return e / 16 * 32 + e % 16 / 4 * 8 + e % 4; }
+
+    __device__ __forceinline__ void first_channel(const int n0, const int first, const int lrow)
+    {
+        k = n0 + 4 * lrow + (first >> 2) * 32 + (first & 3) * 8;
+    }
+
+    __device__ __forceinline__ void fetch_bias(const IgemmArgs *const c)
+    {
+        const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(c->bias ? c->bias : c->y), 0, c->bias ? c->K * 4 : 0, 0x00020000);
+        static_for<QW * 4>([&](auto E) WPK_LAMBDA {
+            constexpr int e = decltype(E)::value;
+            b[e] = __builtin_bit_cast(float,
+                                      __builtin_amdgcn_raw_buffer_load_b32(brsrc, (k + channel(e)) * 4, 0, 0));
+        });
+    }
+
+    __device__ __forceinline__ void find_place(const IgemmArgs *const c, const int m)
+    {
+        const int n = fdiv(m, WPK_COLD_DIV(c, div_pq)), pq = m - n * c->PQ;
+        const unsigned at = c->yl ? (unsigned)(((size_t)m * c->K + k) * 4)
+                                  : (unsigned)((((size_t)n * c->K + k) * c->PQ + pq) * 4);
+        place = m < c->M ? at : 0xffffffffu;
+    }
+
+    // (the channel's offset is in the lane's, which the range check covers: what lies past the last channel is not used)
+    __device__ __forceinline__ void fetch_residual(const IgemmArgs *const c, const bool live)
+    {
+        const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(c->res ? c->res : c->y), 0, c->res && live ? (int)c->y_bytes : 0, 0x00020000);
+        const int ch4 = c->yl ? 4 : c->PQ * 4;
+        static_for<QW * 4>([&](auto E) WPK_LAMBDA {
+            constexpr int e = decltype(E)::value;
+            r[e] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, place + (unsigned)(channel(e) * ch4), 0, 0));
+        });
+    }
+
+    __device__ __forceinline__ void store(const IgemmArgs *const c, const v4f (&sum)[QW], const bool whole, const bool atomic)
+    {
+        if (place == 0xffffffffu) return;
+        const __amdgpu_buffer_rsrc_t yrsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)c->y, 0, (int)c->y_bytes, 0x00020000);
+        const int ch4 = c->yl ? 4 : c->PQ * 4;
+        if (atomic) {
+            static_for<QW * 4>([&](auto E) WPK_LAMBDA {
+                constexpr int e = decltype(E)::value;
+                const float v = sum[e / 4][e % 4];
+                if (whole || k + channel(e) < c->K)
+                    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(v, yrsrc, place, channel(e) * ch4, 0);
+            });
+            return;
+        }
+        float v[QW * 4];
+        static_for<QW * 4>([&](auto E) WPK_LAMBDA {
+            constexpr int e = decltype(E)::value;
+            const float t = sum[e / 4][e % 4] + (b[e] + r[e]);
+            v[e] = c->relu ? fmaxf(t, 0.0f) : t;
+        });
+        // WHOLE: every channel exists (the usual case), no check per register
+        auto emit = [&](auto WHOLE, auto POLICY) WPK_LAMBDA {
+            static_for<QW * 4>([&](auto E) WPK_LAMBDA {
+                constexpr int e = decltype(E)::value;
+                if (decltype(WHOLE)::value || k + channel(e) < c->K)
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v[e]), yrsrc, place, channel(e) * ch4,
+                                                          decltype(POLICY)::value);
+            });
+        };
+        // whole 128-byte runs are written through, channels-last pieces are not (kYStorePolicy)
+        using Through = std::integral_constant<int, kYStorePolicy>;
+        using Back = std::integral_constant<int, 0>;
+        if (c->yl == 2) {  // (K a multiple of four, everything 16-byte aligned)
+            static_for<QW>([&](auto Q) WPK_LAMBDA {
+                constexpr int q = decltype(Q)::value;
+                if (whole || k + channel(q * 4) < c->K)
+                    __builtin_amdgcn_raw_buffer_store_b128(
+                        __builtin_bit_cast(v4u, (v4f){v[q * 4], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]}), yrsrc, place,
+                        channel(q * 4) * 4, 0);
+            });
+        } else if (c->yl == 1) {
+            emit(std::false_type{}, Back{});
+        } else if (whole) {
+            emit(std::true_type{}, Through{});
+        } else {
+            emit(std::false_type{}, Through{});
+        }
+    }
+};
+
 // QUAD: x is channels-last and moves as channel quads (a.xl == 2); else [N][C][H][W] (a.xl == 3).
 template <int BN, int WK, int PD, bool QUAD>
 __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
@@ -40,9 +141,13 @@ __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
     static_assert(BN % 32 == 0 && NNT >= 1 && NNT <= 2, "one or two 32-channel blocks per wave");
     static_assert(WK >= 1 && WK <= 8 && (WK & (WK - 1)) == 0, "1, 2, 4 or 8 waves");
     static_assert(PD >= 2 && PD <= 12, "octets in flight");
-    // partial tiles of waves 1..WK-1: accumulator quad (block i, quad qd) of lane l at float
-    // (((wk-1)*NNT + i)*4 + qd)*256 + 4*l -- 16-byte accesses, consecutive lanes, no conflicts
-    __shared__ __attribute__((aligned(16))) float red[(WK > 1 ? WK - 1 : 1) * NNT * 16 * 64];
+    // the waves' partial tiles: accumulator quad q (= 4 * block + quad of the block) of wave w and lane l at float
+    // (w * NQ + q) * 256 + 4 * l -- 16-byte accesses, consecutive lanes, no conflicts
+    constexpr int NQ = NNT * 4;                      // accumulator quads of a tile
+    constexpr int OUT = WK < NQ ? WK : NQ;           // waves that carry the tile out,
+    constexpr int QW = NQ / OUT;                     // so many quads each
+    __shared__ __attribute__((aligned(16))) float red[WK > 1 ? WK * NQ * 256 : 4];
+    int *const arrival = reinterpret_cast<int *>(red);  // (64 KB are taken by eight waves of 64 channels: no room beside them)
 
     touch_kernarg_lines();
     const int tid = threadIdx.x;
@@ -74,75 +179,94 @@ __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
     const int obeg = s0 + (s1 - s0) * wk / WK, oend = s0 + (s1 - s0) * (wk + 1) / WK;
     const int nr = oend - obeg;
 
-    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
+    __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const char *)a.x - a.x_bias), 0, (int)(a.x_bytes + a.x_bias), 0x00020000);
-    const __amdgpu_buffer_rsrc_t wrsrc =
+    __amdgpu_buffer_rsrc_t wrsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)a.wp, 0, (int)a.w_bytes, 0x00020000);
+    // (kept whole: the compiler puts descriptors together from their words at every load otherwise, four scalar
+    // instructions an octet, 0.3-0.6 us per launch)
+    asm volatile("" : "+s"(xrsrc), "+s"(wrsrc));
 
-    // ---- the loader's place in the reduction: the next octet to fetch, its first channel, and its
-    //      filter tap (r, s) with the tap's byte offset in x.  Kept by arithmetic on the scalar unit
-    //      (a step along the filter row, or to the start of the next one), not read from the tap table:
-    //      a table entry costs a memory round trip before the first fetch can go out, which a launch
-    //      of a few microseconds notices. ---------------------------------------------------------------
+    // ---- the loader's place in the reduction: its filter tap (r, s) and the offsets of the next octet to fetch.  Kept by
+    //      arithmetic on the scalar unit, not read from the tap table: a table entry costs a memory round trip before the first
+    //      fetch can go out, which a launch of a few microseconds notices.  Between two events -- a change of tap, the end of
+    //      the run -- an octet moves the offsets on by constants and counts down to the next event, nine scalar
+    //      instructions; what an event changes is behind a branch.  (A wave issues one instruction every four or
+    //      five cycles whatever it is, and four MFMAs give it time for 50: with selects instead of the branch, 35 scalar
+    //      instructions an octet, 3x3 with 64 channels at 56x56, N = 1, takes 6.4 us instead of 5.6, 1x1 512 -> 128 at 28x28
+    //      5.8 instead of 5.1.)
     const int px4 = QUAD ? a.C * 4 : 4;  // bytes between neighbouring pixels of x
     const int tap_step_s = c->dil_w * px4;
     const int tap_step_r = (c->dil_h * a.W - (a.S - 1) * c->dil_w) * px4;
-    int ld_o = obeg;
     const int tap0 = fdiv(obeg * 8, WPK_COLD_DIV(c, div_tap));  // by C
-    int ld_c0 = obeg * 8 - tap0 * a.C;
+    const int ch0 = obeg * 8 - tap0 * a.C;
     int tap_r = fdiv(tap0, WPK_COLD_DIV(c, div_s));
     int tap_s = tap0 - tap_r * a.S;
     int tap_off = (tap_r * c->dil_h * a.W + tap_s * c->dil_w) * px4;
+    const int ch4 = a.HW4;               // bytes between channels of x
+    int xo[QUAD ? 1 : 4];                // offsets of the octet's channels behind the lane's
+    auto at_channel = [&](const int ch) WPK_LAMBDA {
+        static_for<QUAD ? 1 : 4>([&](auto Q) WPK_LAMBDA { xo[decltype(Q)::value] = tap_off + (ch + decltype(Q)::value) * ch4; });
+    };
+    at_channel(ch0);
+    int seg = min(nr, (a.C - ch0) >> 3);  // octets up to the next event
+    int left = nr - seg;                  // and behind it
     // weights: the lane's quad of the octet's first block row, its channel
     const int wvoff = (lrow * a.Kpad + n0 + lcol) * 16;
     const int woct_bytes = 2 * a.Kpad * 16;  // one octet further
+    int wv = nr > 0 ? wvoff : -1, wo = obeg * woct_bytes;
     // activations: the pixel's window, the half-wave's four channels
     int xvoff;
     unsigned xinv;
     pixel_window(c, m0 + lcol, xvoff, xinv);
     xvoff += lrow * 4 * (QUAD ? 4 : a.HW4);
+    auto masked = [&]() WPK_LAMBDA {  // the lane's offset under the present tap, or all ones
+        return xvoff | __builtin_amdgcn_sbfe((int)xinv, tap_r, 1) | __builtin_amdgcn_sbfe((int)xinv, 16 + tap_s, 1);
+    };
+    int xvb = nr > 0 ? masked() : -1;
 
     float xr[PD * 4];
     v4f wr[PD * NNT];
     // Loads of the loader's octet into register set SET; then the loader moves one octet on.
-    // Every call issues the same instructions whether the octet is inside the run or past its end,
+    // Every call issues the same loads whether the octet is inside the run or past its end,
     // so that the count of loads in flight behind any register is the same on every path and the
     // waits the compiler places stay exact; an octet past the end gets lane offsets of all ones
     // (nothing is fetched, nobody reads the registers).
     auto issue = [&](auto SET) WPK_LAMBDA {
         constexpr int set = decltype(SET)::value;
-        const int dead = ld_o < oend ? 0 : -1;
-        const int xvb = xvoff | __builtin_amdgcn_sbfe((int)xinv, tap_r, 1) |
-                        __builtin_amdgcn_sbfe((int)xinv, 16 + tap_s, 1) | dead;  // offset, or all ones
         if constexpr (QUAD) {
-            v4f v = __builtin_bit_cast(
-                v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xvb, tap_off + ld_c0 * 4, 0));
+            v4f v = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xvb, xo[0], 0));
             xr[set * 4] = v[0];
             xr[set * 4 + 1] = v[1];
             xr[set * 4 + 2] = v[2];
             xr[set * 4 + 3] = v[3];
+            xo[0] += 8 * 4;
         } else {
             static_for<4>([&](auto Q) WPK_LAMBDA {
                 constexpr int q = decltype(Q)::value;
-                xr[set * 4 + q] = __builtin_bit_cast(
-                    float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xvb, tap_off + (ld_c0 + q) * a.HW4, 0));
+                xr[set * 4 + q] =
+                    __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xvb, xo[q], 0));
+                xo[q] += 8 * ch4;
             });
         }
-        const int wv = wvoff | dead;
         static_for<NNT>([&](auto I) WPK_LAMBDA {
             constexpr int i = decltype(I)::value;
-            wr[set * NNT + i] = __builtin_bit_cast(
-                v4f, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wv, ld_o * woct_bytes + i * 32 * 16, 0));
+            wr[set * NNT + i] =
+                __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wv, wo + i * 32 * 16, 0));
         });
-        // (no branch at the change of tap: selects on the scalar unit; past the last tap the place keeps
-        // moving, but nothing more is fetched)
-        ld_o += 1;
-        const bool next_tap = ld_c0 + 8 >= a.C;
-        const bool next_row = next_tap && tap_s + 1 == a.S;
-        ld_c0 = next_tap ? 0 : ld_c0 + 8;
-        tap_off += next_row ? tap_step_r : next_tap ? tap_step_s : 0;
-        tap_s = next_row ? 0 : next_tap ? tap_s + 1 : tap_s;
-        tap_r += next_row ? 1 : 0;
+        wo += woct_bytes;
+        if (--seg == 0) {
+            asm volatile("");  // (keeps this a branch)
+            const bool row = tap_s + 1 == a.S;
+            tap_off += row ? tap_step_r : tap_step_s;
+            tap_r += row ? 1 : 0;
+            tap_s = row ? 0 : tap_s + 1;
+            at_channel(0);
+            seg = left > 0 ? min(left, a.C >> 3) : 0x7fffffff;
+            xvb = left > 0 ? masked() : -1;
+            wv = left > 0 ? wv : -1;
+            left -= seg;
+        }
     };
 
     v16f acc[NNT];
@@ -169,6 +293,17 @@ __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
         issue(P);
         __builtin_amdgcn_sched_barrier(0);
     });
+    // The residual of this wave's outputs is asked for behind the first octets: it arrives while they are multiplied instead
+    // of after the last one, a round trip to memory less.  Not where slices meet, of which only one stores, and not by one or two
+    // waves, which have four times or twice as many outputs each.
+    constexpr bool AHEAD = QW == 1;
+    OutQuads<QW> out;
+    if constexpr (AHEAD) {
+        out.first_channel(n0, wk * QW, lrow);
+        out.find_place(c, m0 + lcol);
+        out.fetch_residual(c, wk < OUT && c->split_k == 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     int r = 0;
     auto step = [&](auto P) WPK_LAMBDA {
         constexpr int p = decltype(P)::value;
@@ -180,25 +315,33 @@ __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
     };
     while (static_all<kGroups * PD>(step)) r += kGroups * PD;
 
-    // ---- the waves' partial tiles meet in wave 0 --------------------------------------------------
-    if constexpr (WK > 1) {
-        if (wk > 0) {
-            static_for<NNT * 4>([&](auto Q) WPK_LAMBDA {
-                constexpr int qd = decltype(Q)::value, i = qd / 4, e4 = qd % 4;
-                v4f v = {acc[i][4 * e4], acc[i][4 * e4 + 1], acc[i][4 * e4 + 2], acc[i][4 * e4 + 3]};
-                *reinterpret_cast<v4f *>(red + (((wk - 1) * NNT + i) * 4 + e4) * 256 + 4 * lane) = v;
-            });
-        }
+    if constexpr (!AHEAD) {
+        out.first_channel(n0, wk * QW, lrow);
+        out.find_place(c, m0 + lcol);
+    }
+    if constexpr (QW < 8) out.fetch_bias(c);
+    // ---- the waves' partial tiles meet in LDS: wave w adds up quads w QW .. of all of them and carries these on ------
+    v4f sum[QW];
+    if constexpr (WK == 1) {
+        static_for<QW>([&](auto Q) WPK_LAMBDA {
+            constexpr int q = decltype(Q)::value, i = q / 4, e = q % 4 * 4;
+            sum[q] = (v4f){acc[i][e], acc[i][e + 1], acc[i][e + 2], acc[i][e + 3]};
+        });
+    } else {
+        static_for<NQ>([&](auto Q) WPK_LAMBDA {
+            constexpr int q = decltype(Q)::value, i = q / 4, e = q % 4 * 4;
+            *reinterpret_cast<v4f *>(red + (wk * NQ + q) * 256 + 4 * lane) =
+                (v4f){acc[i][e], acc[i][e + 1], acc[i][e + 2], acc[i][e + 3]};
+        });
         __syncthreads();
-        if (wk > 0) return;
-        static_for<WK - 1>([&](auto U) WPK_LAMBDA {
-            static_for<NNT * 4>([&](auto Q) WPK_LAMBDA {
-                constexpr int u = decltype(U)::value, qd = decltype(Q)::value, i = qd / 4, e4 = qd % 4;
-                const v4f v = *reinterpret_cast<const v4f *>(red + ((u * NNT + i) * 4 + e4) * 256 + 4 * lane);
-                acc[i][4 * e4] += v[0];
-                acc[i][4 * e4 + 1] += v[1];
-                acc[i][4 * e4 + 2] += v[2];
-                acc[i][4 * e4 + 3] += v[3];
+        if (wk >= OUT && c->split_k == 1) return;
+        const float *const mine = red + (wk < OUT ? wk : 0) * QW * 256 + 4 * lane;
+        static_for<WK>([&](auto U) WPK_LAMBDA {
+            static_for<QW>([&](auto Q) WPK_LAMBDA {
+                constexpr int u = decltype(U)::value, q = decltype(Q)::value;
+                const v4f v = *reinterpret_cast<const v4f *>(mine + (u * NQ + q) * 256);
+                if constexpr (u == 0) sum[q] = v;
+                else sum[q] += v;
             });
         });
     }
@@ -206,57 +349,54 @@ __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
     // ---- a reduction cut between workgroups: the slices of a tile meet through the workspace (each
     //      stores its partial tile to its slot and counts itself in; whoever comes last adds up the
     //      others and stores y), or, without one, through atomics into y, which the host zeroed ------
-    const IgemmArgs *const ce = &a;
     bool atomic = false;
-    if (ce->split_k > 1) {
-        if (!ce->ws) {
+    if (c->split_k > 1) {
+        if (!c->ws) {
             atomic = true;
+            if (wk >= OUT) return;
         } else {
             constexpr int kCoherent = 17;  // sc0 | sc1: past the L2s, which do not snoop each other
-            constexpr int SLOT = 32 * BN;  // floats; quad (i, e4) of lane l at (i*4 + e4)*256 + 4*l
+            constexpr int SLOT = 32 * BN;  // floats; quad q of lane l at q * 256 + 4 * l
             const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
-                (void *)(ce->ws + (size_t)tile * ce->ws_maxc * SLOT), 0, ce->ws_maxc * SLOT * 4, 0x00020000);
-            static_for<NNT * 4>([&](auto Q) WPK_LAMBDA {
-                constexpr int qd = decltype(Q)::value, i = qd / 4, e4 = qd % 4;
-                v4f v = {acc[i][4 * e4], acc[i][4 * e4 + 1], acc[i][4 * e4 + 2], acc[i][4 * e4 + 3]};
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), srsrc,
-                                                       (slice * SLOT + 4 * lane) * 4, qd * 1024, kCoherent);
-            });
-            // every store acknowledged before the arrival is counted
+                (void *)(c->ws + (size_t)tile * c->ws_maxc * SLOT), 0, c->ws_maxc * SLOT * 4, 0x00020000);
+            const int at = (wk * QW * 256 + 4 * lane) * 4;
+            if (wk < OUT)
+                static_for<QW>([&](auto Q) WPK_LAMBDA {
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, sum[decltype(Q)::value]), srsrc, at,
+                                                           slice * SLOT * 4 + decltype(Q)::value * 1024, kCoherent);
+                });
+            // every store of this wave acknowledged, then every wave's, before the arrival is counted
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_s_waitcnt(0);
-            int before = 0;
-            if (lane == 0) before = atomicAdd(ce->ws_cnt + tile, 1);
-            before = __builtin_amdgcn_readfirstlane(before);
-            if (before != ce->split_k - 1) return;      // not the last: done with this tile
-            if (lane == 0) ce->ws_cnt[tile] = 0;          // leave the counter clean for the next launch
-            // four slots at a time, all requested before the first is added (a slot number past the
-            // last becomes an out-of-range offset, which loads 0)
-            constexpr int kGang = 4;
-            for (int t0 = 0; t0 < ce->split_k - 1; t0 += kGang) {
-                v4f part[kGang][NNT * 4];
+            __syncthreads();
+            if (tid == 0) *arrival = atomicAdd(c->ws_cnt + tile, 1);
+            __syncthreads();
+            if (*arrival != c->split_k - 1 || wk >= OUT) return;  // not the last: done with this tile
+            if (tid == 0) c->ws_cnt[tile] = 0;                   // leave the counter clean for the next launch
+            // seven slots at a time (one quad per lane; fewer where a wave carries more), all requested before the
+            // first is added (a slot number past the last becomes an out-of-range offset, which loads 0)
+            constexpr int kGang = QW == 1 ? 7 : 4;
+            for (int t0 = 0; t0 < c->split_k - 1; t0 += kGang) {
+                v4f part[kGang][QW];
                 static_for<kGang>([&](auto U) WPK_LAMBDA {
                     constexpr int u = decltype(U)::value;
                     const int t = t0 + u, sl = t + (t >= slice ? 1 : 0);  // t-th slot not mine
-                    const unsigned off = t < ce->split_k - 1 ? (unsigned)((sl * SLOT + 4 * lane) * 4) : 0xffffffffu;
-                    static_for<NNT * 4>([&](auto Q) WPK_LAMBDA {
-                        constexpr int qd = decltype(Q)::value;
-                        part[u][qd] = __builtin_bit_cast(
-                            v4f, __builtin_amdgcn_raw_buffer_load_b128(srsrc, off, qd * 1024, kCoherent));
+                    const unsigned off = t < c->split_k - 1 ? (unsigned)(sl * SLOT * 4 + at) : 0xffffffffu;
+                    static_for<QW>([&](auto Q) WPK_LAMBDA {
+                        part[u][decltype(Q)::value] = __builtin_bit_cast(
+                            v4f, __builtin_amdgcn_raw_buffer_load_b128(srsrc, off, decltype(Q)::value * 1024, kCoherent));
                     });
                 });
-                static_for<kGang * NNT * 4>([&](auto UQ) WPK_LAMBDA {
-                    constexpr int u = decltype(UQ)::value / (NNT * 4), qd = decltype(UQ)::value % (NNT * 4);
-                    constexpr int i = qd / 4, e4 = qd % 4;
-                    acc[i][4 * e4] += part[u][qd][0];
-                    acc[i][4 * e4 + 1] += part[u][qd][1];
-                    acc[i][4 * e4 + 2] += part[u][qd][2];
-                    acc[i][4 * e4 + 3] += part[u][qd][3];
+                static_for<kGang * QW>([&](auto UQ) WPK_LAMBDA {
+                    constexpr int u = decltype(UQ)::value / QW, q = decltype(UQ)::value % QW;
+                    sum[q] += part[u][q];
                 });
             }
         }
     }
-    store_wave_tile<NNT, 1>(ce, acc, m0, n0, lrow, lcol, atomic);
+    if constexpr (QW == 8) out.fetch_bias(c);
+    if (!AHEAD || c->split_k > 1) out.fetch_residual(c, !atomic);
+    out.store(c, sum, n0 + BN <= c->K, atomic);
 }
 
 template <int BN, int WK, int PD>
