@@ -92,6 +92,15 @@ __device__ __forceinline__ int fdiv(int n, const FastDiv &f)
 // 0.8 us per launch on a layer that writes 12.8 MB, nothing on small outputs.
 constexpr int kYStorePolicy = 17;
 
+// A 16-byte store.  Its whole offset is the lane's: where a scalar register holds a part of it, the compiler takes the data
+// registers as free at the very next instruction, but the store reads them later than that, and what the next instruction
+// leaves in the first of them has been found in memory.  Without one it keeps the distance.
+template <class POLICY>
+__device__ __forceinline__ void store_quad(const v4u v, const __amdgpu_buffer_rsrc_t rsrc, const unsigned offset, POLICY)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, offset, 0, POLICY::value);
+}
+
 // Arguments that only a segment's set-up, its epilogue or the work iterator use are read from the
 // kernel-argument segment at the place of use (scalar loads that hit the scalar cache) instead of
 // being held in scalar registers from the kernel's entry on: together with everything the compiler
@@ -177,142 +186,144 @@ __device__ __forceinline__ void pixel_window(const ARGS c, const int m, int &vof
 }
 
 // ---- what leaves a wave: its NNT x NMT accumulator blocks, whose first pixel is mbase and first
-//      channel nbase, go to y -- plain stores with the fused epilogue applied, or fp32 atomics.  lds_bias, where
-//      given: the bias of channels nbase .. in LDS, zeros where there is none ----
-template <int NNT, int NMT, class ARGS>
+//      channel nbase, go to y -- plain stores with the fused epilogue applied, or fp32 atomics.  lds_bias, with
+//      LDS_BIAS: the bias of channels nbase .. in LDS, zeros where there is none.
+//
+//      Memory operations return in order, so whoever waits for a load waits for every store issued before it, and a
+//      store that is written through is acknowledged a microsecond after it was issued.  So what a block adds is
+//      asked for before the block ahead of it is stored, and nothing is asked for where there is nothing to add.
+//      (Block by block, loads then stores, the 32 stores of a split member's wave took 2.2 to 2.9 us whether there was a residual
+//      or not: 3x3, 128 channels, 28x28, N = 16, 23.0 -> 21.1 us; 1x1, 64 -> 256 channels, 56x56 with a residual, 31.9 -> 30.4;
+//      ResNet-50, N = 16, 1334 -> 1258.) ----
+template <int NNT, int NMT, bool LDS_BIAS, class ARGS>
 __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)[NNT * NMT], const int mbase,
                                                 const int nbase, const int lrow, const int lcol, const bool atomic,
                                                 const float *const lds_bias = nullptr)
 {
-    // the host applies the epilogue itself after a launch that accumulates with atomics
-    const bool fused = !atomic && (ce->bias || ce->res || ce->relu);
-
     // ---- epilogue: D[row = channel][col = pixel]; register e of lane l holds row
     //      8*(e/4) + 4*(l/32) + e%4 and column l%32 of its 32x32 block.  Buffer addressing: one
-    //      32-bit lane offset per block plus a wave-uniform offset per register, instead of a
+    //      32-bit lane offset per pixel block plus a wave-uniform offset per register, instead of a
     //      64-bit address per output.  A NULL bias or residual becomes a buffer of zero records,
-    //      whose loads return 0. ------------------------------------------------------------------
+    //      whose loads return 0; a pixel past the last one and a channel past the last one get an offset past every tensor
+    //      (they are smaller than 2 GiB; the wave-uniform part cannot carry it round), whose loads and stores do nothing.
+    //      Not so for atomics, which such lanes have to stay out of. ------------------------------------------------
+    constexpr unsigned kNowhere = 0x80000000u;
     const __amdgpu_buffer_rsrc_t yrsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)ce->y, 0, (int)ce->y_bytes, 0x00020000);
     // y[n][k][p][q]: consecutive channels are PQ elements apart; channels-last y[n][p][q][k]: 1
-    const int PQ4 = ce->yl ? 4 : ce->PQ * 4;
+    const int ch4 = ce->yl ? 4 : ce->PQ * 4;
+    const int kfirst = nbase + 4 * lrow;
+    unsigned place[NMT];  // byte offset in y of channel kfirst of the lane's pixel
     static_for<NMT>([&](auto J) WPK_LAMBDA {
         constexpr int j = decltype(J)::value;
-        int m = mbase + j * 32 + lcol;
-        if (m < ce->M) {
-            int n = fdiv(m, WPK_COLD_DIV(ce, div_pq)), pq = m - n * ce->PQ;
-            static_for<NNT>([&](auto I) WPK_LAMBDA {
-                constexpr int i = decltype(I)::value;
-                const int kbase = nbase + i * 32 + 4 * lrow;  // + 8*(e/4) + e%4
-                // byte offset of (n, kbase, pq) in y; only used for channels below K, where it
-                // is below y_bytes < 2^32
-                const unsigned voff = ce->yl ? (unsigned)(((size_t)m * ce->K + kbase) * 4)
-                                           : (unsigned)((((size_t)n * ce->K + kbase) * ce->PQ + pq) * 4);
-                // A 32-channel block that lies wholly below K (the usual case) stores without a
-                // bound check per register; the check costs an exec-mask round trip each.
-                auto emit = [&](auto FULL, auto THROUGH) WPK_LAMBDA {
-                    constexpr bool full = decltype(FULL)::value;
-                    // channels-last outputs leave a lane in 16-byte pieces that only the L2 merges
-                    // into whole lines: they keep the default write-back policy
-                    constexpr int policy = decltype(THROUGH)::value ? kYStorePolicy : 0;
-                    if (ce->yl == 2 && !atomic) {
-                        // channels-last y with K a multiple of 4 and 16-byte aligned tensors: the four
-                        // registers 4g..4g+3 of a lane are four consecutive channels of its pixel
-                        const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
-                            (void *)(ce->bias ? ce->bias : ce->y), 0, ce->bias ? ce->K * 4 : 0, 0x00020000);
-                        const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
-                            (void *)(ce->res ? ce->res : ce->y), 0, ce->res ? (int)ce->y_bytes : 0, 0x00020000);
-                        v4f add[4];
-                        if (fused)
-                            static_for<4>([&](auto G) WPK_LAMBDA {
-                                constexpr int g = decltype(G)::value;
-                                v4f t = lds_bias ? *reinterpret_cast<const v4f *>(lds_bias + i * 32 + 4 * lrow + 8 * g)
-                                                 : __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
-                                                                               brsrc, kbase * 4, 32 * g, 0));
-                                if (full || kbase + 8 * g < ce->K)
-                                    t += __builtin_bit_cast(
-                                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, voff, 32 * g, 0));
-                                add[g] = t;
-                            });
-                        static_for<4>([&](auto G) WPK_LAMBDA {
-                            constexpr int g = decltype(G)::value;
-                            if (full || kbase + 8 * g < ce->K) {
-                                v4f v = {acc[i * NMT + j][4 * g], acc[i * NMT + j][4 * g + 1],
-                                         acc[i * NMT + j][4 * g + 2], acc[i * NMT + j][4 * g + 3]};
-                                if (fused) {
-                                    v += add[g];
-                                    if (ce->relu)
-                                        v = (v4f){fmaxf(v[0], 0.0f), fmaxf(v[1], 0.0f), fmaxf(v[2], 0.0f),
-                                                  fmaxf(v[3], 0.0f)};
-                                }
-                                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), yrsrc, voff,
-                                                                       32 * g, policy);
-                            }
-                        });
-                    } else if (fused) {
-                        const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
-                            (void *)(ce->bias ? ce->bias : ce->y), 0, ce->bias ? ce->K * 4 : 0, 0x00020000);
-                        const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
-                            (void *)(ce->res ? ce->res : ce->y), 0, ce->res ? (int)ce->y_bytes : 0, 0x00020000);
-                        // everything the 16 outputs of this block add is fetched first, so the loads
-                        // are all in flight together; then the stores
-                        float add[16];
-                        static_for<16>([&](auto E) WPK_LAMBDA {
-                            constexpr int e = decltype(E)::value, de = 8 * (e / 4) + (e & 3);
-                            float t = lds_bias ? lds_bias[i * 32 + 4 * lrow + de]
-                                               : __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                                               brsrc, kbase * 4, de * 4, 0));
-                            if (full || kbase + de < ce->K)
-                                t += __builtin_bit_cast(
-                                    float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, voff, de * PQ4, 0));
-                            add[e] = t;
-                        });
-                        static_for<16>([&](auto E) WPK_LAMBDA {
-                            constexpr int e = decltype(E)::value, de = 8 * (e / 4) + (e & 3);
-                            if (full || kbase + de < ce->K) {
-                                float v = acc[i * NMT + j][e] + add[e];
-                                v = ce->relu ? fmaxf(v, 0.0f) : v;
-                                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), yrsrc,
-                                                                      voff, de * PQ4, policy);
-                            }
-                        });
-                    } else if (atomic) {
-                        // (no-return fp32 adds, addressed like the stores)
-                        static_for<16>([&](auto E) WPK_LAMBDA {
-                            constexpr int e = decltype(E)::value, de = 8 * (e / 4) + (e & 3);
-                            if (full || kbase + de < ce->K) {
-                                const float v = acc[i * NMT + j][e];
-                                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(v, yrsrc, voff, de * PQ4, 0);
-                            }
-                        });
-                    } else {
-                        static_for<16>([&](auto E) WPK_LAMBDA {
-                            constexpr int e = decltype(E)::value, de = 8 * (e / 4) + (e & 3);
-                            if (full || kbase + de < ce->K) {
-                                // a copy first: a bit cast taken straight from a vector element
-                                // reads element 0 with this compiler
-                                const float v = acc[i * NMT + j][e];
-                                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), yrsrc,
-                                                                      voff, de * PQ4, policy);
-                            }
-                        });
+        const int m = mbase + j * 32 + lcol;
+        const int n = fdiv(m, WPK_COLD_DIV(ce, div_pq)), pq = m - n * ce->PQ;
+        const unsigned at = ce->yl ? (unsigned)(((size_t)m * ce->K + kfirst) * 4)
+                                   : (unsigned)((((size_t)n * ce->K + kfirst) * ce->PQ + pq) * 4);
+        place[j] = m < ce->M ? at : kNowhere;
+    });
+    // FETCH: something is to be loaded; FULL: every channel exists (the usual case), no check per register; QUADS: channels-last y,
+    // K a multiple of four and everything 16-byte aligned: the registers 4 g .. 4 g + 3 of a lane are four
+    // consecutive channels of its pixel
+    auto emit = [&](auto FETCH, auto FULL, auto QUADS, auto POLICY) WPK_LAMBDA {
+        constexpr bool quads = decltype(QUADS)::value;
+        const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(ce->bias ? ce->bias : ce->y), 0, ce->bias ? ce->K * 4 : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(ce->res ? ce->res : ce->y), 0, ce->res ? (int)ce->y_bytes : 0, 0x00020000);
+        float res[2 * 16], bias[2 * 16];
+        auto masked = [&](const int j, const int k) WPK_LAMBDA {
+            return decltype(FULL)::value || k < ce->K ? place[j] : kNowhere;
+        };
+        auto fetch = [&](auto B) WPK_LAMBDA {
+            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT, set = b & 1;
+            if constexpr (quads) {
+                static_for<4>([&](auto G) WPK_LAMBDA {
+                    constexpr int g = decltype(G)::value, dk = i * 32 + 8 * g;
+                    const v4f r = __builtin_bit_cast(
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, masked(j, kfirst + dk), dk * 4, 0));
+                    static_for<4>([&](auto E) WPK_LAMBDA { res[set * 16 + 4 * g + decltype(E)::value] = r[decltype(E)::value]; });
+                    if constexpr (!LDS_BIAS) {
+                        const v4f q = __builtin_bit_cast(
+                            v4f, __builtin_amdgcn_raw_buffer_load_b128(brsrc, (kfirst + dk) * 4, 0, 0));
+                        static_for<4>([&](auto E) WPK_LAMBDA { bias[set * 16 + 4 * g + decltype(E)::value] = q[decltype(E)::value]; });
                     }
-                };
-                const bool whole = nbase + i * 32 + 32 <= ce->K;
-                if (ce->yl == 0) {
-                    if (whole)
-                        emit(std::true_type{}, std::true_type{});
-                    else
-                        emit(std::false_type{}, std::true_type{});
+                });
+            } else {
+                static_for<16>([&](auto E) WPK_LAMBDA {
+                    constexpr int e = decltype(E)::value, dk = i * 32 + 8 * (e / 4) + (e & 3);
+                    res[set * 16 + e] = __builtin_bit_cast(
+                        float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, masked(j, kfirst + dk), dk * ch4, 0));
+                    if constexpr (!LDS_BIAS)
+                        bias[set * 16 + e] = __builtin_bit_cast(
+                            float, __builtin_amdgcn_raw_buffer_load_b32(brsrc, (kfirst + dk) * 4, 0, 0));
+                });
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto store = [&](auto B) WPK_LAMBDA {
+            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT, set = b & 1;
+            static_for<4>([&](auto G) WPK_LAMBDA {
+                constexpr int g = decltype(G)::value, dk = i * 32 + 8 * g;
+                v4f add = {0.0f, 0.0f, 0.0f, 0.0f}, v;
+                if constexpr (LDS_BIAS) add = *reinterpret_cast<const v4f *>(lds_bias + dk + 4 * lrow);
+                static_for<4>([&](auto E) WPK_LAMBDA {
+                    constexpr int e = decltype(E)::value;
+                    // (a copy first: a bit cast taken straight from a vector element reads element 0 with this compiler)
+                    float t = acc[i * NMT + j][4 * g + e];
+                    if constexpr (decltype(FETCH)::value && LDS_BIAS) t += add[e] + res[set * 16 + 4 * g + e];
+                    else if constexpr (decltype(FETCH)::value) t += bias[set * 16 + 4 * g + e] + res[set * 16 + 4 * g + e];
+                    else if constexpr (LDS_BIAS) t += add[e];
+                    v[e] = ce->relu ? fmaxf(t, 0.0f) : t;
+                });
+                if constexpr (quads) {
+                    store_quad(__builtin_bit_cast(v4u, v), yrsrc, masked(j, kfirst + dk) + dk * 4, POLICY);
                 } else {
-                    if (whole)
-                        emit(std::true_type{}, std::false_type{});
-                    else
-                        emit(std::false_type{}, std::false_type{});
+                    static_for<4>([&](auto E) WPK_LAMBDA {
+                        constexpr int e = decltype(E)::value;
+                        const float t = v[e];
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, t), yrsrc,
+                                                              masked(j, kfirst + dk + e), (dk + e) * ch4,
+                                                              decltype(POLICY)::value);
+                    });
                 }
             });
-        }
-    });
+        };
+        constexpr int NB = NNT * NMT;
+        if constexpr (decltype(FETCH)::value) fetch(std::integral_constant<int, 0>{});
+        static_for<NB>([&](auto B) WPK_LAMBDA {
+            constexpr int b = decltype(B)::value;
+            if constexpr (decltype(FETCH)::value && b + 1 < NB) fetch(std::integral_constant<int, b + 1>{});
+            store(B);
+        });
+    };
+    // (the host applies the epilogue itself after a launch that accumulates with atomics)
+    if (atomic) {
+        // (no-return fp32 adds, addressed like the stores)
+        static_for<NNT * NMT>([&](auto B) WPK_LAMBDA {
+            static_for<16>([&](auto E) WPK_LAMBDA {
+                constexpr int i = decltype(B)::value % NNT, j = decltype(B)::value / NNT;
+                constexpr int e = decltype(E)::value, dk = i * 32 + 8 * (e / 4) + (e & 3);
+                const float v = acc[i * NMT + j][e];
+                if (place[j] != kNowhere && kfirst + dk < ce->K)
+                    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(v, yrsrc, place[j], dk * ch4, 0);
+            });
+        });
+        return;
+    }
+    // whole 128-byte runs are written through; channels-last outputs leave a lane in pieces that only the L2 merges into
+    // whole lines: they keep the default write-back policy
+    using Through = std::integral_constant<int, kYStorePolicy>;
+    using Back = std::integral_constant<int, 0>;
+    const bool whole = nbase + 32 * NNT <= ce->K;
+    auto choose = [&](auto FETCH) WPK_LAMBDA {
+        if (ce->yl == 2) emit(FETCH, std::false_type{}, std::true_type{}, Back{});
+        else if (ce->yl == 1) emit(FETCH, std::false_type{}, std::false_type{}, Back{});
+        else if (whole) emit(FETCH, std::true_type{}, std::false_type{}, Through{});
+        else emit(FETCH, std::false_type{}, std::false_type{}, Through{});
+    };
+    if (ce->res || (!LDS_BIAS && ce->bias)) choose(std::true_type{});
+    else choose(std::false_type{});
 }
 
 // How the result of one segment of work leaves a workgroup:
@@ -345,7 +356,7 @@ __device__ __forceinline__ bool meet_shared_tile(const cold_ptr ce, v16f (&acc)[
     static_for<NBLK * 4>([&](auto Q) WPK_LAMBDA {
         constexpr int qd = decltype(Q)::value, ij = qd / 4, e4 = qd % 4;
         v4f v = {acc[ij][4 * e4], acc[ij][4 * e4 + 1], acc[ij][4 * e4 + 2], acc[ij][4 * e4 + 3]};
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), srsrc, mine, qd * 16 * T, kCoherent);
+        store_quad(__builtin_bit_cast(v4u, v), srsrc, mine + qd * 16 * T, std::integral_constant<int, kCoherent>{});
     });
     // every store of this wave acknowledged, then every wave of the workgroup, before the
     // arrival is counted
@@ -845,7 +856,7 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
     if (mode == kFixup &&
         !meet_shared_tile<NNT * NMT, T>(ce, acc, BM * BN, tid, fix_j, fix_slot, fix_n, &arrival))
         return;  // not the last: done with this tile
-    store_wave_tile<NNT, NMT>(ce, acc, m0 + wave_m * TM, n0 + wave_n * TN, lrow, lcol, mode == kAtomic);
+    store_wave_tile<NNT, NMT, false>(ce, acc, m0 + wave_m * TM, n0 + wave_n * TN, lrow, lcol, mode == kAtomic);
     };  // run_segment
 
     for_each_segment(a, run_segment);

@@ -728,7 +728,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     if (mode == kFixup &&
         !meet_shared_tile<NMT, T>(ce, acc, BM * BN, tid, fix_j, fix_slot, fix_n, &arrival))
         return;  // not the last: done with this tile
-    store_wave_tile<1, NMT>(ce, acc, m0, n0, lrow, lcol, mode == kAtomic, &bias[parity][wave * 32]);
+    store_wave_tile<1, NMT, true>(ce, acc, m0, n0, lrow, lcol, mode == kAtomic, &bias[parity][wave * 32]);
     };  // run_segment
 
     for_each_segment(a, run_segment);

@@ -119,9 +119,8 @@ struct OutQuads {
             static_for<QW>([&](auto Q) WPK_LAMBDA {
                 constexpr int q = decltype(Q)::value;
                 if (whole || k + channel(q * 4) < c->K)
-                    __builtin_amdgcn_raw_buffer_store_b128(
-                        __builtin_bit_cast(v4u, (v4f){v[q * 4], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]}), yrsrc, place,
-                        channel(q * 4) * 4, 0);
+                    store_quad(__builtin_bit_cast(v4u, (v4f){v[q * 4], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]}), yrsrc,
+                               place + channel(q * 4) * 4, Back{});
             });
         } else if (c->yl == 1) {
             emit(std::false_type{}, Back{});
@@ -362,8 +361,9 @@ __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
             const int at = (wk * QW * 256 + 4 * lane) * 4;
             if (wk < OUT)
                 static_for<QW>([&](auto Q) WPK_LAMBDA {
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, sum[decltype(Q)::value]), srsrc, at,
-                                                           slice * SLOT * 4 + decltype(Q)::value * 1024, kCoherent);
+                    store_quad(__builtin_bit_cast(v4u, sum[decltype(Q)::value]), srsrc,
+                               slice * SLOT * 4 + at + decltype(Q)::value * 1024,
+                               std::integral_constant<int, kCoherent>{});
                 });
             // every store of this wave acknowledged, then every wave's, before the arrival is counted
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
