@@ -182,20 +182,24 @@ def make_config(bm, bn, bk, wm, wn, split_k=1, xcd_remap=1, persist=0, stages=2,
     return ConvConfig(bm, bn, bk, wm, wn, split_k, 1 if persist else xcd_remap, persist, stages, reduce)
 
 
+# (plain integers: the signatures below make void pointers of them; a c_void_p made here is one object more per argument,
+# and a call on a small layer takes no longer on the device than in Python)
 def _ptr(t):
     if t is None:
         return None
-    if hasattr(t, "data_ptr"):
-        return ctypes.c_void_p(t.data_ptr())
-    return ctypes.c_void_p(int(t))
+    try:
+        return t.data_ptr()
+    except AttributeError:
+        return int(t)
 
 
 def _stream(s):
     if s is None:
         return None
-    if hasattr(s, "cuda_stream"):
-        return ctypes.c_void_p(s.cuda_stream)
-    return ctypes.c_void_p(int(s))
+    try:
+        return s.cuda_stream
+    except AttributeError:
+        return int(s)
 
 
 def _check(status, where):

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <charconv>
 #include <map>
 #include <mutex>
 #include <numeric>
@@ -153,13 +154,17 @@ int make_problem(const wpk_conv_desc *d, Problem *out)
     return WPK_OK;
 }
 
+// (every one-shot call makes one or two of these; snprintf took a microsecond for each)
 std::string desc_key(const wpk_conv_desc *d)
 {
-    char buf[256];
-    snprintf(buf, sizeof buf, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", d->n, d->c, d->h,
-             d->w, d->k, d->r, d->s, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dil_h,
-             d->dil_w, d->dtype, d->layout);
-    return buf;
+    const int32_t fields[] = {d->n, d->c, d->h, d->w, d->k, d->r, d->s, d->stride_h, d->stride_w, d->pad_h, d->pad_w,
+                              d->dil_h, d->dil_w, d->dtype, d->layout};
+    char buf[15 * 12], *at = buf;  // eleven characters at most and a comma
+    for (const int32_t f : fields) {
+        if (at != buf) *at++ = ',';
+        at = std::to_chars(at, buf + sizeof buf, f).ptr;
+    }
+    return std::string(buf, at);
 }
 
 static const int32_t *cfg_fields(const wpk_conv_config *c, int32_t f[WPK_N_GENES])
@@ -811,6 +816,7 @@ int wpk_cache_lookup(const wpk_conv_desc *d, wpk_conv_config *out)
     int rc = make_problem(d, &pr);
     if (rc != WPK_OK) return rc;
     std::lock_guard<std::mutex> g(g_cache_mu);
+    if (g_cache.empty()) return 0;
     auto it = g_cache.find(cache_key(d));
     if (it == g_cache.end()) return 0;
     if (out) *out = it->second.cfg;
