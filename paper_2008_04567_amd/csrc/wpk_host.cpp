@@ -347,10 +347,12 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
     // The reduction is cut until there is one wave per SIMD, but not into runs of fewer than ten octets (five for eight tiles
     // or fewer, whose slices meet sooner): the meeting through the workspace takes as long as eight or so (1x1, 512 -> 2048
     // channels, 7x7, N = 1: 5.1 us in one, 6.1 in two; 512 -> 128 at 28x28: 5.1, 5.9; 3x3, 512 channels, 7x7: 8.4 in eight).
+    // Sixteen slices at most, and 24 for eight tiles or fewer (5x5, 544 -> 32 channels, 12x12, N = 1, five tiles: 15.2 us in
+    // sixteen, 14.4 in 24).
     // Atomics take two more launches, y zeroed and the epilogue: 13.9 us for that layer with the rule before, 9.5 without them.
     // (233 layers, ResNet-50 at N = 1 and 2 and drawn ones, bias and rectifier fused: 1.4 % above the best of all
     // waves, slices and channels on average, 8 by more than a tenth; the rule before: 3.2 %, 28.)
-    int64_t want = std::min<int64_t>(16, std::max<int64_t>(1, 4 * (int64_t)compute_units / (blocks * wk)));
+    int64_t want = std::min<int64_t>(blocks <= 8 ? 24 : 16, std::max<int64_t>(1, 4 * (int64_t)compute_units / (blocks * wk)));
     while (want > 1 && octets / (wk * want) < (blocks <= 8 ? 5 : 10)) --want;
     wpk_conv_config c = {kWaveSplitBm, 32, 8, wk, 1, 1, 1, 0, 1, 0};
     for (int i = 0; i < kGeneCounts[5]; ++i)
