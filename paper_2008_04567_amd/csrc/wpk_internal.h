@@ -262,6 +262,22 @@ WPK_HOST_DEVICE inline uint32_t split_weights_at(bool patch, uint32_t block, int
 {
     return block + (uint32_t)split_depth(patch, step < nsteps ? step : nsteps - 1, 0) * depth_bytes;
 }
+// Where outputs lie in y (and in a residual laid out alike), as the offsets of buffer accesses.  A lane of no output gets
+// kNowhere: past every tensor (they are smaller than 2 GiB), a multiple of four, and still past all of them with any
+// existing channel's offset added.
+static const uint32_t kNowhere = 0x80000000u;
+// Byte offset of channel k of pixel m, number pq of image n; M pixels, K channels; channels-last where yl.  (Of a channel past the
+// last one it says nothing: see output_at.)
+WPK_HOST_DEVICE inline uint32_t output_place(int m, int M, int n, int pq, int k, int K, int PQ, bool yl)
+{
+    const uint32_t at = yl ? (uint32_t)m * (uint32_t)K + (uint32_t)k : ((uint32_t)n * (uint32_t)K + (uint32_t)k) * (uint32_t)PQ + (uint32_t)pq;
+    return m < M ? at * 4u : kNowhere;
+}
+// The same for channel k + dk, from channel k's; ch4: bytes between channels.
+WPK_HOST_DEVICE inline uint32_t output_at(uint32_t place, int k, int dk, int K, uint32_t ch4)
+{
+    return k + dk < K ? place + (uint32_t)dk * ch4 : kNowhere;
+}
 // What a configuration counts the reduction in: K-steps, or chunks of 16 channels where it works from patches.
 struct Reduction {
     int32_t steps, rows;  // how many, and how many rows of the reduction each holds

@@ -40,7 +40,7 @@ template <int QW>
 struct OutQuads {
     float b[QW * 4], r[QW * 4];
     int k;           // the lane's first channel
-    unsigned place;  // byte offset in y of that channel of the lane's pixel; all ones past the last pixel
+    unsigned place;  // byte offset in y of that channel of the lane's pixel; kNowhere past the last pixel
 
     // channel of register e behind the first
     static constexpr int channel(const int e) { return e / 16 * 32 + e % 16 / 4 * 8 + e % 4; }
@@ -64,27 +64,25 @@ struct OutQuads {
     __device__ __forceinline__ void find_place(const IgemmArgs *const c, const int m)
     {
         const int n = fdiv(m, WPK_COLD_DIV(c, div_pq)), pq = m - n * c->PQ;
-        const unsigned at = c->yl ? (unsigned)(((size_t)m * c->K + k) * 4)
-                                  : (unsigned)((((size_t)n * c->K + k) * c->PQ + pq) * 4);
-        place = m < c->M ? at : 0xffffffffu;
+        place = output_place(m, c->M, n, pq, k, c->K, c->PQ, c->yl != 0);
     }
 
-    // (the channel's offset is in the lane's, which the range check covers: what lies past the last channel is not used)
+    // (the whole offset is the lane's, which the range check covers: a pixel or a channel past the last one loads zero)
     __device__ __forceinline__ void fetch_residual(const IgemmArgs *const c, const bool live)
     {
         const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(c->res ? c->res : c->y), 0, c->res && live ? (int)c->y_bytes : 0, 0x00020000);
-        const int ch4 = c->yl ? 4 : c->PQ * 4;
+        const unsigned ch4 = c->yl ? 4 : c->PQ * 4;
         static_for<QW * 4>([&](auto E) WPK_LAMBDA {
             constexpr int e = decltype(E)::value;
             r[e] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, place + (unsigned)(channel(e) * ch4), 0, 0));
+                float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, output_at(place, k, channel(e), c->K, ch4), 0, 0));
         });
     }
 
     __device__ __forceinline__ void store(const IgemmArgs *const c, const v4f (&sum)[QW], const bool whole, const bool atomic)
     {
-        if (place == 0xffffffffu) return;
+        if (place == kNowhere) return;
         const __amdgpu_buffer_rsrc_t yrsrc =
             __builtin_amdgcn_make_buffer_rsrc((void *)c->y, 0, (int)c->y_bytes, 0x00020000);
         const int ch4 = c->yl ? 4 : c->PQ * 4;
