@@ -205,22 +205,19 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
     //      32-bit lane offset per pixel block plus a wave-uniform offset per register, instead of a
     //      64-bit address per output.  A NULL bias or residual becomes a buffer of zero records,
     //      whose loads return 0; a pixel past the last one and a channel past the last one get an offset past every tensor
-    //      (they are smaller than 2 GiB; the wave-uniform part cannot carry it round), whose loads and stores do nothing.
+    //      (kNowhere, output_access), whose loads and stores do nothing.
     //      Not so for atomics, which such lanes have to stay out of. ------------------------------------------------
-    constexpr unsigned kNowhere = 0x80000000u;
     const __amdgpu_buffer_rsrc_t yrsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)ce->y, 0, (int)ce->y_bytes, 0x00020000);
     // y[n][k][p][q]: consecutive channels are PQ elements apart; channels-last y[n][p][q][k]: 1
-    const int ch4 = ce->yl ? 4 : ce->PQ * 4;
+    const unsigned ch4 = ce->yl ? 4 : ce->PQ * 4;
     const int kfirst = nbase + 4 * lrow;
     unsigned place[NMT];  // byte offset in y of channel kfirst of the lane's pixel
     static_for<NMT>([&](auto J) WPK_LAMBDA {
         constexpr int j = decltype(J)::value;
         const int m = mbase + j * 32 + lcol;
         const int n = fdiv(m, WPK_COLD_DIV(ce, div_pq)), pq = m - n * ce->PQ;
-        const unsigned at = ce->yl ? (unsigned)(((size_t)m * ce->K + kfirst) * 4)
-                                   : (unsigned)((((size_t)n * ce->K + kfirst) * ce->PQ + pq) * 4);
-        place[j] = m < ce->M ? at : kNowhere;
+        place[j] = output_place(m, ce->M, n, pq, kfirst, ce->K, ce->PQ, ce->yl != 0);
     });
     // FETCH: something is to be loaded; FULL: every channel exists (the usual case), no check per register; QUADS: channels-last y,
     // K a multiple of four and everything 16-byte aligned: the registers 4 g .. 4 g + 3 of a lane are four
@@ -232,8 +229,8 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
         const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(ce->res ? ce->res : ce->y), 0, ce->res ? (int)ce->y_bytes : 0, 0x00020000);
         float res[2 * 16], bias[2 * 16];
-        auto masked = [&](const int j, const int k) WPK_LAMBDA {
-            return decltype(FULL)::value || k < ce->K ? place[j] : kNowhere;
+        auto access = [&](const int j, const int dk) WPK_LAMBDA {
+            return output_access<decltype(FULL)::value>(place[j], kfirst, dk, ce->K, ch4);
         };
         auto fetch = [&](auto B) WPK_LAMBDA {
             constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT, set = b & 1;
@@ -241,7 +238,7 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
                 static_for<4>([&](auto G) WPK_LAMBDA {
                     constexpr int g = decltype(G)::value, dk = i * 32 + 8 * g;
                     const v4f r = __builtin_bit_cast(
-                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, masked(j, kfirst + dk), dk * 4, 0));
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, access(j, dk).lane, 0, 0));
                     static_for<4>([&](auto E) WPK_LAMBDA { res[set * 16 + 4 * g + decltype(E)::value] = r[decltype(E)::value]; });
                     if constexpr (!LDS_BIAS) {
                         const v4f q = __builtin_bit_cast(
@@ -252,8 +249,9 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
             } else {
                 static_for<16>([&](auto E) WPK_LAMBDA {
                     constexpr int e = decltype(E)::value, dk = i * 32 + 8 * (e / 4) + (e & 3);
-                    res[set * 16 + e] = __builtin_bit_cast(
-                        float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, masked(j, kfirst + dk), dk * ch4, 0));
+                    const OutputAccess at = access(j, dk);
+                    res[set * 16 + e] =
+                        __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, at.lane, at.uniform, 0));
                     if constexpr (!LDS_BIAS)
                         bias[set * 16 + e] = __builtin_bit_cast(
                             float, __builtin_amdgcn_raw_buffer_load_b32(brsrc, (kfirst + dk) * 4, 0, 0));
@@ -277,13 +275,13 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
                     v[e] = ce->relu ? fmaxf(t, 0.0f) : t;
                 });
                 if constexpr (quads) {
-                    store_quad(__builtin_bit_cast(v4u, v), yrsrc, masked(j, kfirst + dk) + dk * 4, POLICY);
+                    store_quad(__builtin_bit_cast(v4u, v), yrsrc, access(j, dk).lane, POLICY);
                 } else {
                     static_for<4>([&](auto E) WPK_LAMBDA {
                         constexpr int e = decltype(E)::value;
                         const float t = v[e];
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, t), yrsrc,
-                                                              masked(j, kfirst + dk + e), (dk + e) * ch4,
+                        const OutputAccess at = access(j, dk + e);
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, t), yrsrc, at.lane, at.uniform,
                                                               decltype(POLICY)::value);
                     });
                 }

@@ -278,6 +278,17 @@ WPK_HOST_DEVICE inline uint32_t output_at(uint32_t place, int k, int dk, int K, 
 {
     return k + dk < K ? place + (uint32_t)dk * ch4 : kNowhere;
 }
+// The same as the lane's and the wave-uniform part of an access.  WHOLE: every channel of the block exists; then the channel's offset
+// may be the uniform part, below 2^31 as it lies inside y.  That of a channel past the last one may be anything (31 channels
+// of 4200 x 4200 pixels are 2.2e9 bytes), and a buffer's range check does not cover the uniform part.
+struct OutputAccess {
+    uint32_t lane, uniform;
+};
+template <bool WHOLE>
+WPK_HOST_DEVICE inline OutputAccess output_access(uint32_t place, int k, int dk, int K, uint32_t ch4)
+{
+    return WHOLE ? OutputAccess{place, (uint32_t)dk * ch4} : OutputAccess{output_at(place, k, dk, K, ch4), 0};
+}
 // What a configuration counts the reduction in: K-steps, or chunks of 16 channels where it works from patches.
 struct Reduction {
     int32_t steps, rows;  // how many, and how many rows of the reduction each holds

@@ -30,8 +30,16 @@ int main()
                     const int n = m / PQ, pq = m % PQ;
                     const uint32_t ch4 = yl ? 4 : (uint32_t)PQ * 4, place = output_place(m, M, n, pq, k, K, PQ, yl != 0);
                     for (int dk = 0; dk < 64; dk += dk % 4 == 3 ? 5 : 1) {  // the channels of a lane's registers
-                        const uint64_t at = output_at(place, k, dk, K, ch4);
-                        bool ok;
+                        // a register of a 32-channel block that has them all, or of one that does not
+                        const bool whole = (k + dk) / 32 * 32 + 32 <= K;
+                        const OutputAccess a = whole ? output_access<true>(place, k, dk, K, ch4)
+                                                     : output_access<false>(place, k, dk, K, ch4);
+                        const uint64_t at = (uint64_t)a.lane + a.uniform;
+                        bool ok = true;
+                        if (at != output_at(place, k, dk, K, ch4)) ok = whole && m >= M && at < (1ull << 32);
+                        // (whether the uniform part counts in the range check or not)
+                        if (m >= M || k + dk >= K) ok = ok && a.lane >= bytes && a.uniform < bytes;
+                        if (!ok) return 4;
                         if (m < M && k + dk < K) {
                             ok = at == 4 * (yl ? (uint64_t)m * K + k + dk : ((uint64_t)n * K + k + dk) * PQ + pq);
                             ++there;
