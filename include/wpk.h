@@ -153,7 +153,8 @@ int wpk_config_legal(const wpk_conv_desc *d, const wpk_conv_config *cfg);
 int wpk_config_id(const wpk_conv_config *cfg);                 /* <0 if a value is not in its list */
 int wpk_config_from_id(int id, wpk_conv_config *out);
 
-/* The library's untuned default for a descriptor (a shape heuristic).  Always legal. */
+/* The library's untuned default for a descriptor (a shape heuristic), for a launch without an epilogue: with one, small layers
+ * may have another number of slices and meet by other means.  Always legal. */
 int wpk_config_default(const wpk_conv_desc *d, wpk_conv_config *out);
 
 /* ---- one-shot convolution ------------------------------------------------------------------ */
@@ -385,6 +386,7 @@ int wpk_plan_run_fused(wpk_plan *plan, const float *const *x, const float *const
 
 int wpk_plan_num_layers(const wpk_plan *plan);
 int wpk_plan_num_unique(const wpk_plan *plan);                       /* distinct descriptors     */
+/* (what a run of the layer without a residual uses, under the epilogue it has now) */
 int wpk_plan_layer_config(const wpk_plan *plan, int32_t layer, wpk_conv_config *out);
 /* (May grow the plan's workspace, and where `cfg` reads the weights in the other packed form, split or not, than the
  * plan holds, allocates that form and fills it from the one at hand: both synchronise the device.) */

@@ -944,7 +944,8 @@ using namespace wpk;
 struct wpk_plan {
     struct Layer {
         Problem pr;
-        wpk_conv_config cfg;
+        wpk_conv_config cfg;       // of a launch without an epilogue,
+        wpk_conv_config cfg_fused; // and with one: two choices where the default rule made them, else the same
         int unique;
         // packed weights, in the form of the split members ([1]) and of the others ([0]): whichever the layer's
         // configurations need; the direct kernel's plain [K][C][R][S] weights are in [0]
@@ -955,7 +956,13 @@ struct wpk_plan {
         bool direct;  // outside the tiled family
         // two-way pipelining: the batch split into images [0, half[0].d.n) and the rest
         Problem half[2];
-        wpk_conv_config half_cfg[2];
+        wpk_conv_config half_cfg[2], half_cfg_fused[2];
+        // what a launch of the layer, or of half its batch, runs with (epilogue: it has a bias, a residual or a rectifier)
+        const wpk_conv_config &config(int which, bool epilogue) const
+        {
+            return which < 0 ? (epilogue ? cfg_fused : cfg) : (epilogue ? half_cfg_fused[which] : half_cfg[which]);
+        }
+        bool epilogue(const float *residual) const { return bias || relu || residual; }
     };
     FixupBuf fix;  // fix-up workspace shared by the layers (they run one after another)
     // two-way pipelining (wpk_plan_set_pipeline): the second half-batch chain runs on `side`
@@ -1005,6 +1012,24 @@ static int plan_need_weights(wpk_plan::Layer &L, const wpk_conv_config &cfg)
     if (rc == WPK_OK) L.wp[s] = packed;
     else (void)hipFree(packed);
     return rc;
+}
+
+// A layer's configurations where nobody set one: the cached result of a search, or the defaults.
+static void plan_choose(const Problem &pr, wpk_conv_config *cfg, wpk_conv_config *cfg_fused)
+{
+    if (wpk_cache_lookup(&pr.d, cfg) == 1 && legal_for(pr, *cfg)) {
+        *cfg_fused = *cfg;
+        return;
+    }
+    default_config(pr, g_cus, cfg, true);
+    default_config(pr, g_cus, cfg_fused, false);
+}
+
+// Room for the shared tiles of either.
+static int plan_reserve(FixupBuf &fix, const Problem &pr, const wpk_conv_config &cfg, const wpk_conv_config &cfg_fused)
+{
+    const int64_t bytes = std::max(fixup_need(pr, cfg, g_cus).bytes, fixup_need(pr, cfg_fused, g_cus).bytes);
+    return bytes > 0 ? fixup_reserve(fix, (size_t)bytes) : WPK_OK;
 }
 
 extern "C" {
@@ -1224,7 +1249,7 @@ static int fwd_fused(const wpk_conv_desc *d, const wpk_conv_config *cfg_in, cons
     }
     wpk_conv_config cfg;
     if (cfg_in) cfg = *cfg_in;
-    else if (wpk_cache_lookup(d, &cfg) != 1 || !legal_for(pr, cfg)) default_config(pr, g_cus, &cfg);
+    else if (wpk_cache_lookup(d, &cfg) != 1 || !legal_for(pr, cfg)) default_config(pr, g_cus, &cfg, !epi.any());
     return fwd_with(pr, cfg, x, w, y, st, epi);
 }
 
@@ -1281,7 +1306,7 @@ int wpk_conv_tune_ex(const wpk_conv_desc *d, const wpk_tune_options *opt_in, int
         return rc;
     }
     wpk_conv_config defcfg;
-    default_config(pr, g_cus, &defcfg);
+    default_config(pr, g_cus, &defcfg, t.opt.epilogue == 0);
     double def_us = 0, def_err = 0;
     rc = measure_us(t, defcfg, &def_us, &def_err);
     if (rc != WPK_OK) {
@@ -1648,6 +1673,7 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
         L.direct = !L.pr.tiled_ok;
         if (L.direct) {  // oversized filter, or a channels-last shape the tiled gather does not take
             memset(&L.cfg, 0, sizeof L.cfg);
+            L.cfg_fused = L.cfg;
             L.unique = -1;
             hipError_t e = hipMalloc((void **)&L.wp[0], (size_t)L.pr.w_elems * sizeof(float));
             if (e != hipSuccess) { set_last_hip_error((int)e); rc = WPK_E_HIP; break; }
@@ -1668,13 +1694,12 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
             }
         }
         L.unique = it->second;
-        if (wpk_cache_lookup(&layers[i], &L.cfg) != 1 || !legal_for(L.pr, L.cfg))
-            default_config(L.pr, g_cus, &L.cfg);
+        plan_choose(L.pr, &L.cfg, &L.cfg_fused);
         rc = plan_need_weights(L, L.cfg);
+        if (rc == WPK_OK) rc = plan_need_weights(L, L.cfg_fused);
         plan->layers.push_back(L);
         if (rc != WPK_OK) break;
-        FixupNeed need = fixup_need(L.pr, L.cfg, g_cus);
-        if (need.bytes > 0) rc = fixup_reserve(plan->fix, (size_t)need.bytes);
+        rc = plan_reserve(plan->fix, L.pr, L.cfg, L.cfg_fused);
     }
     if (rc == WPK_OK) {  // the tap tables were written on the null stream: complete before any stream reads them
         hipError_t e = hipDeviceSynchronize();
@@ -1728,7 +1753,7 @@ static int plan_launch(wpk_plan *plan, wpk_plan::Layer &L, int which, const floa
                        const float *residual, float *y, hipStream_t st, bool y_zeroed = false)
 {
     const Problem &pr = which < 0 ? L.pr : L.half[which];
-    const wpk_conv_config &cfg = which < 0 ? L.cfg : L.half_cfg[which];
+    const wpk_conv_config &cfg = L.config(which, L.epilogue(residual));
     if (which == 1) {  // the second half starts after the images of the first
         x += L.half[0].x_elems;
         y += L.half[0].y_elems;
@@ -1796,15 +1821,11 @@ int wpk_plan_set_pipeline(wpk_plan *plan, int32_t ways)
             int rc = make_problem(&d, &L.half[h]);
             if (rc != WPK_OK) return rc;
             if (L.direct) continue;
-            if (wpk_cache_lookup(&d, &L.half_cfg[h]) != 1 || !legal_for(L.half[h], L.half_cfg[h]))
-                default_config(L.half[h], g_cus, &L.half_cfg[h]);
+            plan_choose(L.half[h], &L.half_cfg[h], &L.half_cfg_fused[h]);
             rc = plan_need_weights(L, L.half_cfg[h]);
+            if (rc == WPK_OK) rc = plan_need_weights(L, L.half_cfg_fused[h]);
+            if (rc == WPK_OK) rc = plan_reserve(h == 0 ? plan->fix : plan->fix_side, L.half[h], L.half_cfg[h], L.half_cfg_fused[h]);
             if (rc != WPK_OK) return rc;
-            FixupNeed need = fixup_need(L.half[h], L.half_cfg[h], g_cus);
-            if (need.bytes > 0) {
-                rc = fixup_reserve(h == 0 ? plan->fix : plan->fix_side, (size_t)need.bytes);
-                if (rc != WPK_OK) return rc;
-            }
         }
     }
     plan->ways = 2;
@@ -1897,7 +1918,8 @@ int wpk_plan_run_fused(wpk_plan *plan, const float *const *x, const float *const
         };
         for (size_t j = 0; j < nl; ++j) {
             const wpk_plan::Layer &L = plan->layers[j];
-            if (L.direct || !zeroes_all_of_y(L.pr, L.cfg, &plan->fix)) continue;
+            const wpk_conv_config &cfg = L.config(-1, L.epilogue(residual ? residual[j] : nullptr));
+            if (L.direct || !zeroes_all_of_y(L.pr, cfg, &plan->fix)) continue;
             const int64_t ny = L.pr.y_elems;
             bool ok = !overlaps(y[j], ny, x[j], L.pr.x_elems) &&
                       !(residual && overlaps(y[j], ny, residual[j], ny));
@@ -1949,7 +1971,8 @@ int wpk_plan_layer_config(const wpk_plan *plan, int32_t layer, wpk_conv_config *
 {
     if (!plan || !out) return WPK_E_NULL_PTR;
     if (layer < 0 || layer >= (int)plan->layers.size()) return WPK_E_BAD_ARG;
-    *out = plan->layers[layer].cfg;
+    const wpk_plan::Layer &L = plan->layers[layer];
+    *out = L.config(-1, L.epilogue(nullptr));
     return WPK_OK;
 }
 
@@ -1966,7 +1989,7 @@ int wpk_plan_set_layer_config(wpk_plan *plan, int32_t layer, const wpk_conv_conf
         int rc = fixup_reserve(plan->fix, (size_t)need.bytes);
         if (rc != WPK_OK) return rc;
     }
-    plan->layers[layer].cfg = *cfg;
+    plan->layers[layer].cfg = plan->layers[layer].cfg_fused = *cfg;
     // the half-batch launches of a pipelined plan follow, where the configuration is legal for them
     if (plan->side) {
         wpk_plan::Layer &L = plan->layers[layer];
@@ -1979,7 +2002,7 @@ int wpk_plan_set_layer_config(wpk_plan *plan, int32_t layer, const wpk_conv_conf
                 int rc = fixup_reserve(fb, (size_t)nh.bytes);
                 if (rc != WPK_OK) return rc;
             }
-            L.half_cfg[h] = *cfg;
+            L.half_cfg[h] = L.half_cfg_fused[h] = *cfg;
         }
     }
     return WPK_OK;

@@ -334,7 +334,7 @@ bool wave_split_candidate(const Problem &pr, int64_t max_block_octets)
     const int64_t blocks = ((pr.M + 31) / 32) * ((pr.d.k + 31) / 32), octets = pr.CRS / 8;
     return blocks * octets <= max_block_octets;
 }
-static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_config *out)
+static bool wave_split_default(const Problem &pr, int compute_units, bool plain, wpk_conv_config *out)
 {
     if (!wave_split_candidate(pr, 20000)) return false;
     const int64_t blocks = ((pr.M + 31) / 32) * ((pr.d.k + 31) / 32), octets = pr.CRS / 8;
@@ -347,16 +347,34 @@ static bool wave_split_default(const Problem &pr, int compute_units, wpk_conv_co
     // The reduction is cut until there is one wave per SIMD, but not into runs of fewer than ten octets (five for eight tiles
     // or fewer, whose slices meet sooner): the meeting through the workspace takes as long as eight or so (1x1, 512 -> 2048
     // channels, 7x7, N = 1: 5.1 us in one, 6.1 in two; 512 -> 128 at 28x28: 5.1, 5.9; 3x3, 512 channels, 7x7: 8.4 in eight).
-    // Sixteen slices at most, and 24 for eight tiles or fewer (5x5, 544 -> 32 channels, 12x12, N = 1, five tiles: 15.2 us in
-    // sixteen, 14.4 in 24).
-    // Atomics take two more launches, y zeroed and the epilogue: 13.9 us for that layer with the rule before, 9.5 without them.
+    // Sixteen slices at most, and 24 for eight tiles or fewer.
+    // With an epilogue, atomics take two more launches, y zeroed and the epilogue: 13.9 us for that layer, 9.5 without them.
     // (233 layers, ResNet-50 at N = 1 and 2 and drawn ones, bias and rectifier fused: 1.4 % above the best of all
-    // waves, slices and channels on average, 8 by more than a tenth; the rule before: 3.2 %, 28.)
-    int64_t want = std::min<int64_t>(blocks <= 8 ? 24 : 16, std::max<int64_t>(1, 4 * (int64_t)compute_units / (blocks * wk)));
-    while (want > 1 && octets / (wk * want) < (blocks <= 8 ? 5 : 10)) --want;
+    // waves, slices and channels on average, 8 by more than a tenth; by the rule below: 3.2 %, 28.)
+    const int64_t most = std::max<int64_t>(1, 4 * (int64_t)compute_units / (blocks * wk));
+    auto slices = [&](int64_t cap, int64_t run) {
+        int64_t n = std::min(cap, most);
+        while (n > 1 && octets / (wk * n) < run) --n;
+        return n;
+    };
+    int64_t want = slices(blocks <= 8 ? 24 : 16, blocks <= 8 ? 5 : 10);
+    // Without one, atomics take the zeroing alone, and in a pass not even that (one launch for all layers): four slices or more add up
+    // with them, and need eight octets only (layers in a pass, then by themselves, workspace and atomics: 3x3, 256 channels, 14x14, N = 1,
+    // 8.2 and 7.2 us, 8.3 and 8.5; 5x5, 544 -> 32 channels, 12x12, N = 1, five tiles in 24 slices, 9.8 and 6.8, 9.7 and 8.1; 40
+    // such layers, 1.18 and 1.02 times the atomics' time).  Three slices of eight octets meet in the workspace (3x3, 96
+    // channels: 6.4, 6.8 in two); two are not worth it (six layers of 64 to 72 octets: 6.3 in two, 5.9 in one).
+    // Not into channels-last outputs: 18 such layers, workspace 0.79 and 0.70 times the atomics' time, 1.2 at worst (289 pixels
+    // of nine channels).
+    bool atomics = false;
+    if (plain && !pr.yl) {
+        const int64_t n = slices(24, 8);
+        if (n != 2) want = n;
+        atomics = n >= 4;
+    }
     wpk_conv_config c = {kWaveSplitBm, 32, 8, wk, 1, 1, 1, 0, 1, 0};
     for (int i = 0; i < kGeneCounts[5]; ++i)
         if (kSplitVals[i] <= want) c.split_k = kSplitVals[i];
+    c.reduce = atomics ? 1 : 0;
     if (!legal_for(pr, c)) return false;
     *out = c;
     return true;
@@ -495,13 +513,13 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     return true;
 }
 static void tiled_default(const Problem &pr, int compute_units, wpk_conv_config *out);
-void default_config(const Problem &pr, int compute_units, wpk_conv_config *out)
+void default_config(const Problem &pr, int compute_units, wpk_conv_config *out, bool plain)
 {
     if (compute_units <= 0) compute_units = 256;
     // A launch with a few microseconds of arithmetic at most (single images, late layers): the
     // wave-split members.  (Measured on the single-image ResNet-50 layers: 3.4-9.1 us where the tiled members' best
     // is 4.9-10.6.)
-    if (wave_split_default(pr, compute_units, out)) return;
+    if (wave_split_default(pr, compute_units, plain, out)) return;
     wpk_conv_config tiled;
     tiled_default(pr, compute_units, &tiled);
     if (!split_default(pr, compute_units, tiled, out)) *out = tiled;

@@ -299,7 +299,8 @@ int persistent_of(const Problem &pr, const wpk_conv_config &cfg, int compute_uni
 // The configuration that stands for all those that make the same launch as cfg: split members have no prefetch depths, K-steps
 // only where they decide about patches, and slices and persistent schedules that come out as another's.
 wpk_conv_config same_launch(const Problem &pr, const wpk_conv_config &cfg, int compute_units);
-void default_config(const Problem &pr, int compute_units, wpk_conv_config *out);
+// (plain: of a launch without an epilogue.  The two differ in the wave-split members' slices and how they meet.)
+void default_config(const Problem &pr, int compute_units, wpk_conv_config *out, bool plain = true);
 // Whether the wave-split members can run pr at all and its 32 x 32 output blocks times its octets of
 // reduction rows stay within the bound (the work is then small enough for them to be worth timing).
 bool wave_split_candidate(const Problem &pr, int64_t max_block_octets);

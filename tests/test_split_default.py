@@ -49,6 +49,28 @@ int main()
             return 1;
         }
     }
+    // Wave-split members: how slices meet follows from what the launch has to do (us, workspace and atomics, in a pass without an
+    // epilogue unless stated).
+    static const struct { wpk_conv_desc d; int plain, fused; } meet[] = {  // (slices; below zero: atomics)
+        {L(1, 512, 7, 7, 512, 3, 3, 1, 1, 1, 0), -8, 8},      // 9.3, 8.0; with an epilogue 9.5, 13.9
+        {L(1, 256, 14, 14, 256, 3, 3, 1, 1, 1, 0), -4, 4},    // 8.2, 7.2
+        {L(1, 544, 12, 12, 32, 5, 5, 1, 2, 1, 0), -24, 24},   // 9.8, 6.8
+        {L(1, 512, 28, 28, 128, 1, 1, 1, 0, 1, 0), 1, 1},     // 5.5; in two slices 6.2
+        {L(1, 512, 7, 7, 512, 3, 3, 1, 1, 1, 2), 8, 8},       // (channels-last: 12.1 and 18 for such layers)
+    };
+    for (const auto &t : meet) {
+        Problem pr;
+        wpk_conv_config c, f;
+        if (make_problem(&t.d, &pr) != WPK_OK) return 3;
+        default_config(pr, 256, &c, true);
+        default_config(pr, 256, &f, false);
+        if (c.bm != kWaveSplitBm || f.bm != kWaveSplitBm || (c.reduce ? -c.split_k : c.split_k) != t.plain ||
+            (f.reduce ? -f.split_k : f.split_k) != t.fused) {
+            printf("c %d %dx%d k %d r %d layout %d: %d slices (reduce %d), fused %d (%d)\n", t.d.c, t.d.h, t.d.w, t.d.k, t.d.r,
+                   t.d.layout, c.split_k, c.reduce, f.split_k, f.reduce);
+            return 1;
+        }
+    }
     srand(5);
     long split = 0, all = 0;
     for (int it = 0; it < 60000; ++it) {
