@@ -347,7 +347,6 @@ static bool wave_split_default(const Problem &pr, int compute_units, bool plain,
     // The reduction is cut until there is one wave per SIMD, but not into runs of fewer than ten octets (five for eight tiles
     // or fewer, whose slices meet sooner): the meeting through the workspace takes as long as eight or so (1x1, 512 -> 2048
     // channels, 7x7, N = 1: 5.1 us in one, 6.1 in two; 512 -> 128 at 28x28: 5.1, 5.9; 3x3, 512 channels, 7x7: 8.4 in eight).
-    // Sixteen slices at most, and 24 for eight tiles or fewer.
     // With an epilogue, atomics take two more launches, y zeroed and the epilogue: 13.9 us for that layer, 9.5 without them.
     // (233 layers, ResNet-50 at N = 1 and 2 and drawn ones, bias and rectifier fused: 1.4 % above the best of all
     // waves, slices and channels on average, 8 by more than a tenth; by the rule below: 3.2 %, 28.)
@@ -357,7 +356,24 @@ static bool wave_split_default(const Problem &pr, int compute_units, bool plain,
         while (n > 1 && octets / (wk * n) < run) --n;
         return n;
     };
-    int64_t want = slices(blocks <= 8 ? 24 : 16, blocks <= 8 ? 5 : 10);
+    int64_t want = slices(24, blocks <= 8 ? 5 : 10);
+    // Beyond eight slices what they cost decides: the last to arrive reads the others seven at a time, a round trip to memory each that
+    // takes as long as six octets, and all of them store first.  (31 such layers of 180 to 3000 octets and 1 to 24 tiles in 2
+    // to 24 slices, rectifier fused: 0.5 % above the best number on average, 8 % at worst; 3.3 and 10 for as many slices as
+    // above, at most 16 or, for eight tiles or fewer, 24: 3x3, 17 tiles, 468 octets 8.1 us in eight, 8.6 in eleven; 5x5, five tiles, 1700
+    // octets 10.4 in 16, 10.0 in 20, 9.9 in 24, and 9.0 or, with y zeroed for it alone, 10.3 by atomics.)
+    if (want > 8) {
+        double least = 1e300;
+        for (int i = 0; i < kGeneCounts[5]; ++i) {
+            const int64_t n = kSplitVals[i];
+            if (n > std::min<int64_t>(24, most)) continue;
+            const double cost = (double)octets / (wk * n) + 6.0 * ((n - 1 + 6) / 7) + blocks * n / 32.0;
+            if (cost < least) {
+                least = cost;
+                want = n;
+            }
+        }
+    }
     // Without one, atomics take the zeroing alone, and in a pass not even that (one launch for all layers): four slices or more add up
     // with them, and need eight octets only (layers in a pass, then by themselves, workspace and atomics: 3x3, 256 channels, 14x14, N = 1,
     // 8.2 and 7.2 us, 8.3 and 8.5; 5x5, 544 -> 32 channels, 12x12, N = 1, five tiles in 24 slices, 9.8 and 6.8, 9.7 and 8.1; 40

@@ -54,7 +54,8 @@ int main()
     static const struct { wpk_conv_desc d; int plain, fused; } meet[] = {  // (slices; below zero: atomics)
         {L(1, 512, 7, 7, 512, 3, 3, 1, 1, 1, 0), -8, 8},      // 9.3, 8.0; with an epilogue 9.5, 13.9
         {L(1, 256, 14, 14, 256, 3, 3, 1, 1, 1, 0), -4, 4},    // 8.2, 7.2
-        {L(1, 544, 12, 12, 32, 5, 5, 1, 2, 1, 0), -24, 24},   // 9.8, 6.8
+        {L(1, 544, 12, 12, 32, 5, 5, 1, 2, 1, 0), -24, 20},   // 9.8, 6.8
+        {L(1, 416, 17, 31, 32, 3, 3, 1, 1, 1, 0), -14, 8},    // (17 tiles: with an epilogue 8.1 in 8 slices, 8.6 in 11)
         {L(1, 512, 28, 28, 128, 1, 1, 1, 0, 1, 0), 1, 1},     // 5.5; in two slices 6.2
         {L(1, 512, 7, 7, 512, 3, 3, 1, 1, 1, 2), 8, 8},       // (channels-last: 12.1 and 18 for such layers)
     };
