@@ -186,19 +186,23 @@ __device__ __forceinline__ void pixel_window(const ARGS c, const int m, int &vof
 }
 
 // ---- what leaves a wave: its NNT x NMT accumulator blocks, whose first pixel is mbase and first
-//      channel nbase, go to y -- plain stores with the fused epilogue applied, or fp32 atomics.  lds_bias, with
-//      LDS_BIAS: the bias of channels nbase .. in LDS, zeros where there is none.
+//      channel nbase, go to y -- plain stores with the fused epilogue applied, or fp32 atomics.  bias: of channels
+//      nbase .. in LDS, zeros where there is none (not read by launches that add nothing).
 //
 //      Memory operations return in order, so whoever waits for a load waits for every store issued before it, and a
-//      store that is written through is acknowledged a microsecond after it was issued.  So what a block adds is
-//      asked for before the block ahead of it is stored, and nothing is asked for where there is nothing to add.
+//      store that is written through is acknowledged a microsecond after it was issued.  So the bias comes from LDS, the residual
+//      of a block is asked for before the block ahead of it is stored, and no residual where there is none.
 //      (Block by block, loads then stores, the 32 stores of a split member's wave took 2.2 to 2.9 us whether there was a residual
 //      or not: 3x3, 128 channels, 28x28, N = 16, 23.0 -> 21.1 us; 1x1, 64 -> 256 channels, 56x56 with a residual, 31.9 -> 30.4;
-//      ResNet-50, N = 16, 1334 -> 1258.) ----
-template <int NNT, int NMT, bool LDS_BIAS, class ARGS>
+//      ResNet-50, N = 16, 1334 -> 1258.)
+//      A tiled member's registers may not grow by it: what a block adds is summed up (16 registers) before the next block's
+//      residual is asked for (16 more).  Two blocks' residuals and biases in registers took waves from half of these members: 78
+//      launches of 13 of them with 6 layers and 2 schedules, plain / bias and rectifier / residual as well, took 1.030, 1.001
+//      and 1.010 times what they take block by block, and take 0.998, 0.935 and 0.975 times now. ----
+template <int NNT, int NMT, class ARGS>
 __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)[NNT * NMT], const int mbase,
                                                 const int nbase, const int lrow, const int lcol, const bool atomic,
-                                                const float *const lds_bias = nullptr)
+                                                const float *const bias)
 {
     // ---- epilogue: D[row = channel][col = pixel]; register e of lane l holds row
     //      8*(e/4) + 4*(l/32) + e%4 and column l%32 of its 32x32 block.  Buffer addressing: one
@@ -210,7 +214,7 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
     const __amdgpu_buffer_rsrc_t yrsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)ce->y, 0, (int)ce->y_bytes, 0x00020000);
     // y[n][k][p][q]: consecutive channels are PQ elements apart; channels-last y[n][p][q][k]: 1
-    const unsigned ch4 = ce->yl ? 4 : ce->PQ * 4;
+    unsigned ch4 = ce->yl ? 4 : ce->PQ * 4;
     const int kfirst = nbase + 4 * lrow;
     unsigned place[NMT];  // byte offset in y of channel kfirst of the lane's pixel
     static_for<NMT>([&](auto J) WPK_LAMBDA {
@@ -219,60 +223,61 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
         const int n = fdiv(m, WPK_COLD_DIV(ce, div_pq)), pq = m - n * ce->PQ;
         place[j] = output_place(m, ce->M, n, pq, kfirst, ce->K, ce->PQ, ce->yl != 0);
     });
-    // FETCH: something is to be loaded; FULL: every channel exists (the usual case), no check per register; QUADS: channels-last y,
-    // K a multiple of four and everything 16-byte aligned: the registers 4 g .. 4 g + 3 of a lane are four
-    // consecutive channels of its pixel
-    auto emit = [&](auto FETCH, auto FULL, auto QUADS, auto POLICY) WPK_LAMBDA {
+    // ADD: 0 the sums as they are, 1 the bias added and the rectifier, 2 the residual as well; FULL: every channel exists (the usual case), no check per register; QUADS:
+    // channels-last y, K a multiple of four and everything 16-byte aligned: the registers 4 g .. 4 g + 3 of a lane are
+    // four consecutive channels of its pixel
+    auto emit = [&](auto ADD, auto FULL, auto QUADS, auto POLICY) WPK_LAMBDA {
+        constexpr int how = decltype(ADD)::value;
         constexpr bool quads = decltype(QUADS)::value;
-        const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(ce->bias ? ce->bias : ce->y), 0, ce->bias ? ce->K * 4 : 0, 0x00020000);
         const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(ce->res ? ce->res : ce->y), 0, ce->res ? (int)ce->y_bytes : 0, 0x00020000);
-        float res[2 * 16], bias[2 * 16];
+        v4f add[4], res[4];
         auto access = [&](const int j, const int dk) WPK_LAMBDA {
             return output_access<decltype(FULL)::value>(place[j], kfirst, dk, ce->K, ch4);
         };
         auto fetch = [&](auto B) WPK_LAMBDA {
-            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT, set = b & 1;
+            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT;
             if constexpr (quads) {
                 static_for<4>([&](auto G) WPK_LAMBDA {
                     constexpr int g = decltype(G)::value, dk = i * 32 + 8 * g;
-                    const v4f r = __builtin_bit_cast(
+                    res[g] = __builtin_bit_cast(
                         v4f, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, access(j, dk).lane, 0, 0));
-                    static_for<4>([&](auto E) WPK_LAMBDA { res[set * 16 + 4 * g + decltype(E)::value] = r[decltype(E)::value]; });
-                    if constexpr (!LDS_BIAS) {
-                        const v4f q = __builtin_bit_cast(
-                            v4f, __builtin_amdgcn_raw_buffer_load_b128(brsrc, (kfirst + dk) * 4, 0, 0));
-                        static_for<4>([&](auto E) WPK_LAMBDA { bias[set * 16 + 4 * g + decltype(E)::value] = q[decltype(E)::value]; });
-                    }
                 });
             } else {
                 static_for<16>([&](auto E) WPK_LAMBDA {
                     constexpr int e = decltype(E)::value, dk = i * 32 + 8 * (e / 4) + (e & 3);
                     const OutputAccess at = access(j, dk);
-                    res[set * 16 + e] =
+                    res[e / 4][e & 3] =
                         __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, at.lane, at.uniform, 0));
-                    if constexpr (!LDS_BIAS)
-                        bias[set * 16 + e] = __builtin_bit_cast(
-                            float, __builtin_amdgcn_raw_buffer_load_b32(brsrc, (kfirst + dk) * 4, 0, 0));
                 });
             }
             __builtin_amdgcn_sched_barrier(0);
         };
+        // what block B adds (and the registers of its residual are free for the next one's)
+        auto fold = [&](auto B) WPK_LAMBDA {
+            static_for<4>([&](auto G) WPK_LAMBDA {
+                constexpr int g = decltype(G)::value;
+                add[g] = *reinterpret_cast<const v4f *>(bias + decltype(B)::value % NNT * 32 + 8 * g + 4 * lrow);
+                if constexpr (how == 2) add[g] += res[g];
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        };
         auto store = [&](auto B) WPK_LAMBDA {
-            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT, set = b & 1;
+            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT;
+            // (offsets formed anew: kept from the loads, and from one block to the next, they take 16 registers each)
+            if constexpr (how == 2) asm volatile("" : "+v"(place[j]), "+s"(ch4));
             static_for<4>([&](auto G) WPK_LAMBDA {
                 constexpr int g = decltype(G)::value, dk = i * 32 + 8 * g;
-                v4f add = {0.0f, 0.0f, 0.0f, 0.0f}, v;
-                if constexpr (LDS_BIAS) add = *reinterpret_cast<const v4f *>(lds_bias + dk + 4 * lrow);
+                v4f v;
                 static_for<4>([&](auto E) WPK_LAMBDA {
                     constexpr int e = decltype(E)::value;
                     // (a copy first: a bit cast taken straight from a vector element reads element 0 with this compiler)
                     float t = acc[i * NMT + j][4 * g + e];
-                    if constexpr (decltype(FETCH)::value && LDS_BIAS) t += add[e] + res[set * 16 + 4 * g + e];
-                    else if constexpr (decltype(FETCH)::value) t += bias[set * 16 + 4 * g + e] + res[set * 16 + 4 * g + e];
-                    else if constexpr (LDS_BIAS) t += add[e];
-                    v[e] = ce->relu ? fmaxf(t, 0.0f) : t;
+                    if constexpr (how != 0) {
+                        t += add[g][e];
+                        t = ce->relu ? fmaxf(t, 0.0f) : t;
+                    }
+                    v[e] = t;
                 });
                 if constexpr (quads) {
                     store_quad(__builtin_bit_cast(v4u, v), yrsrc, access(j, dk).lane, POLICY);
@@ -285,13 +290,15 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
                                                               decltype(POLICY)::value);
                     });
                 }
+                if constexpr (how == 2) __builtin_amdgcn_sched_barrier(0);
             });
         };
         constexpr int NB = NNT * NMT;
-        if constexpr (decltype(FETCH)::value) fetch(std::integral_constant<int, 0>{});
+        if constexpr (how == 2) fetch(std::integral_constant<int, 0>{});
         static_for<NB>([&](auto B) WPK_LAMBDA {
             constexpr int b = decltype(B)::value;
-            if constexpr (decltype(FETCH)::value && b + 1 < NB) fetch(std::integral_constant<int, b + 1>{});
+            if constexpr (how != 0) fold(B);
+            if constexpr (how == 2 && b + 1 < NB) fetch(std::integral_constant<int, b + 1>{});
             store(B);
         });
     };
@@ -314,14 +321,15 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
     using Through = std::integral_constant<int, kYStorePolicy>;
     using Back = std::integral_constant<int, 0>;
     const bool whole = nbase + 32 * NNT <= ce->K;
-    auto choose = [&](auto FETCH) WPK_LAMBDA {
-        if (ce->yl == 2) emit(FETCH, std::false_type{}, std::true_type{}, Back{});
-        else if (ce->yl == 1) emit(FETCH, std::false_type{}, std::false_type{}, Back{});
-        else if (whole) emit(FETCH, std::true_type{}, std::false_type{}, Through{});
-        else emit(FETCH, std::false_type{}, std::false_type{}, Through{});
+    auto choose = [&](auto ADD) WPK_LAMBDA {
+        if (ce->yl == 2) emit(ADD, std::false_type{}, std::true_type{}, Back{});
+        else if (ce->yl == 1) emit(ADD, std::false_type{}, std::false_type{}, Back{});
+        else if (whole) emit(ADD, std::true_type{}, std::false_type{}, Through{});
+        else emit(ADD, std::false_type{}, std::false_type{}, Through{});
     };
-    if (ce->res || (!LDS_BIAS && ce->bias)) choose(std::true_type{});
-    else choose(std::false_type{});
+    if (ce->res) choose(std::integral_constant<int, 2>{});
+    else if (ce->bias || ce->relu) choose(std::integral_constant<int, 1>{});
+    else choose(std::integral_constant<int, 0>{});
 }
 
 // How the result of one segment of work leaves a workgroup:
@@ -519,8 +527,18 @@ __device__ __forceinline__ void for_each_segment(const IgemmArgs &a, F &&run)
 //   element of the XL = 0 form cost 10-15 % of the arithmetic time; this form has three per step.
 //   A pointwise (1x1) layer is the single-tap case of it.
 // The layout of y (and of a fused residual) is a run-time flag of the epilogue (a.yl).
+// Waves per SIMD that the registers of a tiled member of `blocks` accumulator blocks per wave have to leave room for: said only
+// where the compiler would otherwise take more registers than the loop needs, for the meeting and the way out.  (Eight waves to a
+// workgroup need an even number.)
+constexpr int tiled_waves(int blocks, int bk, int lanes, int pd, int xl)
+{
+    if (blocks == 1) return bk == 8 ? 5 : bk == 16 && lanes == 512 && pd < 3 ? 6 : 1;
+    if (blocks == 2) return bk == 16 && lanes == 512 && xl == 0 ? 4 : 1;
+    return blocks == 4 && bk == 8 && lanes == 512 ? 4 : 1;
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int PD, int XL>
-__global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
+__global__ void __launch_bounds__(64 * WM * WN, tiled_waves(BM * BN / (1024 * WM * WN), BK, 64 * WM * WN, PD, XL)) igemm_kernel(const IgemmArgs a)
 {
     constexpr int T = 64 * WM * WN;
     constexpr int TM = BM / WM, TN = BN / WN;    // wave tile
@@ -562,6 +580,8 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
     const int wquad_bytes = (T / BN) * a.Kpad * 16;  // this thread's next quad in the same step
 
     // One segment of work: reduction steps [kbeg, kend) of output tile `tile`.
+    __shared__ __attribute__((aligned(16))) float bias[2][BN];  // of this segment's channels and of the one before
+    int parity = 0;                                             // of the segment
     __shared__ int arrival;
     auto run_segment = [&](const int tile, const int kbeg, const int kend, const int mode,
                            const int fix_j, const int fix_slot, const int fix_n) WPK_LAMBDA {
@@ -578,6 +598,7 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
         }
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
+    parity ^= 1;
 
     // ---- per-thread gather state ---------------------------------------------------------------
     // xvoff: byte offset of the pixel's window origin (before padding is subtracted; the padding
@@ -823,11 +844,22 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
     gather_state();
     if constexpr (TAPM) fold_mask();
     static_for<NXL>([&](auto E) WPK_LAMBDA { load_x(std::integral_constant<int, 0>{}, E); });
+    // the bias of the tile's channels, zeros where there is none (behind tile 0, which has to arrive first; asked for out of range
+    // then: a branch here costs 0.5 of 9.6 us on a layer of two steps)
+    float bval;
+    {
+        const cold_ptr c = cold_args();
+        bval = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                   __builtin_amdgcn_make_buffer_rsrc((void *)(c->bias ? c->bias : c->y), 0, c->bias ? c->K * 4 : 0, 0x00020000),
+                   (n0 + tid) * 4, 0, 0));
+    }
     static_for<PD - 1>([&](auto P) WPK_LAMBDA {
         constexpr int t = decltype(P)::value + 1;
         if (t < nr) load_tile(std::integral_constant<int, t>{}, kbeg + t);
     });
     store_tile(std::integral_constant<int, 0>{}, 0);
+    asm volatile("" : "+v"(bval));  // (waited for here by all lanes: left to the branch, the loop waits for every load in flight)
+    if (tid < BN) bias[parity][tid] = bval;
     if (PD < nr) load_tile(std::integral_constant<int, 0>{}, kbeg + PD);
     __syncthreads();
     if constexpr (PIPE) read_octet(0, std::integral_constant<int, 0>{}, 0);
@@ -854,7 +886,8 @@ __global__ void __launch_bounds__(64 * WM * WN) igemm_kernel(const IgemmArgs a)
     if (mode == kFixup &&
         !meet_shared_tile<NNT * NMT, T>(ce, acc, BM * BN, tid, fix_j, fix_slot, fix_n, &arrival))
         return;  // not the last: done with this tile
-    store_wave_tile<NNT, NMT, false>(ce, acc, m0 + wave_m * TM, n0 + wave_n * TN, lrow, lcol, mode == kAtomic);
+    store_wave_tile<NNT, NMT>(ce, acc, m0 + wave_m * TM, n0 + wave_n * TN, lrow, lcol, mode == kAtomic,
+                              bias[parity] + wave_n * TN);
     };  // run_segment
 
     for_each_segment(a, run_segment);

@@ -235,9 +235,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
 
     touch_kernarg_lines();
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lrow = lane >> 5, lcol = lane & 31;
     const int buf_bytes = PATCH ? (a.halo + 1) * kHaloPitch : BM * kStepPitch;
     int parity = 0;                            // of the segment
 
@@ -253,7 +251,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     // Step 0 goes to LDS, then while the others multiply step r, step r + 1 does, from registers into which it was
     // fetched DEPTH steps (patches: one) before.  Past the end of the segment the same instructions are issued with lane
     // offsets of all ones: nothing is fetched, zeros are stored and nobody reads them.
-    auto fetch_segment = [&](const int m0, const int n0, const int kbeg, const int kend) WPK_LAMBDA {
+    auto fetch_segment = [&](const int m0, const int n0, const int kbeg, const int kend, const int lane) WPK_LAMBDA {
         const int nr = kend - kbeg;
         const int prod = wave - WN;
         // the channels' bias: asked for now, stored once the first fetches are on their way
@@ -576,6 +574,11 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     auto run_segment = [&](const int tile, const int kbeg, const int kend, const int mode,
                            const int fix_j, const int fix_slot, const int fix_n) WPK_LAMBDA {
     if (kbeg >= kend) return;
+    // (the lane's numbers formed anew for every segment and for the way out: what is derived from those of the kernel's entry is
+    // held all through otherwise, and the patch forms spill three to twelve registers)
+    int seg_tid = tid;
+    asm volatile("" : "+v"(seg_tid));
+    const int lane = seg_tid & 63, lrow = lane >> 5, lcol = lane & 31;
     int tile_m, tile_n;
     {
         const cold_ptr c = cold_args();
@@ -590,7 +593,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     const int m0 = tile_m * BM;
     parity ^= 1;
     if (wave >= WN) {
-        fetch_segment(m0, tile_n * BN, kbeg, kend);
+        fetch_segment(m0, tile_n * BN, kbeg, kend, lane);
         if (mode == kFixup) {  // (the three barriers of the meeting)
             __syncthreads();
             __syncthreads();
@@ -725,10 +728,11 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
             return split_depth(PATCH, kbeg + i / NT, i % NT);
         }, lane);
     const cold_ptr ce = cold_args();
+    asm volatile("" : "+v"(seg_tid));
     if (mode == kFixup &&
-        !meet_shared_tile<NMT, T>(ce, acc, BM * BN, tid, fix_j, fix_slot, fix_n, &arrival))
+        !meet_shared_tile<NMT, T>(ce, acc, BM * BN, seg_tid, fix_j, fix_slot, fix_n, &arrival))
         return;  // not the last: done with this tile
-    store_wave_tile<1, NMT, true>(ce, acc, m0, n0, lrow, lcol, mode == kAtomic, &bias[parity][wave * 32]);
+    store_wave_tile<1, NMT>(ce, acc, m0, n0, seg_tid >> 5 & 1, seg_tid & 31, mode == kAtomic, &bias[parity][wave * 32]);
     };  // run_segment
 
     for_each_segment(a, run_segment);
