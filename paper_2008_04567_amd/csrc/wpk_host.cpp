@@ -191,7 +191,7 @@ bool legal_for(const Problem &pr, const wpk_conv_config &cfg)
     if (cfg.bm == kWaveSplitBm) {
         // the wave-split members: tap-major reduction order only, one workgroup per tile and slice
         if (!(pr.tapmajor || pr.xquad) || cfg.persist != 0) return false;
-        if ((cfg.wm * cfg.wn - 1) * cfg.bn * 32 * 4 > kMaxLdsBytes) return false;  // the other waves' partial tiles
+        if (wave_split_floats(cfg.bn, cfg.wm * cfg.wn) * 4 > kMaxLdsBytes) return false;
     } else {
         if (2 * (cfg.bk + 4) * (cfg.bm + cfg.bn) * 4 > kMaxLdsBytes) return false;    // two LDS stages
         if (threads > cfg.bm && (cfg.bk * cfg.bm / threads) % 4 != 0) return false;   // whole k quads per thread

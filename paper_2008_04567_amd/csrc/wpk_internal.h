@@ -47,6 +47,9 @@ static const int kNumXcd = 8;
 // Members with this pixel tile are the wave-split form (wpk_wsplit.h): their wm x wn waves cut the
 // reduction between them, bk is the octet they work in, and `stages` counts four octets in flight each.
 static const int kWaveSplitBm = 32;
+// Floats of LDS that their waves meet in: every wave's partial tile of 32 pixels and bn channels (none for one wave, whose
+// slices leave a word there).
+constexpr int wave_split_floats(int bn, int waves) { return waves > 1 ? waves * bn * 32 : 4; }
 // Tiled members whose waves all lie along the channels (wm = 1) are the split form (wpk_split.h): fp32
 // products formed on the bf16 matrix pipes, weights packed as three bf16 parts (kSplitWeightBytes each).
 inline bool split_member(const wpk_conv_config &c) { return c.bm != kWaveSplitBm && c.wm == 1; }

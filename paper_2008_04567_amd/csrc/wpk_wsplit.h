@@ -1,9 +1,9 @@
 // The wave-split members of the convolution kernel family for gfx950: for launches whose
 // arithmetic is a few microseconds at most (single images, late layers of few pixels).
 //
-// Same GEMM view, same packed weights and same output code as the tiled members (wpk_igemm.h);
-// the filter taps are followed by arithmetic instead of being read from the tap table.  What
-// differs is who shares what.  A tiled workgroup stages its operands through
+// Same GEMM view and same packed weights as the tiled members (wpk_igemm.h);
+// the filter taps are followed by arithmetic instead of being read from the tap table, and every wave carries out
+// a part of the tile.  What differs is who shares what.  A tiled workgroup stages its operands through
 // LDS so that every wave reuses them, and it needs a long reduction per workgroup to repay the
 // staging, the barriers and -- when the reduction has to be cut between workgroups to fill the
 // device -- the meeting of the partial tiles in memory, several dependent memory round trips at
@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(64 * WK) wsplit_kernel(const IgemmArgs a)
     constexpr int NQ = NNT * 4;                      // accumulator quads of a tile
     constexpr int OUT = WK < NQ ? WK : NQ;           // waves that carry the tile out,
     constexpr int QW = NQ / OUT;                     // so many quads each
-    __shared__ __attribute__((aligned(16))) float red[WK > 1 ? WK * NQ * 256 : 4];
+    __shared__ __attribute__((aligned(16))) float red[wave_split_floats(BN, WK)];
     int *const arrival = reinterpret_cast<int *>(red);  // (64 KB are taken by eight waves of 64 channels: no room beside them)
 
     touch_kernarg_lines();
