@@ -51,3 +51,21 @@ def test_residual_that_y_takes_the_place_of(tile):
     print(cfg, flush=True)
     B.conv2d_fwd_fused(desc, PT.to_dev(x), PT.to_dev(w), y, residual=y, relu=True, cfg=cfg)
     PT.assert_close(y.cpu().numpy(), y_ref, d_ref, repr(cfg))
+
+
+@pytest.mark.parametrize("tile", [(64, 32, 8, 2, 1), (64, 64, 32, 2, 2), (128, 64, 16, 2, 2), (64, 64, 32, 1, 2)])
+def test_biases_of_tiles_that_follow_each_other(tile):
+    """Persistent workgroups take tiles of other channels one after the other: each is stored with its own bias, which waits in LDS while
+    others of the workgroup still store the tile before; also the tiles dealt out in runs."""
+    layer = W.layer("store_persist", 2, 32, (61, 83), 232, 1, x_dist="u11", w_dist="u11", seed=430)
+    x, w = W.make_inputs(layer)
+    rng = np.random.default_rng(9)
+    bias = rng.uniform(-4, 4, 232).astype(np.float32)
+    y_ref, d_ref = oc.conv2d_fused(oc.shape_from_layer(layer), x, w, bias=bias)
+    desc = B.make_desc(layer)
+    for persist in (1, 2):
+        cfg = B.make_config(*tile, persist=persist)
+        assert B.config_legal(desc, cfg)
+        print(cfg, flush=True)
+        y = PT.run_gpu_fused(layer, x, w, bias=bias, cfg=cfg)
+        PT.assert_close(y, y_ref, d_ref, repr(cfg))

@@ -4,6 +4,7 @@ a filter tap, cut between workgroups or not.  Bar: 1e-4 * sum|x*w| against the C
 import numpy as np
 import pytest
 
+from oracle import conv as oc
 from paper_2008_04567_amd import binding as B
 from paper_2008_04567_amd import workloads as W
 from tests import parity as PT
@@ -40,3 +41,31 @@ def test_wave_split_members_carry_tiles_out(layer, layout):
                 PT.check_layout(layer, layout, cfg=cfg, bias=bias, residual=res, relu=True)
                 ran += 1
     assert ran >= 8
+
+
+@pytest.mark.parametrize("k", [16, 37, 64])
+def test_residual_that_y_takes_the_place_of(k):
+    """Residuals are read ahead of the loop where four waves or more share a tile (and no slices meet): each wave reads and writes its
+    own outputs.  Pixels and channels that fill no tile; 16 channels: lanes past the last pixel would be just past the tensor."""
+    layer = W.layer("ws_inplace_%d" % k, 1, 64, (11, 13), k, 3, 1, 1, x_dist="u11", w_dist="u11", seed=320 + k)
+    desc = B.make_desc(layer)
+    P, Q = B.conv_out_shape(desc)
+    x, w = W.make_inputs(layer)
+    rng = np.random.default_rng(k)
+    res = rng.uniform(-2, 2, (1, k, P, Q)).astype(np.float32)
+    bias = rng.uniform(-1, 1, k).astype(np.float32)
+    y_ref, d_ref = oc.conv2d_fused(oc.shape_from_layer(layer), x, w, bias=bias, residual=res, relu=True)
+    xd, wd, bd = PT.to_dev(x), PT.to_dev(w), PT.to_dev(bias)
+    ran = 0
+    for bn in (32, 64):
+        for wm, wn in ((1, 1), (2, 1), (4, 1), (4, 2)):
+            for split in (1, 3):
+                cfg = B.make_config(32, bn, 8, wm, wn, split, 1, 0, 1, 0)
+                if not B.config_legal(desc, cfg):
+                    continue
+                print(cfg, flush=True)
+                y = PT.to_dev(res)
+                B.conv2d_fwd_fused(desc, xd, wd, y, bias=bd, residual=y, relu=True, cfg=cfg)
+                PT.assert_close(y.cpu().numpy(), y_ref, d_ref, repr(cfg))
+                ran += 1
+    assert ran >= 12
