@@ -544,13 +544,13 @@ static int run_epilogue(const Problem &pr, const Epilogue &epi, float *y, hipStr
 struct FixupBuf {
     char *ptr = nullptr;
     size_t bytes = 0;
-    bool lent = false;  // part of a larger allocation, which somebody else frees
 };
 static int fixup_reserve(FixupBuf &b, size_t bytes)
 {
     if (bytes <= b.bytes) return WPK_OK;
-    if (b.ptr && !b.lent) WPK_HIP(hipFree(b.ptr));  // synchronises: earlier users are done
-    b = FixupBuf();
+    if (b.ptr) WPK_HIP(hipFree(b.ptr));  // synchronises: earlier users are done
+    b.ptr = nullptr;
+    b.bytes = 0;
     WPK_HIP(hipMalloc((void **)&b.ptr, bytes));
     WPK_HIP(hipMemset(b.ptr, 0, kFixupCounterBytes));
     WPK_HIP(hipDeviceSynchronize());  // filled before a launch on any stream can follow
@@ -559,8 +559,9 @@ static int fixup_reserve(FixupBuf &b, size_t bytes)
 }
 static void fixup_release(FixupBuf &b)
 {
-    if (b.ptr && !b.lent) (void)hipFree(b.ptr);
-    b = FixupBuf();
+    if (b.ptr) (void)hipFree(b.ptr);
+    b.ptr = nullptr;
+    b.bytes = 0;
 }
 
 // Launch one member of the tiled family.  cfg must be legal for pr (checked by the callers).
@@ -971,7 +972,6 @@ struct wpk_plan {
     hipEvent_t fork = nullptr, join = nullptr;
     FixupBuf fix_side;
     std::vector<Layer> layers;
-    char *block = nullptr;         // one allocation: the tables, and the workspace that the plan begins with
     std::vector<int32_t *> ktabs;  // one per distinct descriptor
     // verdict of the last check whether a pass's two half-batch chains touch disjoint memory,
     // and the pointers it was made for
@@ -1025,33 +1025,11 @@ static void plan_choose(const Problem &pr, wpk_conv_config *cfg, wpk_conv_config
     default_config(pr, g_cus, cfg_fused, false);
 }
 
-// Bytes for the shared tiles of either.
-static size_t plan_room(const Problem &pr, const wpk_conv_config &cfg, const wpk_conv_config &cfg_fused)
+// Room for the shared tiles of either.
+static int plan_reserve(FixupBuf &fix, const Problem &pr, const wpk_conv_config &cfg, const wpk_conv_config &cfg_fused)
 {
-    return (size_t)std::max(fixup_need(pr, cfg, g_cus).bytes, fixup_need(pr, cfg_fused, g_cus).bytes);
-}
-
-// Tap tables and workspace, one behind the other in one allocation (ResNet-50, N = 1: 0.9 ms to build, 1.25 with an allocation for
-// each and a wait for every growth of the workspace).  Tables and counters are written on the null stream.
-static int plan_block(wpk_plan *plan, const std::vector<Problem> &tables, const size_t room)
-{
-    auto round256 = [](size_t v) { return (v + 255) / 256 * 256; };
-    size_t bytes = 0;
-    for (const Problem &pr : tables) bytes += round256(tap_table_bytes(pr));
-    if (bytes + room == 0) return WPK_OK;
-    WPK_HIP(hipMalloc((void **)&plan->block, bytes + room));
-    char *at = plan->block;
-    for (const Problem &pr : tables) {
-        plan->ktabs.push_back((int32_t *)at);
-        int rc = write_tap_table(pr, (int32_t *)at, nullptr);
-        if (rc != WPK_OK) return rc;
-        at += round256(tap_table_bytes(pr));
-    }
-    if (room == 0) return WPK_OK;
-    plan->fix.ptr = at;
-    plan->fix.bytes = room;
-    plan->fix.lent = true;
-    return zero_fill((float *)at, kFixupCounterBytes / 4, nullptr);
+    const int64_t bytes = std::max(fixup_need(pr, cfg, g_cus).bytes, fixup_need(pr, cfg_fused, g_cus).bytes);
+    return bytes > 0 ? fixup_reserve(fix, (size_t)bytes) : WPK_OK;
 }
 
 extern "C" {
@@ -1683,8 +1661,6 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
     }
     wpk_plan *plan = new wpk_plan();
     std::map<std::string, int> seen;  // identical descriptors share one search and one tap table
-    std::vector<Problem> tables;
-    size_t room = 0;
     int rc = WPK_OK;
     for (int i = 0; i < n_layers && rc == WPK_OK; ++i) {
         wpk_plan::Layer L;
@@ -1707,8 +1683,11 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
         std::string key = desc_key(&layers[i]);
         auto it = seen.find(key);
         if (it == seen.end()) {
-            tables.push_back(L.pr);
-            it = seen.emplace(key, (int)tables.size() - 1).first;
+            int32_t *ktab = nullptr;
+            rc = upload_tap_table(L.pr, &ktab, nullptr);
+            if (rc != WPK_OK) break;
+            plan->ktabs.push_back(ktab);
+            it = seen.emplace(key, (int)plan->ktabs.size() - 1).first;
             if (tune) {
                 int id = wpk_conv_tune(&layers[i]);
                 if (id < 0) { rc = id; break; }
@@ -1720,9 +1699,8 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
         if (rc == WPK_OK) rc = plan_need_weights(L, L.cfg_fused);
         plan->layers.push_back(L);
         if (rc != WPK_OK) break;
-        room = std::max(room, plan_room(L.pr, L.cfg, L.cfg_fused));
+        rc = plan_reserve(plan->fix, L.pr, L.cfg, L.cfg_fused);
     }
-    if (rc == WPK_OK) rc = plan_block(plan, tables, room);
     if (rc == WPK_OK) {  // the tap tables were written on the null stream: complete before any stream reads them
         hipError_t e = hipDeviceSynchronize();
         if (e != hipSuccess) { set_last_hip_error((int)e); rc = WPK_E_HIP; }
@@ -1846,7 +1824,7 @@ int wpk_plan_set_pipeline(wpk_plan *plan, int32_t ways)
             plan_choose(L.half[h], &L.half_cfg[h], &L.half_cfg_fused[h]);
             rc = plan_need_weights(L, L.half_cfg[h]);
             if (rc == WPK_OK) rc = plan_need_weights(L, L.half_cfg_fused[h]);
-            if (rc == WPK_OK) rc = fixup_reserve(h == 0 ? plan->fix : plan->fix_side, plan_room(L.half[h], L.half_cfg[h], L.half_cfg_fused[h]));
+            if (rc == WPK_OK) rc = plan_reserve(h == 0 ? plan->fix : plan->fix_side, L.half[h], L.half_cfg[h], L.half_cfg_fused[h]);
             if (rc != WPK_OK) return rc;
         }
     }
@@ -2038,7 +2016,8 @@ void wpk_plan_destroy(wpk_plan *plan)
             if (p) (void)hipFree(p);
         if (L.bias) (void)hipFree(L.bias);
     }
-    if (plan->block) (void)hipFree(plan->block);
+    for (int32_t *t : plan->ktabs)
+        if (t) (void)hipFree(t);
     fixup_release(plan->fix);
     fixup_release(plan->fix_side);
     if (plan->fork) (void)hipEventDestroy(plan->fork);
