@@ -1022,7 +1022,8 @@ static void plan_choose(const Problem &pr, wpk_conv_config *cfg, wpk_conv_config
         return;
     }
     default_config(pr, g_cus, cfg, true);
-    default_config(pr, g_cus, cfg_fused, false);
+    *cfg_fused = *cfg;  // (only the wave-split members have two; the others would be priced twice)
+    if (cfg->bm == kWaveSplitBm) default_config(pr, g_cus, cfg_fused, false);
 }
 
 // Room for the shared tiles of either.
