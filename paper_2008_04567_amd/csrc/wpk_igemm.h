@@ -195,11 +195,11 @@ __device__ __forceinline__ void pixel_window(const ARGS c, const int m, int &vof
 //      (Block by block, loads then stores, the 32 stores of a split member's wave took 2.2 to 2.9 us whether there was a residual
 //      or not: 3x3, 128 channels, 28x28, N = 16, 23.0 -> 21.1 us; 1x1, 64 -> 256 channels, 56x56 with a residual, 31.9 -> 30.4;
 //      ResNet-50, N = 16, 1334 -> 1258.)
-//      A tiled member's registers may not grow by it: what a block adds is summed up (16 registers) before the next block's
-//      residual is asked for (16 more).  Two blocks' residuals and biases in registers took waves from half of these members: 78
+//      SETS: blocks whose residuals are in registers, two in the split members.  A tiled member's registers may not grow by it:
+//      what a block adds is summed up (16 registers) before the next block's residual is asked for (16 more).  Two blocks' residuals and biases in registers took waves from half of these members: 78
 //      launches of 13 of them with 6 layers and 2 schedules, plain / bias and rectifier / residual as well, took 1.030, 1.001
 //      and 1.010 times what they take block by block, and take 0.998, 0.935 and 0.975 times now. ----
-template <int NNT, int NMT, class ARGS>
+template <int NNT, int NMT, int SETS, class ARGS>
 __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)[NNT * NMT], const int mbase,
                                                 const int nbase, const int lrow, const int lcol, const bool atomic,
                                                 const float *const bias)
@@ -231,23 +231,23 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
         constexpr bool quads = decltype(QUADS)::value;
         const __amdgpu_buffer_rsrc_t rrsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(ce->res ? ce->res : ce->y), 0, ce->res ? (int)ce->y_bytes : 0, 0x00020000);
-        v4f add[4], res[4];
+        v4f add[4], res[4 * SETS];
         auto access = [&](const int j, const int dk) WPK_LAMBDA {
             return output_access<decltype(FULL)::value>(place[j], kfirst, dk, ce->K, ch4);
         };
         auto fetch = [&](auto B) WPK_LAMBDA {
-            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT;
+            constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT, set = b % SETS * 4;
             if constexpr (quads) {
                 static_for<4>([&](auto G) WPK_LAMBDA {
                     constexpr int g = decltype(G)::value, dk = i * 32 + 8 * g;
-                    res[g] = __builtin_bit_cast(
+                    res[set + g] = __builtin_bit_cast(
                         v4f, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, access(j, dk).lane, 0, 0));
                 });
             } else {
                 static_for<16>([&](auto E) WPK_LAMBDA {
                     constexpr int e = decltype(E)::value, dk = i * 32 + 8 * (e / 4) + (e & 3);
                     const OutputAccess at = access(j, dk);
-                    res[e / 4][e & 3] =
+                    res[set + e / 4][e & 3] =
                         __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rrsrc, at.lane, at.uniform, 0));
                 });
             }
@@ -258,9 +258,9 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
             static_for<4>([&](auto G) WPK_LAMBDA {
                 constexpr int g = decltype(G)::value;
                 add[g] = *reinterpret_cast<const v4f *>(bias + decltype(B)::value % NNT * 32 + 8 * g + 4 * lrow);
-                if constexpr (how == 2) add[g] += res[g];
+                if constexpr (how == 2) add[g] += res[decltype(B)::value % SETS * 4 + g];
             });
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (how == 2 && SETS == 1) __builtin_amdgcn_sched_barrier(0);
         };
         auto store = [&](auto B) WPK_LAMBDA {
             constexpr int b = decltype(B)::value, i = b % NNT, j = b / NNT;
@@ -290,15 +290,16 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
                                                               decltype(POLICY)::value);
                     });
                 }
-                if constexpr (how == 2) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (how == 2 && SETS == 1) __builtin_amdgcn_sched_barrier(0);
             });
         };
         constexpr int NB = NNT * NMT;
         if constexpr (how == 2) fetch(std::integral_constant<int, 0>{});
         static_for<NB>([&](auto B) WPK_LAMBDA {
             constexpr int b = decltype(B)::value;
+            if constexpr (how == 2 && SETS == 2 && b + 1 < NB) fetch(std::integral_constant<int, b + 1>{});
             if constexpr (how != 0) fold(B);
-            if constexpr (how == 2 && b + 1 < NB) fetch(std::integral_constant<int, b + 1>{});
+            if constexpr (how == 2 && SETS == 1 && b + 1 < NB) fetch(std::integral_constant<int, b + 1>{});
             store(B);
         });
     };
@@ -886,7 +887,7 @@ __global__ void __launch_bounds__(64 * WM * WN, tiled_waves(BM * BN / (1024 * WM
     if (mode == kFixup &&
         !meet_shared_tile<NNT * NMT, T>(ce, acc, BM * BN, tid, fix_j, fix_slot, fix_n, &arrival))
         return;  // not the last: done with this tile
-    store_wave_tile<NNT, NMT>(ce, acc, m0 + wave_m * TM, n0 + wave_n * TN, lrow, lcol, mode == kAtomic,
+    store_wave_tile<NNT, NMT, 1>(ce, acc, m0 + wave_m * TM, n0 + wave_n * TN, lrow, lcol, mode == kAtomic,
                               bias[parity] + wave_n * TN);
     };  // run_segment
 

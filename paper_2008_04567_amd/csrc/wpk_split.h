@@ -732,7 +732,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     if (mode == kFixup &&
         !meet_shared_tile<NMT, T>(ce, acc, BM * BN, seg_tid, fix_j, fix_slot, fix_n, &arrival))
         return;  // not the last: done with this tile
-    store_wave_tile<1, NMT>(ce, acc, m0, n0, seg_tid >> 5 & 1, seg_tid & 31, mode == kAtomic, &bias[parity][wave * 32]);
+    store_wave_tile<1, NMT, 2>(ce, acc, m0, n0, seg_tid >> 5 & 1, seg_tid & 31, mode == kAtomic, &bias[parity][wave * 32]);
     };  // run_segment
 
     for_each_segment(a, run_segment);
