@@ -602,12 +602,13 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.bk_div_rs = red.rows / a.RS;
     a.bk_mod_rs = red.rows % a.RS;
     a.ttab = ktab + ((size_t)a.RS + (red.rows == 8 ? 0 : red.rows == 16 ? 1 : 2)) * 32 * 2;
-    a.N = d.n; a.C = d.c; a.H = d.h; a.W = d.w; a.K = d.k; a.P = pr.P; a.Q = pr.Q; a.R = d.r; a.S = d.s;
+    a.N = d.n; a.C = d.c; a.H = d.h; a.W = d.w; a.K = d.k; a.Q = pr.Q; a.R = d.r; a.S = d.s;
     a.stride_h = d.stride_h; a.stride_w = d.stride_w; a.pad_h = d.pad_h; a.pad_w = d.pad_w;
     a.dil_h = d.dil_h; a.dil_w = d.dil_w;
     a.M = (int32_t)pr.M; a.PQ = pr.P * pr.Q; a.HW = d.h * d.w; a.CRS = pr.CRS; a.Kpad = pr.Kpad;
     a.nsteps = red.steps;
     a.halo = split_member(cfg) && split_point(pr) ? -1 : halo_positions(pr, cfg);
+    a.producers = (int16_t)split_producers(pr, cfg);
     // slices of ceil(nsteps/split_k) steps; launch only as many as are not empty
     a.steps_per_split = (a.nsteps + cfg.split_k - 1) / cfg.split_k;
     a.split_k = (a.nsteps + a.steps_per_split - 1) / a.steps_per_split;
@@ -628,6 +629,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.grid_persist = persist * (g_cus > 0 ? g_cus : 256);
     a.tiles = a.tiles_m * a.tiles_n;
     a.tiles_dp = persist > 0 ? a.tiles / a.grid_persist * a.grid_persist : 0;
+    a.two_per_unit = persist > 0 ? persist <= 2 : (int64_t)a.tiles * a.split_k <= 2 * (int64_t)(g_cus > 0 ? g_cus : 256);
     {
         int64_t units = (int64_t)(a.tiles - a.tiles_dp) * a.nsteps;  // < 2^31: checked by legal_for
         int64_t groups = persist > 0 ? streamk_groups(units, a.grid_persist, red.rows) : 0;

@@ -241,6 +241,25 @@ int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
     return patch_bound(pr);
 }
 
+int split_lds_units(int halo, int wn)
+{
+    return ((halo > 0 ? (halo + 1) * 224 : 30720) + 256 * wn + 4 + 1279) / 1280;
+}
+
+int split_producers(const Problem &pr, const wpk_conv_config &cfg)
+{
+    if (!split_member(cfg)) return 0;
+    const int halo = halo_positions(pr, cfg);
+    if (halo > 0) {
+        // a second one wherever as many workgroups as with one fit a compute unit (twelve waves)
+        const int fit = std::min(12 / (cfg.wn + 1), 128 / split_lds_units(halo, cfg.wn));
+        return 12 / (cfg.wn + 2) >= fit ? 2 : 1;
+    }
+    if (pr.xquad) return cfg.wn == 4 ? 2 : 1;
+    if (split_point(pr)) return cfg.wn == 4 || (cfg.wn == 2 && cfg.bk == 32) ? 2 : 1;
+    return 2;
+}
+
 Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg)
 {
     if (halo_positions(pr, cfg) > 0) return Reduction{(pr.d.c + 15) / 16, 9 * 16};
@@ -267,7 +286,7 @@ wpk_conv_config same_launch(const Problem &pr, const wpk_conv_config &cfg, int c
     c.stages = 1;
     wpk_conv_config other = c;
     other.bk = 16;
-    if (halo_positions(pr, other) == halo_positions(pr, c)) c.bk = 16;
+    if (halo_positions(pr, other) == halo_positions(pr, c) && split_producers(pr, other) == split_producers(pr, c)) c.bk = 16;
     if (c.persist > 0 && persistent_of(pr, c, compute_units) == 0) {
         c.persist = 0;
         c.reduce = 0;
@@ -405,11 +424,11 @@ static double split_time(const Problem &pr, const wpk_conv_config &c, int comput
     const wpk_conv_desc &d = pr.d;
     const int halo = halo_positions(pr, c), wn = c.wn;
     const bool patch = halo > 0, point = !patch && split_point(pr), taps = !patch && !point && !pr.xquad;
-    const int producers = !patch && (wn == 4 || taps) ? 2 : 1;
+    const int producers = split_producers(pr, c);
     const Reduction red = reduction_of(pr, c);
     const int per = (red.steps + c.split_k - 1) / c.split_k, slices = (red.steps + per - 1) / per;
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((d.k + c.bn - 1) / c.bn);
-    const int64_t lds = ((patch ? (halo + 1) * 224 : 30720) + 256 * wn + 256 + 1279) / 1280;  // (of 128 units)
+    const int64_t lds = split_lds_units(halo, wn);  // (of 128)
     const double resident = (double)std::min<int64_t>(128 / lds, 12 / (wn + producers));
     const double depths = per * (patch ? 9 : 2);
     const double fetched = patch ? (halo + 63) / 64 * 64 * 16 / 9.0 : 1024.0;  // elements split per depth
@@ -471,7 +490,8 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     if (!split_taps(pr)) return false;
     const double flops = 2.0 * pr.M * pr.d.k * pr.CRS;
     if (flops < 0.45e9 && !(pr.yl && tiled.reduce)) return false;
-    const bool point = split_point(pr);
+    const bool small_point = split_point(pr) && (pr.M + 63) / 64 * ((pr.d.k + 63) / 64) <= 2 * (int64_t)compute_units;
+    const bool point = split_point(pr) && !small_point;
     int wn = 4;
     double best = 1e300;
     for (int w = point ? 2 : 4; w >= 1; w /= 2) {
@@ -484,7 +504,7 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     }
     wpk_conv_config c = {64, 32 * wn, 16, 1, wn, 1, 1, 0, 1, 0};
     const int halo = halo_positions(pr, c);
-    if (halo == 0) c.bk = 32;
+    if (halo == 0 && !point) c.bk = 32;
     const Reduction red = reduction_of(pr, c);
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);
     const int64_t want = point ? 5 * (int64_t)compute_units / 2 : 4 / wn * (int64_t)compute_units;

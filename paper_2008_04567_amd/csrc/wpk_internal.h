@@ -128,7 +128,7 @@ struct IgemmArgs {
     const int32_t *ktab;  // periodic tap table [R*S phases][32 rows][2]: byte offset relative to the
                           // step's channel base (biased); mask bit of r | mask bit of s << 8
     const int32_t *ttab;  // the same for the 32 rows from the start of the last reduction step, exact
-    int32_t N, C, H, W, K, P, Q, R, S;
+    int32_t N, C, H, W, K, Q, R, S;
     int32_t stride_h, stride_w, pad_h, pad_w, dil_h, dil_w;
     int32_t M, PQ, HW, CRS, Kpad;
     int32_t RS, HW4;               // R*S, H*W*4
@@ -173,6 +173,8 @@ struct IgemmArgs {
                         // bias 16-byte aligned, so a pixel's channel quads move as 16-byte accesses
     int32_t halo;       // split members: positions of x the patch of a 3x3 tile holds, 0: each tap fetched by itself, -1: a
                         // 1x1 layer fetched four pixels at a time (split_point)
+    int16_t producers;     // split members: waves of a workgroup that fetch,
+    int16_t two_per_unit;  // and whether no compute unit gets more than two workgroups
 };
 
 // What follows the convolution inside the same launch (Section 2.1, operator fusion).
@@ -265,6 +267,10 @@ WPK_HOST_DEVICE inline uint32_t split_weights_at(bool patch, uint32_t block, int
 {
     return block + (uint32_t)split_depth(patch, step < nsteps ? step : nsteps - 1, 0) * depth_bytes;
 }
+// Waves of a split member's workgroup that fetch and split activations.
+int split_producers(const Problem &pr, const wpk_conv_config &cfg);
+// LDS that such a workgroup takes, in the units of 1280 bytes (128 per compute unit) it is given out in.
+int split_lds_units(int halo, int wn);
 // Where outputs lie in y (and in a residual laid out alike), as the offsets of buffer accesses.  A lane of no output gets
 // kNowhere: past every tensor (they are smaller than 2 GiB), a multiple of four, and still past all of them with any
 // existing channel's offset added.

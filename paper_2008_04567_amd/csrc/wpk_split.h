@@ -217,16 +217,27 @@ constexpr int kStepPitch = 240;    // per pixel of a step: two depths, 48 of pad
                                    // lost to bank conflicts over cycles of LDS instructions 0.10 at 56x56, 0.28 at 28x28,
                                    // 0.39 at 14x14, 0.44 at 7x7 (waves wait for LDS 2 % of their time).
 __host__ __device__ constexpr int step_place(int px) { return px * kStepPitch + (px >> 4) * 16; }
-__host__ __device__ constexpr int split_producers(int wn, SplitForm form)
+// What a wave of a workgroup does: 0 .. WN - 1 multiply, the others fetch.
+// A compute unit deals the waves of a workgroup to its four SIMDs in turn and begins the next workgroup one SIMD further on (read
+// from HW_ID, workgroups of three, four and six waves).  So of two workgroups with two multiplying waves each, the first ones, one
+// SIMD would have two of them and another none, and the loop takes twice as long as it could; the second workgroup of a
+// compute unit has waves 1 and 2 multiply instead.  (3x3, 128 channels, 28x28, 16 images, 392 workgroups: 22.7 us, 29.7 without;
+// 256 channels, 14x14 in two slices 24.8, 32.0; 1x1, 512 to 128 channels at 28x28 16.1, 19.0.)  With three or four workgroups on a
+// compute unit the SIMDs have as much to do either way, and asking costs 0.4 us (64 channels, 56x56: 22.5, 22.9 with): not done there.
+template <int WN, int NP>
+__device__ __forceinline__ int role_of_wave(const int wave, const bool two_per_unit)
 {
-    return form == kPatch || form == kPatchQuads ? 1 : wn == 4 || form == kRows || form == kTaps ? 2 : 1;
+    if (WN != 2 || !two_per_unit) return wave;
+    // (the second workgroup's LDS begins where the first one's ends; LDS_ALLOC: base in bits 0 .. 8, size in bits 12 .. 20)
+    const unsigned alloc = __builtin_amdgcn_s_getreg(6 | 31 << 11);
+    if ((alloc & 0x1ff) != (alloc >> 12 & 0x1ff)) return wave;
+    return wave == 0 ? WN + NP - 1 : wave - 1;
 }
 
-template <int WN, SplitForm FORM>
-__global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) split_kernel(const IgemmArgs a)
+template <int WN, SplitForm FORM, int NP>
+__global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArgs a)
 {
     constexpr bool PATCH = FORM == kPatch || FORM == kPatchQuads, QUAD = FORM == kQuads || FORM == kPatchQuads;
-    constexpr int NP = split_producers(WN, FORM);
     constexpr int BM = 64, BN = 32 * WN, NMT = 2, T = 64 * WN;
     constexpr int NT = PATCH ? 9 : 2;          // MFMA depths (of 16 rows) per step
     extern __shared__ __attribute__((aligned(16))) char lds[];  // two steps of activations
@@ -234,8 +245,8 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     __shared__ int arrival;
 
     touch_kernarg_lines();
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = role_of_wave<WN, NP>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), a.two_per_unit != 0);
+    const int tid = wave * 64 + (threadIdx.x & 63);
     const int buf_bytes = PATCH ? (a.halo + 1) * kHaloPitch : BM * kStepPitch;
     int parity = 0;                            // of the segment
 
@@ -274,7 +285,9 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
             });
         };
         if constexpr (PATCH) {
-            constexpr int NPB = kHaloMax / 64;  // blocks of 64 positions
+            // Blocks of 64 positions, of which each of the NP waves takes every NP-th.
+            constexpr int NPB = kHaloMax / 64 / NP;
+            static_assert(kHaloMax % (64 * NP) == 0, "as many blocks for each");
             int j0, npos;
             {
                 const cold_ptr c = cold_args();
@@ -291,6 +304,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
             // lane / 2 and 32 + lane / 2
             float v[NPB][16];
             int off[NPB][2];
+            auto block = [&](auto PB) WPK_LAMBDA { return decltype(PB)::value * NP + prod; };
             auto fetch = [&](auto PB, const int chunk) WPK_LAMBDA {
                 constexpr int pb = decltype(PB)::value;
                 static_for<2>([&](auto O) WPK_LAMBDA {
@@ -317,7 +331,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
                 constexpr int pb = decltype(PB)::value;
                 static_for<2>([&](auto O) WPK_LAMBDA {
                     constexpr int o = decltype(O)::value;
-                    const int pos = QUAD ? pb * 64 + o * 32 + (lane >> 1) : pb * 64 + lane;
+                    const int pos = QUAD ? block(PB) * 64 + o * 32 + (lane >> 1) : block(PB) * 64 + lane;
                     float e[8];
                     static_for<8>([&](auto J) WPK_LAMBDA { e[decltype(J)::value] = v[pb][o * 8 + decltype(J)::value]; });
                     v4u h, m, l;
@@ -332,7 +346,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
             };
             auto each_block = [&](auto &&f) WPK_LAMBDA {
                 static_for<NPB>([&](auto PB) WPK_LAMBDA {
-                    if (decltype(PB)::value * 64 < npos) f(PB);
+                    if (block(PB) * 64 < npos) f(PB);
                 });
             };
             each_block([&](auto PB) WPK_LAMBDA {
@@ -340,7 +354,7 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
                 static_for<2>([&](auto O) WPK_LAMBDA {  // byte offset of a position in x, or all ones
                     constexpr int o = decltype(O)::value;
                     if constexpr (o == 0 || QUAD) {
-                        const int pos = QUAD ? pb * 64 + o * 32 + (lane >> 1) : pb * 64 + lane, j = j0 + pos;
+                        const int pos = QUAD ? block(PB) * 64 + o * 32 + (lane >> 1) : block(PB) * 64 + lane, j = j0 + pos;
                         const int n = fdiv(j, a.div_tap);
                         const int at = (QUAD ? j * a.C * 4 + (lane & 1) * 32 : (n * a.C * a.HW + j - n * a.HW) * 4) +
                                        (int)a.x_bias;
@@ -364,36 +378,45 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
                 __syncthreads();
             }
         } else if constexpr (FORM == kPoint) {
-            // A lane holds four pixels of an octet: pixels 4 (lane % 16) .., octet lane / 16.  The NP waves take turns, a
-            // whole step each: one that stores step r + 1 while step r is multiplied has NP steps' time for it.
-            constexpr int DEPTH = 3;  // of this wave's steps: 24 KB in flight
-            const int m = m0 + 4 * (lane & 15);
+            // A lane holds PX pixels of an octet.  One wave fetches and splits whole steps (four pixels a lane), two half of each step,
+            // an MFMA depth each.
+            constexpr int PX = 4 / NP, LANES = 64 / PX;  // (lanes per octet)
+            constexpr int DEPTH = 3 * NP;                // steps in flight: 24 KB per wave
+            const int px0 = lane % LANES * PX, oct = prod * (4 / NP) + lane / LANES;
+            const int m = m0 + px0;
             int voff;
             {
                 const cold_ptr c = cold_args();
                 const int n = fdiv(m, WPK_COLD_DIV(c, div_pq));
-                voff = m < c->M ? (n * c->C * c->HW + m - n * c->HW + (lane >> 4) * 8 * c->HW) * 4 : -1;
+                voff = m < c->M ? (n * c->C * c->HW + m - n * c->HW + oct * 8 * c->HW) * 4 : -1;
             }
-            const int place = step_place((lane & 15) * 4) + (lane >> 5) * 96 + (lane >> 4 & 1) * 16;
-            float v[DEPTH][32];  // channel of the octet, pixel
-            int step = kbeg + prod;
+            const int place = step_place(px0) + (oct >> 1) * 96 + (oct & 1) * 16;
+            float v[DEPTH][8 * PX];  // channel of the octet, pixel
+            int step = kbeg;
             auto fetch = [&](auto SLOT) WPK_LAMBDA {
                 constexpr int sl = decltype(SLOT)::value;
                 const int at = voff | (step < kend ? 0 : -1), first = step * 32 * a.HW4;
                 static_for<8>([&](auto J) WPK_LAMBDA {
                     constexpr int j = decltype(J)::value;
-                    const v4f q = __builtin_bit_cast(
-                        v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, at, first + j * a.HW4, 0));
-                    static_for<4>([&](auto E) WPK_LAMBDA { v[sl][j * 4 + decltype(E)::value] = q[decltype(E)::value]; });
+                    if constexpr (PX == 4) {
+                        const v4f q = __builtin_bit_cast(
+                            v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, at, first + j * a.HW4, 0));
+                        static_for<4>([&](auto E) WPK_LAMBDA { v[sl][j * 4 + decltype(E)::value] = q[decltype(E)::value]; });
+                    } else {
+                        const v2f q = __builtin_bit_cast(
+                            v2f, __builtin_amdgcn_raw_buffer_load_b64(xrsrc, at, first + j * a.HW4, 0));
+                        v[sl][j * 2] = q[0];
+                        v[sl][j * 2 + 1] = q[1];
+                    }
                 });
-                step += NP;
+                step += 1;
             };
             auto put = [&](auto SLOT, const int buf) WPK_LAMBDA {
                 constexpr int sl = decltype(SLOT)::value;
-                static_for<4>([&](auto PX) WPK_LAMBDA {
-                    constexpr int px = decltype(PX)::value;
+                static_for<PX>([&](auto P) WPK_LAMBDA {
+                    constexpr int px = decltype(P)::value;
                     float e[8];
-                    static_for<8>([&](auto J) WPK_LAMBDA { e[decltype(J)::value] = v[sl][decltype(J)::value * 4 + px]; });
+                    static_for<8>([&](auto J) WPK_LAMBDA { e[decltype(J)::value] = v[sl][decltype(J)::value * PX + px]; });
                     v4u h, m, l;
                     split_octet(e, h, m, l);
                     char *const p = lds + place + buf * buf_bytes + px * kStepPitch;
@@ -409,29 +432,18 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
             store_bias();
             // nr + 1 meetings in all: number r has step r in place and the buffer of step r - 1 free.  Step r is stored
             // between meetings r - 1 and r.
-            int left = nr + 1, turn = 0;  // (of the two buffers, where one wave fills both)
-            static_for<NP>([&](auto P) WPK_LAMBDA {
-                if (decltype(P)::value < prod) {
-                    __syncthreads();
-                    --left;
-                }
-            });
+            int left = nr + 1, turn = 0;  // (of the two buffers)
             auto one = [&](auto P) WPK_LAMBDA {
                 constexpr int p = decltype(P)::value;
                 using SLOT = std::integral_constant<int, p % DEPTH>;
                 if (left <= 0) return false;
-                put(SLOT{}, NP == 2 ? prod : turn);
+                put(SLOT{}, turn);
                 turn ^= 1;
                 __builtin_amdgcn_sched_barrier(0);
                 fetch(SLOT{});
                 __builtin_amdgcn_sched_barrier(0);
                 __syncthreads();
                 --left;
-                if constexpr (NP == 2) {
-                    if (left <= 0) return false;
-                    __syncthreads();
-                    --left;
-                }
                 __builtin_amdgcn_sched_barrier(0);
                 return true;
             };
@@ -738,11 +750,11 @@ __global__ void __launch_bounds__(64 * (WN + split_producers(WN, FORM)), 3) spli
     for_each_segment(a, run_segment);
 }
 
-template <int WN, SplitForm FORM>
+template <int WN, SplitForm FORM, int NP>
 hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 {
     const size_t lds = 2 * (size_t)(FORM >= kPatch ? (a.halo + 1) * kHaloPitch : 64 * kStepPitch);
-    return launch_kernel<split_kernel<WN, FORM>, 64 * (WN + split_producers(WN, FORM)), 2 * (kHaloMax + 1) * kHaloPitch>(
+    return launch_kernel<split_kernel<WN, FORM, NP>, 64 * (WN + NP), 2 * (kHaloMax + 1) * kHaloPitch>(
         a, stream, lds, 2 * 32 * WN * sizeof(float) + sizeof(int));  // (bias, arrival)
 }
 
@@ -750,12 +762,20 @@ hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 template <int WN>
 hipError_t launch_split(const IgemmArgs &a, hipStream_t stream)
 {
-    if (a.halo > 0)
-        return a.xl == 2 ? launch_split_form<WN, kPatchQuads>(a, stream) : launch_split_form<WN, kPatch>(a, stream);
-    if (a.xl == 2) return launch_split_form<WN, kQuads>(a, stream);
-    if (a.halo < 0) return launch_split_form<WN, kPoint>(a, stream);
-    if (a.xl == 3) return launch_split_form<WN, kTaps>(a, stream);
-    return launch_split_form<WN, kRows>(a, stream);
+    if (a.halo > 0) {
+        if (a.producers == 2)
+            return a.xl == 2 ? launch_split_form<WN, kPatchQuads, 2>(a, stream) : launch_split_form<WN, kPatch, 2>(a, stream);
+        if constexpr (WN < 4)
+            return a.xl == 2 ? launch_split_form<WN, kPatchQuads, 1>(a, stream) : launch_split_form<WN, kPatch, 1>(a, stream);
+    }
+    if (a.xl == 2) return launch_split_form<WN, kQuads, WN == 4 ? 2 : 1>(a, stream);
+    if (a.halo < 0) {
+        if constexpr (WN >= 2)
+            if (a.producers == 2) return launch_split_form<WN, kPoint, 2>(a, stream);
+        if constexpr (WN < 4) return launch_split_form<WN, kPoint, 1>(a, stream);
+    }
+    if (a.xl == 3) return launch_split_form<WN, kTaps, 2>(a, stream);
+    return launch_split_form<WN, kRows, 2>(a, stream);
 }
 
 }  // namespace wpk
