@@ -3,7 +3,7 @@
 ``python -m paper_2008_04567_amd.build`` (add ``--changed`` to compile only what is stale) or
 ``build_library()``.  Translation units are compiled
 in parallel: the host part, the API/dispatch part, eight instantiation parts of the tiled
-kernel family and three of its split members.  Works without a GPU (hipcc cross-compiles).
+kernel family, three of its split members and one of their strip form.  Works without a GPU (hipcc cross-compiles).
 """
 import concurrent.futures
 import os
@@ -84,6 +84,8 @@ def build_library(force=True, verbose=False):
         add([hipcc] + COMMON + DEVICE + ["-DWPK_PART=%d" % wn, "-c", src("wpk_split_inst.hip"),
                                          "-o", os.path.join(OBJ, "wpk_split_%d.o" % wn)],
             headers + [src("wpk_igemm.h"), src("wpk_split.h"), src("wpk_split_inst.hip")])
+    add([hipcc] + COMMON + DEVICE + ["-c", src("wpk_strip_inst.hip"), "-o", os.path.join(OBJ, "wpk_strip.o")],
+        headers + [src("wpk_igemm.h"), src("wpk_split.h"), src("wpk_strip.h"), src("wpk_strip_inst.hip")])
     if jobs:
         workers = min(len(jobs), max(1, (os.cpu_count() or 4)), 16)
         with concurrent.futures.ThreadPoolExecutor(workers) as ex:

@@ -65,10 +65,15 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restri
 }
 
 // Where row kk of the split members' reduction comes from: its place among the C*R*S rows of the source, or
-// -1 for a padding row.  With RS > 0 the rows run (c / 32, r, s, c % 32), else in the source's order.
+// -1 for a padding row.  With RS > 0 the rows run (c / 32, r, s, c % 32), with RS = -S (c, r, s) with s padded to eight, else in
+// the source's order.
 __device__ inline int split_source_row(int kk, int C, int CRS, int RS)
 {
-    if (RS <= 0) return kk < CRS ? kk : -1;
+    if (RS < 0) {
+        const int row = (kk >> 3) * -RS + (kk & 7);
+        return (kk & 7) < -RS && row < CRS ? row : -1;
+    }
+    if (RS == 0) return kk < CRS ? kk : -1;
     const int c32 = kk / (32 * RS), t = kk - c32 * 32 * RS, c = c32 * 32 + (t & 31);
     // (sixteen rows at a time: the two halves of the 32 channels follow each other for every tap)
     return c < C ? c * RS + (t >> 5) : -1;
@@ -147,7 +152,7 @@ __global__ void __launch_bounds__(256) unpack_weights_kernel(const void *__restr
         const int k = (int)(i / CRS), row = (int)(i - (long long)k * CRS);
         const int c = RS > 0 ? row / RS : 0, rs = RS > 0 ? row - c * RS : 0;
         if (split) {
-            const int kk = RS > 0 ? (c / 32 * RS + rs) * 32 + c % 32 : row;
+            const int kk = RS > 0 ? (c / 32 * RS + rs) * 32 + c % 32 : RS < 0 ? row / -RS * 8 + row % -RS : row;
             const int lane = (kk >> 3 & 1) * 32 + (k & 31);
             const unsigned short *p = (const unsigned short *)packed +
                                       (((size_t)(kk >> 4) * (Kpad / 32) + k / 32) * 3 * 64 + lane) * 8 + (kk & 7);
@@ -475,15 +480,22 @@ static size_t packed_bytes(const Problem &pr, bool split)
     return split ? (size_t)split_rows(pr) * pr.Kpad * kSplitWeightBytes : (size_t)pr.CRSpad * pr.Kpad * sizeof(float);
 }
 
+// The order of the packed rows, as split_source_row and pack_weights_kernel have it.
+static int packed_order(const Problem &pr, bool split)
+{
+    if (split && strip_depths(pr)) return -pr.d.s;
+    return (split ? split_taps(pr) : pr.xquad || pr.tapmajor) ? pr.d.r * pr.d.s : 0;
+}
+
 static int pack_weights(const Problem &pr, bool split, const float *w, float *wp, hipStream_t st)
 {
-    const int RS = (split ? split_taps(pr) : pr.xquad || pr.tapmajor) ? pr.d.r * pr.d.s : 0;
+    const int RS = packed_order(pr, split);
     if (split) {
         const int blocks = pr.Kpad / 32, taps = RS > 0 ? RS : 1;
         const int all_octets = (int)(split_rows(pr) / taps / 8), octets = std::max(1, 8 / taps);
         const int chunks = (all_octets + octets - 1) / octets;
         // a block per compute unit, or a single tap (see there); at most 64 KB of LDS
-        if ((taps == 1 || (int64_t)chunks * blocks >= 256) && taps < 64) {
+        if (RS >= 0 && (taps == 1 || (int64_t)chunks * blocks >= 256) && taps < 64) {
             hipLaunchKernelGGL(pack_split_staged_kernel, dim3(chunks, blocks), dim3(256),
                                32 * (octets * 8 * taps + 1) * sizeof(float), st, w, (v4u *)wp, pr.d.k,
                                RS > 0 ? pr.d.c : pr.CRS, taps, blocks, octets, all_octets);
@@ -607,7 +619,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.dil_h = d.dil_h; a.dil_w = d.dil_w;
     a.M = (int32_t)pr.M; a.PQ = pr.P * pr.Q; a.HW = d.h * d.w; a.CRS = pr.CRS; a.Kpad = pr.Kpad;
     a.nsteps = red.steps;
-    a.halo = split_member(cfg) && split_point(pr) ? -1 : halo_positions(pr, cfg);
+    a.halo = !split_member(cfg) ? 0 : strip_depths(pr) ? -2 : split_point(pr) ? -1 : halo_positions(pr, cfg);
     a.producers = (int16_t)split_producers(pr, cfg);
     // slices of ceil(nsteps/split_k) steps; launch only as many as are not empty
     a.steps_per_split = (a.nsteps + cfg.split_k - 1) / cfg.split_k;
@@ -995,7 +1007,7 @@ static int plan_need_weights(wpk_plan::Layer &L, const wpk_conv_config &cfg)
         L.wp[s] = packed;
         return WPK_OK;
     }
-    const int RS = (s ? L.pr.xquad || L.pr.tapmajor : split_taps(L.pr)) ? L.pr.d.r * L.pr.d.s : 0;  // (of the form at hand)
+    const int RS = packed_order(L.pr, s == 0);  // (of the form at hand)
     int rc = WPK_OK;
     hipError_t e = hipDeviceSynchronize();
     if (e == hipSuccess) e = hipMalloc((void **)&plain, (size_t)L.pr.w_elems * sizeof(float));

@@ -241,6 +241,45 @@ int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
     return patch_bound(pr);
 }
 
+// A strip's rows: as few as keep all compute units busy with as little filling as possible.  The cost of a choice, in cycles, from
+// what the kernel was measured to take: a workgroup's start and end, a row of x (per 64 columns / 2), a block of 32 pixels by 32
+// channels; two workgroups share a compute unit and its matrix pipes.
+StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stride_h, int stride_w, int dil_h, int dil_w)
+{
+    StripShape best = {0, 0, 0, 0, 0, 0, 0.0};
+    const int64_t octets = (int64_t)C * R, columns = (int64_t)(Q - 1) * stride_w + 8 + (stride_w % 2 ? 2 : 0);
+    if (octets > 22 || S < 2 || S > 8 || dil_w != 1 || columns > 240) return best;
+    const int depths = octets <= 6 ? 3 : octets <= 10 ? 5 : octets <= 16 ? 8 : 11, pairs = columns <= 128 ? 64 : 120;
+    const int waves_c = K > 64 ? 4 : K > 32 ? 2 : 1, groups = (K + 32 * waves_c - 1) / (32 * waves_c);
+    double least = 1e300;
+    for (int rows = 1; rows <= P && rows <= 64; ++rows) {
+        const int64_t lines = C * ((int64_t)(rows - 1) * stride_h + (int64_t)(R - 1) * dil_h + 1), lds = lines * pairs * 12;
+        if (lds > 78 * 1024) break;
+        const int64_t strips = (int64_t)N * ((P + rows - 1) / rows), blocks = ((int64_t)rows * Q + 31) / 32;
+        const int64_t wave_blocks = (blocks + 4 / waves_c - 1) / (4 / waves_c);
+        for (int per = groups; per >= 1; per = per == 1 ? 0 : (per + 1) / 2) {
+            const int64_t work = strips * ((groups + per - 1) / per);
+            if (work > 0x7fffffff) continue;
+            const double fill = 8000.0 + lines * ((pairs + 63) / 64) * 60.0;
+            const double multiply = per * (1500.0 + wave_blocks * (depths * 225.0 + 1900.0));
+            const double units = 256.0;
+            const double cost = ceil(work / (2 * units)) * fill + std::max(0.62 * ceil(work / units), 1.0) * multiply;
+            if (cost < least) {
+                least = cost;
+                best = StripShape{depths, pairs, rows, (int32_t)lds, waves_c, per, 3.5 + cost / 2000.0};
+            }
+        }
+    }
+    return best;
+}
+
+int strip_depths(const Problem &pr)
+{
+    const wpk_conv_desc &d = pr.d;
+    if (pr.tapmajor || pr.xquad || !pr.tiled_ok || (int64_t)d.c * d.r > 22) return 0;
+    return strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w).depths;
+}
+
 int split_lds_units(int halo, int wn)
 {
     return ((halo > 0 ? (halo + 1) * 224 : 30720) + 256 * wn + 4 + 1279) / 1280;
@@ -263,6 +302,8 @@ int split_producers(const Problem &pr, const wpk_conv_config &cfg)
 Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg)
 {
     if (halo_positions(pr, cfg) > 0) return Reduction{(pr.d.c + 15) / 16, 9 * 16};
+    if (split_member(cfg))
+        if (const int depths = strip_depths(pr)) return Reduction{1, depths * 16};  // (strips have the whole of it)
     const int rows = split_member(cfg) ? 32 : cfg.bk;
     if (split_member(cfg) && split_taps(pr)) return Reduction{(int32_t)(split_rows(pr) / 32), 32};
     return Reduction{(pr.CRS + rows - 1) / rows, rows};
@@ -274,6 +315,7 @@ Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg)
 int persistent_of(const Problem &pr, const wpk_conv_config &cfg, int compute_units)
 {
     if (cfg.persist == 0 || !split_member(cfg)) return cfg.persist;
+    if (strip_depths(pr)) return 0;
     const int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
     const int64_t G = (int64_t)cfg.persist * (compute_units > 0 ? compute_units : 256);
     return tiles <= G && 2 * tiles > G ? 0 : cfg.persist;
@@ -284,6 +326,7 @@ wpk_conv_config same_launch(const Problem &pr, const wpk_conv_config &cfg, int c
     wpk_conv_config c = cfg;
     if (!split_member(cfg)) return c;
     c.stages = 1;
+    if (strip_depths(pr)) return wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
     wpk_conv_config other = c;
     other.bk = 16;
     if (halo_positions(pr, other) == halo_positions(pr, c) && split_producers(pr, other) == split_producers(pr, c)) c.bk = 16;
@@ -487,8 +530,15 @@ static double tiled_time(const Problem &pr, const wpk_conv_config &c, int comput
 // are 1.22 (1.27) times as fast as the tiled default alone, 1.14 (1.21) before.
 static bool split_default(const Problem &pr, int compute_units, const wpk_conv_config &tiled, wpk_conv_config *out)
 {
-    if (!split_taps(pr)) return false;
     const double flops = 2.0 * pr.M * pr.d.k * pr.CRS;
+    if (strip_depths(pr)) {
+        const wpk_conv_desc &d = pr.d;
+        *out = wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
+        const double us = strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w).us;
+        // (not where y leaves a lane four bytes at a time: 2 to 130 channels, channels-last, 403 us against 273)
+        return flops >= 0.45e9 && !(pr.yl && d.k % 4) && 1.1 * us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);
+    }
+    if (!split_taps(pr)) return false;
     if (flops < 0.45e9 && !(pr.yl && tiled.reduce)) return false;
     const bool small_point = split_point(pr) && (pr.M + 63) / 64 * ((pr.d.k + 63) / 64) <= 2 * (int64_t)compute_units;
     const bool point = split_point(pr) && !small_point;

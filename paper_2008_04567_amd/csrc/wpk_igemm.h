@@ -187,7 +187,7 @@ __device__ __forceinline__ void pixel_window(const ARGS c, const int m, int &vof
 
 // ---- what leaves a wave: its NNT x NMT accumulator blocks, whose first pixel is mbase and first
 //      channel nbase, go to y -- plain stores with the fused epilogue applied, or fp32 atomics.  bias: of channels
-//      nbase .. in LDS, zeros where there is none (not read by launches that add nothing).
+//      nbase .. in LDS, zeros where there is none (not read by launches that add nothing); mend: pixels from it on are not stored.
 //
 //      Memory operations return in order, so whoever waits for a load waits for every store issued before it, and a
 //      store that is written through is acknowledged a microsecond after it was issued.  So the bias comes from LDS, the residual
@@ -202,7 +202,7 @@ __device__ __forceinline__ void pixel_window(const ARGS c, const int m, int &vof
 template <int NNT, int NMT, int SETS, class ARGS>
 __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)[NNT * NMT], const int mbase,
                                                 const int nbase, const int lrow, const int lcol, const bool atomic,
-                                                const float *const bias)
+                                                const float *const bias, const int mend = 0x7fffffff)
 {
     // ---- epilogue: D[row = channel][col = pixel]; register e of lane l holds row
     //      8*(e/4) + 4*(l/32) + e%4 and column l%32 of its 32x32 block.  Buffer addressing: one
@@ -221,7 +221,7 @@ __device__ __forceinline__ void store_wave_tile(const ARGS ce, const v16f (&acc)
         constexpr int j = decltype(J)::value;
         const int m = mbase + j * 32 + lcol;
         const int n = fdiv(m, WPK_COLD_DIV(ce, div_pq)), pq = m - n * ce->PQ;
-        place[j] = output_place(m, ce->M, n, pq, kfirst, ce->K, ce->PQ, ce->yl != 0);
+        place[j] = output_place(m, min(ce->M, mend), n, pq, kfirst, ce->K, ce->PQ, ce->yl != 0);
     });
     // ADD: 0 the sums as they are, 1 the bias added and the rectifier, 2 the residual as well; FULL: every channel exists (the usual case), no check per register; QUADS:
     // channels-last y, K a multiple of four and everything 16-byte aligned: the registers 4 g .. 4 g + 3 of a lane are

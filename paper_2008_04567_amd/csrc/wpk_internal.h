@@ -172,7 +172,7 @@ struct IgemmArgs {
     int32_t yl;         // 1: y (and the residual) are channels-last; 2: also K % 4 == 0 and y, residual and
                         // bias 16-byte aligned, so a pixel's channel quads move as 16-byte accesses
     int32_t halo;       // split members: positions of x the patch of a 3x3 tile holds, 0: each tap fetched by itself, -1: a
-                        // 1x1 layer fetched four pixels at a time (split_point)
+                        // 1x1 layer fetched four pixels at a time (split_point), -2: strips (strip_shape)
     int16_t producers;     // split members: waves of a workgroup that fetch,
     int16_t two_per_unit;  // and whether no compute unit gets more than two workgroups
 };
@@ -232,9 +232,12 @@ WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int str
 // zero, and the activations fetched for it are those of the last channel: what is finite adds nothing, and what is not
 // has the tile computed again (wpk_split.h).
 bool split_taps(const Problem &pr);
+// MFMA depths of pr on the strip form of the split members, 0 where they run it otherwise.
+int strip_depths(const Problem &pr);
 // Rows of the reduction as the split members pack it.
 inline int64_t split_rows(const Problem &pr)
 {
+    if (const int depths = strip_depths(pr)) return depths * 16;
     return split_taps(pr) ? (int64_t)((pr.d.c + 31) / 32 * 32) * pr.d.r * pr.d.s : pr.CRSpad;
 }
 // Whether a split member fetches pr's x four neighbouring pixels at a time: 1x1 filters on [N][C][H][W], C a multiple of
@@ -267,6 +270,17 @@ WPK_HOST_DEVICE inline uint32_t split_weights_at(bool patch, uint32_t block, int
 {
     return block + (uint32_t)split_depth(patch, step < nsteps ? step : nsteps - 1, 0) * depth_bytes;
 }
+// Layers of few channels on the split members (wpk_strip.h): strips of whole output rows, the rows of x under them in LDS.
+struct StripShape {
+    int32_t depths;     // MFMA depths of two filter rows each; 0: not so
+    int32_t pairs;      // columns / 2 that a row of the strip has room for
+    int32_t rows;       // output rows of a strip
+    int32_t lds;        // bytes
+    int32_t waves_c;    // waves side by side along the channels
+    int32_t per_group;  // groups of 32 * waves_c channels that a workgroup does
+    double us;          // what a launch is estimated to take
+};
+StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stride_h, int stride_w, int dil_h, int dil_w);
 // Waves of a split member's workgroup that fetch and split activations.
 int split_producers(const Problem &pr, const wpk_conv_config &cfg);
 // LDS that such a workgroup takes, in the units of 1280 bytes (128 per compute unit) it is given out in.

@@ -124,13 +124,13 @@ __device__ __forceinline__ bool join_sums(v16f (&acc)[NB], const v16f (&sml)[NB]
 //           tap of its pixels from the start; a tap outside the image has the address of a row of zeros.
 // Rows of the reduction are ordered (c / 32, r, s, c % 32) but for kRows, so that the taps of 32 channels follow each
 // other and find their pixels in the L1; a step is 32 rows, for patches the nine taps of sixteen channels.
-enum SplitForm { kRows, kQuads, kTaps, kPoint, kPatch, kPatchQuads };
+enum SplitForm { kStrip, kRows, kQuads, kTaps, kPoint, kPatch, kPatchQuads };  // (kStrip: wpk_strip.h)
 // The wave's blocks again, in fp32, over the MFMA depths depth(0 .. count - 1), with the operands where a lane's eight rows of a
 // depth are: MFMA number q of eight contracts rows q and 8 + q.  Bound by the 16 MFMAs of 64 cycles and some 240 other instructions
 // of a depth, without branches (masks instead of selects) and with the next two depths' operands on their way.  A launch with
 // one infinity in x takes 86 us on the 256-channel 3x3 layer at 14x14 (N = 16; 24 without one) and 51 on the 64-channel
 // one at 56x56 (24); with branches and one depth after the other 232 and 125.  The tiled members take 40 and 42 on any data.
-template <SplitForm FORM, int NMT, class D>
+template <SplitForm FORM, int NMT, int DEPTH = 2, class D>
 __device__ __forceinline__ void fp32_tile(v16f (&acc)[NMT], const __amdgpu_buffer_rsrc_t xrsrc,
                                           const __amdgpu_buffer_rsrc_t wrsrc, const int m0, const unsigned wbase,
                                           const int count, D &&depth, const int lane)
@@ -147,8 +147,7 @@ __device__ __forceinline__ void fp32_tile(v16f (&acc)[NMT], const __amdgpu_buffe
         pixel_window(c, m0 + j * 32 + lcol, voff[j], inv[j]);
         static_for<16>([&](auto E) WPK_LAMBDA { acc[j][decltype(E)::value] = 0.0f; });
     });
-    constexpr int DEPTH = 2;
-    float xv[DEPTH][NMT][8];
+    float xv[DEPTH][NMT][8];  // (DEPTH: depths in flight)
     v4u wv[DEPTH][3];
     auto fetch = [&](auto SET, const int it) WPK_LAMBDA {
         constexpr int set = decltype(SET)::value;
@@ -165,6 +164,12 @@ __device__ __forceinline__ void fp32_tile(v16f (&acc)[NMT], const __amdgpu_buffe
                 ch = fdiv(kk, WPK_COLD_DIV(c, div_tap));
                 rs = kk - ch * c->RS;
                 past = (c->CRS - 1 - kk) >> 31;
+            } else if constexpr (FORM == kStrip) {  // (c, r, s), s padded to eight
+                const int o = t * 2 + lrow;
+                past = (c->C * c->R - 1 - o) >> 31 | (c->S - 1 - q) >> 31;
+                ch = o / c->R;
+                rs = ((o - ch * c->R) * c->S + q) & ~past;
+                ch &= ~past;
             } else {                        // (c / 32, r, s, c % 32)
                 const int c32 = PATCH ? t / 18 : fdiv(t >> 1, WPK_COLD_DIV(c, div_tap));
                 rs = (t >> 1) - c32 * c->RS;
@@ -195,7 +200,7 @@ __device__ __forceinline__ void fp32_tile(v16f (&acc)[NMT], const __amdgpu_buffe
         });
     };
     static_for<DEPTH>([&](auto S) WPK_LAMBDA { fetch(S, decltype(S)::value); });
-    constexpr int LAPS = 4;
+    constexpr int LAPS = DEPTH == 1 ? 1 : 4;
     int it = 0;
     auto one = [&](auto P) WPK_LAMBDA {
         constexpr int p = decltype(P)::value;
@@ -264,7 +269,7 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
     // offsets of all ones: nothing is fetched, zeros are stored and nobody reads them.
     auto fetch_segment = [&](const int m0, const int n0, const int kbeg, const int kend, const int lane) WPK_LAMBDA {
         const int nr = kend - kbeg;
-        const int prod = wave - WN;
+        const int prod = NP == 1 ? 0 : wave - WN;
         // the channels' bias: asked for now, stored once the first fetches are on their way
         constexpr int BI = (BN + NP * 64 - 1) / (NP * 64);
         float bval[BI];
@@ -750,6 +755,9 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
     for_each_segment(a, run_segment);
 }
 
+// (wpk_strip.h)
+hipError_t launch_strip(const IgemmArgs &a, hipStream_t stream);
+
 template <int WN, SplitForm FORM, int NP>
 hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 {
@@ -762,6 +770,7 @@ hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 template <int WN>
 hipError_t launch_split(const IgemmArgs &a, hipStream_t stream)
 {
+    if (a.halo == -2) return launch_strip(a, stream);
     if (a.halo > 0) {
         if (a.producers == 2)
             return a.xl == 2 ? launch_split_form<WN, kPatchQuads, 2>(a, stream) : launch_split_form<WN, kPatch, 2>(a, stream);

@@ -1,0 +1,62 @@
+"""Strips of the split members (CPU): what strip_shape chooses against every access of the kernel -- the columns and rows of a
+pixel's octets inside the strip's LDS, every output row in one strip, the weights' rows inside the packed ones."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "wpk_internal.h"
+using namespace wpk;
+int main()
+{
+    srand(11);
+    long taken = 0, refused = 0, edge = 0;
+    auto pick = [](int lo, int hi) { return lo + rand() % (hi - lo + 1); };
+    for (int it = 0; it < 20000; ++it) {
+        wpk_conv_desc d = {pick(1, 9), pick(1, 7), pick(1, 70), pick(1, 260), pick(1, 300), pick(1, 11), pick(1, 10), pick(1, 3), pick(1, 3),
+                           pick(0, 3), pick(0, 3), pick(1, 2), rand() % 4 ? 1 : 2, WPK_F32, pick(0, 3)};
+        Problem pr;
+        if (make_problem(&d, &pr) != WPK_OK) continue;
+        const int depths = strip_depths(pr);
+        if (depths == 0) { ++refused; continue; }
+        ++taken;
+        const StripShape s = strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w);
+        const int in_rows = (s.rows - 1) * d.stride_h + (d.r - 1) * d.dil_h + 1, line = 3 * s.pairs * 4;
+        const int per_image = (pr.P + s.rows - 1) / s.rows, groups = (d.k + 32 * s.waves_c - 1) / (32 * s.waves_c);
+        bool bad = s.depths != depths || 2 * depths < d.c * d.r || d.s > 8 || s.rows < 1 || s.lds > 78 * 1024 ||
+                   s.lds < d.c * in_rows * line || per_image * s.rows < pr.P || (per_image - 1) * s.rows >= pr.P ||
+                   s.per_group < 1 || s.per_group > groups || split_rows(pr) != depths * 16 ||
+                   groups * 32 * s.waves_c > pr.Kpad;
+        // the last byte that the octet of any pixel, filter row and channel reaches
+        const int q = (pr.Q - 1) * d.stride_w, words = d.stride_w % 2 ? 5 : 4;
+        bad = bad || (q >> 1) + words > s.pairs;
+        const int row = (d.c - 1) * in_rows + (s.rows - 1) * d.stride_h + (d.r - 1) * d.dil_h;
+        bad = bad || (row + 1) * line > s.lds;
+        edge += (q >> 1) + words == s.pairs;
+        // every column that a tap of the last pixel reads is one that the lanes fetch
+        bad = bad || q + d.s > 2 * s.pairs;
+        const wpk_conv_config c = {64, 64, 16, 1, 2, 1, 1, 0, 1, 0}, e = {64, 128, 32, 1, 4, 1, 1, 2, 1, 0};
+        bad = bad || persistent_of(pr, e, 256) != 0 || fixup_need(pr, c, 256).bytes != 0 || reduction_of(pr, c).steps != 1;
+        if (bad) {
+            printf("n %d c %d h %d w %d k %d r %d s %d stride %d %d: rows %d pairs %d lds %d\n", d.n, d.c, d.h, d.w, d.k, d.r, d.s,
+                   d.stride_h, d.stride_w, s.rows, s.pairs, s.lds);
+            return 1;
+        }
+    }
+    printf("%ld %ld %ld\n", taken, refused, edge);
+    return taken > 2000 && refused > 2000 && edge > 10 ? 0 : 2;
+}
+"""
+
+
+def test_strips_hold_what_is_read(tmp_path):
+    src, exe = tmp_path / "strip.cpp", tmp_path / "strip"
+    src.write_text(PROGRAM)
+    csrc = os.path.join(ROOT, "paper_2008_04567_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I" + csrc, "-I" + os.path.join(ROOT, "include"), str(src),
+                    os.path.join(csrc, "wpk_host.cpp"), "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
+    assert res.returncode == 0, res.stdout
