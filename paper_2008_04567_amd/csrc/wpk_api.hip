@@ -629,7 +629,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.remap = cfg.xcd_remap;
     a.x_bytes = (uint32_t)(pr.x_elems * 4);
     a.x_bias = (uint32_t)((d.pad_h * d.w + d.pad_w) * 4 * (pr.xl ? d.c : 1));
-    a.xl = pr.xquad ? 2 : pr.tapmajor || (split_member(cfg) && split_taps(pr)) ? 3 : pr.xl ? 1 : 0;
+    a.xl = pr.xquad ? 2 : pr.tapmajor ? 3 : split_member(cfg) && split_taps(pr) ? (pr.xl ? 2 : 3) : pr.xl ? 1 : 0;
     a.yl = pr.yl ? 1 : 0;
     // whole channel quads with 16-byte stores when the tensors allow it
     if (pr.yl && d.k % 4 == 0 && ((uintptr_t)y & 15) == 0 && ((uintptr_t)epi.res & 15) == 0 &&

@@ -230,9 +230,12 @@ static int patch_bound(const Problem &pr)
 bool split_taps(const Problem &pr)
 {
     if (pr.tapmajor || pr.xquad) return true;
-    const int64_t c16 = (pr.d.c + 15) / 16 * 16, c32 = (pr.d.c + 31) / 32 * 32;
-    return !pr.xl && 2 * c16 <= 3 * (int64_t)pr.d.c && patch_bound(pr) > 0 &&
-           c32 * 9 * pr.Kpad * kSplitWeightBytes <= kMaxSplitBytes;
+    const int64_t C = pr.d.c, c16 = (C + 15) / 16 * 16, c32 = (C + 31) / 32 * 32;
+    if (c32 * pr.d.r * pr.d.s * pr.Kpad * kSplitWeightBytes > kMaxSplitBytes) return false;
+    const bool patch = patch_bound(pr) > 0;
+    if (2 * (patch ? c16 : c32) > 3 * C) return false;
+    // (offsets of the channels that fill the last group up)
+    return (patch && !pr.xl) || (pr.d.n * c32 + 32) * pr.d.h * pr.d.w * 4 <= kMaxTiledBytes;
 }
 
 int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
@@ -294,7 +297,7 @@ int split_producers(const Problem &pr, const wpk_conv_config &cfg)
         const int fit = std::min(12 / (cfg.wn + 1), 128 / split_lds_units(halo, cfg.wn));
         return 12 / (cfg.wn + 2) >= fit ? 2 : 1;
     }
-    if (pr.xquad) return cfg.wn == 4 ? 2 : 1;
+    if (pr.xl && split_taps(pr)) return cfg.wn == 4 ? 2 : 1;
     if (split_point(pr)) return cfg.wn == 4 || (cfg.wn == 2 && cfg.bk == 32) ? 2 : 1;
     return 2;
 }
@@ -466,7 +469,7 @@ static double split_time(const Problem &pr, const wpk_conv_config &c, int comput
 {
     const wpk_conv_desc &d = pr.d;
     const int halo = halo_positions(pr, c), wn = c.wn;
-    const bool patch = halo > 0, point = !patch && split_point(pr), taps = !patch && !point && !pr.xquad;
+    const bool patch = halo > 0, point = !patch && split_point(pr), taps = !patch && !point && !pr.xl;
     const int producers = split_producers(pr, c);
     const Reduction red = reduction_of(pr, c);
     const int per = (red.steps + c.split_k - 1) / c.split_k, slices = (red.steps + per - 1) / per;

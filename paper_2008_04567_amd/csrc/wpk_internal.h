@@ -225,12 +225,10 @@ WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int str
     const int r = p * stride_h - pad_h + 2 * dil_h, c = q * stride_w - pad_w + 2 * dil_w;
     return (n * H + (r < H - 1 ? r : H - 1)) * W + (r - stride_h < H - 1 && c < W - 1 ? c : W - 1);
 }
-// Whether the split members order pr's reduction by filter taps, (c / 32, r, s, c % 32): where the tiled members do, and for
-// 3x3 filters on [N][C][H][W] that can work from patches if padding C to whole groups of 16 lengthens the reduction by
-// half at most (72 to 144 channels, 28x28, 16 images: 27.4 us against 36 on the tiled members; for other filters the
-// padding, to 32, takes what it gives: 1x1, 48 to 96 channels, 56x56: 19.9 against 16.3).  The weights of the padding are
-// zero, and the activations fetched for it are those of the last channel: what is finite adds nothing, and what is not
-// has the tile computed again (wpk_split.h).
+// Whether the split members order pr's reduction by filter taps, (c / 32, r, s, c % 32): where the tiled members do, and where padding
+// C to whole groups of 32, of 16 where they work from patches, lengthens it by half at most.  The weights of the padding are
+// zero, and what is fetched for it lies in x (wpk_split.h): what is finite adds nothing, and what is not has the tile
+// computed again.
 bool split_taps(const Problem &pr);
 // MFMA depths of pr on the strip form of the split members, 0 where they run it otherwise.
 int strip_depths(const Problem &pr);
@@ -240,12 +238,12 @@ inline int64_t split_rows(const Problem &pr)
     if (const int depths = strip_depths(pr)) return depths * 16;
     return split_taps(pr) ? (int64_t)((pr.d.c + 31) / 32 * 32) * pr.d.r * pr.d.s : pr.CRSpad;
 }
-// Whether a split member fetches pr's x four neighbouring pixels at a time: 1x1 filters on [N][C][H][W], C a multiple of
-// 32, stride 1, no padding, images of a multiple of four pixels.
+// Whether a split member fetches pr's x four neighbouring pixels at a time: 1x1 filters on [N][C][H][W] in the order of taps,
+// stride 1, no padding, images of a multiple of four pixels.
 inline bool split_point(const Problem &pr)
 {
     const wpk_conv_desc &d = pr.d;
-    return pr.tapmajor && d.r == 1 && d.s == 1 && d.stride_h == 1 && d.stride_w == 1 && d.pad_h == 0 && d.pad_w == 0 &&
+    return !pr.xl && split_taps(pr) && d.r == 1 && d.s == 1 && d.stride_h == 1 && d.stride_w == 1 && d.pad_h == 0 && d.pad_w == 0 &&
            (int64_t)d.h * d.w % 4 == 0;
 }
 // Byte offset of channel ch in an image of [N][C][H][W], HW4 bytes per channel.  Chunks of 16 channels may run past the

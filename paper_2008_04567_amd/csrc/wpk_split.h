@@ -113,11 +113,11 @@ __device__ __forceinline__ bool join_sums(v16f (&acc)[NB], const v16f (&sml)[NB]
 
 // How activations are found (the XL of the tiled members, and the patch):
 //   kRows   row by row through the tap table, any C; rows in the source's order (c, r, s)
-//   kQuads  channels-last, C a multiple of 32: a lane fetches an octet of one pixel with two 16-byte loads
-//   kTaps   [N][C][H][W], C a multiple of 32: one filter tap per step, eight one-dword loads per octet
-//   kPoint  [N][C][H][W], C a multiple of 32, 1x1 filters, stride 1, no padding, H * W a multiple of 4: four neighbouring pixels of a
+//   kQuads  channels-last, C padded to 32: a lane fetches an octet of one pixel with two 16-byte loads
+//   kTaps   [N][C][H][W], C padded to 32: one filter tap per step, eight one-dword loads per octet
+//   kPoint  [N][C][H][W], C padded to 32, 1x1 filters, stride 1, no padding, H * W a multiple of 4: four neighbouring pixels of a
 //           channel are sixteen contiguous bytes, so a wave fetches a whole step with eight loads instead of 32
-//   kPatch, kPatchQuads: 3x3 filters ([N][C][H][W], any C; channels-last, C a multiple of 32): the nine taps of sixteen channels read one patch of x.  The pixels of a
+//   kPatch, kPatchQuads: 3x3 filters (C padded to 16): the nine taps of sixteen channels read one patch of x.  The pixels of a
 //           tile are consecutive, and so are the positions of x that their windows cover (numbered through the
 //           images): `halo` of them at most, any stride and dilation for which that fits.  A position is fetched and
 //           split once per sixteen channels instead of nine times.  A multiplying wave knows the LDS address of every
@@ -239,7 +239,10 @@ __device__ __forceinline__ int role_of_wave(const int wave, const bool two_per_u
     return wave == 0 ? WN + NP - 1 : wave - 1;
 }
 
-template <int WN, SplitForm FORM, int NP>
+// ANY: C may be no multiple of 32 (of 16 for kPatchQuads).  What is fetched for the channels that fill the last group up has weights of
+// zero: kTaps and kPatch fetch the last channel again, the others what lies behind it, the next pixel or image, or zeros
+// past the tensor, whose end the range check knows only where the whole offset is the lane's.
+template <int WN, SplitForm FORM, int NP, bool ANY>
 __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArgs a)
 {
     constexpr bool PATCH = FORM == kPatch || FORM == kPatchQuads, QUAD = FORM == kQuads || FORM == kPatchQuads;
@@ -317,9 +320,10 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
                     if constexpr (QUAD) {
                         static_for<2>([&](auto H) WPK_LAMBDA {
                             constexpr int b = o * 8 + decltype(H)::value * 4;
+                            const int at = chunk * 64 + decltype(H)::value * 16;
                             const v4f q = __builtin_bit_cast(
-                                v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, off[pb][o],
-                                                                           chunk * 64 + decltype(H)::value * 16, 0));
+                                v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                                         xrsrc, ANY ? (off[pb][o] + at) | off[pb][o] >> 31 : off[pb][o], ANY ? 0 : at, 0));
                             static_for<4>([&](auto E) WPK_LAMBDA { v[pb][b + decltype(E)::value] = q[decltype(E)::value]; });
                         });
                     } else {
@@ -400,16 +404,17 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
             int step = kbeg;
             auto fetch = [&](auto SLOT) WPK_LAMBDA {
                 constexpr int sl = decltype(SLOT)::value;
-                const int at = voff | (step < kend ? 0 : -1), first = step * 32 * a.HW4;
+                const int live = voff | (step < kend ? 0 : -1), first = step * 32 * a.HW4;
                 static_for<8>([&](auto J) WPK_LAMBDA {
                     constexpr int j = decltype(J)::value;
+                    const int ch = first + j * a.HW4, at = ANY ? (live + ch) | live >> 31 : live, past = ANY ? 0 : ch;
                     if constexpr (PX == 4) {
                         const v4f q = __builtin_bit_cast(
-                            v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, at, first + j * a.HW4, 0));
+                            v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, at, past, 0));
                         static_for<4>([&](auto E) WPK_LAMBDA { v[sl][j * 4 + decltype(E)::value] = q[decltype(E)::value]; });
                     } else {
                         const v2f q = __builtin_bit_cast(
-                            v2f, __builtin_amdgcn_raw_buffer_load_b64(xrsrc, at, first + j * a.HW4, 0));
+                            v2f, __builtin_amdgcn_raw_buffer_load_b64(xrsrc, at, past, 0));
                         v[sl][j * 2] = q[0];
                         v[sl][j * 2 + 1] = q[1];
                     }
@@ -520,18 +525,21 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
                         if constexpr (QUAD) {
                             static_for<2>([&](auto H) WPK_LAMBDA {
                                 constexpr int hf = decltype(H)::value;
+                                const int at = tap_off + ch * 4 + hf * 16;
                                 const v4f q = __builtin_bit_cast(
-                                    v4f, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xvb[u], tap_off + ch * 4 + hf * 16, 0));
+                                    v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                                             xrsrc, ANY ? (xvb[u] + at) | xvb[u] >> 31 : xvb[u], ANY ? 0 : at, 0));
                                 static_for<4>([&](auto E) WPK_LAMBDA {
                                     v[sl][u * 8 + hf * 4 + decltype(E)::value] = q[decltype(E)::value];
                                 });
                             });
                         } else {
-                            const int first = tap_off + (ch + (prod * UN + u) * 8) * a.HW4;
+                            const int first = (ch + (prod * UN + u) * 8) * a.HW4, last = (a.C - 1) * a.HW4;
                             static_for<8>([&](auto J) WPK_LAMBDA {
                                 constexpr int j = decltype(J)::value;
+                                const int at = ANY ? min(first + j * a.HW4, last) : first + j * a.HW4;
                                 v[sl][u * 8 + j] = __builtin_bit_cast(
-                                    float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xvb[0], first + j * a.HW4, 0));
+                                    float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xvb[0], tap_off + at, 0));
                             });
                         }
                     });
@@ -758,12 +766,23 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
 // (wpk_strip.h)
 hipError_t launch_strip(const IgemmArgs &a, hipStream_t stream);
 
-template <int WN, SplitForm FORM, int NP>
+template <int WN, SplitForm FORM, int NP, bool ANY>
 hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 {
     const size_t lds = 2 * (size_t)(FORM >= kPatch ? (a.halo + 1) * kHaloPitch : 64 * kStepPitch);
-    return launch_kernel<split_kernel<WN, FORM, NP>, 64 * (WN + NP), 2 * (kHaloMax + 1) * kHaloPitch>(
+    return launch_kernel<split_kernel<WN, FORM, NP, ANY>, 64 * (WN + NP), 2 * (kHaloMax + 1) * kHaloPitch>(
         a, stream, lds, 2 * 32 * WN * sizeof(float) + sizeof(int));  // (bias, arrival)
+}
+
+// How activations are found, with or without padded channels, by NP fetching waves; ONE: there is a form with one for these WN.
+template <int WN, SplitForm FORM, bool ANY, bool ONE>
+hipError_t launch_split_waves(const IgemmArgs &a, hipStream_t stream)
+{
+    if constexpr (ONE)
+        if (a.producers == 1) return launch_split_form<WN, FORM, 1, ANY>(a, stream);
+    if constexpr (!ONE || WN >= 2 || FORM >= kPatch)
+        return launch_split_form<WN, FORM, 2, ANY>(a, stream);
+    return hipErrorInvalidValue;
 }
 
 // (the K-step gene says whether patches may be used, which the host has looked at; `stages` has no meaning here)
@@ -771,20 +790,21 @@ template <int WN>
 hipError_t launch_split(const IgemmArgs &a, hipStream_t stream)
 {
     if (a.halo == -2) return launch_strip(a, stream);
+    const bool any = a.C % 32 != 0;
     if (a.halo > 0) {
-        if (a.producers == 2)
-            return a.xl == 2 ? launch_split_form<WN, kPatchQuads, 2>(a, stream) : launch_split_form<WN, kPatch, 2>(a, stream);
-        if constexpr (WN < 4)
-            return a.xl == 2 ? launch_split_form<WN, kPatchQuads, 1>(a, stream) : launch_split_form<WN, kPatch, 1>(a, stream);
+        if (a.xl != 2) return launch_split_waves<WN, kPatch, false, (WN < 4)>(a, stream);
+        return any ? launch_split_waves<WN, kPatchQuads, true, (WN < 4)>(a, stream)
+                   : launch_split_waves<WN, kPatchQuads, false, (WN < 4)>(a, stream);
     }
-    if (a.xl == 2) return launch_split_form<WN, kQuads, WN == 4 ? 2 : 1>(a, stream);
-    if (a.halo < 0) {
-        if constexpr (WN >= 2)
-            if (a.producers == 2) return launch_split_form<WN, kPoint, 2>(a, stream);
-        if constexpr (WN < 4) return launch_split_form<WN, kPoint, 1>(a, stream);
-    }
-    if (a.xl == 3) return launch_split_form<WN, kTaps, 2>(a, stream);
-    return launch_split_form<WN, kRows, 2>(a, stream);
+    if (a.xl == 2)
+        return any ? launch_split_form<WN, kQuads, WN == 4 ? 2 : 1, true>(a, stream)
+                   : launch_split_form<WN, kQuads, WN == 4 ? 2 : 1, false>(a, stream);
+    if (a.halo == -1)
+        return any ? launch_split_waves<WN, kPoint, true, (WN < 4)>(a, stream)
+                   : launch_split_waves<WN, kPoint, false, (WN < 4)>(a, stream);
+    if (a.xl == 3)
+        return any ? launch_split_form<WN, kTaps, 2, true>(a, stream) : launch_split_form<WN, kTaps, 2, false>(a, stream);
+    return launch_split_form<WN, kRows, 2, false>(a, stream);
 }
 
 }  // namespace wpk

@@ -55,3 +55,24 @@ ROLES = [
 def test_fetching_waves(layer, steps, more, wn):
     for bk in steps:
         check_layer(layer, cfg(wn, bk, **more), what="%s wn%d bk%d" % (layer["name"], wn, bk))
+
+
+# Channels that are no multiple of 32 on the forms that pad them: 1x1 four pixels and two pixels a lane, taps, channels-last quads and
+# patches, with the last group one channel short, one channel long and half full; a last pixel at the very end of the tensor.
+ANY = [
+    W.layer("point_c31", 2, 31, (6, 10), 70, 1, x_dist="u11", seed=30),
+    W.layer("point_c97", 1, 97, (4, 33), 64, 1, x_dist="u11", seed=31),
+    W.layer("taps_c48_s2", 2, 48, (9, 13), 40, 1, 2, x_dist="u11", seed=32),
+    W.layer("taps_c61_5x5", 1, 61, (7, 12), 64, 5, 1, 2, x_dist="u11", seed=33),
+    W.layer("patch_c50", 2, 50, 9, 96, 3, 1, 1, x_dist="u11", seed=34),
+    W.layer("patch_c33_s2", 1, 33, (11, 8), 64, 3, 2, 0, x_dist="u11", seed=35),
+]
+
+
+@pytest.mark.parametrize("layer", ANY, ids=lambda l: l["name"])
+@pytest.mark.parametrize("wn", [1, 2, 4])
+def test_padded_channels(layer, wn):
+    for bk in (16, 32):
+        for layout in range(4):
+            check_layout(layer, layout, cfg(wn, bk), what="%s wn%d bk%d layout %d" % (layer["name"], wn, bk, layout))
+    check_layout(layer, 1, cfg(wn, 16, split_k=2), what="%s slices" % layer["name"])
