@@ -561,7 +561,7 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     const Reduction red = reduction_of(pr, c);
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);
     const int64_t want = point ? 5 * (int64_t)compute_units / 2 : 4 / wn * (int64_t)compute_units;
-    const int64_t G = 3 * (int64_t)compute_units;
+    const int64_t G = 3 * (int64_t)compute_units, pairs = (pr.M + 63) / 64 * ((pr.d.k + 63) / 64);
     if (2 * tiles <= want) {
         // (slices of 64 rows at least, see kMinRunRows)
         const int64_t most = std::min<int64_t>(want / tiles, red.steps / std::max(1, kMinRunRows / red.rows));
@@ -579,6 +579,16 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         // with more tiles left over, patches of which three do not fit, taps or single steps it loses up to half.
         c.persist = 3;
         time *= 0.95;
+    } else if (!point && pr.d.k > 32 && split_lds_units(halo, 2) <= 64 &&
+               ((pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units) ||
+                (halo > 0 && pairs > 4 * (int64_t)compute_units))) {
+        // Two persistent workgroups of two waves per compute unit, whose SIMDs then have one multiplying wave each, and the tiles beyond
+        // whole rounds dealt out.  Of 64 pixels and channels each, two to two and a half tiles per compute unit: 0.81 to 0.92 of the time of what the rules
+        // around this one give (patches 17 layers, channels-last 7; taps take one workgroup of four waves, 0.84, 11 layers); patches of more
+        // than four, 0.89 to 0.99 (60 layers).  With two and a half to four it is 0.99 to 1.23 of it.
+        const bool taps = halo == 0 && !pr.xl;
+        c = wpk_conv_config{64, taps ? 128 : 64, c.bk, 1, taps ? 4 : 2, 1, 1, taps ? 1 : 2, 1, 0};
+        time = 0.9 * std::min(time, split_time(pr, c, compute_units));
     } else {
         wpk_conv_config other = c;
         double least = 1e300;
