@@ -580,12 +580,12 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         c.persist = 3;
         time *= 0.95;
     } else if (!point && pr.d.k > 32 && split_lds_units(halo, 2) <= 64 &&
-               ((pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units) ||
-                (halo > 0 && pairs > 4 * (int64_t)compute_units))) {
+               ((pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units && red.steps >= 4) ||
+                (halo > 0 && pairs > 4 * (int64_t)compute_units && red.steps >= 2))) {
         // Two persistent workgroups of two waves per compute unit, whose SIMDs then have one multiplying wave each, and the tiles beyond
         // whole rounds dealt out.  Of 64 pixels and channels each, two to two and a half tiles per compute unit: 0.81 to 0.92 of the time of what the rules
         // around this one give (patches 17 layers, channels-last 7; taps take one workgroup of four waves, 0.84, 11 layers); patches of more
-        // than four, 0.89 to 0.99 (60 layers).  With two and a half to four it is 0.99 to 1.23 of it.
+        // than four, 0.89 to 0.99 (60 layers).  With two and a half to four it is 0.99 to 1.23 of it, with fewer steps to deal out than that 0.97 to 1.1.
         const bool taps = halo == 0 && !pr.xl;
         c = wpk_conv_config{64, taps ? 128 : 64, c.bk, 1, taps ? 4 : 2, 1, 1, taps ? 1 : 2, 1, 0};
         time = 0.9 * std::min(time, split_time(pr, c, compute_units));
