@@ -244,15 +244,25 @@ int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
     return patch_bound(pr);
 }
 
+// MFMA depths of a strip and the columns / 2 its rows have room for, 0 depths where a layer does not fit.
+static int strip_fits(int C, int Q, int R, int S, int stride_w, int dil_h, int dil_w, int *pairs)
+{
+    const int64_t octets = (int64_t)C * R, columns = (int64_t)(Q - 1) * stride_w + 8 + (stride_w % 2 ? 2 : 0);
+    if (octets > 22 || S < 2 || S > 8 || dil_w != 1 || columns > 240) return 0;
+    *pairs = columns <= 128 ? 64 : 120;
+    if (C * ((int64_t)(R - 1) * dil_h + 1) * *pairs * 12 > 78 * 1024) return 0;  // (a strip of one row)
+    return octets <= 6 ? 3 : octets <= 10 ? 5 : octets <= 16 ? 8 : 11;
+}
+
 // A strip's rows: as few as keep all compute units busy with as little filling as possible.  The cost of a choice, in cycles, from
 // what the kernel was measured to take: a workgroup's start and end, a row of x (per 64 columns / 2), a block of 32 pixels by 32
 // channels; two workgroups share a compute unit and its matrix pipes.
 StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stride_h, int stride_w, int dil_h, int dil_w)
 {
     StripShape best = {0, 0, 0, 0, 0, 0, 0.0};
-    const int64_t octets = (int64_t)C * R, columns = (int64_t)(Q - 1) * stride_w + 8 + (stride_w % 2 ? 2 : 0);
-    if (octets > 22 || S < 2 || S > 8 || dil_w != 1 || columns > 240) return best;
-    const int depths = octets <= 6 ? 3 : octets <= 10 ? 5 : octets <= 16 ? 8 : 11, pairs = columns <= 128 ? 64 : 120;
+    int pairs;
+    const int depths = strip_fits(C, Q, R, S, stride_w, dil_h, dil_w, &pairs);
+    if (depths == 0) return best;
     const int waves_c = K > 64 ? 4 : K > 32 ? 2 : 1, groups = (K + 32 * waves_c - 1) / (32 * waves_c);
     double least = 1e300;
     for (int rows = 1; rows <= P && rows <= 64; ++rows) {
@@ -279,8 +289,9 @@ StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stri
 int strip_depths(const Problem &pr)
 {
     const wpk_conv_desc &d = pr.d;
-    if (pr.tapmajor || pr.xquad || !pr.tiled_ok || (int64_t)d.c * d.r > 22) return 0;
-    return strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w).depths;
+    int pairs;
+    if (pr.tapmajor || pr.xquad || !pr.tiled_ok) return 0;
+    return strip_fits(d.c, pr.Q, d.r, d.s, d.stride_w, d.dil_h, d.dil_w, &pairs);
 }
 
 int split_lds_units(int halo, int wn)
@@ -299,6 +310,12 @@ int split_producers(const Problem &pr, const wpk_conv_config &cfg)
     }
     if (pr.xl && split_taps(pr)) return cfg.wn == 4 ? 2 : 1;
     if (split_point(pr)) return cfg.wn == 4 || (cfg.wn == 2 && cfg.bk == 32) ? 2 : 1;
+    if (cfg.wn == 4 && split_taps(pr) && persistent_of(pr, cfg, 256) == 0) {
+        // taps, a dword per load, of which a wave has 48 in flight: four waves, six steps, where a compute unit has one workgroup anyway (3x3,
+        // stride 2, 128 channels, 56x56, 16 images: 30.0 -> 28.7 us; 5x5, 64 to 128 at 30x30, 8 images in two slices: 25.4 -> 24.3)
+        const int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
+        if (tiles * cfg.split_k <= 256) return 4;
+    }
     return 2;
 }
 
@@ -536,10 +553,11 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     const double flops = 2.0 * pr.M * pr.d.k * pr.CRS;
     if (strip_depths(pr)) {
         const wpk_conv_desc &d = pr.d;
+        // (nor where y leaves a lane four bytes at a time: 2 to 130 channels, channels-last, 403 us against 273)
+        if (flops < 0.45e9 || (pr.yl && d.k % 4)) return false;
         *out = wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
         const double us = strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w).us;
-        // (not where y leaves a lane four bytes at a time: 2 to 130 channels, channels-last, 403 us against 273)
-        return flops >= 0.45e9 && !(pr.yl && d.k % 4) && 1.1 * us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);
+        return 1.1 * us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);
     }
     if (!split_taps(pr)) return false;
     // (padded channels, but for patches of [N][C][H][W]: 46 to 128 channels, 5x5, 12x8, one image, 0.03 GFLOP, 17.8 us against 14.9 one shot; 300

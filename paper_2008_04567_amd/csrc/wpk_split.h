@@ -229,10 +229,12 @@ __host__ __device__ constexpr int step_place(int px) { return px * kStepPitch + 
 // compute unit has waves 1 and 2 multiply instead.  (3x3, 128 channels, 28x28, 16 images, 392 workgroups: 22.7 us, 29.7 without;
 // 256 channels, 14x14 in two slices 24.8, 32.0; 1x1, 512 to 128 channels at 28x28 16.1, 19.0.)  With three or four workgroups on a
 // compute unit the SIMDs have as much to do either way, and asking costs 0.4 us (64 channels, 56x56: 22.5, 22.9 with): not done there.
-template <int WN, int NP>
-__device__ __forceinline__ int role_of_wave(const int wave, const bool two_per_unit)
+// Nor by 1x1 layers with one fetching wave, which waits for nobody (17.4 either way).
+template <int WN, int NP, bool CHANGE, class F>
+__device__ __forceinline__ int role_of_wave(const int wave, F &&two_per_unit)
 {
-    if (WN != 2 || !two_per_unit) return wave;
+    if constexpr (!CHANGE) return wave;
+    if (!two_per_unit()) return wave;
     // (the second workgroup's LDS begins where the first one's ends; LDS_ALLOC: base in bits 0 .. 8, size in bits 12 .. 20)
     const unsigned alloc = __builtin_amdgcn_s_getreg(6 | 31 << 11);
     if ((alloc & 0x1ff) != (alloc >> 12 & 0x1ff)) return wave;
@@ -253,7 +255,8 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
     __shared__ int arrival;
 
     touch_kernarg_lines();
-    const int wave = role_of_wave<WN, NP>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), a.two_per_unit != 0);
+    const int wave = role_of_wave<WN, NP, WN == 2 && !(FORM == kPoint && NP == 1)>(
+        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), [&] { return a.two_per_unit != 0; });
     const int tid = wave * 64 + (threadIdx.x & 63);
     const int buf_bytes = PATCH ? (a.halo + 1) * kHaloPitch : BM * kStepPitch;
     int parity = 0;                            // of the segment
@@ -461,8 +464,8 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
         } else {
             constexpr int UN = 4 / NP;                  // octets of 64 pixels per wave and step
             // steps in flight: 24 KB of x per wave, or as much as the counter of loads in flight (63) allows
-            constexpr int DEPTH = QUAD ? 3 * NP : 3;
-            static_assert(QUAD || NP == 2, "three steps of 16 loads");
+            constexpr int DEPTH = QUAD ? 3 * NP : 3 * NP / 2;
+            static_assert(QUAD || NP == 2 || NP == 4, "48 loads");
             constexpr int XP = QUAD ? UN : 1;           // pixels per lane
             // QUAD: four lanes hold the four octets of a pixel (128 contiguous bytes of x), else a lane its pixel's
             int xvoff[XP], xvb[XP];
@@ -803,7 +806,12 @@ hipError_t launch_split(const IgemmArgs &a, hipStream_t stream)
         return any ? launch_split_waves<WN, kPoint, true, (WN < 4)>(a, stream)
                    : launch_split_waves<WN, kPoint, false, (WN < 4)>(a, stream);
     if (a.xl == 3)
+    {
+        if constexpr (WN == 4)
+            if (a.producers == 4)
+                return any ? launch_split_form<WN, kTaps, 4, true>(a, stream) : launch_split_form<WN, kTaps, 4, false>(a, stream);
         return any ? launch_split_form<WN, kTaps, 2, true>(a, stream) : launch_split_form<WN, kTaps, 2, false>(a, stream);
+    }
     return launch_split_form<WN, kRows, 2, false>(a, stream);
 }
 
