@@ -526,15 +526,16 @@ static double tiled_time(const Problem &pr, const wpk_conv_config &c, int comput
     return 2.9 + sqrt(chain * chain + pipes * pipes + memory * memory) +
            (atomics ? 5.7 + 3 * y_mb / 7.7 + (pr.yl ? 5.5 * y_mb * slices : 0.0) : 0.0);
 }
-// The split members' default, where they order the reduction by taps (row by row they gain nothing over the tiled
-// members: 53 against 47 us on the 7x7 stride-2 stem of three channels).  Waves of 64 pixels by 32 channels; patches where a 3x3
-// layer allows them.
+// The split members' default, where they order the reduction by taps or take the layer in strips (row by row they gain nothing over
+// the tiled members).  Waves of 64 pixels by 32 channels; patches where a 3x3 layer allows them.
 //  - As many waves per workgroup as the channels call for, four at most: a wider workgroup fetches and splits its pixels
 //    for more channels at once; what that is worth against padded channels is the weight of 20 / bn, from the measured
 //    times of 64- and 128-channel tiles.  1x1 layers fetched four pixels at a time take two: fetching is cheap there, the
 //    launch is bound by memory, and four small workgroups on a compute unit are out of step with each other where two
 //    large ones fetch, multiply and store at the same time (256 to 128 channels, 56x56, 16 images: 29.5 us against 42;
 //    256 to 1024 at 14x14: 15.3 against 21.4).
+//    With up to two tiles of 64 channels per compute unit they take four waves and two that fetch, like the others (512 to 128 at 28x28:
+//    12.6 us, with two and one that fetches 16.3, two and two 15.2).
 //  - The reduction is cut until there is about one wave per SIMD, no further: a second wave hides what a second
 //    slice's prologue and meeting cost, no more (3x3, 256 channels, 14x14, 16 images, 98 tiles: 25.5 us in 2 slices,
 //    27-30 in 1 or 3-5; 512 channels at 7x7, 52 tiles: 28.0 in 4, 28.7 in 3, 32.6 in 8).

@@ -25,6 +25,10 @@
 // packed for that (pack_split_kernel), already split, 16 bytes per lane.  Activations are shared by the waves: NP further
 // waves fetch them as fp32, split them once and put them into LDS, from where a lane of a multiplying wave
 // reads eight consecutive rows of its pixel per part with one 16-byte access.  Two buffers, one barrier per step.
+// NP: a wave issues an instruction every five cycles, so splitting a step of 64 pixels and 32 rows, 250 of them, takes it 1570 cycles,
+// in which two multiplying waves of a SIMD are done with theirs (1536), but one has waited half of the time.  So two waves fetch
+// where a compute unit has few workgroups, each half of every step (in turns they gain nothing: with two buffers a step is split
+// while the one before it is multiplied), and one where it has four (split_producers).
 // Why waves of their own for it: (a) loads return in order, so in a wave that fetches both, a weight waits for
 // every activation asked for before it, however far ahead that was -- with both in one wave a 1x1 layer of 256
 // channels at 56x56 (N = 16, K = 128) ran at 2.2 TB/s whatever the depth of its prefetch; (b) the splitting (6.5 vector
