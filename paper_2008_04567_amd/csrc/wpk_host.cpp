@@ -310,12 +310,6 @@ int split_producers(const Problem &pr, const wpk_conv_config &cfg)
     }
     if (pr.xl && split_taps(pr)) return cfg.wn == 4 ? 2 : 1;
     if (split_point(pr)) return cfg.wn == 4 || (cfg.wn == 2 && cfg.bk == 32) ? 2 : 1;
-    if (cfg.wn == 4 && split_taps(pr) && persistent_of(pr, cfg, 256) == 0) {
-        // taps, a dword per load, of which a wave has 48 in flight: four waves, six steps, where a compute unit has one workgroup anyway (3x3,
-        // stride 2, 128 channels, 56x56, 16 images: 30.0 -> 28.7 us; 5x5, 64 to 128 at 30x30, 8 images in two slices: 25.4 -> 24.3)
-        const int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
-        if (tiles * cfg.split_k <= 256) return 4;
-    }
     return 2;
 }
 

@@ -468,8 +468,8 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
         } else {
             constexpr int UN = 4 / NP;                  // octets of 64 pixels per wave and step
             // steps in flight: 24 KB of x per wave, or as much as the counter of loads in flight (63) allows
-            constexpr int DEPTH = QUAD ? 3 * NP : 3 * NP / 2;
-            static_assert(QUAD || NP == 2 || NP == 4, "48 loads");
+            constexpr int DEPTH = QUAD ? 3 * NP : 3;
+            static_assert(QUAD || NP == 2, "three steps of 16 loads");
             constexpr int XP = QUAD ? UN : 1;           // pixels per lane
             // QUAD: four lanes hold the four octets of a pixel (128 contiguous bytes of x), else a lane its pixel's
             int xvoff[XP], xvb[XP];
@@ -810,12 +810,7 @@ hipError_t launch_split(const IgemmArgs &a, hipStream_t stream)
         return any ? launch_split_waves<WN, kPoint, true, (WN < 4)>(a, stream)
                    : launch_split_waves<WN, kPoint, false, (WN < 4)>(a, stream);
     if (a.xl == 3)
-    {
-        if constexpr (WN == 4)
-            if (a.producers == 4)
-                return any ? launch_split_form<WN, kTaps, 4, true>(a, stream) : launch_split_form<WN, kTaps, 4, false>(a, stream);
         return any ? launch_split_form<WN, kTaps, 2, true>(a, stream) : launch_split_form<WN, kTaps, 2, false>(a, stream);
-    }
     return launch_split_form<WN, kRows, 2, false>(a, stream);
 }
 
