@@ -230,6 +230,7 @@ static int patch_bound(const Problem &pr)
 bool split_taps(const Problem &pr)
 {
     if (pr.tapmajor || pr.xquad) return true;
+    if (strip_depths(pr)) return false;  // (an order of their own: 22 channels of one filter row would be both)
     const int64_t C = pr.d.c, c16 = (C + 15) / 16 * 16, c32 = (C + 31) / 32 * 32;
     if (c32 * pr.d.r * pr.d.s * pr.Kpad * kSplitWeightBytes > kMaxSplitBytes) return false;
     const bool patch = patch_bound(pr) > 0;

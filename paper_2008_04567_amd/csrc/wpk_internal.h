@@ -226,7 +226,7 @@ WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int str
     return (n * H + (r < H - 1 ? r : H - 1)) * W + (r - stride_h < H - 1 && c < W - 1 ? c : W - 1);
 }
 // Whether the split members order pr's reduction by filter taps, (c / 32, r, s, c % 32): where the tiled members do, and where padding
-// C to whole groups of 32, of 16 where they work from patches, lengthens it by half at most.  The weights of the padding are
+// C to whole groups of 32, of 16 where they work from patches, lengthens it by half at most and the layer does not fit strips.  The weights of the padding are
 // zero, and what is fetched for it lies in x (wpk_split.h): what is finite adds nothing, and what is not has the tile
 // computed again.
 bool split_taps(const Problem &pr);

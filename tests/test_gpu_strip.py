@@ -29,6 +29,10 @@ STRIP = [
     W.layer("wide_odd", 1, 1, (5, 231), 64, 7, 1, 3, x_dist="u11", seed=10),
     W.layer("dil_rows", 1, 3, (31, 20), 64, 5, (1, 2), (4, 2), dil=(2, 1), x_dist="u11", seed=11),
     W.layer("one_pixel", 2, 3, 7, 16, 7, x_dist="u11", seed=12),
+    # (as many octets from many channels of one filter row)
+    W.layer("c22_1x2", 2, 22, (9, 33), 40, (1, 2), (1, 2), 0, x_dist="u11", seed=13),
+    W.layer("c22_1x3", 2, 22, (9, 33), 70, (1, 3), 1, (0, 1), x_dist="u11", seed=14),
+    W.layer("c22_1x7", 1, 22, (5, 40), 64, (1, 7), 1, (0, 3), x_dist="u11", seed=15),
 ]
 
 
