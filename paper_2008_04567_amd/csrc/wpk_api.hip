@@ -1831,9 +1831,7 @@ int wpk_plan_set_pipeline(wpk_plan *plan, int32_t ways)
     WPK_HIP(hipDeviceSynchronize());  // workspaces may grow below
     for (auto &L : plan->layers) {
         for (int h = 0; h < 2; ++h) {
-            wpk_conv_desc d = L.pr.d;
-            d.n = h == 0 ? (L.pr.d.n + 1) / 2 : L.pr.d.n / 2;
-            int rc = make_problem(&d, &L.half[h]);
+            int rc = make_part(L.pr, h == 0 ? (L.pr.d.n + 1) / 2 : L.pr.d.n / 2, &L.half[h]);
             if (rc != WPK_OK) return rc;
             if (L.direct) continue;
             plan_choose(L.half[h], &L.half_cfg[h], &L.half_cfg_fused[h]);

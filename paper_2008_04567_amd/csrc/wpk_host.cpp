@@ -116,6 +116,7 @@ static int64_t out_extent(int64_t in, int64_t pad, int64_t dil, int64_t win, int
     return span < 0 ? 0 : span / stride + 1;
 }
 
+static bool pads_to_taps(const Problem &pr);
 int make_problem(const wpk_conv_desc *d, Problem *out)
 {
     if (!d || !out) return WPK_E_NULL_PTR;
@@ -150,8 +151,18 @@ int make_problem(const wpk_conv_desc *d, Problem *out)
     pr.tiled_ok = d->r <= kMaxFilterRows && d->s <= kMaxFilterCols &&
                   pr.x_elems * 4 + bias <= kMaxTiledBytes &&
                   pr.y_elems * 4 <= kMaxTiledBytes && (int64_t)pr.CRSpad * pr.Kpad * 4 <= kMaxTiledBytes;
+    pr.padtaps = pads_to_taps(pr);
     *out = pr;
     return WPK_OK;
+}
+
+int make_part(const Problem &whole, int images, Problem *out)
+{
+    wpk_conv_desc d = whole.d;
+    d.n = images;
+    const int rc = make_problem(&d, out);
+    if (rc == WPK_OK) out->padtaps = whole.padtaps;
+    return rc;
 }
 
 // (every one-shot call makes one or two of these; snprintf took a microsecond for each)
@@ -227,9 +238,9 @@ static int patch_bound(const Problem &pr)
     return span <= kHaloMax ? (int)span : 0;
 }
 
-bool split_taps(const Problem &pr)
+static bool pads_to_taps(const Problem &pr)
 {
-    if (pr.tapmajor || pr.xquad) return true;
+    if (pr.tapmajor || pr.xquad) return false;
     if (strip_depths(pr)) return false;  // (an order of their own: 22 channels of one filter row would be both)
     const int64_t C = pr.d.c, c16 = (C + 15) / 16 * 16, c32 = (C + 31) / 32 * 32;
     if (c32 * pr.d.r * pr.d.s * pr.Kpad * kSplitWeightBytes > kMaxSplitBytes) return false;

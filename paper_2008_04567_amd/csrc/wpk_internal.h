@@ -85,8 +85,12 @@ struct Problem {
     bool xl, yl;     // x / y channels-last (bits 0 and 1 of the descriptor's layout)
     bool xquad;      // channels-last x gathered as 16-byte channel quads (C a multiple of every K-step)
     bool tapmajor;   // x [N][C][H][W] with C a multiple of every K-step: reduction ordered (r, s, c) as well
+    bool padtaps;    // neither, but the split members pad C and order the reduction by taps (split_taps)
 };
 int make_problem(const wpk_conv_desc *d, Problem *out);  // WPK_OK or a WPK_E_* code
+// The first or last `images` images of a problem, to be run on weights that were packed for the whole of it: whether channels are padded
+// depends on the number of images too (offsets), and the packed order is that of the whole.
+int make_part(const Problem &whole, int images, Problem *out);
 std::string desc_key(const wpk_conv_desc *d);
 
 // Division of a 31-bit number by a launch constant as a multiply, an add and a shift (the
@@ -229,7 +233,7 @@ WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int str
 // C to whole groups of 32, of 16 where they work from patches, lengthens it by half at most and the layer does not fit strips.  The weights of the padding are
 // zero, and what is fetched for it lies in x (wpk_split.h): what is finite adds nothing, and what is not has the tile
 // computed again.
-bool split_taps(const Problem &pr);
+inline bool split_taps(const Problem &pr) { return pr.tapmajor || pr.xquad || pr.padtaps; }
 // MFMA depths of pr on the strip form of the split members, 0 where they run it otherwise.
 int strip_depths(const Problem &pr);
 // Rows of the reduction as the split members pack it.
