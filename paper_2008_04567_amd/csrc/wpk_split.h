@@ -230,10 +230,12 @@ __host__ __device__ constexpr int step_place(int px) { return px * kStepPitch + 
 // A compute unit deals the waves of a workgroup to its four SIMDs in turn and begins the next workgroup one SIMD further on (read
 // from HW_ID, workgroups of three, four and six waves).  So of two workgroups with two multiplying waves each, the first ones, one
 // SIMD would have two of them and another none, and the loop takes twice as long as it could; the second workgroup of a
-// compute unit has waves 1 and 2 multiply instead.  (3x3, 128 channels, 28x28, 16 images, 392 workgroups: 22.7 us, 29.7 without;
-// 256 channels, 14x14 in two slices 24.8, 32.0; 1x1, 512 to 128 channels at 28x28 16.1, 19.0.)  With three or four workgroups on a
+// compute unit has waves 1 and 2 multiply instead.  (Workgroups of two waves set by hand, which no default chose before: 3x3, 128 channels, 28x28,
+// 16 images, 392 workgroups, 22.7 us, 29.7 without; 256 channels, 14x14 in two slices 24.8, 32.0; 1x1, 512 to 128 channels at 28x28 16.1, 19.0.
+// The defaults of these three then took 21.4, 24.1 and 16.3.)  With three or four workgroups on a
 // compute unit the SIMDs have as much to do either way, and asking costs 0.4 us (64 channels, 56x56: 22.5, 22.9 with): not done there.
-// Nor by 1x1 layers with one fetching wave, which waits for nobody (17.4 either way).
+// Nor where a single wave fetches, but for patches: 1x1 layers took 17.4 either way, channels-last ones 4 to 9 % longer with
+// it (55 layers of one or two workgroups per compute unit; 5x5, 640 to 64 channels, 17x45, 8 images, 90.1 us, 83.5 without).
 template <int WN, int NP, bool CHANGE, class F>
 __device__ __forceinline__ int role_of_wave(const int wave, F &&two_per_unit)
 {
@@ -259,7 +261,7 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
     __shared__ int arrival;
 
     touch_kernarg_lines();
-    const int wave = role_of_wave<WN, NP, WN == 2 && !(FORM == kPoint && NP == 1)>(
+    const int wave = role_of_wave<WN, NP, WN == 2 && (PATCH || NP == 2)>(
         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), [&] { return a.two_per_unit != 0; });
     const int tid = wave * 64 + (threadIdx.x & 63);
     const int buf_bytes = PATCH ? (a.halo + 1) * kHaloPitch : BM * kStepPitch;
