@@ -590,6 +590,7 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);
     const int64_t want = point ? 5 * (int64_t)compute_units / 2 : 4 / wn * (int64_t)compute_units;
     const int64_t G = 3 * (int64_t)compute_units, pairs = (pr.M + 63) / 64 * ((pr.d.k + 63) / 64);
+    const bool taps = halo == 0 && !pr.xl;
     if (2 * tiles <= want) {
         // (slices of 64 rows at least, see kMinRunRows)
         const int64_t most = std::min<int64_t>(want / tiles, red.steps / std::max(1, kMinRunRows / red.rows));
@@ -608,13 +609,16 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         c.persist = 3;
         time *= 0.95;
     } else if (!point && pr.d.k > 32 && split_lds_units(halo, 2) <= 64 &&
-               ((pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units && red.steps >= 4) ||
+               ((pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units && red.steps >= 4 &&
+                 (!taps || (pr.d.k > 64 && pr.d.r * pr.d.s > 1 && red.steps >= 16))) ||
                 (halo > 0 && pairs > 4 * (int64_t)compute_units && red.steps >= 2))) {
         // Two persistent workgroups of two waves per compute unit, whose SIMDs then have one multiplying wave each, and the tiles beyond
         // whole rounds dealt out.  Of 64 pixels and channels each, two to two and a half tiles per compute unit: 0.81 to 0.92 of the time of what the rules
-        // around this one give (patches 17 layers, channels-last 7; taps take one workgroup of four waves, 0.84, 11 layers); patches of more
-        // than four, 0.89 to 0.99 (60 layers).  With two and a half to four it is 0.99 to 1.23 of it, with fewer steps to deal out than that 0.97 to 1.1.
-        const bool taps = halo == 0 && !pr.xl;
+        // around this one give (patches 17 layers, channels-last 7); patches of more than four, 0.89 to 0.99 (60 layers).  With two and a half
+        // to four it is 0.99 to 1.23 of it, with fewer steps to deal out than that 0.97 to 1.1.
+        // Taps take one workgroup of four waves: 0.82 to 0.94 of the time, 85 layers of more than 64 channels and filters of 3x3 and more.  Not with up to
+        // 64, where two of the waves have no channel (1.27 to 1.6, 42 layers; 3x3, stride 2, 32 to 64, 56x56, 48 images, 20.1 us against 30.7), nor
+        // 1x1 (1.03 to 1.14, 72 layers), nor below 16 steps (3x3, 32 to 100, 19.8 against 22.6).
         c = wpk_conv_config{64, taps ? 128 : 64, c.bk, 1, taps ? 4 : 2, 1, 1, taps ? 1 : 2, 1, 0};
         time = 0.9 * std::min(time, split_time(pr, c, compute_units));
     } else {
