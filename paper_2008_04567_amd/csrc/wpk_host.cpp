@@ -600,6 +600,19 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         c.persist = std::min(4 / wn, 2);  // one round: whole tiles (persistent_of)
     }
     double time = split_time(pr, c, compute_units);
+    wpk_conv_config other = c;  // the best by the model
+    double least = 1e300;
+    for (int w = point ? 2 : 4; w >= 1; w /= 2)
+        for (const int slices : {1, 2, 3, 4, 5, 6, 8, 12}) {
+            if (slices > red.steps) break;
+            wpk_conv_config o = {64, 32 * w, c.bk, 1, w, slices, 1, 0, 1, 0};
+            const double t = split_time(pr, o, compute_units);
+            if (t < least) {
+                least = t;
+                other = o;
+            }
+        }
+    const bool narrow = 1.2 * least < time && other.wn == 1 && other.split_k == 1;
     if (wn <= 2 && tiles > G && tiles < (point && wn == 2 ? 5 : 3) * G && tiles % G * 12 <= G &&
         (point ? red.steps >= 2 : halo > 0 && halo <= 240 && tiles % G * 20 <= G)) {
         // Just over one or two whole rounds of three workgroups per compute unit (1x1 layers of two waves: four): the tiles
@@ -609,35 +622,22 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         c.persist = 3;
         time *= 0.95;
     } else if (!point && pr.d.k > 32 && split_lds_units(halo, 2) <= 64 &&
-               ((pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units && red.steps >= 4 &&
+               ((!narrow && pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units && red.steps >= 4 &&
                  (!taps || (pr.d.k > 64 && pr.d.r * pr.d.s > 1 && red.steps >= 16))) ||
                 (halo > 0 && pairs > 4 * (int64_t)compute_units && red.steps >= 2))) {
         // Two persistent workgroups of two waves per compute unit, whose SIMDs then have one multiplying wave each, and the tiles beyond
         // whole rounds dealt out.  Of 64 pixels and channels each, two to two and a half tiles per compute unit: 0.81 to 0.92 of the time of what the rules
         // around this one give (patches 17 layers, channels-last 7); patches of more than four, 0.89 to 0.99 (60 layers).  With two and a half
-        // to four it is 0.99 to 1.23 of it, with fewer steps to deal out than that 0.97 to 1.1.
+        // to four it is 0.99 to 1.23 of it, with fewer steps to deal out than that 0.97 to 1.1.  (narrow: where whole tiles of 32 channels are priced
+        // a sixth faster, as with 96 or 160 channels, they stay: two to two and a half tiles dealt out took 0.78 to 1.18 of it, 14 layers, half of them more.)
         // Taps take one workgroup of four waves: 0.82 to 0.94 of the time, 85 layers of more than 64 channels and filters of 3x3 and more.  Not with up to
         // 64, where two of the waves have no channel (1.27 to 1.6, 42 layers; 3x3, stride 2, 32 to 64, 56x56, 48 images, 20.1 us against 30.7), nor
         // 1x1 (1.03 to 1.14, 72 layers), nor below 16 steps (3x3, 32 to 100, 19.8 against 22.6).
         c = wpk_conv_config{64, taps ? 128 : 64, c.bk, 1, taps ? 4 : 2, 1, 1, taps ? 1 : 2, 1, 0};
         time = 0.9 * std::min(time, split_time(pr, c, compute_units));
-    } else {
-        wpk_conv_config other = c;
-        double least = 1e300;
-        for (int w = point ? 2 : 4; w >= 1; w /= 2)
-            for (const int slices : {1, 2, 3, 4, 5, 6, 8, 12}) {
-                if (slices > red.steps) break;
-                wpk_conv_config o = {64, 32 * w, c.bk, 1, w, slices, 1, 0, 1, 0};
-                const double t = split_time(pr, o, compute_units);
-                if (t < least) {
-                    least = t;
-                    other = o;
-                }
-            }
-        if (1.2 * least < time) {
-            c = other;
-            time = least;
-        }
+    } else if (1.2 * least < time) {
+        c = other;
+        time = least;
     }
     if (time > 1.1 * tiled_time(pr, tiled, compute_units) || !legal_for(pr, c)) return false;
     *out = c;

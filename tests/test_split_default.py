@@ -33,11 +33,12 @@ static const Case cases[] = {
     {L(4, 96, 69, 69, 64, 5, 5, 1, 0, 1, 1), 1, 0, 2, 6, 0},           // 45, 60
     // two to two and a half tiles per compute unit, taps: one workgroup of four waves each and the rest dealt out; not where two of the
     // waves have no channels, 1x1 filters or few steps
-    {L(14, 160, 44, 44, 96, 5, 5, 1, 2, 1, 0), 1, 4, 1, 1, 0},
+    {L(24, 160, 56, 56, 128, 5, 5, 2, 2, 1, 0), 1, 4, 1, 1, 1},
     {L(48, 32, 56, 56, 64, 3, 3, 2, 1, 1, 0), 1, 2, 1, 1, 0},          // 20.1 by waves per SIMD, 30.7 dealt out
     {L(12, 64, 57, 57, 64, 3, 3, 1, 1, 2, 0), 1, 2, 1, 1, 0},          // 24.7, 42.7
     {L(5, 224, 101, 101, 192, 1, 1, 2, 0, 1, 0), 1, 2, 1, 1, 0},       // 16.9, 24.4
     {L(64, 32, 17, 64, 100, 3, 3, 2, 1, 1, 0), 1, 4, 1, 1, 0},         // 19.8, 22.6
+    {L(31, 208, 13, 44, 96, 3, 3, 1, 1, 1, 0), 1, 1, 1, 1, 0},         // (channels of three 32-wide workgroups) 37.0, 43.5
     // single steps: nothing to deal out
     {L(21, 32, 26, 26, 864, 1, 1, 1, 0, 1, 0), 1, 2, 1, 1, 0},         // 21.5, 45.7 dealt out, 23.3 whole
 };
