@@ -316,9 +316,11 @@ int split_producers(const Problem &pr, const wpk_conv_config &cfg)
     if (!split_member(cfg)) return 0;
     const int halo = halo_positions(pr, cfg);
     if (halo > 0) {
-        // a second one wherever as many workgroups as with one fit a compute unit (twelve waves)
+        // A second one wherever as many workgroups as with one fit a compute unit (twelve waves): 0.6 to 0.95 of the time with four or more
+        // blocks of 64 positions, 0.9 to 1 with three.  Not where four workgroups fit: of three blocks one wave takes two
+        // either way, and the four second waves are in the way (one multiplying wave each, 75 layers, median 1.02, up to 1.41).
         const int fit = std::min(12 / (cfg.wn + 1), 128 / split_lds_units(halo, cfg.wn));
-        return 12 / (cfg.wn + 2) >= fit ? 2 : 1;
+        return fit < 4 && 12 / (cfg.wn + 2) >= fit ? 2 : 1;
     }
     if (pr.xl && split_taps(pr)) return cfg.wn == 4 ? 2 : 1;
     if (split_point(pr)) return cfg.wn == 4 || (cfg.wn == 2 && cfg.bk == 32) ? 2 : 1;

@@ -57,6 +57,23 @@ int main()
             return 1;
         }
     }
+    // Waves that fetch patches: two where that costs no workgroup, but for four workgroups of one multiplying wave (39.6 us with one, 49.5).
+    static const struct { wpk_conv_desc d; int wn, producers; } fetch[] = {
+        {L(7, 182, 45, 38, 160, 3, 3, 1, 1, 1, 0), 1, 1},
+        {L(7, 182, 45, 38, 160, 3, 3, 1, 1, 1, 0), 4, 2},
+        {L(4, 64, 80, 80, 64, 3, 3, 1, 1, 1, 0), 1, 2},      // (three fit)
+        {L(16, 64, 56, 56, 64, 3, 3, 1, 1, 1, 0), 2, 2},
+        {L(16, 256, 14, 14, 256, 3, 3, 1, 1, 1, 0), 2, 1},   // (four with one, three with two)
+    };
+    for (const auto &t : fetch) {
+        Problem pr;
+        const wpk_conv_config c = {64, 32 * t.wn, 16, 1, t.wn, 1, 1, 0, 1, 0};
+        if (make_problem(&t.d, &pr) != WPK_OK || halo_positions(pr, c) == 0) return 3;
+        if (split_producers(pr, c) != t.producers) {
+            printf("c %d %dx%d, %d waves: %d fetch\n", t.d.c, t.d.h, t.d.w, t.wn, split_producers(pr, c));
+            return 1;
+        }
+    }
     // Wave-split members: how slices meet follows from what the launch has to do (us, workspace and atomics, in a pass without an
     // epilogue unless stated).
     static const struct { wpk_conv_desc d; int plain, fused; } meet[] = {  // (slices; below zero: atomics)
