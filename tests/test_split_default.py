@@ -62,7 +62,7 @@ int main()
         {L(7, 182, 45, 38, 160, 3, 3, 1, 1, 1, 0), 1, 1},
         {L(7, 182, 45, 38, 160, 3, 3, 1, 1, 1, 0), 4, 2},
         {L(4, 64, 80, 80, 64, 3, 3, 1, 1, 1, 0), 1, 2},      // (three fit)
-        {L(16, 64, 56, 56, 64, 3, 3, 1, 1, 1, 0), 2, 2},
+        {L(4, 64, 80, 80, 64, 3, 3, 1, 1, 1, 0), 2, 2},
         {L(16, 256, 14, 14, 256, 3, 3, 1, 1, 1, 0), 2, 1},   // (four with one, three with two)
     };
     for (const auto &t : fetch) {
