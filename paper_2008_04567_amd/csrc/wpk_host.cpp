@@ -542,8 +542,11 @@ static double tiled_time(const Problem &pr, const wpk_conv_config &c, int comput
 //    launch is bound by memory, and four small workgroups on a compute unit are out of step with each other where two
 //    large ones fetch, multiply and store at the same time (256 to 128 channels, 56x56, 16 images: 29.5 us against 42;
 //    256 to 1024 at 14x14: 15.3 against 21.4).
-//    With up to two tiles of 64 channels per compute unit they take four waves and two that fetch, like the others (512 to 128 at 28x28:
-//    12.6 us, with two and one that fetches 16.3, two and two 15.2).
+//    With up to two tiles of 64 channels per compute unit they take four waves and two that fetch, like the others (512 to 128 at 28x28, hot:
+//    12.6 us, with two and one that fetches 16.3, two and two 15.2; 110 layers, 0.6 to 0.99 of the time), in slices only as far as each
+//    compute unit gets one workgroup (1440 to 768 at 16x16, 7 images, in 3 slices of 168 workgroups 33.1, in two waves 29.5).  Not up to 32
+//    channels (1.0 to 1.3, 7 layers), up to a quarter of a tile, where that makes eight slices and more (1.1 to 1.2, 5 layers), or where 65 to 96 channels
+//    fit three 32-wide workgroups and there are fewer than 5 / 8 of a tile (0.99 to 1.09, 5 layers).
 //  - The reduction is cut until there is about one wave per SIMD, no further: a second wave hides what a second
 //    slice's prologue and meeting cost, no more (3x3, 256 channels, 14x14, 16 images, 98 tiles: 25.5 us in 2 slices,
 //    27-30 in 1 or 3-5; 512 channels at 7x7, 52 tiles: 28.0 in 4, 28.7 in 3, 32.6 in 8).
@@ -573,7 +576,9 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     // to 224, 3x3, 12x16, 0.17 GFLOP, 14.8 against 26.7)
     const bool whole = pr.tapmajor || pr.xquad || (!pr.xl && patch_bound(pr) > 0);
     if (flops < 0.45e9 && !(pr.yl && tiled.reduce && (whole || flops >= 0.1e9))) return false;
-    const bool small_point = split_point(pr) && (pr.M + 63) / 64 * ((pr.d.k + 63) / 64) <= 2 * (int64_t)compute_units;
+    const int64_t pairs = (pr.M + 63) / 64 * ((pr.d.k + 63) / 64);
+    const bool small_point = split_point(pr) && pr.d.k > 32 && pairs <= 2 * (int64_t)compute_units && 4 * pairs > compute_units &&
+                             (pr.d.k <= 64 || pr.d.k > 96 || 8 * pairs >= 5 * (int64_t)compute_units);
     const bool point = split_point(pr) && !small_point;
     int wn = 4;
     double best = 1e300;
@@ -591,7 +596,7 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     const Reduction red = reduction_of(pr, c);
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((pr.d.k + c.bn - 1) / c.bn);
     const int64_t want = point ? 5 * (int64_t)compute_units / 2 : 4 / wn * (int64_t)compute_units;
-    const int64_t G = 3 * (int64_t)compute_units, pairs = (pr.M + 63) / 64 * ((pr.d.k + 63) / 64);
+    const int64_t G = 3 * (int64_t)compute_units;
     const bool taps = halo == 0 && !pr.xl;
     if (2 * tiles <= want) {
         // (slices of 64 rows at least, see kMinRunRows)
@@ -608,6 +613,7 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         for (const int slices : {1, 2, 3, 4, 5, 6, 8, 12}) {
             if (slices > red.steps) break;
             wpk_conv_config o = {64, 32 * w, c.bk, 1, w, slices, 1, 0, 1, 0};
+            if (small_point && w == 4 && slices > 1 && (pr.M + 63) / 64 * ((pr.d.k + 127) / 128) * slices > compute_units) break;
             const double t = split_time(pr, o, compute_units);
             if (t < least) {
                 least = t;

@@ -39,6 +39,12 @@ static const Case cases[] = {
     {L(5, 224, 101, 101, 192, 1, 1, 2, 0, 1, 0), 1, 2, 1, 1, 0},       // 16.9, 24.4
     {L(64, 32, 17, 64, 100, 3, 3, 2, 1, 1, 0), 1, 4, 1, 1, 0},         // 19.8, 22.6
     {L(31, 208, 13, 44, 96, 3, 3, 1, 1, 1, 0), 1, 1, 1, 1, 0},         // (channels of three 32-wide workgroups) 37.0, 43.5
+    // 1x1, up to two tiles: two fetching waves, but not for few channels, many slices or a second round
+    {L(16, 512, 28, 28, 128, 1, 1, 1, 0, 1, 0), 1, 4, 1, 1, 0},        // 16.3 with one, 12.6
+    {L(20, 896, 10, 10, 128, 1, 1, 1, 0, 1, 0), 1, 2, 4, 4, 0},        // 13.8, 16.6 in 8 slices
+    {L(10, 992, 28, 28, 32, 1, 1, 1, 0, 1, 0), 1, 1, 5, 5, 0},         // 14.8, 16.1
+    {L(12, 1344, 14, 14, 96, 1, 1, 1, 0, 1, 0), 1, 1, 5, 5, 0},        // 15.2, 16.5
+    {L(7, 1440, 16, 16, 768, 1, 1, 1, 0, 1, 0), 1, 4, 1, 1, 0},        // 29.5, 33.1 in 3 slices
     // single steps: nothing to deal out
     {L(21, 32, 26, 26, 864, 1, 1, 1, 0, 1, 0), 1, 2, 1, 1, 0},         // 21.5, 45.7 dealt out, 23.3 whole
 };
