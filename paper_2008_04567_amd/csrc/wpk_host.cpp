@@ -577,6 +577,12 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     const bool whole = pr.tapmajor || pr.xquad || (!pr.xl && patch_bound(pr) > 0);
     if (flops < 0.45e9 && !(pr.yl && tiled.reduce && (whole || flops >= 0.1e9))) return false;
     const int64_t pairs = (pr.M + 63) / 64 * ((pr.d.k + 63) / 64);
+    // (and those of 1x1 filters fetched pixel by pixel, where there are many tiles of few steps: 1.0 to 1.45 of the time of the tiled members up to seven
+    // steps of [N][C][H][W], 26 layers, 0.86 to 1.0 beyond, 20; channels-last up to two, 0.97 to 1.07; and of 17 to 23 channels and 5x5, 1.06 to 1.17, 3)
+    if (!whole && !split_point(pr) && pairs > 2 * (int64_t)compute_units) {
+        const int64_t steps = split_rows(pr) / 32, RS = (int64_t)pr.d.r * pr.d.s;
+        if (RS == 1 ? steps < (pr.xl ? 3 : 8) : !pr.xl && pr.d.c < 24 && RS <= 25) return false;
+    }
     const bool small_point = split_point(pr) && pr.d.k > 32 && pairs <= 2 * (int64_t)compute_units && 4 * pairs > compute_units &&
                              (pr.d.k <= 64 || pr.d.k > 96 || 8 * pairs >= 5 * (int64_t)compute_units);
     const bool point = split_point(pr) && !small_point;

@@ -39,6 +39,12 @@ static const Case cases[] = {
     {L(5, 224, 101, 101, 192, 1, 1, 2, 0, 1, 0), 1, 2, 1, 1, 0},       // 16.9, 24.4
     {L(64, 32, 17, 64, 100, 3, 3, 2, 1, 1, 0), 1, 4, 1, 1, 0},         // 19.8, 22.6
     {L(31, 208, 13, 44, 96, 3, 3, 1, 1, 1, 0), 1, 1, 1, 1, 0},         // (channels of three 32-wide workgroups) 37.0, 43.5
+    // padded channels, pixel by pixel: not for 1x1 filters of few steps and many tiles
+    {L(27, 44, 64, 64, 384, 1, 1, 2, 0, 1, 0), 0, 0, 1, 1, 0},         // 19.6, 28.4
+    {L(33, 87, 51, 51, 512, 1, 1, 1, 0, 1, 0), 0, 0, 1, 1, 0},         // 135, 145
+    {L(2, 23, 82, 82, 480, 5, 5, 1, 2, 1, 0), 0, 0, 1, 1, 0},          // 73.5, 79.4
+    {L(20, 320 + 1, 45, 45, 256, 1, 1, 1, 0, 1, 0), 1, 4, 1, 1, 0},    // (eleven steps)
+    {L(8, 329, 35, 35, 256, 1, 1, 1, 0, 1, 3), 1, 2, 1, 1, 2},         // (channels-last) 31.6, 23.2
     // 1x1, up to two tiles: two fetching waves, but not for few channels, many slices or a second round
     {L(16, 512, 28, 28, 128, 1, 1, 1, 0, 1, 0), 1, 4, 1, 1, 0},        // 16.3 with one, 12.6
     {L(20, 896, 10, 10, 128, 1, 1, 1, 0, 1, 0), 1, 2, 4, 4, 0},        // 13.8, 16.6 in 8 slices
