@@ -565,8 +565,12 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     const double flops = 2.0 * pr.M * pr.d.k * pr.CRS;
     if (strip_depths(pr)) {
         const wpk_conv_desc &d = pr.d;
-        // (nor where y leaves a lane four bytes at a time: 2 to 130 channels, channels-last, 403 us against 273)
-        if (flops < 0.45e9 || (pr.yl && d.k % 4)) return false;
+        // Only where half of what is multiplied is no padding, S to eight and C * R to the depths: filters of five columns and more (two to four: 1.04
+        // and 0.96 of the time of the tiled members, up to 1.41, 38 layers; five to eight 0.69 to 0.80, 188 layers).  Nor with short reductions and a
+        // large y, which both forms wait for (up to ten octets, 100 MB and more: 0.57 to 1.30, 18 layers), nor where y leaves a lane four bytes
+        // at a time (2 to 130 channels, channels-last, 403 us against 273).
+        const int depths = strip_depths(pr);
+        if (flops < 0.45e9 || (pr.yl && d.k % 4) || d.s < 5 || pr.CRS < 8 * depths || (depths <= 5 && pr.y_elems >= 25000000)) return false;
         *out = wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
         const double us = strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w).us;
         return 1.1 * us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);

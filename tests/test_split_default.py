@@ -39,6 +39,12 @@ static const Case cases[] = {
     {L(5, 224, 101, 101, 192, 1, 1, 2, 0, 1, 0), 1, 2, 1, 1, 0},       // 16.9, 24.4
     {L(64, 32, 17, 64, 100, 3, 3, 2, 1, 1, 0), 1, 4, 1, 1, 0},         // 19.8, 22.6
     {L(31, 208, 13, 44, 96, 3, 3, 1, 1, 1, 0), 1, 1, 1, 1, 0},         // (channels of three 32-wide workgroups) 37.0, 43.5
+    // strips: where little of them is padding
+    {L(16, 3, 224, 224, 64, 7, 7, 2, 3, 1, 0), 1, 2, 1, 1, 0},         // 44.3, 28.4
+    {L(32, 3, 112, 112, 64, 5, 5, 1, 2, 1, 3), 1, 2, 1, 1, 0},
+    {L(32, 6, 112, 112, 256, 3, 3, 2, 1, 1, 0), 0, 0, 1, 1, 0},        // 46.7, 66.0
+    {L(32, 3, 112, 112, 32, 4, 4, 1, 2, 1, 0), 0, 0, 1, 1, 0},         // 25.8, 29.7
+    {L(32, 6, 160, 160, 96, 1, 7, 1, 0, 1, 1), 0, 0, 1, 1, 0},         // 157, 183
     // padded channels, pixel by pixel: not for 1x1 filters of few steps and many tiles
     {L(27, 44, 64, 64, 384, 1, 1, 2, 0, 1, 0), 0, 0, 1, 1, 0},         // 19.6, 28.4
     {L(33, 87, 51, 51, 512, 1, 1, 1, 0, 1, 0), 0, 0, 1, 1, 0},         // 135, 145
