@@ -65,14 +65,15 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restri
 }
 
 // Where row kk of the split members' reduction comes from: its place among the C*R*S rows of the source, or
-// -1 for a padding row.  With RS > 0 the rows run (c / 32, r, s, c % 32), with RS = -S (c, r, s) with s padded to eight, else in
-// the source's order.
-__device__ inline int split_source_row(int kk, int C, int CRS, int RS)
+// -1 for a padding row.  The first `strips` rows run (c, r, s) with s padded to eight; the others with RS > 0 (c / 32, r, s, c % 32), else
+// in the source's order.
+__device__ inline int split_source_row(int kk, int C, int CRS, int RS, int strips, int S)
 {
-    if (RS < 0) {
-        const int row = (kk >> 3) * -RS + (kk & 7);
-        return (kk & 7) < -RS && row < CRS ? row : -1;
+    if (kk < strips) {
+        const int row = (kk >> 3) * S + (kk & 7);
+        return (kk & 7) < S && row < CRS ? row : -1;
     }
+    kk -= strips;
     if (RS == 0) return kk < CRS ? kk : -1;
     const int c32 = kk / (32 * RS), t = kk - c32 * 32 * RS, c = c32 * 32 + (t & 31);
     // (sixteen rows at a time: the two halves of the 32 channels follow each other for every tap)
@@ -82,7 +83,7 @@ __device__ inline int split_source_row(int kk, int C, int CRS, int RS)
 // w[K][CRS] -> [depths of 16 rows][Kpad/32][3 parts][64 lanes][8 bf16], zero padded: what lane l of a wave feeds the
 // bf16 MFMA of one depth and 32-channel block is channel l % 32, rows (l / 32)*8 .. +7.  Parts: see split_weight.
 __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict__ w, v4u *__restrict__ wp, int K,
-                                                         int C, int CRS, int depths, int blocks, int RS)
+                                                         int C, int CRS, int depths, int blocks, int RS, int strips, int S)
 {
     const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6), kb = blockIdx.y;
     if (t >= depths) return;
@@ -90,7 +91,7 @@ __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict
     unsigned part[3][4];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int row = split_source_row(t * 16 + (lane >> 5) * 8 + j, C, CRS, RS);
+        const int row = split_source_row(t * 16 + (lane >> 5) * 8 + j, C, CRS, RS, strips, S);
         const float v = k < K && row >= 0 ? w[(size_t)k * CRS + row] : 0.0f;
         unsigned v3[3];
         split_weight(v, v3);
@@ -152,7 +153,7 @@ __global__ void __launch_bounds__(256) unpack_weights_kernel(const void *__restr
         const int k = (int)(i / CRS), row = (int)(i - (long long)k * CRS);
         const int c = RS > 0 ? row / RS : 0, rs = RS > 0 ? row - c * RS : 0;
         if (split) {
-            const int kk = RS > 0 ? (c / 32 * RS + rs) * 32 + c % 32 : RS < 0 ? row / -RS * 8 + row % -RS : row;
+            const int kk = RS > 0 ? (c / 32 * RS + rs) * 32 + c % 32 : row;
             const int lane = (kk >> 3 & 1) * 32 + (k & 31);
             const unsigned short *p = (const unsigned short *)packed +
                                       (((size_t)(kk >> 4) * (Kpad / 32) + k / 32) * 3 * 64 + lane) * 8 + (kk & 7);
@@ -480,10 +481,12 @@ static size_t packed_bytes(const Problem &pr, bool split)
     return split ? (size_t)split_rows(pr) * pr.Kpad * kSplitWeightBytes : (size_t)pr.CRSpad * pr.Kpad * sizeof(float);
 }
 
-// The order of the packed rows, as split_source_row and pack_weights_kernel have it.
+// Of these, the bytes in the strips' order that lie ahead of the others.
+static size_t strip_bytes(const Problem &pr) { return (size_t)strip_depths(pr) * 16 * pr.Kpad * kSplitWeightBytes; }
+
+// The order of the packed rows (but for strips), as split_source_row and pack_weights_kernel have it.
 static int packed_order(const Problem &pr, bool split)
 {
-    if (split && strip_depths(pr)) return -pr.d.s;
     return (split ? split_taps(pr) : pr.xquad || pr.tapmajor) ? pr.d.r * pr.d.s : 0;
 }
 
@@ -491,18 +494,18 @@ static int pack_weights(const Problem &pr, bool split, const float *w, float *wp
 {
     const int RS = packed_order(pr, split);
     if (split) {
-        const int blocks = pr.Kpad / 32, taps = RS > 0 ? RS : 1;
+        const int blocks = pr.Kpad / 32, taps = RS > 0 ? RS : 1, strips = strip_depths(pr) * 16;
         const int all_octets = (int)(split_rows(pr) / taps / 8), octets = std::max(1, 8 / taps);
         const int chunks = (all_octets + octets - 1) / octets;
         // a block per compute unit, or a single tap (see there); at most 64 KB of LDS
-        if (RS >= 0 && (taps == 1 || (int64_t)chunks * blocks >= 256) && taps < 64) {
+        if (strips == 0 && (taps == 1 || (int64_t)chunks * blocks >= 256) && taps < 64) {
             hipLaunchKernelGGL(pack_split_staged_kernel, dim3(chunks, blocks), dim3(256),
                                32 * (octets * 8 * taps + 1) * sizeof(float), st, w, (v4u *)wp, pr.d.k,
                                RS > 0 ? pr.d.c : pr.CRS, taps, blocks, octets, all_octets);
         } else {
             const int depths = (int)(split_rows(pr) / 16);
             hipLaunchKernelGGL(pack_split_kernel, dim3((depths + 3) / 4, blocks), dim3(256), 0, st, w, (v4u *)wp, pr.d.k,
-                               pr.d.c, pr.CRS, depths, blocks, RS);
+                               pr.d.c, pr.CRS, depths, blocks, RS, strips, pr.d.s);
         }
     } else {
         dim3 grid(pr.CRSpad / 32, pr.Kpad / 32);
@@ -606,7 +609,9 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     if (vi < 0) return WPK_E_NO_CONFIG;
     const wpk_conv_desc &d = pr.d;
     IgemmArgs a;
-    a.x = x; a.wp = wp; a.y = y; a.ktab = ktab;
+    const bool strip = runs_strip(pr, cfg);
+    const size_t ahead = split_member(cfg) && !strip ? strip_bytes(pr) : 0;  // (weights of the other order)
+    a.x = x; a.wp = (const float *)((const char *)wp + ahead); a.y = y; a.ktab = ktab;
     a.RS = d.r * d.s;
     a.HW4 = pr.xl ? 4 : d.h * d.w * 4;  // byte stride between channels of x
     const Reduction red = reduction_of(pr, cfg);
@@ -619,7 +624,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.dil_h = d.dil_h; a.dil_w = d.dil_w;
     a.M = (int32_t)pr.M; a.PQ = pr.P * pr.Q; a.HW = d.h * d.w; a.CRS = pr.CRS; a.Kpad = pr.Kpad;
     a.nsteps = red.steps;
-    a.halo = !split_member(cfg) ? 0 : strip_depths(pr) ? -2 : split_point(pr) ? -1 : halo_positions(pr, cfg);
+    a.halo = !split_member(cfg) ? 0 : strip ? -2 : split_point(pr) ? -1 : halo_positions(pr, cfg);
     a.producers = (int16_t)split_producers(pr, cfg);
     // slices of ceil(nsteps/split_k) steps; launch only as many as are not empty
     a.steps_per_split = (a.nsteps + cfg.split_k - 1) / cfg.split_k;
@@ -635,7 +640,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     if (pr.yl && d.k % 4 == 0 && ((uintptr_t)y & 15) == 0 && ((uintptr_t)epi.res & 15) == 0 &&
         ((uintptr_t)epi.bias & 15) == 0)
         a.yl = 2;
-    a.w_bytes = (uint32_t)packed_bytes(pr, split_member(cfg));
+    a.w_bytes = (uint32_t)(strip ? strip_bytes(pr) : packed_bytes(pr, split_member(cfg)) - ahead);
     a.y_bytes = (uint32_t)(pr.y_elems * 4);
     a.persist = persist;
     a.grid_persist = persist * (g_cus > 0 ? g_cus : 256);
@@ -1008,12 +1013,13 @@ static int plan_need_weights(wpk_plan::Layer &L, const wpk_conv_config &cfg)
         return WPK_OK;
     }
     const int RS = packed_order(L.pr, s == 0);  // (of the form at hand)
+    const void *const from = (const char *)L.wp[1 - s] + (s == 0 ? strip_bytes(L.pr) : 0);
     int rc = WPK_OK;
     hipError_t e = hipDeviceSynchronize();
     if (e == hipSuccess) e = hipMalloc((void **)&plain, (size_t)L.pr.w_elems * sizeof(float));
     if (e == hipSuccess) {
         hipLaunchKernelGGL(unpack_weights_kernel, dim3((unsigned)std::min<int64_t>(4096, (L.pr.w_elems + 255) / 256)),
-                           dim3(256), 0, nullptr, (const void *)L.wp[1 - s], plain, L.pr.d.k, L.pr.d.c, L.pr.CRS,
+                           dim3(256), 0, nullptr, from, plain, L.pr.d.k, L.pr.d.c, L.pr.CRS,
                            L.pr.Kpad, RS, 1 - s);
         rc = pack_weights(L.pr, s != 0, plain, packed, nullptr);
         e = hipDeviceSynchronize();

@@ -303,7 +303,9 @@ int strip_depths(const Problem &pr)
     const wpk_conv_desc &d = pr.d;
     int pairs;
     if (pr.tapmajor || pr.xquad || !pr.tiled_ok) return 0;
-    return strip_fits(d.c, pr.Q, d.r, d.s, d.stride_w, d.dil_h, d.dil_w, &pairs);
+    const int depths = strip_fits(d.c, pr.Q, d.r, d.s, d.stride_w, d.dil_h, d.dil_w, &pairs);
+    // (the weights' offsets, of both orders)
+    return ((int64_t)depths * 16 + pr.CRSpad) * pr.Kpad * kSplitWeightBytes <= kMaxSplitBytes ? depths : 0;
 }
 
 int split_lds_units(int halo, int wn)
@@ -330,8 +332,7 @@ int split_producers(const Problem &pr, const wpk_conv_config &cfg)
 Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg)
 {
     if (halo_positions(pr, cfg) > 0) return Reduction{(pr.d.c + 15) / 16, 9 * 16};
-    if (split_member(cfg))
-        if (const int depths = strip_depths(pr)) return Reduction{1, depths * 16};  // (strips have the whole of it)
+    if (runs_strip(pr, cfg)) return Reduction{1, strip_depths(pr) * 16};  // (strips have the whole of it)
     const int rows = split_member(cfg) ? 32 : cfg.bk;
     if (split_member(cfg) && split_taps(pr)) return Reduction{(int32_t)(split_rows(pr) / 32), 32};
     return Reduction{(pr.CRS + rows - 1) / rows, rows};
@@ -343,7 +344,6 @@ Reduction reduction_of(const Problem &pr, const wpk_conv_config &cfg)
 int persistent_of(const Problem &pr, const wpk_conv_config &cfg, int compute_units)
 {
     if (cfg.persist == 0 || !split_member(cfg)) return cfg.persist;
-    if (strip_depths(pr)) return 0;
     const int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
     const int64_t G = (int64_t)cfg.persist * (compute_units > 0 ? compute_units : 256);
     return tiles <= G && 2 * tiles > G ? 0 : cfg.persist;
@@ -354,10 +354,11 @@ wpk_conv_config same_launch(const Problem &pr, const wpk_conv_config &cfg, int c
     wpk_conv_config c = cfg;
     if (!split_member(cfg)) return c;
     c.stages = 1;
-    if (strip_depths(pr)) return wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
+    if (runs_strip(pr, cfg)) return wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
     wpk_conv_config other = c;
     other.bk = 16;
-    if (halo_positions(pr, other) == halo_positions(pr, c) && split_producers(pr, other) == split_producers(pr, c)) c.bk = 16;
+    if (strip_depths(pr)) c.bk = 32;  // (row by row; what is a round of whole tiles has neither slices nor persistent workgroups below)
+    else if (halo_positions(pr, other) == halo_positions(pr, c) && split_producers(pr, other) == split_producers(pr, c)) c.bk = 16;
     if (c.persist > 0 && persistent_of(pr, c, compute_units) == 0) {
         c.persist = 0;
         c.reduce = 0;

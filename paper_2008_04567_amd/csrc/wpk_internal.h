@@ -234,12 +234,18 @@ WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int str
 // zero, and what is fetched for it lies in x (wpk_split.h): what is finite adds nothing, and what is not has the tile
 // computed again.
 inline bool split_taps(const Problem &pr) { return pr.tapmajor || pr.xquad || pr.padtaps; }
-// MFMA depths of pr on the strip form of the split members, 0 where they run it otherwise.
+// MFMA depths of pr on the strip form of the split members, 0 where it does not fit that.
 int strip_depths(const Problem &pr);
-// Rows of the reduction as the split members pack it.
+// Whether cfg runs pr in strips.  Where pr fits them, the split members' configurations of K-step 16 without slices or persistent
+// workgroups do (a strip has the whole reduction, and a workgroup its own strips); the others go row by row, as the caller asked for.
+inline bool runs_strip(const Problem &pr, const wpk_conv_config &cfg)
+{
+    return split_member(cfg) && cfg.bk == 16 && cfg.split_k == 1 && cfg.persist == 0 && strip_depths(pr) > 0;
+}
+// Rows of the reduction as the split members pack it: where pr fits strips, those in the strips' order and then those in the source's.
 inline int64_t split_rows(const Problem &pr)
 {
-    if (const int depths = strip_depths(pr)) return depths * 16;
+    if (const int depths = strip_depths(pr)) return depths * 16 + pr.CRSpad;
     return split_taps(pr) ? (int64_t)((pr.d.c + 31) / 32 * 32) * pr.d.r * pr.d.s : pr.CRSpad;
 }
 // Whether a split member fetches pr's x four neighbouring pixels at a time: 1x1 filters on [N][C][H][W] in the order of taps,

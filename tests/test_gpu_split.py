@@ -283,14 +283,17 @@ def test_plan_moves_its_weights_between_the_two_packed_forms():
     torch, dev = torch_dev()
     for layer in (W.layer("mv_tap", 2, 64, 10, 72, 3, 1, 1, x_dist="u11", seed=60),
                   W.layer("mv_patch", 2, 24, 10, 72, 3, 1, 1, x_dist="u11", seed=62),
-                  W.layer("mv_rows", 2, 20, 10, 72, 3, 1, 1, x_dist="u11", seed=61)):
+                  W.layer("mv_rows", 2, 20, 10, 72, 3, 1, 1, x_dist="u11", seed=61),
+                  W.layer("mv_strip", 2, 3, 20, 72, 7, 2, 3, x_dist="u11", seed=64),
+                  W.layer("mv_strip_c22", 2, 22, 10, 40, (1, 3), 1, (0, 1), x_dist="u11", seed=65)):
         desc = B.make_desc(layer)
         x, w = W.make_inputs(layer)
         xd, wd = to_dev(x), to_dev(w)
         shape = (layer["n"], layer["k"]) + B.conv_out_shape(desc)
         a, b = torch.empty(shape, device=dev), torch.empty(shape, device=dev)
-        tiled, split = B.make_config(64, 64, 32, 2, 2), cfg(2, 32)
-        for first, second in ((tiled, split), (split, tiled)):
+        tiled, split, other = B.make_config(64, 64, 32, 2, 2), cfg(2, 32), cfg(2, 16)
+        # (other: patches, or strips, which have an order of their own beside that of the rows)
+        for first, second in ((tiled, split), (split, tiled), (tiled, other), (other, tiled), (split, other), (other, split)):
             plan = B.Plan([desc])
             plan.set_layer_config(0, first)
             plan.set_weights(0, wd)

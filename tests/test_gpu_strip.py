@@ -43,6 +43,16 @@ def test_strips(layer):
         check_layout(layer, layout, cfg(2, 16), what="%s layout %d" % (layer["name"], layout))
 
 
+@pytest.mark.parametrize("kw", [dict(bk=32), dict(bk=32, split_k=3), dict(bk=16, split_k=2), dict(bk=16, split_k=2, reduce=1),
+                                dict(bk=16, persist=1), dict(bk=32, persist=3, reduce=1)], ids=str)
+def test_row_by_row_where_strips_fit(kw):
+    """Other configurations than the strips' run as asked for: slices, persistent workgroups and any number of waves, row by row."""
+    for layer in (STRIP[0], STRIP[2], STRIP[-2]):
+        for wn in (1, 2, 4):
+            for layout in (0, 3):
+                check_layout(layer, layout, cfg(wn, **kw), what="%s %r wn%d layout %d" % (layer["name"], kw, wn, layout))
+
+
 # One and two fetching waves of 1x1 layers (K-steps of 16 and 32), one and two workgroups on a compute unit (the second one's
 # waves change roles) and more; patches of more than 256 positions, fetched by two waves.
 ROLES = [

@@ -150,15 +150,17 @@ using namespace wpk;
 int main()
 {
     srand(3);
-    long points = 0, launches = 0;
-    for (int it = 0; it < 60; ++it) {
+    long points = 0, launches = 0, strips = 0, rows = 0;
+    for (int it = 0; it < 90; ++it) {
         auto pick = [](int lo, int hi) { return lo + rand() % (hi - lo + 1); };
         const int r = rand() % 2 ? 3 : pick(1, 5);
-        wpk_conv_desc d = {pick(1, 16), rand() % 2 ? 32 * pick(1, 20) : pick(1, 300), pick(r, 60), pick(r, 60), pick(1, 600), r, r,
+        wpk_conv_desc d = {pick(1, 16), it >= 60 ? pick(1, 7) : rand() % 2 ? 32 * pick(1, 20) : pick(1, 300), pick(r, 60), pick(r, 60), pick(1, 600), r, r,
                            1, 1, r / 2, r / 2, 1, 1, WPK_F32, rand() % 4};
         Problem pr;
         if (make_problem(&d, &pr) != WPK_OK || !pr.tiled_ok) continue;
         std::set<int> ids;
+        const wpk_conv_config strip = {64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
+        const int strip_id = wpk_config_id(&strip);
         for (int id = 0;; ++id) {
             wpk_conv_config c;
             if (wpk_config_from_id(id, &c) != WPK_OK) break;
@@ -171,6 +173,14 @@ int main()
             }
             ++points;
             ids.insert(wpk_config_id(&s));
+            // (strips are one launch, whose workgroups follow from the layer)
+            if (runs_strip(pr, c) != runs_strip(pr, s)) return 5;
+            if (runs_strip(pr, c)) {
+                ++strips;
+                if (wpk_config_id(&s) != strip_id) return 6;
+                continue;
+            }
+            rows += strip_depths(pr) > 0;
             const Reduction a = reduction_of(pr, c), b = reduction_of(pr, s);
             const int pa = (a.steps + c.split_k - 1) / c.split_k, pb = (b.steps + s.split_k - 1) / s.split_k;
             const FixupNeed fa = fixup_need(pr, c, 256), fb = fixup_need(pr, s, 256);
@@ -183,8 +193,8 @@ int main()
         }
         launches += ids.size();
     }
-    printf("%ld points, %ld launches\n", points, launches);
-    return points > 2 * launches && launches > 500 ? 0 : 4;
+    printf("%ld points, %ld launches, %ld in strips, %ld row by row instead\n", points, launches, strips, rows);
+    return points > 2 * launches && launches > 500 && strips > 50 && rows > 1000 ? 0 : 4;
 }
 """
 

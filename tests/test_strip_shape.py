@@ -28,7 +28,7 @@ int main()
         const int per_image = (pr.P + s.rows - 1) / s.rows, groups = (d.k + 32 * s.waves_c - 1) / (32 * s.waves_c);
         bool bad = s.depths != depths || 2 * depths < d.c * d.r || d.s > 8 || s.rows < 1 || s.lds > 78 * 1024 ||
                    s.lds < d.c * in_rows * line || per_image * s.rows < pr.P || (per_image - 1) * s.rows >= pr.P ||
-                   s.per_group < 1 || s.per_group > groups || split_rows(pr) != depths * 16 ||
+                   s.per_group < 1 || s.per_group > groups || split_rows(pr) != depths * 16 + pr.CRSpad ||
                    groups * 32 * s.waves_c > pr.Kpad;
         // the last byte that the octet of any pixel, filter row and channel reaches
         const int q = (pr.Q - 1) * d.stride_w, words = d.stride_w % 2 ? 5 : 4;
@@ -39,7 +39,8 @@ int main()
         // every column that a tap of the last pixel reads is one that the lanes fetch
         bad = bad || q + d.s > 2 * s.pairs;
         const wpk_conv_config c = {64, 64, 16, 1, 2, 1, 1, 0, 1, 0}, e = {64, 128, 32, 1, 4, 1, 1, 2, 1, 0};
-        bad = bad || persistent_of(pr, e, 256) != 0 || fixup_need(pr, c, 256).bytes != 0 || reduction_of(pr, c).steps != 1;
+        bad = bad || !runs_strip(pr, c) || runs_strip(pr, e) || fixup_need(pr, c, 256).bytes != 0 || reduction_of(pr, c).steps != 1 ||
+              reduction_of(pr, e).steps != (pr.CRS + 31) / 32;
         if (bad) {
             printf("n %d c %d h %d w %d k %d r %d s %d stride %d %d: rows %d pairs %d lds %d\n", d.n, d.c, d.h, d.w, d.k, d.r, d.s,
                    d.stride_h, d.stride_w, s.rows, s.pairs, s.lds);
