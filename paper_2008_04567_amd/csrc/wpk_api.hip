@@ -38,6 +38,7 @@ static const LaunchFn kLaunch[] = {
 #include WPK_VARIANTS_FILE
 };
 #undef WPK_VARIANT
+hipError_t launch_strip(const IgemmArgs &, const StripShape &, hipStream_t);  // wpk_strip.h
 
 // ---- helper kernels ---------------------------------------------------------------------------------
 // w[K][CRS] -> wp[CRSpad/4][Kpad][4] (element (kk, k) at ((kk/4)*Kpad + k)*4 + kk%4), zero padded,
@@ -705,7 +706,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
             }
         }
     }
-    WPK_HIP(kLaunch[vi](a, st));
+    WPK_HIP(strip ? launch_strip(a, strip_shape(pr, g_cus), st) : kLaunch[vi](a, st));
     if (shared_by_atomics) return run_epilogue(pr, epi, y, st);
     return WPK_OK;
 }
@@ -728,6 +729,7 @@ static int get_prepared(const Problem &pr, Prepared **out, hipStream_t st)
         Prepared p{pr, nullptr};
         int rc = upload_tap_table(pr, &p.ktab, st);
         if (rc != WPK_OK) return rc;
+        prepare_strip(&p.pr, g_cus);
         it = g_prepared.emplace(key, p).first;
     }
     *out = &it->second;
@@ -775,7 +777,7 @@ static int fwd_with(const Problem &pr, const wpk_conv_config &cfg, const float *
         rc = fixup_reserve(g_fixup, (size_t)need.bytes);
         if (rc != WPK_OK) return rc;
     }
-    return run_config(pr, cfg, prep->ktab, x, wp, y, &g_fixup, st, epi);
+    return run_config(prep->pr, cfg, prep->ktab, x, wp, y, &g_fixup, st, epi);
 }
 
 // ---- timing protocol of the tuner ------------------------------------------------------------------
@@ -1315,6 +1317,7 @@ int wpk_conv_tune_ex(const wpk_conv_desc *d, const wpk_tune_options *opt_in, int
     auto t_start = std::chrono::steady_clock::now();
     TuneCtx t;
     t.pr = pr;
+    prepare_strip(&t.pr, g_cus);
     if (opt_in) t.opt = *opt_in; else wpk_tune_default_options(&t.opt);
     t.st = nullptr; t.e0 = t.e1 = nullptr;
     t.x = t.w = t.wp[0] = t.wp[1] = t.y = t.yref = t.dref = nullptr;
@@ -1592,6 +1595,7 @@ static int layer_runtime_us(const wpk_conv_desc *d, int32_t tune, double *us)
     }
     TuneCtx t;
     t.pr = pr;
+    prepare_strip(&t.pr, g_cus);
     wpk_tune_default_options(&t.opt);
     t.opt.reps = 3;
     t.st = nullptr; t.e0 = t.e1 = nullptr;
@@ -1715,6 +1719,7 @@ int wpk_conv_plan(const wpk_conv_desc *layers, int32_t n_layers, int32_t tune, w
             }
         }
         L.unique = it->second;
+        prepare_strip(&L.pr, g_cus);
         plan_choose(L.pr, &L.cfg, &L.cfg_fused);
         rc = plan_need_weights(L, L.cfg);
         if (rc == WPK_OK) rc = plan_need_weights(L, L.cfg_fused);
@@ -1840,6 +1845,7 @@ int wpk_plan_set_pipeline(wpk_plan *plan, int32_t ways)
             int rc = make_part(L.pr, h == 0 ? (L.pr.d.n + 1) / 2 : L.pr.d.n / 2, &L.half[h]);
             if (rc != WPK_OK) return rc;
             if (L.direct) continue;
+            prepare_strip(&L.half[h], g_cus);
             plan_choose(L.half[h], &L.half_cfg[h], &L.half_cfg_fused[h]);
             rc = plan_need_weights(L, L.half_cfg[h]);
             if (rc == WPK_OK) rc = plan_need_weights(L, L.half_cfg_fused[h]);

@@ -151,6 +151,7 @@ int make_problem(const wpk_conv_desc *d, Problem *out)
     pr.tiled_ok = d->r <= kMaxFilterRows && d->s <= kMaxFilterCols &&
                   pr.x_elems * 4 + bias <= kMaxTiledBytes &&
                   pr.y_elems * 4 <= kMaxTiledBytes && (int64_t)pr.CRSpad * pr.Kpad * 4 <= kMaxTiledBytes;
+    pr.strip = StripShape();
     pr.padtaps = pads_to_taps(pr);
     *out = pr;
     return WPK_OK;
@@ -269,11 +270,13 @@ static int strip_fits(int C, int Q, int R, int S, int stride_w, int dil_h, int d
 // A strip's rows: as few as keep all compute units busy with as little filling as possible.  The cost of a choice, in cycles, from
 // what the kernel was measured to take: a workgroup's start and end, a row of x (per 64 columns / 2), a block of 32 pixels by 32
 // channels; two workgroups share a compute unit and its matrix pipes.
-StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stride_h, int stride_w, int dil_h, int dil_w)
+static StripShape price_strip(const Problem &pr, int compute_units)
 {
+    const wpk_conv_desc &d = pr.d;
+    const int N = d.n, C = d.c, P = pr.P, Q = pr.Q, K = d.k, R = d.r, stride_h = d.stride_h, dil_h = d.dil_h;
     StripShape best = {0, 0, 0, 0, 0, 0, 0.0};
     int pairs;
-    const int depths = strip_fits(C, Q, R, S, stride_w, dil_h, dil_w, &pairs);
+    const int depths = strip_fits(C, Q, R, d.s, d.stride_w, dil_h, d.dil_w, &pairs);
     if (depths == 0) return best;
     const int waves_c = K > 64 ? 4 : K > 32 ? 2 : 1, groups = (K + 32 * waves_c - 1) / (32 * waves_c);
     double least = 1e300;
@@ -287,7 +290,7 @@ StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stri
             if (work > 0x7fffffff) continue;
             const double fill = 8000.0 + lines * ((pairs + 63) / 64) * 60.0;
             const double multiply = per * (1500.0 + wave_blocks * (depths * 225.0 + 1900.0));
-            const double units = 256.0;
+            const double units = compute_units > 0 ? compute_units : 256;
             const double cost = ceil(work / (2 * units)) * fill + std::max(0.62 * ceil(work / units), 1.0) * multiply;
             if (cost < least) {
                 least = cost;
@@ -296,6 +299,16 @@ StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stri
         }
     }
     return best;
+}
+
+StripShape strip_shape(const Problem &pr, int compute_units)
+{
+    return pr.strip.depths ? pr.strip : price_strip(pr, compute_units);
+}
+
+void prepare_strip(Problem *pr, int compute_units)
+{
+    if (strip_depths(*pr)) pr->strip = strip_shape(*pr, compute_units);
 }
 
 int strip_depths(const Problem &pr)
@@ -573,8 +586,7 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         const int depths = strip_depths(pr);
         if (flops < 0.45e9 || (pr.yl && d.k % 4) || d.s < 5 || pr.CRS < 8 * depths || (depths <= 5 && pr.y_elems >= 25000000)) return false;
         *out = wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
-        const double us = strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w).us;
-        return 1.1 * us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);
+        return 1.1 * strip_shape(pr, compute_units).us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);
     }
     if (!split_taps(pr)) return false;
     // (padded channels, but for patches of [N][C][H][W]: 46 to 128 channels, 5x5, 12x8, one image, 0.03 GFLOP, 17.8 us against 14.9 one shot; 300

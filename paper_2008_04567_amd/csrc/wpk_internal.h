@@ -72,6 +72,17 @@ extern const Variant kVariants[];
 extern const int kNumVariants;
 int find_variant(int bm, int bn, int bk, int wm, int wn, int stages);  // index or -1
 
+// Layers of few channels on the split members (wpk_strip.h): strips of whole output rows, the rows of x under them in LDS.
+struct StripShape {
+    int32_t depths;     // MFMA depths of two filter rows each; 0: not so
+    int32_t pairs;      // columns / 2 that a row of the strip has room for
+    int32_t rows;       // output rows of a strip
+    int32_t lds;        // bytes
+    int32_t waves_c;    // waves side by side along the channels
+    int32_t per_group;  // groups of 32 * waves_c channels that a workgroup does
+    double us;          // what a launch is estimated to take
+};
+
 // ---- everything derived from one descriptor ------------------------------------------------------
 struct Problem {
     wpk_conv_desc d;
@@ -86,6 +97,7 @@ struct Problem {
     bool xquad;      // channels-last x gathered as 16-byte channel quads (C a multiple of every K-step)
     bool tapmajor;   // x [N][C][H][W] with C a multiple of every K-step: reduction ordered (r, s, c) as well
     bool padtaps;    // neither, but the split members pad C and order the reduction by taps (split_taps)
+    StripShape strip;  // of a prepared layer (prepare_strip), depths 0 before
 };
 int make_problem(const wpk_conv_desc *d, Problem *out);  // WPK_OK or a WPK_E_* code
 // The first or last `images` images of a problem, to be run on weights that were packed for the whole of it: whether channels are padded
@@ -176,7 +188,7 @@ struct IgemmArgs {
     int32_t yl;         // 1: y (and the residual) are channels-last; 2: also K % 4 == 0 and y, residual and
                         // bias 16-byte aligned, so a pixel's channel quads move as 16-byte accesses
     int32_t halo;       // split members: positions of x the patch of a 3x3 tile holds, 0: each tap fetched by itself, -1: a
-                        // 1x1 layer fetched four pixels at a time (split_point), -2: strips (strip_shape)
+                        // 1x1 layer fetched four pixels at a time (split_point), -2: strips (wpk_strip.h)
     int16_t producers;     // split members: waves of a workgroup that fetch,
     int16_t two_per_unit;  // and whether no compute unit gets more than two workgroups
 };
@@ -278,17 +290,10 @@ WPK_HOST_DEVICE inline uint32_t split_weights_at(bool patch, uint32_t block, int
 {
     return block + (uint32_t)split_depth(patch, step < nsteps ? step : nsteps - 1, 0) * depth_bytes;
 }
-// Layers of few channels on the split members (wpk_strip.h): strips of whole output rows, the rows of x under them in LDS.
-struct StripShape {
-    int32_t depths;     // MFMA depths of two filter rows each; 0: not so
-    int32_t pairs;      // columns / 2 that a row of the strip has room for
-    int32_t rows;       // output rows of a strip
-    int32_t lds;        // bytes
-    int32_t waves_c;    // waves side by side along the channels
-    int32_t per_group;  // groups of 32 * waves_c channels that a workgroup does
-    double us;          // what a launch is estimated to take
-};
-StripShape strip_shape(int N, int C, int P, int Q, int K, int R, int S, int stride_h, int stride_w, int dil_h, int dil_w);
+// The shape that pr's strips have: the prepared one, or priced for this many compute units.  Pricing takes 1 us (one group of
+// channels) to 5 (K = 4096), so what is run again and again is prepared once.
+StripShape strip_shape(const Problem &pr, int compute_units);
+void prepare_strip(Problem *pr, int compute_units);
 // Waves of a split member's workgroup that fetch and split activations.
 int split_producers(const Problem &pr, const wpk_conv_config &cfg);
 // LDS that such a workgroup takes, in the units of 1280 bytes (128 per compute unit) it is given out in.

@@ -772,9 +772,6 @@ __global__ void __launch_bounds__(64 * (WN + NP), 3) split_kernel(const IgemmArg
     for_each_segment(a, run_segment);
 }
 
-// (wpk_strip.h)
-hipError_t launch_strip(const IgemmArgs &a, hipStream_t stream);
-
 template <int WN, SplitForm FORM, int NP, bool ANY>
 hipError_t launch_split_form(const IgemmArgs &a, hipStream_t stream)
 {
@@ -798,7 +795,6 @@ hipError_t launch_split_waves(const IgemmArgs &a, hipStream_t stream)
 template <int WN>
 hipError_t launch_split(const IgemmArgs &a, hipStream_t stream)
 {
-    if (a.halo == -2) return launch_strip(a, stream);
     const bool any = a.C % 32 != 0;
     if (a.halo > 0) {
         if (a.xl != 2) return launch_split_waves<WN, kPatch, false, (WN < 4)>(a, stream);

@@ -26,7 +26,7 @@ struct StripGeom {
     int32_t per_image;   // strips of an image
     int32_t strips;      // of all images
     int32_t P;
-    int32_t groups;      // groups of 32 * lanes_c channels, of which a workgroup does `per_group`
+    int32_t groups;      // groups of 32 * waves_c channels, of which a workgroup does `per_group`
     int32_t per_group;
     int32_t waves_c;     // waves side by side along the channels: 1, 2 or 4
     int32_t in_rows;     // rows of x under a strip, of each channel
@@ -220,10 +220,9 @@ hipError_t launch_strip_odd(const IgemmArgs &a, const StripGeom &g, size_t bytes
                           : launch_strip_form<DEPTHS, PAIRS, false>(a, g, bytes, stream);
 }
 
-// strip_shape has said that the layer can be run so.
-hipError_t launch_strip(const IgemmArgs &a, hipStream_t stream)
+// s: the layer's, from strip_shape.
+hipError_t launch_strip(const IgemmArgs &a, const StripShape &s, hipStream_t stream)
 {
-    const StripShape s = strip_shape(a.N, a.C, a.PQ / a.Q, a.Q, a.K, a.R, a.S, a.stride_h, a.stride_w, a.dil_h, a.dil_w);
     StripGeom g;
     g.P = a.PQ / a.Q;
     g.rows = s.rows;

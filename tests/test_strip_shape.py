@@ -8,12 +8,13 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 #include "wpk_internal.h"
 using namespace wpk;
 int main()
 {
     srand(11);
-    long taken = 0, refused = 0, edge = 0;
+    long taken = 0, refused = 0, edge = 0, units = 0;
     auto pick = [](int lo, int hi) { return lo + rand() % (hi - lo + 1); };
     for (int it = 0; it < 20000; ++it) {
         wpk_conv_desc d = {pick(1, 9), pick(1, 7), pick(1, 70), pick(1, 260), pick(1, 300), pick(1, 11), pick(1, 10), pick(1, 3), pick(1, 3),
@@ -23,7 +24,14 @@ int main()
         const int depths = strip_depths(pr);
         if (depths == 0) { ++refused; continue; }
         ++taken;
-        const StripShape s = strip_shape(d.n, d.c, pr.P, pr.Q, d.k, d.r, d.s, d.stride_h, d.stride_w, d.dil_h, d.dil_w);
+        const StripShape s = strip_shape(pr, 256), fewer = strip_shape(pr, 16);
+        units += s.rows != fewer.rows || s.per_group != fewer.per_group;
+        // a prepared layer's is the one that it was prepared with, and no launch prices another
+        Problem once = pr;
+        prepare_strip(&once, 16);
+        if (memcmp(&once.strip, &fewer, sizeof s) || pr.strip.depths) return 3;
+        const StripShape kept = strip_shape(once, 256);
+        if (memcmp(&kept, &fewer, sizeof s)) return 3;
         const int in_rows = (s.rows - 1) * d.stride_h + (d.r - 1) * d.dil_h + 1, line = 3 * s.pairs * 4;
         const int per_image = (pr.P + s.rows - 1) / s.rows, groups = (d.k + 32 * s.waves_c - 1) / (32 * s.waves_c);
         bool bad = s.depths != depths || 2 * depths < d.c * d.r || d.s > 8 || s.rows < 1 || s.lds > 78 * 1024 ||
@@ -47,8 +55,8 @@ int main()
             return 1;
         }
     }
-    printf("%ld %ld %ld\n", taken, refused, edge);
-    return taken > 2000 && refused > 2000 && edge > 10 ? 0 : 2;
+    printf("%ld %ld %ld %ld\n", taken, refused, edge, units);
+    return taken > 2000 && refused > 2000 && edge > 10 && units > 100 ? 0 : 2;
 }
 """
 
