@@ -287,7 +287,7 @@ static StripShape price_strip(const Problem &pr, int compute_units)
         const int64_t wave_blocks = (blocks + 4 / waves_c - 1) / (4 / waves_c);
         for (int per = groups; per >= 1; per = per == 1 ? 0 : (per + 1) / 2) {
             const int64_t work = strips * ((groups + per - 1) / per);
-            if (work > 0x7fffffff) continue;
+            if (work > kMaxStripGroups) continue;
             const double fill = 8000.0 + lines * ((pairs + 63) / 64) * 60.0;
             const double multiply = per * (1500.0 + wave_blocks * (depths * 225.0 + 1900.0));
             const double units = compute_units > 0 ? compute_units : 256;
@@ -586,7 +586,7 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         const int depths = strip_depths(pr);
         if (flops < 0.45e9 || (pr.yl && d.k % 4) || d.s < 5 || pr.CRS < 8 * depths || (depths <= 5 && pr.y_elems >= 25000000)) return false;
         *out = wpk_conv_config{64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
-        return 1.1 * strip_shape(pr, compute_units).us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);
+        return runs_strip(pr, *out) && 1.1 * strip_shape(pr, compute_units).us < tiled_time(pr, tiled, compute_units) && legal_for(pr, *out);
     }
     if (!split_taps(pr)) return false;
     // (padded channels, but for patches of [N][C][H][W]: 46 to 128 channels, 5x5, 12x8, one image, 0.03 GFLOP, 17.8 us against 14.9 one shot; 300

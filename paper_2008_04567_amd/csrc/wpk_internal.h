@@ -248,11 +248,14 @@ WPK_HOST_DEVICE inline int patch_last(int n, int p, int q, int stride_h, int str
 inline bool split_taps(const Problem &pr) { return pr.tapmajor || pr.xquad || pr.padtaps; }
 // MFMA depths of pr on the strip form of the split members, 0 where it does not fit that.
 int strip_depths(const Problem &pr);
+static const int64_t kMaxStripGroups = 0xffffff;  // workgroups of a launch
 // Whether cfg runs pr in strips.  Where pr fits them, the split members' configurations of K-step 16 without slices or persistent
 // workgroups do (a strip has the whole reduction, and a workgroup its own strips); the others go row by row, as the caller asked for.
+// So do more output rows than a launch has workgroups of 256 threads for, 2^32 threads in all (strips of one row each, one group of channels).
 inline bool runs_strip(const Problem &pr, const wpk_conv_config &cfg)
 {
-    return split_member(cfg) && cfg.bk == 16 && cfg.split_k == 1 && cfg.persist == 0 && strip_depths(pr) > 0;
+    return split_member(cfg) && cfg.bk == 16 && cfg.split_k == 1 && cfg.persist == 0 && strip_depths(pr) > 0 &&
+           (int64_t)pr.d.n * pr.P <= kMaxStripGroups;
 }
 // Rows of the reduction as the split members pack it: where pr fits strips, those in the strips' order and then those in the source's.
 inline int64_t split_rows(const Problem &pr)

@@ -55,6 +55,22 @@ int main()
             return 1;
         }
     }
+    // As many strips as a launch of 256 threads per workgroup has room for (2^32 threads), and one more: row by row.
+    const wpk_conv_config one = {64, 64, 16, 1, 2, 1, 1, 0, 1, 0};
+    for (const int rows : {1, 3})
+        for (const int more : {0, 1, 1000000}) {
+            const wpk_conv_desc d = {0xffffff / rows + more, 3, rows, 1, 1, 7, 7, 1, 1, 3, 3, 1, 1, WPK_F32, 0};
+            Problem pr;
+            if (make_problem(&d, &pr) != WPK_OK || !strip_depths(pr) || !legal_for(pr, one)) return 4;
+            if (runs_strip(pr, one) != (more == 0)) return 5;
+            wpk_conv_config c;
+            default_config(pr, 256, &c);
+            if (more && runs_strip(pr, c)) return 6;
+            if (more) continue;
+            const StripShape s = strip_shape(pr, 256);
+            const int64_t groups = (int64_t)d.n * ((pr.P + s.rows - 1) / s.rows);
+            if (s.rows < 1 || groups * 256 > 0xffffffffll) return 7;
+        }
     printf("%ld %ld %ld %ld\n", taken, refused, edge, units);
     return taken > 2000 && refused > 2000 && edge > 10 && units > 100 ? 0 : 2;
 }
