@@ -66,15 +66,16 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float *__restri
 }
 
 // Where row kk of the split members' reduction comes from: its place among the C*R*S rows of the source, or
-// -1 for a padding row.  The first `strips` rows run (c, r, s) with s padded to eight; the others with RS > 0 (c / 32, r, s, c % 32), else
-// in the source's order.
+// -1 for a padding row.  Of layers that fit STRIPS the first `strips` rows run (c, r, s) with s padded to eight and the others in the source's
+// order; of others all rows with RS > 0 (c / 32, r, s, c % 32), else in the source's order.
+template <bool STRIPS>
 __device__ inline int split_source_row(int kk, int C, int CRS, int RS, int strips, int S)
 {
-    if (kk < strips) {
+    if (STRIPS) {
+        if (kk >= strips) return kk - strips < CRS ? kk - strips : -1;
         const int row = (kk >> 3) * S + (kk & 7);
         return (kk & 7) < S && row < CRS ? row : -1;
     }
-    kk -= strips;
     if (RS == 0) return kk < CRS ? kk : -1;
     const int c32 = kk / (32 * RS), t = kk - c32 * 32 * RS, c = c32 * 32 + (t & 31);
     // (sixteen rows at a time: the two halves of the 32 channels follow each other for every tap)
@@ -83,6 +84,8 @@ __device__ inline int split_source_row(int kk, int C, int CRS, int RS, int strip
 
 // w[K][CRS] -> [depths of 16 rows][Kpad/32][3 parts][64 lanes][8 bf16], zero padded: what lane l of a wave feeds the
 // bf16 MFMA of one depth and 32-channel block is channel l % 32, rows (l / 32)*8 .. +7.  Parts: see split_weight.
+// (STRIPS by template: looking for strips' rows in every layer cost one-shot calls 1 %, 352 to 32 channels, 1x3, 18x18, 31 images, 19.1 us, 19.3.)
+template <bool STRIPS>
 __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict__ w, v4u *__restrict__ wp, int K,
                                                          int C, int CRS, int depths, int blocks, int RS, int strips, int S)
 {
@@ -92,7 +95,7 @@ __global__ void __launch_bounds__(256) pack_split_kernel(const float *__restrict
     unsigned part[3][4];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int row = split_source_row(t * 16 + (lane >> 5) * 8 + j, C, CRS, RS, strips, S);
+        const int row = split_source_row<STRIPS>(t * 16 + (lane >> 5) * 8 + j, C, CRS, RS, strips, S);
         const float v = k < K && row >= 0 ? w[(size_t)k * CRS + row] : 0.0f;
         unsigned v3[3];
         split_weight(v, v3);
@@ -505,8 +508,8 @@ static int pack_weights(const Problem &pr, bool split, const float *w, float *wp
                                RS > 0 ? pr.d.c : pr.CRS, taps, blocks, octets, all_octets);
         } else {
             const int depths = (int)(split_rows(pr) / 16);
-            hipLaunchKernelGGL(pack_split_kernel, dim3((depths + 3) / 4, blocks), dim3(256), 0, st, w, (v4u *)wp, pr.d.k,
-                               pr.d.c, pr.CRS, depths, blocks, RS, strips, pr.d.s);
+            hipLaunchKernelGGL(strips ? pack_split_kernel<true> : pack_split_kernel<false>, dim3((depths + 3) / 4, blocks),
+                               dim3(256), 0, st, w, (v4u *)wp, pr.d.k, pr.d.c, pr.CRS, depths, blocks, RS, strips, pr.d.s);
         }
     } else {
         dim3 grid(pr.CRSpad / 32, pr.Kpad / 32);
