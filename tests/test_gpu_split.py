@@ -45,7 +45,8 @@ def test_patches(layer, wn):
     check_layout(layer, B.NHWC, cfg(wn, 16), what=layer["name"] + " nhwc")
 
 
-# the other ways: 1x1 four pixels at a time (H * W % 4 == 0, stride 1), 1x1 and larger filters tap by tap, rows (any C).
+# the other ways: 1x1 four pixels at a time (H * W % 4 == 0, stride 1), 1x1 and larger filters tap by tap, rows where padded channels
+# would lengthen the reduction by more than half.
 # Reductions of one step up to more than the steps in flight, odd and even.
 OTHER = [
     W.layer("point_1step", 3, 32, (6, 6), 64, 1, x_dist="u11", seed=20),
@@ -56,9 +57,9 @@ OTHER = [
     W.layer("taps_5x5", 2, 32, (9, 12), 96, 5, 1, 2, x_dist="u11", seed=25),
     W.layer("taps_3x3_s2", 2, 64, (11, 14), 64, 3, 2, 1, x_dist="u11", seed=26),
     W.layer("taps_1x7", 1, 64, (8, 17), 48, (1, 7), 1, (0, 3), x_dist="u11", seed=27),
-    W.layer("rows_c24_1x1", 2, 24, 9, 64, 1, x_dist="u11", seed=31),
-    W.layer("rows_c43_5x5", 1, 43, (8, 15), 40, 5, 1, 2, x_dist="u11", seed=32),
-    W.layer("rows_c72_wide", 1, 72, (6, 130), 40, 3, 1, 2, dil=2, x_dist="u11", seed=33),
+    W.layer("taps_c24_1x1", 2, 24, 9, 64, 1, x_dist="u11", seed=31),
+    W.layer("taps_c43_5x5", 1, 43, (8, 15), 40, 5, 1, 2, x_dist="u11", seed=32),
+    W.layer("taps_c72_wide", 1, 72, (6, 130), 40, 3, 1, 2, dil=2, x_dist="u11", seed=33),
     # (weights packed through LDS, by eight c of all taps, and of 63 and of 64 taps in place)
     W.layer("taps_5x5_k1100", 1, 96, (5, 6), 1100, 5, 1, 2, x_dist="u11", seed=37),
     W.layer("taps_9x7", 1, 64, (13, 12), 70, (9, 7), 1, (4, 3), x_dist="u11", seed=34),
@@ -100,7 +101,8 @@ def test_schedules_and_epilogue(kw):
                              what="%s %r layout %d" % (layer["name"], kw, layout))
 
 
-# Every way of finding activations (the kernel's six forms, the patch with and without padded channels): layer, layout, bk.
+# Every way of finding activations, those that pad channels with and without padding (there infinities and NaN of the next pixel or image,
+# or of the last channel again, meet weights of zero): layer, layout, bk.  tests/test_split_forms.py looks up that each is what it is called.
 FORMS = {
     "patch": (W.layer("f_patch", 2, 32, 9, 40, 3, 1, 1, x_dist="u11", seed=70), B.NCHW, 16),
     "patch_c27": (W.layer("f_patch27", 2, 27, 9, 40, 3, 1, 1, x_dist="u11", seed=71), B.NCHW, 16),
@@ -108,6 +110,14 @@ FORMS = {
     "point": (W.layer("f_point", 2, 64, 8, 40, 1, x_dist="u11", seed=73), B.NCHW, 32),
     "taps": (W.layer("f_taps", 2, 32, 9, 40, 5, 1, 2, x_dist="u11", seed=74), B.NCHW, 32),
     "quads": (W.layer("f_quads", 2, 32, 9, 40, 3, 1, 1, x_dist="u11", seed=75), B.NHWC, 32),
+    "patch_quads_c27": (W.layer("f_pquads27", 2, 27, 9, 40, 3, 1, 1, x_dist="u11", seed=80), B.NHWC, 16),
+    "point_c61": (W.layer("f_point61", 2, 61, 8, 40, 1, x_dist="u11", seed=81), B.NCHW, 16),       # (one wave fetches)
+    "point_two_c61": (W.layer("f_point61_2", 2, 61, 8, 40, 1, x_dist="u11", seed=82), B.NCHW, 32),  # (two do)
+    "taps_c27": (W.layer("f_taps27", 2, 27, 9, 40, 5, 1, 2, x_dist="u11", seed=83), B.NCHW, 32),
+    "quads_c27": (W.layer("f_quads27", 2, 27, 9, 40, 5, 1, 2, x_dist="u11", seed=84), B.NHWC, 32),
+    "strip": (W.layer("f_strip", 2, 3, 9, 40, 5, 2, 2, x_dist="u11", seed=85), B.NCHW, 16),
+    "strip_odd_nhwc": (W.layer("f_strip_cl", 2, 3, 9, 40, 7, 1, 3, x_dist="u11", seed=86), B.NHWC, 16),
+    "strip_c22": (W.layer("f_strip22", 2, 22, 9, 40, (1, 3), 1, (0, 1), x_dist="u11", seed=87), B.NCHW, 16),
     "rows": (W.layer("f_rows", 2, 5, 9, 40, 3, 1, 1, x_dist="u11", seed=76), B.NCHW, 32),
     "rows_nhwc": (W.layer("f_rows_cl", 2, 20, 9, 40, 3, 1, 1, x_dist="u11", seed=77), B.NHWC, 32),
 }
