@@ -257,7 +257,8 @@ int halo_positions(const Problem &pr, const wpk_conv_config &cfg)
     return patch_bound(pr);
 }
 
-// MFMA depths of a strip and the columns / 2 its rows have room for, 0 depths where a layer does not fit.
+// MFMA depths of a strip and the columns / 2 its rows have room for, 0 depths where a layer does not fit.  (240 columns: what the kernel is
+// instantiated for, one or two columns / 2 a lane, the second 56 lanes of them; wider rows were neither built nor measured.)
 static int strip_fits(int C, int Q, int R, int S, int stride_w, int dil_h, int dil_w, int *pairs)
 {
     const int64_t octets = (int64_t)C * R, columns = (int64_t)(Q - 1) * stride_w + 8 + (stride_w % 2 ? 2 : 0);

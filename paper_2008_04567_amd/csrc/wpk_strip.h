@@ -11,8 +11,9 @@
 // of C * R octets at most 22, stay in registers (132 for 22 octets) while the wave goes through its pixels in blocks of 32, so that the loop
 // asks memory for nothing.  Two workgroups per compute unit.  What bounds it: the six MFMAs of a depth take 192 cycles, the wave's other
 // instructions (six LDS reads of two dwords for an even stride) 60; the strip's filling is not overlapped within a workgroup.
-// 7x7, stride 2, 3 -> 64 channels, 224x224, 16 images: 28.0 us, the tiled members 44.3 (row by row on the split members 47.5); of 57000 cycles of a workgroup beside
-// another 15000 are the start and the strip, 2600 to 4800 each of seven blocks (2112 of MFMAs), 1500 each of their ways out.
+// 7x7, stride 2, 3 -> 64 channels, 224x224, 16 images: 28.4 to 30.5 us by the device's clock, the tiled members 44.2 to 44.9 (row by row on the
+// split members 47.5).  Of 43300 cycles of a workgroup (median; up to 59100 beside another) 12800 are the start and the strip, 4000 to 4400 each of
+// seven blocks (up to 8000 beside another; 2112 of MFMAs, 1350 the way out); the matrix pipes are busy 47 % of a compute unit's time, no bank conflicts.
 #ifndef WPK_STRIP_H
 #define WPK_STRIP_H
 
