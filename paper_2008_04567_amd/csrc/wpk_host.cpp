@@ -549,6 +549,38 @@ static double tiled_time(const Problem &pr, const wpk_conv_config &c, int comput
     return 2.9 + sqrt(chain * chain + pipes * pipes + memory * memory) +
            (atomics ? 5.7 + 3 * y_mb / 7.7 + (pr.yl ? 5.5 * y_mb * slices : 0.0) : 0.0);
 }
+// Whether tiles beyond whole rounds of two persistent workgroups per compute unit (taps: of one with four waves) are dealt out.  pairs: tiles of
+// 64 pixels and channels; whole: what would be taken else, estimated to take us.  Times are of that.
+static bool deals_out(const Problem &pr, int halo, bool taps, bool narrow, const wpk_conv_config &whole, double us, int64_t pairs, int steps,
+                      int compute_units)
+{
+    const int64_t round = 2 * (int64_t)compute_units, beyond = pairs % round;
+    // Two to two and a half tiles per compute unit.  (narrow: where whole tiles of 32 channels are priced a sixth faster, as with 96 or 160
+    // channels, they stay: 0.78 to 1.18, 14 layers, half of them more.)
+    if (pairs > round && 4 * pairs <= 5 * round && steps >= 4 && !narrow) {
+        // patches: 0.85 on average, three of 112 layers slower by more than 3 %
+        if (halo > 0) return true;
+        // Taps against four waves: 0.87, 0.97 at worst, 77 layers.  Against two, of whose 128-wide tiles some channels are padding, with a stride, 0.89,
+        // 11 layers; not without (1.03, up to 1.18, 22 layers; 32 to 320 channels, 5x5, 31x31, nine images, 28.8 us, 34.0 dealt out).  Not with up to 64
+        // channels, where two of the waves have none (1.27 to 1.6, 42 layers; 3x3, stride 2, 32 to 64, 56x56, 48 images, 20.1 us, 30.7), nor 1x1
+        // (1.03 to 1.14, 72 layers), nor below 16 steps (3x3, 32 to 100, 19.8, 22.6).
+        if (taps)
+            return pr.d.k > 64 && pr.d.r * pr.d.s > 1 && steps >= 16 && (whole.wn == 4 || pr.d.stride_h > 1 || pr.d.stride_w > 1);
+        // Channels-last against four waves: 0.84 to 0.98, 105 layers, unless those in slices are estimated to be a quarter faster (1.04, 12
+        // layers); against two, 0.95 from twelve steps on, 48 layers; below that 1.08, up to 1.34, 17 layers (160 to 160 channels, 1x1, 49x49, five images,
+        // 11.3 us, 15.2 dealt out).
+        const wpk_conv_config dealt = {64, 64, 32, 1, 2, 1, 1, 2, 1, 0};
+        return whole.wn == 4 ? split_time(pr, dealt, compute_units) <= 1.35 * us : steps >= 12;
+    }
+    // Patches, more than four tiles per compute unit.  Against four waves (two tiles of 64 channels in one) 0.93 with less than half of a round left
+    // over, 176 layers; with more, 0.95 with two steps, 43 layers, and 1.02 from three steps on, half of 99 layers slower by more than 3 %.  Against fewer waves 0.87
+    // from five steps on, 101 layers, 0.96 with four, 59 layers; with two or three 0.95 where less than a quarter of a round is left over and the rounds are few, 1.01
+    // elsewhere, 0.85 to 1.34, 73 layers (37 to 138 channels, 43x43, 61 images, 99.6 us, 117.8 dealt out).
+    if (halo > 0 && pairs > 2 * round && steps >= 2)
+        return whole.wn == 4 ? steps == 2 || 2 * beyond < round : steps >= 4 || (4 * beyond < round && pairs < 8 * round);
+    return false;
+}
+
 // The split members' default, where they order the reduction by taps or take the layer in strips (row by row they gain nothing over
 // the tiled members).  Waves of 64 pixels by 32 channels; patches where a 3x3 layer allows them.
 //  - As many waves per workgroup as the channels call for, four at most: a wider workgroup fetches and splits its pixels
@@ -644,7 +676,8 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
                 other = o;
             }
         }
-    const bool narrow = 1.2 * least < time && other.wn == 1 && other.split_k == 1;
+    const bool better = 1.2 * least < time, narrow = better && other.wn == 1 && other.split_k == 1;
+    const wpk_conv_config whole_tiles = better ? other : c;  // what is taken where nothing is dealt out
     if (wn <= 2 && tiles > G && tiles < (point && wn == 2 ? 5 : 3) * G && tiles % G * 12 <= G &&
         (point ? red.steps >= 2 : halo > 0 && halo <= 240 && tiles % G * 20 <= G)) {
         // Just over one or two whole rounds of three workgroups per compute unit (1x1 layers of two waves: four): the tiles
@@ -654,24 +687,20 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
         c.persist = 3;
         time *= 0.95;
     } else if (!point && pr.d.k > 32 && split_lds_units(halo, 2) <= 64 &&
-               ((!narrow && pairs > 2 * (int64_t)compute_units && 2 * pairs <= 5 * (int64_t)compute_units && red.steps >= 4 &&
-                 (!taps || (pr.d.k > 64 && pr.d.r * pr.d.s > 1 && red.steps >= 16))) ||
-                (halo > 0 && pairs > 4 * (int64_t)compute_units && red.steps >= 2))) {
+               deals_out(pr, halo, taps, narrow, whole_tiles, better ? least : time, pairs, red.steps, compute_units)) {
         // Two persistent workgroups of two waves per compute unit, whose SIMDs then have one multiplying wave each, and the tiles beyond
-        // whole rounds dealt out.  Of 64 pixels and channels each, two to two and a half tiles per compute unit: 0.81 to 0.92 of the time of what the rules
-        // around this one give (patches 17 layers, channels-last 7); patches of more than four, 0.89 to 0.99 (60 layers).  With two and a half
-        // to four it is 0.99 to 1.23 of it, with fewer steps to deal out than that 0.97 to 1.1.  (narrow: where whole tiles of 32 channels are priced
-        // a sixth faster, as with 96 or 160 channels, they stay: two to two and a half tiles dealt out took 0.78 to 1.18 of it, 14 layers, half of them more.)
-        // Taps take one workgroup of four waves: 0.82 to 0.94 of the time, 85 layers of more than 64 channels and filters of 3x3 and more.  Not with up to
-        // 64, where two of the waves have no channel (1.27 to 1.6, 42 layers; 3x3, stride 2, 32 to 64, 56x56, 48 images, 20.1 us against 30.7), nor
-        // 1x1 (1.03 to 1.14, 72 layers), nor below 16 steps (3x3, 32 to 100, 19.8 against 22.6).
+        // whole rounds dealt out (deals_out).
+        // Taps take one workgroup of four waves.
         c = wpk_conv_config{64, taps ? 128 : 64, c.bk, 1, taps ? 4 : 2, 1, 1, taps ? 1 : 2, 1, 0};
         time = 0.9 * std::min(time, split_time(pr, c, compute_units));
-    } else if (1.2 * least < time) {
+    } else if (better) {
         c = other;
         time = least;
     }
-    if (time > 1.1 * tiled_time(pr, tiled, compute_units) || !legal_for(pr, c)) return false;
+    // (channels-last with padded channels the tiled members fetch four bytes at a time and take 1.5 times their estimate, 483 layers: up to where the
+    // split ones were estimated a fifth slower they took 0.47 of the time, 1.03 at worst)
+    const double margin = pr.xl && pr.padtaps ? 1.2 : 1.1;
+    if (time > margin * tiled_time(pr, tiled, compute_units) || !legal_for(pr, c)) return false;
     *out = c;
     return true;
 }

@@ -39,6 +39,14 @@ static const Case cases[] = {
     {L(5, 224, 101, 101, 192, 1, 1, 2, 0, 1, 0), 1, 2, 1, 1, 0},       // 16.9, 24.4
     {L(64, 32, 17, 64, 100, 3, 3, 2, 1, 1, 0), 1, 4, 1, 1, 0},         // 19.8, 22.6
     {L(31, 208, 13, 44, 96, 3, 3, 1, 1, 1, 0), 1, 1, 1, 1, 0},         // (channels of three 32-wide workgroups) 37.0, 43.5
+    {L(9, 32, 31, 31, 320, 5, 5, 1, 0, 1, 0), 1, 2, 1, 1, 0},          // (128-wide tiles of 320 channels) 28.8, 34.0
+    // channels-last, and patches beyond four tiles per compute unit: whole tiles where steps are few, most of a round is left over, or slices of
+    // four waves are estimated to be a quarter faster
+    {L(5, 160, 49, 49, 160, 1, 1, 1, 0, 1, 3), 1, 2, 1, 1, 0},         // 11.3, 15.2 dealt out
+    {L(1, 256, 93, 97, 209, 5, 5, 1, 2, 1, 3), 1, 4, 5, 5, 0},
+    {L(61, 37, 43, 43, 138, 3, 3, 1, 1, 1, 0), 1, 2, 1, 1, 0},         // 99.6, 117.8
+    {L(9, 64, 78, 65, 96, 3, 3, 1, 1, 1, 2), 1, 4, 1, 1, 0},           // 39.2, 43.6
+    {L(6, 64, 65, 73, 174, 3, 3, 1, 1, 1, 1), 1, 2, 1, 1, 2},          // (four steps)
     // strips: where little of them is padding
     {L(16, 3, 224, 224, 64, 7, 7, 2, 3, 1, 0), 1, 2, 1, 1, 0},         // 44.3, 28.4
     {L(32, 3, 112, 112, 64, 5, 5, 1, 2, 1, 3), 1, 2, 1, 1, 0},
