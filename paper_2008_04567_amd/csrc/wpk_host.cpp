@@ -699,8 +699,19 @@ static bool split_default(const Problem &pr, int compute_units, const wpk_conv_c
     }
     // (channels-last with padded channels the tiled members fetch four bytes at a time and take 1.5 times their estimate, 483 layers: up to where the
     // split ones were estimated a fifth slower they took 0.47 of the time, 1.03 at worst)
-    const double margin = pr.xl && pr.padtaps ? 1.2 : 1.1;
-    if (time > margin * tiled_time(pr, tiled, compute_units) || !legal_for(pr, c)) return false;
+    const double margin = pr.xl && pr.padtaps ? 1.2 : 1.1, tiled_us = tiled_time(pr, tiled, compute_units);
+    if (time > margin * tiled_us || !legal_for(pr, c)) return false;
+    if (taps && pr.padtaps && !split_point(pr)) {
+        // Padded channels fetched pixel by pixel.  Up to 32 channels, where the fetched pixels serve a single wave: against tiled members that deal
+        // tiles out, or add slices up by atomics into channels-last outputs, 0.60, 0.91 at worst, 30 layers; against others 0.99, up to 1.40, 74 layers (168
+        // to 32, 5x5, stride 2, 43x22, 43 images, 51.4 us against 36.8), but 0.87, 1.10 at worst, without a stride where the estimate is by 13 % less.
+        const bool strides = pr.d.stride_h > 1 || pr.d.stride_w > 1;
+        if (pr.d.k <= 32 && tiled.persist != 1 && !(tiled.reduce && pr.yl) && (strides || time > 0.87 * tiled_us)) return false;
+        // Above, up to three steps 1.08 to 1.24, 6 layers; with more than one and a half waves per SIMD only where the estimate is less: 1.05 where it
+        // is not, up to 1.24, 34 layers.
+        const int64_t waves = ((pr.M + 63) / 64) * ((pr.d.k + c.bn - 1) / c.bn) * c.wn * c.split_k;
+        if (pr.d.k > 32 && (red.steps <= 3 || (c.persist == 0 && waves > 6 * (int64_t)compute_units && time > tiled_us))) return false;
+    }
     *out = c;
     return true;
 }

@@ -59,6 +59,11 @@ static const Case cases[] = {
     {L(2, 23, 82, 82, 480, 5, 5, 1, 2, 1, 0), 0, 0, 1, 1, 0},          // 73.5, 79.4
     {L(20, 320 + 1, 45, 45, 256, 1, 1, 1, 0, 1, 0), 1, 4, 1, 1, 0},    // (eleven steps)
     {L(8, 329, 35, 35, 256, 1, 1, 1, 0, 1, 3), 1, 2, 1, 1, 2},         // (channels-last) 31.6, 23.2
+    // the same up to 32 channels, with few steps, or with many waves per SIMD
+    {L(43, 168, 43, 22, 32, 5, 5, 2, 0, 1, 0), 0, 0, 7, 7, 0},         // 36.8, 51.4
+    {L(11, 51, 37, 11, 29, 7, 7, 1, 3, 1, 2), 1, 1, 14, 14, 0},        // (atomics into channels-last) 62.2, 22.1
+    {L(3, 97, 75, 75, 32, 7, 7, 1, 3, 1, 0), 1, 1, 3, 3, 0},           // (tiles dealt out) 118, 68.4
+    {L(6, 28, 79, 79, 736, 3, 1, 1, 1, 1, 2), 0, 0, 1, 1, 0},          // 68.7, 82.7
     // 1x1, up to two tiles: two fetching waves, but not for few channels, many slices or a second round
     {L(16, 512, 28, 28, 128, 1, 1, 1, 0, 1, 0), 1, 4, 1, 1, 0},        // 16.3 with one, 12.6
     {L(20, 896, 10, 10, 128, 1, 1, 1, 0, 1, 0), 1, 2, 4, 4, 0},        // 13.8, 16.6 in 8 slices
