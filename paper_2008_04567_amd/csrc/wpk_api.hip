@@ -629,7 +629,7 @@ static int run_config(const Problem &pr, const wpk_conv_config &cfg, const int32
     a.M = (int32_t)pr.M; a.PQ = pr.P * pr.Q; a.HW = d.h * d.w; a.CRS = pr.CRS; a.Kpad = pr.Kpad;
     a.nsteps = red.steps;
     a.halo = !split_member(cfg) ? 0 : strip ? -2 : split_point(pr) ? -1 : halo_positions(pr, cfg);
-    a.producers = (int16_t)split_producers(pr, cfg);
+    a.producers = (int16_t)split_producers(pr, cfg, g_cus);
     // slices of ceil(nsteps/split_k) steps; launch only as many as are not empty
     a.steps_per_split = (a.nsteps + cfg.split_k - 1) / cfg.split_k;
     a.split_k = (a.nsteps + a.steps_per_split - 1) / a.steps_per_split;

@@ -327,16 +327,20 @@ int split_lds_units(int halo, int wn)
     return ((halo > 0 ? (halo + 1) * 224 : 30720) + 256 * wn + 4 + 1279) / 1280;
 }
 
-int split_producers(const Problem &pr, const wpk_conv_config &cfg)
+int split_producers(const Problem &pr, const wpk_conv_config &cfg, int compute_units)
 {
     if (!split_member(cfg)) return 0;
     const int halo = halo_positions(pr, cfg);
     if (halo > 0) {
         // A second one wherever as many workgroups as with one fit a compute unit (twelve waves): 0.6 to 0.95 of the time with four or more
         // blocks of 64 positions, 0.9 to 1 with three.  Not where four workgroups fit: of three blocks one wave takes two
-        // either way, and the four second waves are in the way (one multiplying wave each, 75 layers, median 1.02, up to 1.41).
+        // either way, and the four second waves are in the way (one multiplying wave each, 75 layers, median 1.02, up to 1.41); where no compute
+        // unit gets more than two, they are not (0.95 to 1, one layer of 144 1.05; with more 0.88 to 1.14 on either side, 196 layers).
         const int fit = std::min(12 / (cfg.wn + 1), 128 / split_lds_units(halo, cfg.wn));
-        return fit < 4 && 12 / (cfg.wn + 2) >= fit ? 2 : 1;
+        const int64_t tiles = ((pr.M + cfg.bm - 1) / cfg.bm) * ((pr.d.k + cfg.bn - 1) / cfg.bn);
+        const int persist = persistent_of(pr, cfg, compute_units), units = compute_units > 0 ? compute_units : 256;
+        const bool few = persist > 0 ? persist <= 2 : tiles * cfg.split_k <= 2 * (int64_t)units;
+        return (fit < 4 || few) && 12 / (cfg.wn + 2) >= fit ? 2 : 1;
     }
     if (pr.xl && split_taps(pr)) return cfg.wn == 4 ? 2 : 1;
     if (split_point(pr)) return cfg.wn == 4 || (cfg.wn == 2 && cfg.bk == 32) ? 2 : 1;
@@ -372,7 +376,7 @@ wpk_conv_config same_launch(const Problem &pr, const wpk_conv_config &cfg, int c
     wpk_conv_config other = c;
     other.bk = 16;
     if (strip_depths(pr)) c.bk = 32;  // (row by row; what is a round of whole tiles has neither slices nor persistent workgroups below)
-    else if (halo_positions(pr, other) == halo_positions(pr, c) && split_producers(pr, other) == split_producers(pr, c)) c.bk = 16;
+    else if (halo_positions(pr, other) == halo_positions(pr, c) && split_producers(pr, other, compute_units) == split_producers(pr, c, compute_units)) c.bk = 16;
     if (c.persist > 0 && persistent_of(pr, c, compute_units) == 0) {
         c.persist = 0;
         c.reduce = 0;
@@ -510,7 +514,7 @@ static double split_time(const Problem &pr, const wpk_conv_config &c, int comput
     const wpk_conv_desc &d = pr.d;
     const int halo = halo_positions(pr, c), wn = c.wn;
     const bool patch = halo > 0, point = !patch && split_point(pr), taps = !patch && !point && !pr.xl;
-    const int producers = split_producers(pr, c);
+    const int producers = split_producers(pr, c, compute_units);
     const Reduction red = reduction_of(pr, c);
     const int per = (red.steps + c.split_k - 1) / c.split_k, slices = (red.steps + per - 1) / per;
     const int64_t tiles = ((pr.M + c.bm - 1) / c.bm) * ((d.k + c.bn - 1) / c.bn);

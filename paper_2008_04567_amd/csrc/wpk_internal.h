@@ -298,7 +298,7 @@ WPK_HOST_DEVICE inline uint32_t split_weights_at(bool patch, uint32_t block, int
 StripShape strip_shape(const Problem &pr, int compute_units);
 void prepare_strip(Problem *pr, int compute_units);
 // Waves of a split member's workgroup that fetch and split activations.
-int split_producers(const Problem &pr, const wpk_conv_config &cfg);
+int split_producers(const Problem &pr, const wpk_conv_config &cfg, int compute_units);
 // LDS that such a workgroup takes, in the units of 1280 bytes (128 per compute unit) it is given out in.
 int split_lds_units(int halo, int wn);
 // Where outputs lie in y (and in a residual laid out alike), as the offsets of buffer accesses.  A lane of no output gets

@@ -92,6 +92,7 @@ int main()
     static const struct { wpk_conv_desc d; int wn, producers; } fetch[] = {
         {L(7, 182, 45, 38, 160, 3, 3, 1, 1, 1, 0), 1, 1},
         {L(7, 182, 45, 38, 160, 3, 3, 1, 1, 1, 0), 4, 2},
+        {L(9, 247, 11, 39, 32, 3, 3, 1, 1, 1, 1), 1, 2},     // (one workgroup per compute unit) 14.2 with two, 14.7
         {L(4, 64, 80, 80, 64, 3, 3, 1, 1, 1, 0), 1, 2},      // (three fit)
         {L(4, 64, 80, 80, 64, 3, 3, 1, 1, 1, 0), 2, 2},
         {L(16, 256, 14, 14, 256, 3, 3, 1, 1, 1, 0), 2, 1},   // (four with one, three with two)
@@ -100,8 +101,8 @@ int main()
         Problem pr;
         const wpk_conv_config c = {64, 32 * t.wn, 16, 1, t.wn, 1, 1, 0, 1, 0};
         if (make_problem(&t.d, &pr) != WPK_OK || halo_positions(pr, c) == 0) return 3;
-        if (split_producers(pr, c) != t.producers) {
-            printf("c %d %dx%d, %d waves: %d fetch\n", t.d.c, t.d.h, t.d.w, t.wn, split_producers(pr, c));
+        if (split_producers(pr, c, 256) != t.producers) {
+            printf("c %d %dx%d, %d waves: %d fetch\n", t.d.c, t.d.h, t.d.w, t.wn, split_producers(pr, c, 256));
             return 1;
         }
     }

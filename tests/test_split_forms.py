@@ -24,7 +24,7 @@ int main()
         const bool patch = halo_positions(pr, c) > 0, taps = split_taps(pr);
         const char *form = runs_strip(pr, c) ? "strip" : patch ? (pr.xl ? "patch_quads" : "patch") : split_point(pr) ? "point"
                            : taps ? (pr.xl ? "quads" : "taps") : "rows";
-        printf("%s %d %d\n", form, taps && d.c % 32 != 0, split_producers(pr, c));
+        printf("%s %d %d\n", form, taps && d.c % 32 != 0, split_producers(pr, c, 256));
     }
     return 0;
 }
