@@ -562,7 +562,7 @@ static bool deals_out(const Problem &pr, int halo, bool taps, bool narrow, const
     // Two to two and a half tiles per compute unit.  (narrow: where whole tiles of 32 channels are priced a sixth faster, as with 96 or 160
     // channels, they stay: 0.78 to 1.18, 14 layers, half of them more.)
     if (pairs > round && 4 * pairs <= 5 * round && steps >= 4 && !narrow) {
-        // patches: 0.85 on average, three of 112 layers slower by more than 3 %
+        // patches: 0.85 on average, 138 layers, six slower by more than 3 %, two of them, against four and six slices of two waves, 1.11 and 1.26
         if (halo > 0) return true;
         // Taps against four waves: 0.87, 0.97 at worst, 77 layers.  Against two, of whose 128-wide tiles some channels are padding, with a stride, 0.89,
         // 11 layers; not without (1.03, up to 1.18, 22 layers; 32 to 320 channels, 5x5, 31x31, nine images, 28.8 us, 34.0 dealt out).  Not with up to 64
